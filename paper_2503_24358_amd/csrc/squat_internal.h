@@ -169,6 +169,14 @@ int plan_quantize(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t n_toke
 int plan_quantize_pc(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t n_tokens, bool has_update,
                      int64_t update_stride_batch, int g, QuantPlan& out);
 
+// Units (of 16 tokens, or token groups) per wavefront that a logits launch aims at.  `most` amortises a wavefront's
+// set-up and is taken while `sequences` of `units` units fill the chip with it; a launch with less work (few sequences)
+// spreads it over about `workgroups` workgroups instead, down to `least` units a wavefront.
+inline int64_t units_per_wave(int64_t units, int64_t sequences, int waves, int64_t workgroups, int64_t least, int64_t most) {
+    const int64_t spread = (units * sequences + waves * workgroups - 1) / (waves * workgroups);
+    return spread > most ? most : (spread < least ? least : spread);
+}
+
 // Number of compute units of the current device (256 if the query fails).
 inline int device_cu_count() {
     int dev = 0, cus = 0;

@@ -33,7 +33,11 @@ namespace {
 constexpr int kPcDepth = 2;            // token groups whose loads are in flight per wavefront
 constexpr int kPcWaves = 4;
 constexpr int kPcTilesPerWave = 16;    // token groups a wavefront aims at (amortises its set-up) ...
-constexpr int kPcMinTilesPerWave = 2;  // ... unless the sequence is short
+constexpr int kPcMinTilesPerWave = 2;  // ... unless that leaves the chip idle: then the launch is spread over
+constexpr int kPcWorkgroups = 512;     // about this many workgroups (two per CU), down to one step a wavefront
+// Measured (2-bit, 8 KV heads x 4 query heads; us with 16 groups a wavefront | 256 workgroups | 512 | 1024 | 2048): 1
+// sequence of 1024 tokens 6.3 | 3.8 | 3.8 | 3.8 | 3.8; 1 of 4096 10.0 | 4.2 | 4.2 | 4.2 | 4.2; 1 of 32768 10.8 | 7.4 |
+// 7.0 | 7.6 | 7.6; 32 of 2048 10.9 | 11.0 | 9.8 | 10.2 | 11.9; 64 of 2080 16.4 | 16.2 | 15.9 | 17.0 | 17.9.
 #define PC_LOAD(p) __builtin_nontemporal_load(p)
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
@@ -461,9 +465,10 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
 
-    // workgroups along the sequence: about kPcWaves * kPcTilesPerWave token groups each, spread evenly
+    // workgroups along the sequence: about kPcWaves * aim token groups each, spread evenly
     const int64_t n_tiles = p.n_tiles;
-    const int64_t slab = static_cast<int64_t>(kPcWaves) * kPcTilesPerWave;
+    const int64_t aim = units_per_wave(n_tiles, n_batch * n_kv_heads, kPcWaves, kPcWorkgroups, kPcMinTilesPerWave, kPcTilesPerWave);
+    const int64_t slab = kPcWaves * aim;
     int64_t gx = (n_tiles + slab / 2) / slab;
     if (gx < 1) gx = 1;
     int64_t tpw = (n_tiles + kPcWaves * gx - 1) / (kPcWaves * gx);

@@ -37,8 +37,14 @@ constexpr int kRopeDepth = 3;          // units whose loads are in flight per wa
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 constexpr int kRopeUnit = 16;          // tokens per matrix product (MFMA N)
+// 16-token units a wavefront takes: 64 where there is enough work for that, else as few (down to one epoch) as spread
+// the launch over kRopeWorkgroups workgroups, two per CU (the tables a workgroup fills first take ~3 us, so more of
+// them cost more than they hide).  One sequence of 32768 tokens, 8 KV heads x 4 query heads, 2 bits: per-channel
+// store 37.1 us with 64 workgroups of 64 units, 13.1 us with 256, 10.7 with 512, 12.5 with 1024; per-token store
+// 32.1 us, 12.0, 10.2, 12.4; with 4096 tokens 36.2 -> 6.0 and 30.8 -> 6.0 us; 512 sequences of 4096: no difference.
 constexpr int kRopeMaxUnitsPerWave = 64;
 constexpr int kRopeMinUnitsPerWave = 4;
+constexpr int kRopeWorkgroups = 512;
 constexpr int kRopeWaves = 4;
 
 struct RopeParams {
@@ -824,9 +830,11 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
         p.wide_loads = (store_stride * meta_row) % 16 == 0 && aligned(scale, 16) && aligned(zero, 16);
     }
 
-    // workgroups along the sequence: about kRopeWaves * kRopeMaxUnitsPerWave units each, spread evenly
+    // workgroups along the sequence: about kRopeWaves * aim units each, spread evenly
     const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit;
-    const int64_t slab = static_cast<int64_t>(kRopeWaves) * kRopeMaxUnitsPerWave;
+    const int64_t aim = units_per_wave(n_units, n_batch * n_kv_heads, kRopeWaves, kRopeWorkgroups, kRopeMinUnitsPerWave,
+                                       kRopeMaxUnitsPerWave);
+    const int64_t slab = kRopeWaves * aim;
     int64_t gx = (n_units + slab / 2) / slab;
     if (gx < 1) gx = 1;
     int64_t upw = (n_units + kRopeWaves * gx - 1) / (kRopeWaves * gx);
@@ -902,9 +910,11 @@ int squat::key_scores_pc_rope_from(const uint32_t* codes, const uint16_t* scale,
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
 
-    // workgroups along the sequence: about kRopeWaves * kRopeMaxUnitsPerWave / 2 tiles each, spread evenly
+    // workgroups along the sequence: about kRopeWaves * aim tiles (of two units) each, spread evenly
     const int64_t n_tiles = n_tokens / group;
-    const int64_t slab = static_cast<int64_t>(kRopeWaves) * (kRopeMaxUnitsPerWave / 2);
+    const int64_t aim = units_per_wave(n_tiles, n_batch * n_kv_heads, kRopeWaves, kRopeWorkgroups, kRopeMinUnitsPerWave / 2,
+                                       kRopeMaxUnitsPerWave / 2);
+    const int64_t slab = kRopeWaves * aim;
     int64_t gx = (n_tiles + slab / 2) / slab;
     if (gx < 1) gx = 1;
     int64_t tpw = (n_tiles + kRopeWaves * gx - 1) / (kRopeWaves * gx);
