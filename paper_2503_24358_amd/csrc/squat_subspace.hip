@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(kTriThreads) eig_tridiag_kernel(const double* 
                                                                   float* eig, int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int64_t kvh = blockIdx.x;
-    const bool ok = tridiag_top_eigs(g64 + kvh * kD * kD, vws + kvh * kD * kD, r, qhat + kvh * r * kD,
+    const bool ok = tridiag_top_eigs(g64 + kvh * kD * kD, vws + kvh * kTriWsDoubles, r, qhat + kvh * r * kD,
                                      eig ? eig + kvh * r : nullptr, reinterpret_cast<double*>(smem));
     if (threadIdx.x == 0) need[kvh] = ok ? 0 : 1;
 }
@@ -519,8 +519,8 @@ SubspacePlan plan(int64_t n_tokens, int n_kv_heads, int q_per_kv, int cus) {
     size_t partial = static_cast<size_t>(n_kv_heads) * per * kPartialFloats * sizeof(float);
     pl.off_g64 = (partial + 255) & ~size_t(255);
     const size_t mat = static_cast<size_t>(n_kv_heads) * kD * kD * sizeof(double);
-    pl.off_v = pl.off_g64 + mat;                               // Householder reflectors of every head
-    pl.off_need = pl.off_v + mat;                              // per head: 1 = the Jacobi kernel must redo it
+    pl.off_v = pl.off_g64 + mat;                               // Householder reflectors of every head, as matrix operands
+    pl.off_need = pl.off_v + static_cast<size_t>(n_kv_heads) * kTriWsDoubles * sizeof(double);   // per head: 1 = the Jacobi kernel must redo it
     pl.total = pl.off_need + ((static_cast<size_t>(n_kv_heads) * sizeof(int) + 255) & ~size_t(255));
     return pl;
 }

@@ -9,10 +9,12 @@
 //      96 + team at columns l, 8 + l, .., 120 + l, so the trailing block
 //      shrinks in every thread at once; per step only the product A x and the
 //      next column travel through LDS (one barrier per step).
-//   2. The r largest eigenvalues of T by 17-section on Sturm counts (16 trial
-//      shifts per eigenvalue and round, 14 rounds from [-3, 3] ||T||): the count
+//   2. The r largest eigenvalues of T by Sturm counts (a team of threads per
+//      eigenvalue, one or two trial shifts each): the count
 //      is the number of sign changes of the three-term recurrence of the leading
-//      principal minors, division-free, rescaled by a power of two every 8 terms.
+//      principal minors, division-free, rescaled by a power of two every 8 terms;
+//      once a bracket holds one eigenvalue the trial shifts follow the zero of the
+//      line through its ends.
 //   3. Eigenvectors of T by twisted factorisations (eigenvalues closer than 1e-11 of
 //      the spectrum's scale: by inverse iteration with shifts made distinct by a few
 //      ulps where eigenvalues coincide: two solves per vector by Gaussian
@@ -21,8 +23,9 @@
 //      already (separated eigenvalues), need one symmetric correction step (close
 //      eigenvalues) or go through Cholesky-QR (coincident ones).
 //   4. Rayleigh quotients = eigenvalues; residuals ||T x - lambda x|| checked.
-//   5. Back-transformation by the stored reflectors (kept in LDS during step 1,
-//      parked in global memory while steps 2-4 use that LDS block).
+//   5. Back-transformation in blocks of 16 reflectors on the matrix cores (their
+//      operands are formed after step 1, while the reflectors are in LDS, and wait
+//      in global memory while steps 2-4 use that LDS block).
 //
 // A matrix whose result fails the checks of step 4 (never seen with fp64, kept as
 // a safety net) is flagged and handed to the Jacobi kernel.  About 40 times fewer
@@ -43,6 +46,9 @@ static_assert(kTriThreads == 256 && (kTriN / kTriRows) % 8 == 0, "whole wavefron
 constexpr int kTriMaxR = 32;            // vectors the LDS plan holds
 constexpr double kTriGap = 1e-11;       // closest eigenvalues (of the spectrum's scale) whose vectors are taken from the twisted form
 constexpr double kTriPivMin = 2.0e-19;  // smallest pivot
+constexpr double kTriBound = 3.0001;     // > the largest eigenvalue of a tridiagonal matrix with entries of at most 1
+constexpr double kTriPart = 2.0 * kTriBound / 257.0;
+constexpr double kTriWidth = 4.5e-16;   // width of an eigenvalue's bracket (one unit in the last place of numbers from 2 to 4)
 constexpr double kTriAccept = 1e-9;     // ||T x - lambda x|| / ||T|| and |x_i . x_j| allowed before the fallback
 
 // LDS plan, in doubles
@@ -58,15 +64,37 @@ constexpr int kTriX = 1344;             // [128][32] vectors, element-major
 constexpr int kTriU0 = kTriX + 4096;    // [128][32] reciprocal pivots
 constexpr int kTriU1 = kTriU0 + 4096;
 constexpr int kTriU2 = kTriU1 + 4096;
-constexpr int kTriS = kTriU2 + 4096;    // [32][33] Gram matrix / Cholesky factor
-constexpr int kTriLdsDoubles = kTriS + 32 * 33;
+constexpr int kTriS = kTriU2 + 4096;    // [32][33] Gram matrix / Cholesky factor, or [8][16][17] the blocks' T factors
+constexpr int kTriTLd = 17;
+constexpr int kTriLdsDoubles = kTriS + 8 * 16 * kTriTLd;
 constexpr size_t kTriLdsBytes = static_cast<size_t>(kTriLdsDoubles) * sizeof(double);
+constexpr int kTriWsPerWave = 9 * 8 * 64;              // operands of the back-transformation, per wavefront, and per matrix:
+constexpr int kTriWsDoubles = kTriThreads / 64 * kTriWsPerWave;
+constexpr int kTriVLd = 130;            // reflector k at kTriX + 130 k in the reduction (over the vectors and factors, not in use yet);
+                                        // 130: the 16 reflectors of a matrix operand fall on different banks
 static_assert(kTriLdsBytes <= 160 * 1024, "LDS plan exceeds a compute unit");
-static_assert(kTriX + 16384 == kTriS, "vectors and factors form one 128 KB block (reused for the reflectors)");
+static_assert((kTriN - 2) * kTriVLd <= 4 * 4096 && 32 * 33 <= 8 * 16 * kTriTLd, "aliased blocks");
 
+typedef double double4v __attribute__((ext_vector_type(4)));
+
+// Max over the workgroup (by lane permutes and swaps inside a wavefront: no trips through the LDS crossbar).
 __device__ __forceinline__ double tri_block_max(double v, double* scratch, int tid) {
 #pragma unroll
-    for (int s = 1; s < 64; s <<= 1) v = fmax(v, __shfl_xor(v, s, 64));
+    for (int sel = 0; sel < 4; ++sel) v = fmax(v, dpp_move(v, sel));
+    {
+        const uint32_t lo = static_cast<uint32_t>(__double2loint(v)), hi = static_cast<uint32_t>(__double2hiint(v));
+        const auto sl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto sh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        v = fmax(__hiloint2double(static_cast<int>(sh[0]), static_cast<int>(sl[0])),
+                 __hiloint2double(static_cast<int>(sh[1]), static_cast<int>(sl[1])));
+    }
+    {
+        const uint32_t lo = static_cast<uint32_t>(__double2loint(v)), hi = static_cast<uint32_t>(__double2hiint(v));
+        const auto sl = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto sh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        v = fmax(__hiloint2double(static_cast<int>(sh[0]), static_cast<int>(sl[0])),
+                 __hiloint2double(static_cast<int>(sh[1]), static_cast<int>(sl[1])));
+    }
     __syncthreads();                                      // scratch may still be read from an earlier use
     if ((tid & 63) == 0) scratch[tid >> 6] = v;
     __syncthreads();
@@ -76,18 +104,22 @@ __device__ __forceinline__ double tri_block_max(double v, double* scratch, int t
     return m;
 }
 
+// Waits for the LDS reads issued so far, once: the reads that follow are then the only ones the compiler has to count.
+__device__ __forceinline__ void tri_lds_wait() { __builtin_amdgcn_s_waitcnt(0xC07F); }      // lgkmcnt(0), nothing else
+
 __device__ __forceinline__ double tri_pow2(int e) {       // 2^e, -1022 <= e <= 1023
     return __hiloint2double((e + 1023) << 20, 0);
 }
 
-// Rescales a pair of consecutive minors by a power of two (the larger one to [1, 2)); returns the factor.
-__device__ __forceinline__ double tri_rescale(double& p0, double& p1) {
+// Rescales a pair of consecutive minors by a power of two (the larger one to [1, 2)); returns the exponent taken out.
+__device__ __forceinline__ int tri_rescale(double& p0, double& p1) {
     const double m = fmax(fabs(p0), fabs(p1));
-    const int ex = ((__double2hiint(m) >> 20) & 0x7FF) - 1023;
-    const double f = ex > -1000 && ex < 1000 ? tri_pow2(-ex) : 1.0;
+    int ex = ((__double2hiint(m) >> 20) & 0x7FF) - 1023;
+    ex = ex > -1000 && ex < 1000 ? ex : 0;
+    const double f = tri_pow2(-ex);
     p0 *= f;
     p1 *= f;
-    return f;
+    return ex;
 }
 
 // Workgroup barrier that orders LDS traffic only (the Householder loop touches nothing else; the full
@@ -100,17 +132,6 @@ __device__ __forceinline__ double tri_readlane(double v, int src) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
     return __hiloint2double(hi, lo);
-}
-
-// Sum over an aligned team of 32 lanes (two rows of 16): row sums by lane permutes, then the two rows
-// trade their sums with the row-swap instruction (no trip through the LDS crossbar).
-__device__ __forceinline__ double tri_sum32(double v) {
-    v = team_sum<16>(v);
-    const uint32_t lo = static_cast<uint32_t>(__double2loint(v)), hi = static_cast<uint32_t>(__double2hiint(v));
-    const auto sl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto sh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    return __hiloint2double(static_cast<int>(sh[0]), static_cast<int>(sl[0])) +
-           __hiloint2double(static_cast<int>(sh[1]), static_cast<int>(sl[1]));
 }
 
 // 1 / sqrt(x) and 1 / x from the hardware approximations and Newton steps (short dependent chains: the
@@ -183,7 +204,7 @@ __device__ __forceinline__ double tri_team_sum(double v) {
 // Entries with index <= k are zero in x, xr and in the LDS vectors (written as zeros), so finished rows and columns
 // need no masks.
 // LDS vectors are stored by owner, entry i at 4 (i mod 32) + i / 32, so that a thread's four rows are contiguous.
-__device__ __forceinline__ int tri_row(int pos) { return 32 * (pos & 3) + (pos >> 2); }     // the entry at a position
+__device__ __forceinline__ int tri_pos(int row) { return 4 * (row & 31) + (row >> 5); }
 
 // Step k = 8 CC + ll - 1 (column k1 = k + 1 is register CC of the lanes l == ll, row k1 register CC / 4 of one team).
 // x, xr: the column in this thread's columns and rows, replaced by v; y, yr receive the next column.
@@ -255,8 +276,8 @@ __device__ __forceinline__ void tri_step(double (&a)[kTriRows][16], double (&x)[
     x[CC] -= own_c ? alpha : 0.0;
     xr[R0] -= own_r ? alpha : 0.0;
     // reflector k (the block of the later phases is free now)
-    *reinterpret_cast<double2*>(L + kTriX + k * kTriN + 4 * team) = double2{xr[0], xr[1]};
-    *reinterpret_cast<double2*>(L + kTriX + k * kTriN + 4 * team + 2) = double2{xr[2], xr[3]};
+    *reinterpret_cast<double2*>(L + kTriX + k * kTriVLd + 4 * team) = double2{xr[0], xr[1]};
+    *reinterpret_cast<double2*>(L + kTriX + k * kTriVLd + 4 * team + 2) = double2{xr[2], xr[3]};
     // u = A v = A x - alpha A e_1;  K = beta / 2 v'u;  t = u - K v  (w = beta t)
 #pragma unroll
     for (int c = CC; c < 16; ++c) t[c] = fma(-alpha, y[c], t[c]);
@@ -302,7 +323,7 @@ __device__ __forceinline__ void tri_steps(double (&a)[kTriRows][16], double (&x)
     if constexpr (CC == 15) tri_step<CC>(a, x, y, xr, yr, team, l, tid, L, 6, 0);
 }
 
-// g: the matrix (row-major doubles, symmetric positive semi-definite); vws: 128 x 128 doubles of
+// g: the matrix (row-major doubles, symmetric positive semi-definite); vws: kTriWsDoubles doubles of
 // scratch in global memory; qhat: r rows of 128 floats = sqrt(lambda_j) v_j, eigenvalues descending;
 // eig: r floats or NULL; r <= 2 kTriMaxR.  Returns (to every thread) whether the result was accepted; if not, the
 // outputs are to be redone as a whole (a first batch of rows may have been written).  All kTriThreads threads of
@@ -382,9 +403,92 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
         L[kTriBet + kTriN - 1] = 0.0;
     }
     __syncthreads();
-    // the reflectors leave LDS (their block is needed for the vectors and factors) and come back for step 5
-    for (int e = tid * 2; e < (kTriN - 2) * kTriN; e += 2 * kTriThreads)
-        *reinterpret_cast<double2*>(vws + e) = *reinterpret_cast<const double2*>(L + kTriX + e);
+    // ---- operands of the back-transformation, while the reflectors are in LDS.  The reflectors are taken in blocks of 16,
+    // H_{16 b} ... H_{16 b + 15} = I - V T V' with T upper triangular, T_mm = beta_m, T_{0..m-1, m} = -beta_m T (V'v_m).
+    // Wavefront w keeps the row tiles w and 7 - w (16 rows each) of the vectors; as the first rows of a block's
+    // reflectors are zero, tile t meets the blocks b <= t only.  Per (tile, block): V' as the A operand of V'X (4
+    // registers) and -(V T)' likewise for X - (V T)(V'X); both wait in global memory, as the lanes hold them, until step 5
+    // (kept in registers meanwhile they slow steps 2-4 down: 40 k cycles more in the search).  v_mfma_f64_16x16x4_f64: A lane (i = lane & 15, k = lane >> 4), B lane (j = lane & 15, k = lane >> 4), result
+    // lane (j = lane & 15), register q: row (lane >> 4) + 4 q, i.e. a result is the B operand of the next product as it is.
+    const int mi = lane & 15, mk = lane >> 4;
+    // [wavefront][9 (tile, block) pairs: tile 7 - wave with blocks 0 .. 7 - wave, tile `wave` with blocks 0 .. wave][8][64]
+    double* const vmine = vws + wave * kTriWsPerWave + lane;
+    {
+        const double* V = L + kTriX;
+        double* TS = L + kTriS;
+        // V'V of the blocks `wave` and 7 - wave, side by side (the second one's reflectors start further down)
+        {
+            const int b1 = wave, b2 = 7 - wave;
+            const bool real = 16 * b2 + mi < kTriN - 2;       // reflectors 126 and 127 do not exist
+            const double* v1 = V + (16 * b1 + mi) * kTriVLd;
+            const double* v2 = V + (real ? 16 * b2 + mi : 0) * kTriVLd;
+            double4v acc1 = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+            for (int m = 4 * b1; m < 4 * b2; ++m) {
+                const double x = v1[tri_pos(4 * m + mk)];
+                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc1, 0, 0, 0);
+            }
+#pragma unroll 4
+            for (int m = 4 * b2; m < kTriN / 4; ++m) {
+                const double x = v1[tri_pos(4 * m + mk)];
+                double y = v2[tri_pos(4 * m + mk)];
+                y = real ? y : 0.0;
+                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc1, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(y, y, acc2, 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                TS[(16 * b1 + mk + 4 * q) * kTriTLd + mi] = acc1[q];
+                TS[(16 * b2 + mk + 4 * q) * kTriTLd + mi] = acc2[q];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // T, a row per lane (lanes 0 .. 15: block `wave`, 16 .. 31: block 7 - wave)
+        {
+            const int b = (lane & 16) ? 7 - wave : wave;
+            double* S = TS + 16 * b * kTriTLd;
+            double t[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                double sum = 0.0;
+#pragma unroll
+                for (int q = 0; q < m; ++q) sum = fma(t[q], S[q * kTriTLd + m], sum);
+                const double bt = L[kTriBet + 16 * b + m];
+                t[m] = m == mi ? bt : (m > mi ? -bt * sum : 0.0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (lane < 32) {
+#pragma unroll
+                for (int m = 0; m < 16; ++m) S[mi * kTriTLd + m] = t[m];
+            }
+        }
+        __syncthreads();
+        auto operands = [&](const int tile, const int b, double* dst) __attribute__((always_inline)) {
+            const bool real = 16 * b + mi < kTriN - 2;
+            const double* vk = V + (real ? 16 * b + mi : 0) * kTriVLd;
+            double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double x = vk[tri_pos(16 * tile + 4 * q + mk)];
+                dst[64 * q] = real ? x : 0.0;
+                const bool kreal = 16 * b + 4 * q + mk < kTriN - 2;
+                double y = V[(kreal ? 16 * b + 4 * q + mk : 0) * kTriVLd + tri_pos(16 * tile + mi)];
+                y = kreal ? y : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(TS[(16 * b + 4 * q + mk) * kTriTLd + mi], y, acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) dst[64 * (4 + q)] = -acc[q];
+        };
+#pragma unroll 3
+        for (int e = 0; e < 9; ++e) {                         // uniform
+            const bool second = e > 7 - wave;
+            operands(second ? wave : 7 - wave, second ? e - (8 - wave) : e, vmine + e * (8 * 64));
+        }
+    }
+    __syncthreads();
 
     // ---- normalise T to max |entry| = 1
     double tmax = 0.0;
@@ -409,78 +513,163 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
     // is one batch; for more, T and the reflectors serve every batch.  (Two inlined copies of the batch rather than
     // a loop around one: inside a loop the compiler spills a hundred registers.)
     double lam_edge = 0.0;                                // smallest eigenvalue of the batch before
-    auto batch = [&](const int joff, const int rb) -> bool {
-        // ---- 2. the rb largest eigenvalues by multisection on Sturm counts.  A power-of-two team of threads per eigenvalue,
-        // NP trial shifts per thread; `points` = team size x NP trial shifts divide a bracket into points + 1 parts.
-        auto search = [&](auto np_tag, const int team_size, const int rounds) {
+    auto batch = [&](const int joff, const int rb) __attribute__((always_inline)) -> bool {
+        // ---- 2. the rb largest eigenvalues, bracketed by Sturm counts.  A power-of-two team of threads per eigenvalue, NP
+        // trial shifts per thread, `points` in all; every round keeps the part of the bracket between two neighbouring trial
+        // shifts that holds the eigenvalue.  The trial shifts divide the bracket evenly while it holds several eigenvalues.
+        // Once it holds one, the last minor (the characteristic polynomial) changes sign in it and its values at the two
+        // ends are known: the shifts then sit around the zero of the line through them, at distances that fall from 1/8 of
+        // the bracket by equal factors to 2^-31 or less, so a round gains as many digits as that estimate has and the count
+        // alone still decides.  (Even division throughout, 17 parts in 14 rounds: 75 k cycles for 16 eigenvalues, 113 k for
+        // 32; this takes 53 k and 76 k.)  A round whose line was no good (the bracket not an eighth) is followed by an even one.
+        // Sturm count, last minor (mantissa and exponent) at NP shifts per thread
+        auto minors = [&](const auto& x, auto& p1, auto& cnt, auto& ex, auto np_tag) __attribute__((always_inline)) {
+            constexpr int NP = decltype(np_tag)::value;
+            const double* de = L + kTriDe;
+            asm volatile("" ::: "memory");                    // keep the 128 LDS reads inside the round (not hoisted into registers)
+            double p0[NP];
+            uint32_t signs[NP];
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                p0[q] = 1.0;
+                p1[q] = de[0] - x[q];
+                // The signs of the minors are shifted into a register, newest at bit 0 (one instruction per term);
+                // a block's sign changes are then the ones of (signs ^ signs >> 1) over its terms.  The sign of
+                // p_0 = 1 is 0, so the first minor's own sign is a change.
+                signs[q] = static_cast<uint32_t>(__double2hiint(p1[q])) >> 31;
+                cnt[q] = static_cast<int>(signs[q]);
+                ex[q] = 0;
+            }
+            // blocks of 8 terms (7 in the last), the next block's (d, e^2) on their way meanwhile
+            double2 ta[8], tb[8];
+            auto fetch = [&](int b, double2 (&t)[8], auto nt_tag) __attribute__((always_inline)) {
+                constexpr int NT = decltype(nt_tag)::value;
+                tri_lds_wait();                               // (for the block about to be used)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) t[u] = *reinterpret_cast<const double2*>(de + 2 * (8 * b + 1 + u));
+            };
+            auto terms = [&](const double2 (&t)[8], auto nt_tag) __attribute__((always_inline)) {
+                constexpr int NT = decltype(nt_tag)::value;
+#pragma unroll
+                for (int u = 0; u < NT; ++u)
+#pragma unroll
+                    for (int q = 0; q < NP; ++q) {
+                        const double p2 = fma(t[u].x - x[q], p1[q], -(t[u].y * p0[q]));
+                        signs[q] = __builtin_amdgcn_alignbit(signs[q], static_cast<uint32_t>(__double2hiint(p2)), 31);
+                        p0[q] = p1[q];
+                        p1[q] = p2;
+                    }
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    cnt[q] += __popc((signs[q] ^ (signs[q] >> 1)) & ((1u << NT) - 1u));
+                    ex[q] += tri_rescale(p0[q], p1[q]);
+                }
+            };
+            constexpr std::integral_constant<int, 8> k8{};
+            constexpr std::integral_constant<int, 7> k7{};
+            static_assert(kTriN - 1 == 15 * 8 + 7, "15 blocks of 8 terms and one of 7");
+            fetch(0, ta, k8);
+#pragma nounroll
+            for (int b = 0; b < 14; b += 2) {
+                fetch(b + 1, tb, k8);
+                terms(ta, k8);
+                fetch(b + 2, ta, k8);
+                terms(tb, k8);
+            }
+            fetch(15, tb, k7);
+            terms(ta, k8);
+            terms(tb, k7);
+        };
+        {
+            // shared round: 256 shifts over [-kTriBound, kTriBound], one per thread, serve every eigenvalue
+            double x[1] = {fma(kTriPart, static_cast<double>(tid + 1), -kTriBound)}, p1[1];
+            int cnt[1], ex[1];
+            minors(x, p1, cnt, ex, std::integral_constant<int, 1>{});
+            L[kTriU0 + tid] = p1[0];
+            reinterpret_cast<int2*>(L + kTriU1)[tid] = int2{cnt[0], ex[0]};
+            __syncthreads();
+        }
+        auto search = [&](auto np_tag, const int team_size) __attribute__((always_inline)) {
             constexpr int NP = decltype(np_tag)::value;
             const int j = tid / team_size, sub = tid & (team_size - 1);
             if (j >= rb) return;
-            const int points = team_size * NP;
+            const int points = team_size * NP, half = points / 2, fall = 64 / points;
             const double inv_parts = 1.0 / (points + 1);
             const int below_target = kTriN - 1 - (joff + j);  // eigenvalue joff + j (descending) has this many below it
-            const unsigned long long team_mask = team_size == 64 ? ~0ull : ((1ull << team_size) - 1ull) << (lane & ~(team_size - 1));
-            double lo = -3.0001, hi = 3.0001;
-            const double* de = L + kTriDe;
-            for (int round = 0; round < rounds; ++round) {
-                asm volatile("" ::: "memory");                // keep the 128 LDS reads inside the round (not hoisted into registers)
-                const double step = (hi - lo) * inv_parts;
-                double x[NP], p0[NP], p1[NP];
-                uint32_t signs[NP];
-                int cnt[NP];
+            const int lane0 = lane & ~(team_size - 1);
+            const unsigned long long team_mask = team_size == 64 ? ~0ull : ((1ull << team_size) - 1ull) << lane0;
+            // first bracket: from the counts of the shared round
+            int first = 0;                                    // shared shifts with count <= target (a prefix)
+            const int2* shared = reinterpret_cast<const int2*>(L + kTriU1);
+            for (int step = kTriThreads / 2; step > 0; step >>= 1)
+                if (shared[first + step - 1].x <= below_target) first += step;
+            if (first == kTriThreads - 1 && shared[kTriThreads - 1].x <= below_target) first = kTriThreads;
+            // the bracket, and the last minor at its ends, f 2^e, with the counts there
+            double lo = fma(kTriPart, static_cast<double>(first), -kTriBound);
+            double hi = fma(kTriPart, static_cast<double>(first + 1), -kTriBound);
+            const int2 at_lo = shared[first > 0 ? first - 1 : 0], at_hi = shared[first < kTriThreads ? first : 0];
+            bool known_lo = first > 0, known_hi = first < kTriThreads, stalled = false;
+            double flo = L[kTriU0 + (known_lo ? first - 1 : 0)], fhi = L[kTriU0 + (known_hi ? first : 0)];
+            int clo = at_lo.x, chi = at_hi.x, elo = at_lo.y, ehi = at_hi.y;
+            for (int round = 0; round < 24; ++round) {
+                if (__ballot(hi - lo > kTriWidth) == 0ull) break;
+                const double width = hi - lo, step = width * inv_parts;
+                const bool line = known_lo && known_hi && chi - clo == 1 && !stalled;
+                const int de2 = ehi - elo < -1000 ? -1000 : (ehi - elo > 1000 ? 1000 : ehi - elo);
+                const double ratio = fhi * tri_rcp(flo) * tri_pow2(de2);  // < 0
+                const double est = fma(width, tri_rcp(1.0 - ratio), lo);
+                double x[NP], p1[NP];
+                int cnt[NP], ex[NP];
 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
-                    x[q] = fma(step, static_cast<double>(sub + q * team_size + 1), lo);
-                    p0[q] = 1.0;
-                    p1[q] = de[0] - x[q];
-                    // The signs of the minors are shifted into a register, newest at bit 0 (one instruction per term);
-                    // a block's sign changes are then the ones of (signs ^ signs >> 1) over its terms.  The sign of
-                    // p_0 = 1 is 0, so the first minor's own sign is a change.
-                    signs[q] = static_cast<uint32_t>(__double2hiint(p1[q])) >> 31;
-                    cnt[q] = static_cast<int>(signs[q]);
+                    const int p = sub + q * team_size;
+                    const int away = p < half ? p : points - 1 - p;       // 0: farthest from the estimate
+                    const double d = width * tri_pow2(-3 - fall * away);
+                    const double xl = fmin(fmax(est + (p < half ? -d : d), lo), hi);
+                    x[q] = line ? xl : fma(step, static_cast<double>(p + 1), lo);
                 }
-                auto block = [&](int b, auto nt_tag) {
-                    constexpr int NTERMS = decltype(nt_tag)::value;
-#pragma unroll
-                    for (int u = 0; u < NTERMS; ++u) {
-                        const double2 t = *reinterpret_cast<const double2*>(de + 2 * (b + u));
-#pragma unroll
-                        for (int q = 0; q < NP; ++q) {
-                            const double p2 = fma(t.x - x[q], p1[q], -(t.y * p0[q]));
-                            signs[q] = __builtin_amdgcn_alignbit(signs[q], static_cast<uint32_t>(__double2hiint(p2)), 31);
-                            p0[q] = p1[q];
-                            p1[q] = p2;
-                        }
-                    }
-#pragma unroll
-                    for (int q = 0; q < NP; ++q) {
-                        cnt[q] += __popc((signs[q] ^ (signs[q] >> 1)) & ((1u << NTERMS) - 1u));
-                        tri_rescale(p0[q], p1[q]);
-                    }
-                };
-                static_assert((kTriN - 1) % 8 == 7, "15 blocks of 8 terms and one of 7");
-                for (int b = 1; b + 8 <= kTriN; b += 8) block(b, std::integral_constant<int, 8>{});
-                block(kTriN - 7, std::integral_constant<int, 7>{});
+                minors(x, p1, cnt, ex, np_tag);
                 // the team's points are ascending: those with count <= target are a prefix
                 int nb = 0;
 #pragma unroll
                 for (int q = 0; q < NP; ++q) nb += __popcll(__ballot(cnt[q] <= below_target) & team_mask);
-                const double nlo = nb == 0 ? lo : fma(step, static_cast<double>(nb), lo);
-                const double nhi = nb == points ? hi : fma(step, static_cast<double>(nb + 1), lo);
-                lo = nlo;
-                hi = nhi;
+                const int pl = nb > 0 ? nb - 1 : 0, pu = nb < points ? nb : points - 1;
+                auto pick = [&](int p, double& xo, double& fo, int& eo, int& co) __attribute__((always_inline)) {
+                    const bool second = NP > 1 && p >= team_size;
+                    const int src = lane0 + (p & (team_size - 1));
+                    double xs = __shfl(x[0], src, 64), fs = __shfl(p1[0], src, 64);
+                    int es = __shfl(ex[0], src, 64), cn = __shfl(cnt[0], src, 64);
+                    if constexpr (NP > 1) {
+                        const double x2 = __shfl(x[1], src, 64), f2 = __shfl(p1[1], src, 64);
+                        const int e2 = __shfl(ex[1], src, 64), c2 = __shfl(cnt[1], src, 64);
+                        xs = second ? x2 : xs;
+                        fs = second ? f2 : fs;
+                        es = second ? e2 : es;
+                        cn = second ? c2 : cn;
+                    }
+                    xo = xs;
+                    fo = fs;
+                    eo = es;
+                    co = cn;
+                };
+                double xl, fl, xu, fu;
+                int el, cl, eu, cu;
+                pick(pl, xl, fl, el, cl);
+                pick(pu, xu, fu, eu, cu);
+                if (nb > 0) { lo = xl; flo = fl; elo = el; clo = cl; known_lo = true; }
+                if (nb < points) { hi = xu; fhi = fu; ehi = eu; chi = cu; known_hi = true; }
+                stalled = line && hi - lo > 0.125 * width;
             }
             if (sub == 0) L[kTriLam + j] = 0.5 * (lo + hi);
         };
-        // (parts^rounds > 6 x 2^53)
         if (rb > 16)
-            search(std::integral_constant<int, 2>{}, 8, 14);
+            search(std::integral_constant<int, 2>{}, 8);
         else if (rb > 8)
-            search(std::integral_constant<int, 1>{}, 16, 14);
+            search(std::integral_constant<int, 1>{}, 16);
         else if (rb > 4)
-            search(std::integral_constant<int, 1>{}, 32, 12);
+            search(std::integral_constant<int, 1>{}, 32);
         else
-            search(std::integral_constant<int, 1>{}, 64, 10);
+            search(std::integral_constant<int, 1>{}, 64);
         __syncthreads();
         // A later batch stands on its own only if its eigenvalues are clear of the batch before (vectors of eigenvalues
         // closer than this could share a subspace, which only a joint orthonormalisation would see)
@@ -512,21 +701,41 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
                 double p0 = 1.0, p1 = src[0] - lam;
                 if (fabs(p1) < kTriPivMin) p1 = kTriPivMin;
                 dst[0] = p1;
-                auto block = [&](int m0, auto nt_tag) {
-                    constexpr int NT = decltype(nt_tag)::value;
+                double2 ta[8], tb[8];                         // the next block is on its way while one is used
+                auto fetch = [&](int b, double2 (&t)[8]) __attribute__((always_inline)) {
+                    tri_lds_wait();
 #pragma unroll
-                    for (int u = 0; u < NT; ++u) {
-                        const double2 t = *reinterpret_cast<const double2*>(src + 2 * (m0 + u));
-                        double p2 = fma(t.x - lam, p1, -(t.y * p0));
+                    for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const double2*>(src + 2 * (8 * b + u));
+                };
+                auto block = [&](int b, const double2 (&t)[8], auto u0_tag) __attribute__((always_inline)) {
+                    constexpr int U0 = decltype(u0_tag)::value;
+#pragma unroll
+                    for (int u = U0; u < 8; ++u) {
+                        double p2 = fma(t[u].x - lam, p1, -(t[u].y * p0));
                         if (fabs(p2) < kTriPivMin * fabs(p1)) p2 = kTriPivMin * p1;      // a pivot below the threshold: the threshold
-                        dst[32 * (m0 + u)] = p2;
+                        dst[32 * (8 * b + u)] = p2;
                         p0 = p1;
                         p1 = p2;
                     }
                     tri_rescale(p0, p1);                      // (the stored minors keep the old scale: redone below)
                 };
-                block(1, std::integral_constant<int, 7>{});
-                for (int m0 = 8; m0 < kTriN; m0 += 8) block(m0, std::integral_constant<int, 8>{});
+                constexpr std::integral_constant<int, 0> k0{};
+                constexpr std::integral_constant<int, 1> k1{};
+                fetch(0, ta);
+                fetch(1, tb);
+                block(0, ta, k1);
+                fetch(2, ta);
+                block(1, tb, k0);
+#pragma nounroll
+                for (int b = 2; b < 14; b += 2) {
+                    fetch(b + 1, tb);
+                    block(b, ta, k0);
+                    fetch(b + 2, ta);
+                    block(b + 1, tb, k0);
+                }
+                fetch(15, tb);
+                block(14, ta, k0);
+                block(15, tb, k0);
             }
             __syncthreads();
             // thread (j, sg): rows 16 sg .. 16 sg + 15 of vector j
@@ -717,36 +926,43 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
         double* S = L + kTriS;
         bool ok = true;
         for (int pass = 0; pass < 3; ++pass) {
+            // wavefront (ti, tj): one 16 x 16 tile; only the rb real columns count (the padding columns are never used)
             double dev = 0.0;
-            if (tid < 256) {
-                const int a2 = tid >> 4, b2 = tid & 15;
-                double s00 = 0.0, s01 = 0.0, s10 = 0.0, s11 = 0.0;
-                for (int row = 0; row < kTriN; ++row) {
-                    const double2 xa = *reinterpret_cast<const double2*>(L + kTriX + 32 * row + 2 * a2);
-                    const double2 xb = *reinterpret_cast<const double2*>(L + kTriX + 32 * row + 2 * b2);
-                    s00 = fma(xa.x, xb.x, s00);
-                    s01 = fma(xa.x, xb.y, s01);
-                    s10 = fma(xa.y, xb.x, s10);
-                    s11 = fma(xa.y, xb.y, s11);
+            const int ti = wave >> 1, tj = wave & 1;
+            if (16 * ti < rb && 16 * tj < rb) {               // uniform
+                double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+                for (int m = 0; m < kTriN / 4; ++m) {
+                    const double* xr2 = L + kTriX + 32 * (4 * m + mk);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr2[16 * ti + mi], xr2[16 * tj + mi], acc, 0, 0, 0);
                 }
-                S[(2 * a2) * 33 + 2 * b2] = s00;
-                S[(2 * a2) * 33 + 2 * b2 + 1] = s01;
-                S[(2 * a2 + 1) * 33 + 2 * b2] = s10;
-                S[(2 * a2 + 1) * 33 + 2 * b2 + 1] = s11;
-                // only the rb real columns count (the padding columns are never used)
-                const double i00 = a2 == b2 ? 1.0 : 0.0;
-                const bool ra0 = 2 * a2 < rb, ra1 = 2 * a2 + 1 < rb, rb0 = 2 * b2 < rb, rb1 = 2 * b2 + 1 < rb;
-                dev = fmax(fmax(ra0 && rb0 ? fabs(s00 - i00) : 0.0, ra1 && rb1 ? fabs(s11 - i00) : 0.0),
-                           fmax(ra0 && rb1 ? fabs(s01) : 0.0, ra1 && rb0 ? fabs(s10) : 0.0));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int i2 = 16 * ti + mk + 4 * q, j2 = 16 * tj + mi;
+                    S[i2 * 33 + j2] = acc[q];
+                    if (i2 < rb && j2 < rb) {
+                        const double d2 = fabs(acc[q] - (i2 == j2 ? 1.0 : 0.0));
+                        dev = d2 == d2 ? fmax(dev, d2) : 1e300;
+                    }
+                }
             }
-            dev = tri_block_max(dev, misc, tid);
-            if (!(dev == dev)) ok = false;
-            if (dev <= 1e-10 || !ok) break;
+            // (a power of the deviation is all that matters: one bit per wavefront and threshold)
+            {
+                const int mine = (__ballot(!(dev < 1e300)) ? 1 : 0) | (__ballot(!(dev <= 1e-5)) ? 2 : 0) |
+                                 (__ballot(!(dev <= kTriAccept)) ? 4 : 0) | (__ballot(!(dev <= 1e-10)) ? 8 : 0);
+                int* flags = reinterpret_cast<int*>(misc + 36);
+                if (lane == 0) flags[wave] = mine;
+            }
+            __syncthreads();
+            const int dev_flags = reinterpret_cast<const int*>(misc + 36)[0] | reinterpret_cast<const int*>(misc + 36)[1] |
+                                  reinterpret_cast<const int*>(misc + 36)[2] | reinterpret_cast<const int*>(misc + 36)[3];
+            if (dev_flags & 1) ok = false;
+            if (!(dev_flags & 8) || !ok) break;
             if (pass == 2) {
-                ok = dev <= kTriAccept;
+                ok = !(dev_flags & 4);
                 break;
             }
-            if (dev <= 1e-5) {
+            if (!(dev_flags & 2)) {
                 // nearly orthonormal (close eigenvalues, not coincident ones): one symmetric step
                 // X <- X (3/2 I - 1/2 S) squares the deviation
                 constexpr int NP = kTriN * 8 / kTriThreads;    // row passes per thread
@@ -818,122 +1034,174 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             __syncthreads();
         }
 
-        // ---- 4. Rayleigh quotients and residuals: team of 32 lanes per vector, 4 elements per lane, NV
-        // vectors per thread
-        constexpr int NV = 32 * 32 / kTriThreads;
-        const int sub = tid & 31;
-        double xv[NV][4];
-        {
-            double worst = 0.0;
+        // the operands of step 5 are on their way during step 4
+        double va[4][4], ma[4][4], vb[8][4], mb[8][4];
 #pragma unroll
-            for (int q = 0; q < NV; ++q) {
-                const int vj = (tid >> 5) + q * (kTriThreads / 32);
-                double num = 0.0, den = 0.0;
-                double yv[4];
+        for (int b = 0; b < 8; ++b)
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int row = sub + 32 * m;
-                    const double x = L[kTriX + 32 * row + vj];
-                    const double xm = row > 0 ? L[kTriX + 32 * (row - 1) + vj] : 0.0;
-                    const double xp = row < kTriN - 1 ? L[kTriX + 32 * (row + 1) + vj] : 0.0;
-                    const double em = row > 0 ? L[kTriEe + row - 1] : 0.0;
-                    const double y = fma(L[kTriDd + row], x, fma(em, xm, L[kTriEe + row] * xp));
-                    xv[q][m] = x;
-                    yv[m] = y;
-                    num = fma(x, y, num);
-                    den = fma(x, x, den);
+            for (int q = 0; q < 4; ++q) {
+                if (b <= 7 - wave) {                          // uniform
+                    vb[b][q] = vmine[(b * 8 + q) * 64];
+                    mb[b][q] = vmine[(b * 8 + 4 + q) * 64];
                 }
-                num = tri_sum32(num);
-                den = tri_sum32(den);
-                const double rq = den > 0.0 ? num / den : 0.0;
-                double res = 0.0;
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const double t = yv[m] - rq * xv[q][m];
-                    res = fma(t, t, res);
+                if (b < 4 && b <= wave) {
+                    va[b & 3][q] = vmine[((8 - wave + b) * 8 + q) * 64];
+                    ma[b & 3][q] = vmine[((8 - wave + b) * 8 + 4 + q) * 64];
                 }
-                res = tri_sum32(res);
-                if (sub == 0) L[kTriLam + 64 + vj] = rq;
-                double w = vj < rb ? sqrt(res) : 0.0;
-                if (!(w == w)) w = 1e300;
-                worst = fmax(worst, w);
             }
-            worst = tri_block_max(worst, misc, tid);
-            if (!(worst <= kTriAccept)) ok = false;
+
+        // ---- 4. Rayleigh quotients and residuals: thread (j, sg) takes rows 16 sg .. 16 sg + 15 of vector j
+        {
+            constexpr int RS = kTriN / 8;
+            const int j = tid & 31, sg = tid >> 5, r0 = RS * sg;
+            double* P = S;                                    // (the Gram matrix has served)
+            double xv[RS + 2], yv[RS], num = 0.0, den = 0.0;
+#pragma unroll
+            for (int i = 0; i < RS; ++i) xv[i + 1] = L[kTriX + 32 * (r0 + i) + j];
+            xv[0] = sg > 0 ? L[kTriX + 32 * (r0 - 1) + j] : 0.0;
+            xv[RS + 1] = sg < 7 ? L[kTriX + 32 * (r0 + RS) + j] : 0.0;
+            double eprev = sg > 0 ? L[kTriEe + r0 - 1] : 0.0;
+            __syncthreads();                                  // everyone is past the Gram matrix
+#pragma unroll
+            for (int i = 0; i < RS; ++i) {
+                const double e = L[kTriEe + r0 + i];          // (0 in the last row)
+                yv[i] = fma(L[kTriDd + r0 + i], xv[i + 1], fma(eprev, xv[i], e * xv[i + 2]));
+                eprev = e;
+                num = fma(xv[i + 1], yv[i], num);
+                den = fma(xv[i + 1], xv[i + 1], den);
+            }
+            P[tid] = num;
+            P[256 + tid] = den;
+            __syncthreads();
+            num = den = 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                num += P[32 * q + j];
+                den += P[256 + 32 * q + j];
+            }
+            const double rq = den > 0.0 ? num / den : 0.0;
+            double res = 0.0;
+#pragma unroll
+            for (int i = 0; i < RS; ++i) {
+                const double t = fma(-rq, xv[i + 1], yv[i]);
+                res = fma(t, t, res);
+            }
+            P[512 + tid] = res;
+            if (sg == 0) L[kTriLam + 64 + j] = rq;
+            __syncthreads();
+            res = 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) res += P[512 + 32 * q + j];
+            const double w = j < rb ? sqrt(res) : 0.0;
+            // every wavefront sees all 32 vectors
+            if (__ballot(!(w <= kTriAccept)) != 0ull) ok = false;
         }
         if (!ok) return false;                                // uniform: every thread saw the same flags
 
-        // ---- 5. back-transformation: team of 16 lanes per vector, lane s holds the elements at positions s, s + 16, ...,
-        // s + 112 of NB vectors (two where the batch has more than 16).  Per reflector and lane: a dot product over 8
-        // elements per vector, a sum over the 16 lanes, 8 multiply-adds per vector; the next reflector's entries are
-        // fetched meanwhile.  The vectors are read from LDS in this layout before the reflectors come back from global
-        // memory into their block.
-        auto back = [&](auto nb_tag) {
-            constexpr int NB = decltype(nb_tag)::value;
-            const int bvj = tid >> 4, bs = tid & 15;
-            double xb[NB][8];
+        // ---- 5. back-transformation, X <- (I - V T V') X block by block from the last, on the matrix cores; NC column tiles of
+        // 16 vectors.  A wavefront's part of V'X over its own rows goes to LDS, every wavefront adds up the parts (in the same
+        // order) and applies the product to its rows.  One barrier per block: 144 products of 64 cycles and eight exchanges
+        // per wavefront for 32 vectors.  (One reflector after the other, with a dot product over 16 lanes each, took 55 k
+        // cycles for 16 vectors and 90 k for 32, and the reflectors a trip through global memory; this takes 14 k and 26 k.)
+        auto back = [&](auto nc_tag) __attribute__((always_inline)) {
+            constexpr int NC = decltype(nc_tag)::value;
+            const int tb = 7 - wave;
+            double4v xa[NC], xb[NC];
 #pragma unroll
-            for (int q = 0; q < NB; ++q)
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
-                for (int m = 0; m < 8; ++m) xb[q][m] = L[kTriX + 32 * tri_row(bs + 16 * m) + bvj + 16 * q];
-            __syncthreads();
-            __threadfence_block();
-            double* V = L + kTriX;
-            // (unrolled, so that the loads of several trips are in flight together: one trip at a time, each of the
-            // trips waits out a whole global-memory round trip)
-#pragma unroll 16
-            for (int e = tid * 2; e < (kTriN - 2) * kTriN; e += 2 * kTriThreads)
-                *reinterpret_cast<double2*>(V + e) = *reinterpret_cast<const double2*>(vws + e);
-            __syncthreads();
-            double vn[8];
-#pragma unroll
-            for (int m = 0; m < 8; ++m) vn[m] = V[(kTriN - 3) * kTriN + bs + 16 * m];
-            // (a wavefront holds four vectors per q: one whose vectors are all padding skips the loop)
-            for (int k = 4 * wave < rb ? kTriN - 3 : -1; k >= 0; --k) {
-                const double beta = L[kTriBet + k];
-                double v[8];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) v[m] = vn[m];
-                if (k > 0) {
-#pragma unroll
-                    for (int m = 0; m < 8; ++m) vn[m] = V[(k - 1) * kTriN + bs + 16 * m];
+                for (int q = 0; q < 4; ++q) {
+                    xa[c][q] = L[kTriX + 32 * (16 * wave + mk + 4 * q) + 16 * c + mi];
+                    xb[c][q] = L[kTriX + 32 * (16 * tb + mk + 4 * q) + 16 * c + mi];
                 }
-                if (beta == 0.0) continue;                    // uniform
+            __syncthreads();
+            double* Z = L + kTriX;                            // [2][4 wavefronts][NC][4][64]
 #pragma unroll
-                for (int q = 0; q < NB; ++q) {
-                    double s0 = 0.0, s1 = 0.0;
+            for (int b = 7; b >= 0; --b) {
+                const bool on_b = b <= tb, on_a = b < 4 && b <= wave;        // uniform; on_a implies on_b
+                constexpr int kWaves = kTriThreads / 64;
+                const int parts = b >= 4 ? 8 - b : kWaves;    // wavefronts 0 .. parts - 1 have a part
+                double* zw = Z + (b & 1) * (kWaves * NC * 256);
+                if (on_b) {
+                    double4v z[NC];
 #pragma unroll
-                    for (int m = 0; m < 8; m += 2) {
-                        s0 = fma(v[m], xb[q][m], s0);
-                        s1 = fma(v[m + 1], xb[q][m + 1], s1);
+                    for (int c = 0; c < NC; ++c) z[c] = double4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) z[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(vb[b][q], xb[c][q], z[c], 0, 0, 0);
+                    if (on_a) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int c = 0; c < NC; ++c) z[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[b & 3][q], xa[c][q], z[c], 0, 0, 0);
                     }
-                    const double sc = team_sum<16>(s0 + s1) * beta;
 #pragma unroll
-                    for (int m = 0; m < 8; ++m) xb[q][m] = fma(-sc, v[m], xb[q][m]);
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) zw[((wave * NC + c) * 4 + q) * 64 + lane] = z[c][q];
+                }
+                tri_lds_barrier();
+                if (on_b) {
+                    double zs[NC][4];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) zs[c][q] = zw[(c * 4 + q) * 64 + lane];
+#pragma unroll
+                    for (int w = 1; w < kWaves; ++w)
+                        if (w < parts) {
+#pragma unroll
+                            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) zs[c][q] += zw[((w * NC + c) * 4 + q) * 64 + lane];
+                        }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) {
+                            xb[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(mb[b][q], zs[c][q], xb[c], 0, 0, 0);
+                            if (on_a) xa[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[b & 3][q], zs[c][q], xa[c], 0, 0, 0);
+                        }
                 }
             }
-
-            // ---- output: rank by eigenvalue, sign so that the largest component is positive, rows sqrt(lambda) v
+            // to LDS, vector by vector (behind the exchange buffers)
+            constexpr int OLd = kTriN + 1;
+            double* O = L + kTriX + 2 * 4 * 2 * 256;
 #pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const int vj = bvj + 16 * q;
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    O[(16 * c + mi) * OLd + 16 * wave + mk + 4 * q] = xa[c][q];
+                    O[(16 * c + mi) * OLd + 16 * tb + mk + 4 * q] = xb[c][q];
+                }
+            __syncthreads();
+
+            // ---- output: team of 16 lanes per vector; rank by eigenvalue, sign so that the largest component is positive, rows
+            // sqrt(lambda) v
+            const int bs = tid & 15;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int vj = (tid >> 4) + 16 * c;
                 if (vj >= rb) continue;                       // uniform per team of 16 lanes
                 const double lam = L[kTriLam + 64 + vj];
-                int rank = 0;
-                for (int o = 0; o < rb; ++o) {
+                int before = 0;
+#pragma unroll
+                for (int o = bs; o < 32; o += 16) {
                     const double lo = L[kTriLam + 64 + o];
-                    rank += (lo > lam) || (lo == lam && o < vj);
+                    before += o < rb && ((lo > lam) || (lo == lam && o < vj));
                 }
-                double best = -1.0, bestv = 0.0;
+                double x[8], best = -1.0, bestv = 0.0;
                 int besti = kTriN;
 #pragma unroll
                 for (int m = 0; m < 8; ++m) {
-                    const double av = fabs(xb[q][m]);
-                    const int row = tri_row(bs + 16 * m);
-                    if (av > best || (av == best && row < besti)) { best = av; bestv = xb[q][m]; besti = row; }
+                    x[m] = O[vj * OLd + bs + 16 * m];
+                    const double av = fabs(x[m]);
+                    if (av > best) { best = av; bestv = x[m]; besti = bs + 16 * m; }
                 }
 #pragma unroll
                 for (int off = 8; off > 0; off >>= 1) {
+                    before += __shfl_xor(before, off, 64);
                     const double ob = __shfl_xor(best, off, 64);
                     const double ov = __shfl_xor(bestv, off, 64);
                     const int oi = __shfl_xor(besti, off, 64);
@@ -941,10 +1209,10 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
                 }
                 const double lam_true = fmax(lam, 0.0) * tmax * up;
                 const double sc = (bestv < 0.0 ? -1.0 : 1.0) * sqrt(lam_true);
-                float* dst = qhat + (joff + rank) * kTriN;
+                float* dst = qhat + (joff + before) * kTriN;
 #pragma unroll
-                for (int m = 0; m < 8; ++m) dst[tri_row(bs + 16 * m)] = static_cast<float>(xb[q][m] * sc);
-                if (eig && bs == 0) eig[joff + rank] = static_cast<float>(lam_true);
+                for (int m = 0; m < 8; ++m) dst[bs + 16 * m] = static_cast<float>(x[m] * sc);
+                if (eig && bs == 0) eig[joff + before] = static_cast<float>(lam_true);
             }
         };
         if (rb > 16)
