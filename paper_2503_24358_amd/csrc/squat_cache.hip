@@ -23,6 +23,7 @@
 #include <new>
 
 #include "squat_internal.h"
+#include "squat_residual.h"
 
 using namespace squat;
 
@@ -101,70 +102,79 @@ __global__ void __launch_bounds__(256) copy_tokens_kernel(const unsigned char* s
     *reinterpret_cast<u32x4*>(dst + (bh * slots + slot0 + t) * row_bytes + piece * 16) = v;
 }
 
-// 8 consecutive elements (16-byte aligned) as floats
-template <int DT>
-__device__ __forceinline__ void load8(const unsigned char* p, float* out) {
-    if constexpr (DT == SQUAT_F32) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(p);
-        const f32x4 b = *reinterpret_cast<const f32x4*>(p + 16);
-        out[0] = a[0]; out[1] = a[1]; out[2] = a[2]; out[3] = a[3];
-        out[4] = b[0]; out[5] = b[1]; out[6] = b[2]; out[7] = b[3];
-    } else {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+// One decoded token per (batch, KV head), keys and values in one launch: the key goes to its residual slot; the oldest value of
+// a full ring is quantized into the store and its slot takes the new one.  Eight lanes per (batch, KV head), 16 channels
+// each.  A decode step's bookkeeping moves a few hundred bytes per head, so it costs what its launches cost: three of
+// them (copy, quantize, copy) took 8.2 us of the GPU's time for 64 heads, this one takes 2.9.
+struct AppendParams {
+    const unsigned char *k, *v;      // v == NULL: keys only
+    int64_t sb, sh;                  // strides of k and v in BYTES
+    unsigned char *kres, *vres;
+    int slots, kslot, vslot;
+    int evict;                       // the value in vslot is quantized first
+    uint32_t* vcodes;
+    uint16_t *vscale, *vzero;
+    int64_t max_tokens, vtoken;      // capacity of the store, and the token it goes to
+    int group;
+    int n_heads;
+    int64_t n_bh;
+};
+
+template <int BITS, int DT>
+__global__ void __launch_bounds__(256) append_token_kernel(const AppendParams p) {
+    constexpr int ES = DT == SQUAT_F32 ? 4 : 2;
+    constexpr int NP = ES;                                // 16-byte pieces of a lane's 16 channels
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int part = static_cast<int>(i & 7);
+    const int64_t r = i >> 3;
+    if (r >= p.n_bh) return;                              // the same for the eight lanes
+    const int64_t b = r / p.n_heads, h = r % p.n_heads;
+    const int64_t src = b * p.sb + h * p.sh + part * (16 * ES);
+    const int64_t dst = r * p.slots * (kD * ES) + part * (16 * ES);
+    u32x4 kn[NP], vn[NP];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            if constexpr (DT == SQUAT_BF16) {
-                out[2 * w] = as_f32(v[w] << 16);
-                out[2 * w + 1] = as_f32(v[w] & 0xFFFF0000u);
-            } else {
-                out[2 * w] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(v[w] & 0xFFFFu)));
-                out[2 * w + 1] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(v[w] >> 16)));
-            }
+    for (int e = 0; e < NP; ++e) kn[e] = *reinterpret_cast<const u32x4*>(p.k + src + 16 * e);
+    unsigned char* vslot = p.vres + dst + static_cast<int64_t>(p.vslot) * (kD * ES);
+    float x[16];
+    if (p.v) {
+#pragma unroll
+        for (int e = 0; e < NP; ++e) vn[e] = *reinterpret_cast<const u32x4*>(p.v + src + 16 * e);
+        if (p.evict) {
+            load8<DT>(vslot, x);
+            load8<DT>(vslot + 8 * ES, x + 8);
         }
     }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) *reinterpret_cast<u32x4*>(p.kres + dst + static_cast<int64_t>(p.kslot) * (kD * ES) + 16 * e) = kn[e];
+    if (!p.v) return;
+    if (p.evict) {
+        uint32_t words[BITS / 2];
+        uint16_t sbits, zbits;
+        quantize_token<BITS>(x, p.group / 16, words, sbits, zbits);
+        const int64_t row = r * p.max_tokens + p.vtoken;
+#pragma unroll
+        for (int w = 0; w < BITS / 2; ++w) p.vcodes[row * (kD * BITS / 32) + part * (BITS / 2) + w] = words[w];
+        if ((part * 16) % p.group == 0) {
+            const int64_t g = row * (kD / p.group) + part * 16 / p.group;
+            p.vscale[g] = sbits;
+            p.vzero[g] = zbits;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) *reinterpret_cast<u32x4*>(vslot + 16 * e) = vn[e];
 }
 
-// scores[b, hq, t0 + t] = out_scale * q[b, hq, :] . res[b, hq / qpk, t, :]   for t < count.  Eight lanes per
-// (batch, KV head, token): each loads its 16 channels of the key once and meets the same channels of the
-// KV head's query heads one after the other (the buffer is read once, not once per query head); a dot
-// product is summed by three lane exchanges inside the group.  total = batch x KV heads x count.
-template <int QDT, int KDT>
-__global__ void __launch_bounds__(256) residual_scores_kernel(const unsigned char* q, int64_t qsb, int64_t qsh,
-                                                             const unsigned char* res, int slots, int count,
-                                                             int n_kv_heads, int qpk, float out_scale, float* scores,
-                                                             int64_t ssb, int64_t ssh, int64_t t0, int64_t total) {
-    constexpr int QES = QDT == SQUAT_F32 ? 4 : 2, KES = KDT == SQUAT_F32 ? 4 : 2;
-    const int64_t gi = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int part = static_cast<int>(gi & 7);
-    int64_t i = gi >> 3;
-    const bool live = i < total;
-    if (!live) i = total - 1;                      // keep the whole wavefront in the shuffles below
-    const int t = static_cast<int>(i % count);
-    const int64_t r = i / count;
-    const int kvh = static_cast<int>(r % n_kv_heads);
-    const int64_t b = r / n_kv_heads;
-    const unsigned char* krow =
-        res + ((b * n_kv_heads + kvh) * slots + t) * static_cast<int64_t>(kD) * KES + part * 16 * KES;
-    float ka[16];
-    load8<KDT>(krow, ka);
-    load8<KDT>(krow + 8 * KES, ka + 8);
-    for (int h = 0; h < qpk; ++h) {
-        const int hq = kvh * qpk + h;
-        const unsigned char* qrow = q + (b * qsb + hq * qsh) * QES + part * 16 * QES;
-        float qa[16];
-        load8<QDT>(qrow, qa);
-        load8<QDT>(qrow + 8 * QES, qa + 8);
-        float acc = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc = fmaf(qa[e], ka[e], acc);
-        acc += __shfl_xor(acc, 1, 64);
-        acc += __shfl_xor(acc, 2, 64);
-        acc += __shfl_xor(acc, 4, 64);
-        if (live && part == 0) scores[b * ssb + hq * ssh + t0 + t] = out_scale * acc;
+template <int BITS>
+void launch_append(squat_dtype dt, dim3 grid, hipStream_t s, const AppendParams& p) {
+    switch (dt) {
+        case SQUAT_F32: hipLaunchKernelGGL((append_token_kernel<BITS, SQUAT_F32>), grid, dim3(256), 0, s, p); break;
+        case SQUAT_F16: hipLaunchKernelGGL((append_token_kernel<BITS, SQUAT_F16>), grid, dim3(256), 0, s, p); break;
+        case SQUAT_BF16: hipLaunchKernelGGL((append_token_kernel<BITS, SQUAT_BF16>), grid, dim3(256), 0, s, p); break;
     }
 }
 
-// The same for keys stored before the rotary embedding: the buffered key of cache token t is rotated to position
+// Logits of the buffered keys, stored before the rotary embedding (the others are computed by the logits kernels
+// themselves, squat_residual.h): eight lanes per token; the buffered key of cache token t is rotated to position
 // pos0 + t first (pairs of channels (c, c + 64), angle position * inv_freq[c]; the partner channels sit in the
 // lane four to the side).  The angles depend on the token only, so a thread keeps its 16 (cos, sin) pairs and
 // goes over kRopeRes (batch, KV head) pairs with them.  total = ceil(batch x KV heads / kRopeRes) x count.
@@ -230,18 +240,6 @@ int launch_residual_rope(squat_dtype kdt, dim3 grid, hipStream_t s, const unsign
         case SQUAT_F32: hipLaunchKernelGGL((residual_scores_rope_kernel<QDT, SQUAT_F32>), grid, dim3(256), 0, s, q, qsb, qsh, res, slots, count, n_bh, n_kv_heads, qpk, inv_freq, pos_first, out_scale, scores, ssb, ssh, t0, total); break;
         case SQUAT_F16: hipLaunchKernelGGL((residual_scores_rope_kernel<QDT, SQUAT_F16>), grid, dim3(256), 0, s, q, qsb, qsh, res, slots, count, n_bh, n_kv_heads, qpk, inv_freq, pos_first, out_scale, scores, ssb, ssh, t0, total); break;
         case SQUAT_BF16: hipLaunchKernelGGL((residual_scores_rope_kernel<QDT, SQUAT_BF16>), grid, dim3(256), 0, s, q, qsb, qsh, res, slots, count, n_bh, n_kv_heads, qpk, inv_freq, pos_first, out_scale, scores, ssb, ssh, t0, total); break;
-    }
-    return check_launch();
-}
-
-template <int QDT>
-int launch_residual(squat_dtype kdt, dim3 grid, hipStream_t s, const unsigned char* q, int64_t qsb, int64_t qsh,
-                    const unsigned char* res, int slots, int count, int n_kv_heads, int qpk, float out_scale,
-                    float* scores, int64_t ssb, int64_t ssh, int64_t t0, int64_t total) {
-    switch (kdt) {
-        case SQUAT_F32: hipLaunchKernelGGL((residual_scores_kernel<QDT, SQUAT_F32>), grid, dim3(256), 0, s, q, qsb, qsh, res, slots, count, n_kv_heads, qpk, out_scale, scores, ssb, ssh, t0, total); break;
-        case SQUAT_F16: hipLaunchKernelGGL((residual_scores_kernel<QDT, SQUAT_F16>), grid, dim3(256), 0, s, q, qsb, qsh, res, slots, count, n_kv_heads, qpk, out_scale, scores, ssb, ssh, t0, total); break;
-        case SQUAT_BF16: hipLaunchKernelGGL((residual_scores_kernel<QDT, SQUAT_BF16>), grid, dim3(256), 0, s, q, qsb, qsh, res, slots, count, n_kv_heads, qpk, out_scale, scores, ssb, ssh, t0, total); break;
     }
     return check_launch();
 }
@@ -382,9 +380,36 @@ extern "C" int squat_cache_append(squat_cache* c, const void* k, const void* v, 
     const bool v_evict = f.quantize_values && c->n_vres == R;
     if (v_evict && c->n_vq + 1 > f.max_tokens) return SQUAT_E_BADSHAPE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // keys: into the next residual slot; a full buffer is quantized as one group of R tokens and emptied
-    int rc = copy_tokens(c, k, stride_batch, stride_head, f.d, 0, c->buf.key_residual, c->n_kres, 1, s);
+    // key into the next residual slot; if the value ring is full its oldest token is quantized and its slot takes the new
+    // token
+    AppendParams p;
+    p.k = static_cast<const unsigned char*>(k);
+    p.v = f.quantize_values ? static_cast<const unsigned char*>(v) : nullptr;
+    p.sb = stride_batch * es;
+    p.sh = stride_head * es;
+    p.kres = static_cast<unsigned char*>(c->buf.key_residual);
+    p.vres = static_cast<unsigned char*>(c->buf.value_residual);
+    p.slots = R;
+    p.kslot = c->n_kres;
+    p.vslot = v_evict ? c->v_head : (c->v_head + c->n_vres) % R;
+    p.evict = v_evict ? 1 : 0;
+    p.vcodes = c->buf.value_codes;
+    p.vscale = c->buf.value_scale;
+    p.vzero = c->buf.value_zero;
+    p.max_tokens = f.max_tokens;
+    p.vtoken = c->n_vq;
+    p.group = f.group;
+    p.n_heads = f.n_kv_heads;
+    p.n_bh = f.n_batch * f.n_kv_heads;
+    const int64_t blocks = (p.n_bh * 8 + 255) / 256;
+    if (blocks > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
+    if (f.bits == 2)
+        launch_append<2>(f.kv_dtype, dim3(static_cast<unsigned>(blocks)), s, p);
+    else
+        launch_append<4>(f.kv_dtype, dim3(static_cast<unsigned>(blocks)), s, p);
+    int rc = check_launch();
     if (rc) return rc;
+    // a full buffer is quantized as one group of R tokens and emptied
     if (flush) {
         const int64_t rsb = static_cast<int64_t>(f.n_kv_heads) * R * f.d, rsh = static_cast<int64_t>(R) * f.d;
         rc = f.key_per_channel
@@ -396,27 +421,11 @@ extern "C" int squat_cache_append(squat_cache* c, const void* k, const void* v, 
                                       c->buf.key_zero, f.max_tokens, c->n_kq, stream);
         if (rc) return rc;
     }
-    if (f.quantize_values) {
-        int slot = (c->v_head + c->n_vres) % R;
-        if (v_evict) {
-            // the ring is full: its oldest token is quantized, its slot takes the new token
-            const unsigned char* oldest = static_cast<const unsigned char*>(c->buf.value_residual) +
-                                          static_cast<int64_t>(c->v_head) * f.d * es;
-            rc = quantize_keys_into(oldest, f.kv_dtype, f.n_batch, f.n_kv_heads, 1, f.d,
-                                    static_cast<int64_t>(f.n_kv_heads) * R * f.d, static_cast<int64_t>(R) * f.d, f.d,
-                                    nullptr, 0, f.bits, f.group, f.d, c->buf.value_codes, c->buf.value_scale,
-                                    c->buf.value_zero, f.max_tokens, c->n_vq, stream);
-            if (rc) return rc;
-            slot = c->v_head;
-        }
-        rc = copy_tokens(c, v, stride_batch, stride_head, f.d, 0, c->buf.value_residual, slot, 1, s);
-        if (rc) return rc;
-        if (v_evict) {
-            c->v_head = (c->v_head + 1) % R;
-            c->n_vq += 1;
-        } else {
-            c->n_vres += 1;
-        }
+    if (v_evict) {
+        c->v_head = (c->v_head + 1) % R;
+        c->n_vq += 1;
+    } else if (f.quantize_values) {
+        c->n_vres += 1;
     }
     if (flush) {
         c->n_kq += R;
@@ -438,29 +447,15 @@ extern "C" int squat_cache_key_scores(const squat_cache* c, const void* q, squat
     if (s_stride_head < c->n_kq + c->n_kres || s_stride_batch < 0 || q_stride_head < f.d || q_stride_batch < 0)
         return SQUAT_E_BADSHAPE;
     if ((q_stride_head % 8) || (q_stride_batch % 8) || !aligned(q, 16) || !aligned(scores, 4)) return SQUAT_E_ALIGN;
-    int rc = f.key_per_channel
-                 ? key_scores_pc_from(c->buf.key_codes, c->buf.key_scale, c->buf.key_zero, f.n_batch, f.n_kv_heads,
-                                      c->n_kq, f.max_tokens, f.d, f.bits, kTileTokens, q, q_dt, f.q_per_kv,
-                                      q_stride_batch, q_stride_head, out_scale, scores, s_stride_batch,
-                                      s_stride_head, stream)
-                 : key_scores_from(c->buf.key_codes, c->buf.key_scale, c->buf.key_zero, f.n_batch, f.n_kv_heads,
-                                   c->n_kq, f.max_tokens, f.d, f.bits, f.group, q, q_dt, f.q_per_kv, q_stride_batch,
-                                   q_stride_head, out_scale, scores, s_stride_batch, s_stride_head, stream);
-    if (rc) return rc;
-    if (c->n_kres == 0) return SQUAT_OK;
-    const int64_t total = f.n_batch * f.n_kv_heads * static_cast<int64_t>(c->n_kres);
-    const int64_t blocks = (total * 8 + 255) / 256;          // eight lanes per buffered key
-    if (blocks > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
-    const dim3 grid(static_cast<unsigned>(blocks));
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const unsigned char* qp = static_cast<const unsigned char*>(q);
-    const unsigned char* res = static_cast<const unsigned char*>(c->buf.key_residual);
-    switch (q_dt) {
-        case SQUAT_F32: return launch_residual<SQUAT_F32>(f.kv_dtype, grid, s, qp, q_stride_batch, q_stride_head, res, f.residual, c->n_kres, f.n_kv_heads, f.q_per_kv, out_scale, scores, s_stride_batch, s_stride_head, c->n_kq, total);
-        case SQUAT_F16: return launch_residual<SQUAT_F16>(f.kv_dtype, grid, s, qp, q_stride_batch, q_stride_head, res, f.residual, c->n_kres, f.n_kv_heads, f.q_per_kv, out_scale, scores, s_stride_batch, s_stride_head, c->n_kq, total);
-        case SQUAT_BF16: return launch_residual<SQUAT_BF16>(f.kv_dtype, grid, s, qp, q_stride_batch, q_stride_head, res, f.residual, c->n_kres, f.n_kv_heads, f.q_per_kv, out_scale, scores, s_stride_batch, s_stride_head, c->n_kq, total);
-    }
-    return SQUAT_E_BADDTYPE;
+    const ResidualKeys res{static_cast<const unsigned char*>(c->buf.key_residual), static_cast<int>(f.kv_dtype), f.residual,
+                           c->n_kres};
+    return f.key_per_channel
+               ? key_scores_pc_from(c->buf.key_codes, c->buf.key_scale, c->buf.key_zero, f.n_batch, f.n_kv_heads, c->n_kq,
+                                    f.max_tokens, f.d, f.bits, kTileTokens, q, q_dt, f.q_per_kv, q_stride_batch,
+                                    q_stride_head, out_scale, scores, s_stride_batch, s_stride_head, &res, stream)
+               : key_scores_from(c->buf.key_codes, c->buf.key_scale, c->buf.key_zero, f.n_batch, f.n_kv_heads, c->n_kq,
+                                 f.max_tokens, f.d, f.bits, f.group, q, q_dt, f.q_per_kv, q_stride_batch, q_stride_head,
+                                 out_scale, scores, s_stride_batch, s_stride_head, &res, stream);
 }
 
 extern "C" int squat_cache_key_scores_rope(const squat_cache* c, const void* q, squat_dtype q_dt,

@@ -13,6 +13,7 @@ namespace squat {
 constexpr int kD = 128;            // head size supported by this version
 constexpr int kWave = 64;          // CDNA wavefront
 constexpr int kTileTokens = 32;    // tokens per wavefront tile (MFMA N dimension)
+constexpr float kQuantFastOffset = 32.0f;   // per-token quantizers: largest |zero| / scale for which the one-multiply-add path is used
 
 inline int elem_size(squat_dtype dt) {
     switch (dt) {
@@ -107,16 +108,17 @@ int quantize_keys_pc_into(const void* k, squat_dtype k_dt, int64_t n_batch, int 
                           int64_t k_stride_batch, int64_t k_stride_head, int64_t k_stride_token, const float* update,
                           int64_t update_stride_batch, int bits, int group, int g, uint32_t* codes, uint16_t* scale,
                           uint16_t* zero, int64_t out_stride, int64_t out_offset, squat_stream stream);
+struct ResidualKeys;               // squat_residual.h; a cache's full-precision keys, or NULL
 int key_scores_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                     int n_kv_heads, int64_t n_tokens, int64_t store_stride, int d, int bits, int group,
                     const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch, int64_t q_stride_head,
                     float out_scale, float* scores, int64_t s_stride_batch, int64_t s_stride_head,
-                    squat_stream stream);
+                    const ResidualKeys* residual, squat_stream stream);
 int key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                        int n_kv_heads, int64_t n_tokens, int64_t store_tokens, int d, int bits, int group,
                        const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch, int64_t q_stride_head,
                        float out_scale, float* scores, int64_t s_stride_batch, int64_t s_stride_head,
-                       squat_stream stream);
+                       const ResidualKeys* residual, squat_stream stream);
 
 int key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                          int n_kv_heads, int64_t n_tokens, int64_t store_stride, int d, int bits, int group,

@@ -34,7 +34,6 @@ __host__ __device__ constexpr int waves_for(int dt, int gt, int bt) {
     return dt == SQUAT_F32 ? 6 : ((bt == 2 || (gt == 4 && bt == 1)) ? 8 : 12);
 }
 constexpr int kWgsPerCU = 1;
-constexpr float kFastOffset = 32.0f;   // largest |zero| / scale for which the one-multiply-add path is used
 
 struct QuantParams {
     const unsigned char* k;
@@ -277,7 +276,7 @@ __global__ void __launch_bounds__(waves_for(DT, GT, BT) * kWave, kWgsPerCU) quan
                     g_scale[gi] = sp;
                     g_inv[gi] = inv;
                     g_top[gi] = live ? LV : 0.0f;
-                    g_risky[gi] = !(sh >= 6.2e-5f) || fabsf(g_zero[gi]) * inv > kFastOffset;
+                    g_risky[gi] = !(sh >= 6.2e-5f) || fabsf(g_zero[gi]) * inv > kQuantFastOffset;
                 }
             }
             // ---- quantize and freeze the block; keep its normalised error as MFMA B operands

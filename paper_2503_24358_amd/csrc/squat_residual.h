@@ -1,0 +1,139 @@
+// Device pieces the cache shares with the kernels it appends to and reads with: the logits of the full-precision tail of
+// a cache (computed by extra workgroups of the logits kernels, so that a decode step's logits are one launch) and the
+// per-token round-to-nearest of one token held by a team of lanes.
+#pragma once
+
+#include "squat_internal.h"
+
+namespace squat {
+
+// The full-precision keys of a cache: [batch, KV head, slots, 128], the first `count` slots in use; logit t of a row goes
+// behind the ones of the packed keys.  rows == nullptr: none.
+struct ResidualKeys {
+    const unsigned char* rows;
+    int dt;                          // squat_dtype
+    int slots;
+    int count;
+};
+
+// 8 consecutive elements (16-byte aligned) as floats
+template <int DT>
+__device__ __forceinline__ void load8(const unsigned char* p, float* out) {
+    if constexpr (DT == SQUAT_F32) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p);
+        const f32x4 b = *reinterpret_cast<const f32x4*>(p + 16);
+        out[0] = a[0]; out[1] = a[1]; out[2] = a[2]; out[3] = a[3];
+        out[4] = b[0]; out[5] = b[1]; out[6] = b[2]; out[7] = b[3];
+    } else {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if constexpr (DT == SQUAT_BF16) {
+                out[2 * w] = as_f32(v[w] << 16);
+                out[2 * w + 1] = as_f32(v[w] & 0xFFFF0000u);
+            } else {
+                out[2 * w] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(v[w] & 0xFFFFu)));
+                out[2 * w + 1] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(v[w] >> 16)));
+            }
+        }
+    }
+}
+
+// scores[b, hq, t0 + t] = out_scale * q[b, hq, :] . rows[b, kvh, t, :] for t < count and the query heads hq of KV head kvh, by
+// one workgroup of 256 threads.  Eight lanes per token: each loads its 16 channels of the key once and meets the same
+// channels of the query heads one after the other (the buffer is read once, not once per query head); a dot product
+// is summed by three lane exchanges inside the group.  (As a launch of its own behind the logits kernel: 3.8 us more
+// per decoded token for 64 heads; as one more workgroup per head it hides behind the others, 5.2 us for both.)
+template <int QDT>
+__device__ __forceinline__ void residual_scores(const ResidualKeys& r, const unsigned char* q, int64_t qsb, int64_t qsh,
+                                                int64_t b, int kvh, int n_kv_heads, int qpk, float out_scale,
+                                                float* scores, int64_t ssb, int64_t ssh, int64_t t0) {
+    constexpr int QES = QDT == SQUAT_F32 ? 4 : 2;
+    const int part = static_cast<int>(threadIdx.x) & 7;
+    const int kes = r.dt == SQUAT_F32 ? 4 : 2;
+    for (int tw = static_cast<int>(threadIdx.x >> 6) * 8; tw < r.count; tw += 32) {      // uniform per wavefront
+        const int slot = tw + ((static_cast<int>(threadIdx.x) & 63) >> 3);
+        const int t = slot < r.count ? slot : r.count - 1;                               // keep the whole wavefront in the exchanges
+        const unsigned char* krow = r.rows + (((b * n_kv_heads + kvh) * r.slots + t) * kD + part * 16) * kes;
+        float ka[16];
+        if (r.dt == SQUAT_F32) {
+            load8<SQUAT_F32>(krow, ka);
+            load8<SQUAT_F32>(krow + 32, ka + 8);
+        } else if (r.dt == SQUAT_BF16) {
+            load8<SQUAT_BF16>(krow, ka);
+            load8<SQUAT_BF16>(krow + 16, ka + 8);
+        } else {
+            load8<SQUAT_F16>(krow, ka);
+            load8<SQUAT_F16>(krow + 16, ka + 8);
+        }
+        for (int h = 0; h < qpk; ++h) {
+            const int hq = kvh * qpk + h;
+            const unsigned char* qrow = q + (b * qsb + hq * qsh) * QES + part * 16 * QES;
+            float qa[16];
+            load8<QDT>(qrow, qa);
+            load8<QDT>(qrow + 8 * QES, qa + 8);
+            float acc = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc = fmaf(qa[e], ka[e], acc);
+            acc += __shfl_xor(acc, 1, 64);
+            acc += __shfl_xor(acc, 2, 64);
+            acc += __shfl_xor(acc, 4, 64);
+            if (part == 0 && slot < r.count) scores[b * ssb + hq * ssh + t0 + slot] = out_scale * acc;
+        }
+    }
+}
+
+// Round-to-nearest (Section 2's quantizer, no update matrix) of one token held by a team of eight lanes (an aligned run of
+// the wavefront), 16 consecutive channels x per lane; groups of LG lanes.  The same arithmetic, instruction by instruction,
+// as the tile kernel of squat_quantize_keys runs with update = NULL on a tile of this one token, so the stored words are
+// the same whichever kernel a token meets.  words: BITS / 2 packed words of the lane's channels; sbits, zbits: its
+// group's scale and zero-point.
+template <int BITS>
+__device__ __forceinline__ void quantize_token(const float (&x)[16], int lg, uint32_t (&words)[BITS / 2], uint16_t& sbits,
+                                               uint16_t& zbits) {
+    constexpr float LV = static_cast<float>((1 << BITS) - 1);
+    constexpr int CPH = 16 / BITS;                        // codes per 16-bit half-word
+    float mn = x[0], mx = x[0];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        mn = fminf(mn, x[e]);
+        mx = fmaxf(mx, x[e]);
+    }
+    for (int o = 1; o < lg; o <<= 1) {                    // uniform
+        mn = raw_min(mn, __shfl_xor(mn, o, 64));
+        mx = raw_max(mx, __shfl_xor(mx, o, 64));
+    }
+    const float rng = mx - mn;
+    constexpr float RL = 1.0f / LV;
+    const float q0 = rng * RL;
+    const float dl = fmaf(fmaf(-q0, LV, rng), RL, q0);    // correctly rounded (max - min) / (2^b - 1)
+    const float sh = round_f16(dl, sbits);
+    const float mh = round_f16(mn, zbits);
+    const bool live = sh > 0.0f;
+    const float sp = live ? sh : 1.0f;
+    float inv = __builtin_amdgcn_rcpf(sp);
+    inv = fmaf(fmaf(-sp, inv, 1.0f), inv, inv);
+    const float top = live ? LV : 0.0f;
+    // the written-out form with the clamp if any group of the token needs it, else one multiply-add per code
+    const bool risky = !(sh >= 6.2e-5f) || fabsf(mh) * inv > kQuantFastOffset;
+    const uint64_t team = 0xFFull << (threadIdx.x & 56);
+    const bool clamp = (__ballot(risky) & team) != 0ull;
+    const float nmi = -mh * inv;
+    uint32_t hw[16 / CPH];
+#pragma unroll
+    for (int q = 16 / CPH - 1; q >= 0; --q) {
+        float accf = 0.0f;
+#pragma unroll
+        for (int e = CPH - 1; e >= 0; --e) {
+            const int c = q * CPH + e;
+            const float u = __builtin_amdgcn_fmed3f((x[c] - mh) * inv, 0.0f, top);
+            const float v = fmaf(x[c], inv, nmi);
+            accf = fmaf(accf, static_cast<float>(1 << BITS), __builtin_rintf(clamp ? u : v));
+        }
+        hw[q] = static_cast<uint32_t>(accf);
+    }
+#pragma unroll
+    for (int w = 0; w < BITS / 2; ++w) words[w] = hw[2 * w] | (hw[2 * w + 1] << 16);
+}
+
+}  // namespace squat

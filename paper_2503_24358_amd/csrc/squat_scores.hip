@@ -25,6 +25,7 @@
 // results, high and low rows add inside the lane, and consecutive lanes store
 // consecutive tokens of one query head.
 #include "squat_internal.h"
+#include "squat_residual.h"
 
 using namespace squat;
 
@@ -62,6 +63,7 @@ struct ScoreParams {
     float out_scale;
     int units_per_wave;
     int wide_loads;                  // rows of the store are 16-byte aligned: whole units are fetched with 16-byte loads
+    ResidualKeys res;                // (RES kernels) logits of these keys by the last workgroup along x
 };
 
 __device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi) {
@@ -69,8 +71,9 @@ __device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi) {
            (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, hi)) << 16);
 }
 
-// grid: x over slabs of kScoreWaves * units_per_wave units, y / z over (batch, KV head)
-template <int BITS, int NG, int QDT>
+// grid: x over slabs of kScoreWaves * units_per_wave units (RES: and one workgroup for the full-precision keys of the
+// (batch, KV head)), y / z over (batch, KV head)
+template <int BITS, int NG, int QDT, bool RES>
 __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const ScoreParams p) {
     constexpr int WPK = kD * BITS / 32;                   // packed words per key
     constexpr int CPG = 4 / NG;                           // 32-channel chunks per group
@@ -87,6 +90,12 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
     const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
     const int64_t b = bh / p.n_kv_heads;
     const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
+    if constexpr (RES) {
+        if (blockIdx.x + 1 == gridDim.x) {                // uniform
+            residual_scores<QDT>(p.res, p.q, p.qsb, p.qsh, b, kvh, p.n_kv_heads, p.qpk, p.out_scale, p.scores, p.ssb, p.ssh, p.n_tokens);
+            return;
+        }
+    }
 
     // ---- this wavefront's 16-token units; the loads of its first units are issued before anything else, so
     // that their latency overlaps the set-up of the query-side operands
@@ -433,13 +442,21 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
     }
 }
 
+template <int BITS, int NG, int QDT>
+void launch_res(const ScoreParams& p, dim3 grid, hipStream_t s) {
+    const dim3 block(kScoreWaves * kWave);
+    if (p.res.rows)
+        hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, true>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, false>), grid, block, 0, s, p);
+}
+
 template <int BITS, int NG>
 int launch_dt(const ScoreParams& p, dim3 grid, hipStream_t s) {
-    const dim3 block(kScoreWaves * kWave);
     switch (p.q_dt) {
-        case SQUAT_F32: hipLaunchKernelGGL((key_scores_kernel<BITS, NG, SQUAT_F32>), grid, block, 0, s, p); break;
-        case SQUAT_F16: hipLaunchKernelGGL((key_scores_kernel<BITS, NG, SQUAT_F16>), grid, block, 0, s, p); break;
-        case SQUAT_BF16: hipLaunchKernelGGL((key_scores_kernel<BITS, NG, SQUAT_BF16>), grid, block, 0, s, p); break;
+        case SQUAT_F32: launch_res<BITS, NG, SQUAT_F32>(p, grid, s); break;
+        case SQUAT_F16: launch_res<BITS, NG, SQUAT_F16>(p, grid, s); break;
+        case SQUAT_BF16: launch_res<BITS, NG, SQUAT_BF16>(p, grid, s); break;
         default: return SQUAT_E_BADDTYPE;
     }
     return check_launch();
@@ -458,12 +475,13 @@ int launch_ng(int ng, const ScoreParams& p, dim3 grid, hipStream_t s) {
 }  // namespace
 
 // squat_key_scores over the first n_tokens tokens of a store that holds store_stride tokens per
-// (batch, KV head).
+// (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, by the same launch.
 int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                            int n_kv_heads, int64_t n_tokens, int64_t store_stride, int d, int bits, int group,
                            const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch,
                            int64_t q_stride_head, float out_scale, float* scores, int64_t s_stride_batch,
-                           int64_t s_stride_head, squat_stream stream) {
+                           int64_t s_stride_head, const ResidualKeys* residual, squat_stream stream) {
+    const bool res = residual && residual->count > 0;
     if (d != kD) return SQUAT_E_BADSHAPE;
     if (bits != 2 && bits != 4) return SQUAT_E_BADSHAPE;
     if (group != 32 && group != 64 && group != 128) return SQUAT_E_BADSHAPE;
@@ -472,7 +490,7 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     if (store_stride < n_tokens) return SQUAT_E_BADSHAPE;
     if (q_dt != SQUAT_F32 && q_dt != SQUAT_F16 && q_dt != SQUAT_BF16) return SQUAT_E_BADDTYPE;
     if (!(out_scale == out_scale)) return SQUAT_E_BADVALUE;
-    if (n_batch == 0 || n_kv_heads == 0 || n_tokens == 0) return SQUAT_OK;
+    if (n_batch == 0 || n_kv_heads == 0 || (n_tokens == 0 && !res)) return SQUAT_OK;
     if (!codes || !scale || !zero || !q || !scores) return SQUAT_E_NULLPTR;
     if (q_stride_head < d || q_stride_batch < 0 || s_stride_head < n_tokens || s_stride_batch < 0) return SQUAT_E_BADSHAPE;
     if ((q_stride_head % 8) || (q_stride_batch % 8)) return SQUAT_E_ALIGN;
@@ -495,6 +513,7 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     p.n_kv_heads = n_kv_heads;
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
+    p.res = res ? *residual : ResidualKeys{nullptr, 0, 0, 0};
     {
         const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
         p.wide_loads = (store_stride * meta_row) % 16 == 0 && aligned(scale, 16) && aligned(zero, 16);
@@ -513,7 +532,7 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     if (upw < kMinUnitsPerWave) upw = kMinUnitsPerWave;
     upw += upw & 1;                                       // even: every wavefront's range starts on a 32-token line
     p.units_per_wave = static_cast<int>(upw);
-    gx = (n_units + kScoreWaves * upw - 1) / (kScoreWaves * upw);
+    gx = (n_units + kScoreWaves * upw - 1) / (kScoreWaves * upw) + (res ? 1 : 0);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {
@@ -535,5 +554,5 @@ extern "C" int squat_key_scores(const uint32_t* codes, const uint16_t* scale, co
                                 int64_t s_stride_batch, int64_t s_stride_head, squat_stream stream) {
     return squat::key_scores_from(codes, scale, zero, n_batch, n_kv_heads, n_tokens, n_tokens, d, bits, group, q,
                                   q_dt, q_per_kv, q_stride_batch, q_stride_head, out_scale, scores,
-                                  s_stride_batch, s_stride_head, stream);
+                                  s_stride_batch, s_stride_head, nullptr, stream);
 }

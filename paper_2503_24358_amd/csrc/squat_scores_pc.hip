@@ -25,6 +25,7 @@
 // chunk with the zero-points as stored as the other operand (every column gets
 // the same sum, so each lane finds it next to its own token's result).
 #include "squat_internal.h"
+#include "squat_residual.h"
 
 using namespace squat;
 
@@ -57,6 +58,7 @@ struct ScorePcParams {
     int qpk;
     float out_scale;
     int tiles_per_wave;
+    ResidualKeys res;                // (RES kernels) logits of these keys by the last workgroup along x
 };
 
 __device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi) {
@@ -71,12 +73,13 @@ __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
     return v > o ? v : o;
 }
 
-// grid: x over slabs of kPcWaves * tiles_per_wave token groups, y / z over (batch, KV head).
+// grid: x over slabs of kPcWaves * tiles_per_wave token groups (RES: and one workgroup for the full-precision keys of the
+// (batch, KV head)), y / z over (batch, KV head).
 // NT = token groups per step.  With at most four query heads per KV head only 8 of the 16 operand rows
 // are in use, so NT = 2 gives rows 0..7 to one token group and rows 8..15 to the next one (same queries,
 // the other group's scales): the instructions that build the query-side operand then serve two groups,
 // and lanes of K blocks 0, 1 find the first group's results in their registers, K blocks 2, 3 the second's.
-template <int BITS, int QDT, int NT>
+template <int BITS, int QDT, int NT, bool RES>
 __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const ScorePcParams p) {
     constexpr int W = BITS;                               // packed words per channel and token group
     constexpr int TH = 16 / BITS;                         // tokens per 16-bit half of a word: 8 or 4
@@ -95,6 +98,13 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
     const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
     const int64_t b = bh / p.n_kv_heads;
     const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
+    if constexpr (RES) {
+        if (blockIdx.x + 1 == gridDim.x) {                // uniform
+            residual_scores<QDT>(p.res, p.q, p.qsb, p.qsh, b, kvh, p.n_kv_heads, p.qpk, p.out_scale, p.scores, p.ssb, p.ssh,
+                                 static_cast<int64_t>(p.n_tiles) * 32);
+            return;
+        }
+    }
 
     // ---- this wavefront's token groups (tiles_per_wave is a multiple of NT); the loads of its first steps are
     // issued before anything else, so that their latency overlaps the set-up of the query-side registers
@@ -412,13 +422,21 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
     }
 }
 
+template <int BITS, int QDT, int NT>
+void launch_res(const ScorePcParams& p, dim3 grid, hipStream_t s) {
+    const dim3 block(kPcWaves * kWave);
+    if (p.res.rows)
+        hipLaunchKernelGGL((key_scores_pc_kernel<BITS, QDT, NT, true>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((key_scores_pc_kernel<BITS, QDT, NT, false>), grid, block, 0, s, p);
+}
+
 template <int BITS, int NT>
 int launch_dt(const ScorePcParams& p, dim3 grid, hipStream_t s) {
-    const dim3 block(kPcWaves * kWave);
     switch (p.q_dt) {
-        case SQUAT_F32: hipLaunchKernelGGL((key_scores_pc_kernel<BITS, SQUAT_F32, NT>), grid, block, 0, s, p); break;
-        case SQUAT_F16: hipLaunchKernelGGL((key_scores_pc_kernel<BITS, SQUAT_F16, NT>), grid, block, 0, s, p); break;
-        case SQUAT_BF16: hipLaunchKernelGGL((key_scores_pc_kernel<BITS, SQUAT_BF16, NT>), grid, block, 0, s, p); break;
+        case SQUAT_F32: launch_res<BITS, SQUAT_F32, NT>(p, grid, s); break;
+        case SQUAT_F16: launch_res<BITS, SQUAT_F16, NT>(p, grid, s); break;
+        case SQUAT_BF16: launch_res<BITS, SQUAT_BF16, NT>(p, grid, s); break;
         default: return SQUAT_E_BADDTYPE;
     }
     return check_launch();
@@ -427,12 +445,14 @@ int launch_dt(const ScorePcParams& p, dim3 grid, hipStream_t s) {
 }  // namespace
 
 // squat_key_scores_per_channel over the first n_tokens tokens of a store that holds store_tokens tokens
-// (a multiple of 32) per (batch, KV head).
+// (a multiple of 32) per (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, by the same
+// launch.
 int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                               int n_kv_heads, int64_t n_tokens, int64_t store_tokens, int d, int bits, int group,
                               const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch,
                               int64_t q_stride_head, float out_scale, float* scores, int64_t s_stride_batch,
-                              int64_t s_stride_head, squat_stream stream) {
+                              int64_t s_stride_head, const ResidualKeys* residual, squat_stream stream) {
+    const bool res = residual && residual->count > 0;
     if (d != kD) return SQUAT_E_BADSHAPE;
     if (bits != 2 && bits != 4) return SQUAT_E_BADSHAPE;
     if (group != 32) return SQUAT_E_BADSHAPE;
@@ -441,7 +461,7 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     if ((n_tokens % 32) || (store_tokens % 32) || store_tokens < n_tokens) return SQUAT_E_BADSHAPE;
     if (q_dt != SQUAT_F32 && q_dt != SQUAT_F16 && q_dt != SQUAT_BF16) return SQUAT_E_BADDTYPE;
     if (!(out_scale == out_scale)) return SQUAT_E_BADVALUE;
-    if (n_batch == 0 || n_kv_heads == 0 || n_tokens == 0) return SQUAT_OK;
+    if (n_batch == 0 || n_kv_heads == 0 || (n_tokens == 0 && !res)) return SQUAT_OK;
     if (!codes || !scale || !zero || !q || !scores) return SQUAT_E_NULLPTR;
     if (q_stride_head < d || q_stride_batch < 0 || s_stride_head < n_tokens || s_stride_batch < 0) return SQUAT_E_BADSHAPE;
     if ((q_stride_head % 8) || (q_stride_batch % 8)) return SQUAT_E_ALIGN;
@@ -464,6 +484,7 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     p.n_kv_heads = n_kv_heads;
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
+    p.res = res ? *residual : ResidualKeys{nullptr, 0, 0, 0};
 
     // workgroups along the sequence: about kPcWaves * aim token groups each, spread evenly
     const int64_t n_tiles = p.n_tiles;
@@ -476,7 +497,7 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     const bool two = q_per_kv <= 4;                       // two token groups per step (see the kernel)
     if (two) tpw += tpw & 1;
     p.tiles_per_wave = static_cast<int>(tpw);
-    gx = (n_tiles + kPcWaves * tpw - 1) / (kPcWaves * tpw);
+    gx = (n_tiles + kPcWaves * tpw - 1) / (kPcWaves * tpw) + (res ? 1 : 0);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {
@@ -500,5 +521,5 @@ extern "C" int squat_key_scores_per_channel(const uint32_t* codes, const uint16_
                                             squat_stream stream) {
     return squat::key_scores_pc_from(codes, scale, zero, n_batch, n_kv_heads, n_tokens, n_tokens, d, bits, group, q,
                                      q_dt, q_per_kv, q_stride_batch, q_stride_head, out_scale, scores,
-                                     s_stride_batch, s_stride_head, stream);
+                                     s_stride_batch, s_stride_head, nullptr, stream);
 }
