@@ -234,11 +234,10 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
 
     const int64_t ustride = static_cast<int64_t>(p.wgs_per_head) * kGramWaves;
-    for (int64_t unit = static_cast<int64_t>(wg) * kGramWaves + wave; unit < p.units_per_head; unit += ustride) {
+    auto load = [&](int64_t unit, f32x4 (&raw)[8]) {
         const int64_t qh = unit / p.chunks_per_qhead;
         const int64_t tok0 = (unit - qh * p.chunks_per_qhead) * 16;
         const unsigned char* base = p.q + (static_cast<int64_t>(kvh) * p.q_per_kv + qh) * p.sh + m * 16;
-        f32x4 raw[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int64_t tok = tok0 + 2 * j + hh;
@@ -247,6 +246,17 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
             else
                 raw[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
+    };
+    // the next chunk is on its way while one is multiplied
+    int64_t unit = static_cast<int64_t>(wg) * kGramWaves + wave;
+    f32x4 next[8];
+    if (unit < p.units_per_head) load(unit, next);
+    while (unit < p.units_per_head) {
+        f32x4 raw[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) raw[j] = next[j];
+        unit += ustride;
+        if (unit < p.units_per_head) load(unit, next);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -352,54 +362,57 @@ __global__ void __launch_bounds__(kRedThreads) gram_reduce(const float* partial,
     }
 }
 
-// The same sums when a head has several partials (a launch with few heads: every head's Gram kernel workgroups
-// left one each): one workgroup per (tile, head) instead of one per head, which then is bound by what one compute
-// unit can read (1.3 MB for the 32 partials of a head of a single layer: 28 us); the sums go straight to their two
-// places in the matrix (the scattered 8-byte writes are 128 KB per head).  Same order of additions, same bits.
-__global__ void __launch_bounds__(kRedThreads) gram_reduce_tiles(const float* partial, int wgs_per_head,
-                                                                 double* g64, float* gram_out, int accumulate) {
-    const int kvh = blockIdx.y, t = blockIdx.x;
-    const float* src = partial + static_cast<int64_t>(kvh) * wgs_per_head * kPartialFloats + t * 1024 + threadIdx.x;
+// The same sums with a thread per entry and as many workgroups per head as that makes: one compute unit reads the 1.3 MB
+// that the 32 partials of a head of a single layer are in 28 us; the sums go straight to their two places in the matrix
+// (the scattered 8-byte writes are 128 KB per head).  Same order of additions, same bits.
+constexpr int kRedTileThreads = 256;
+constexpr int kRedTileBlocks = kPartialFloats / kRedTileThreads;         // workgroups per head, one entry per thread
+
+__global__ void __launch_bounds__(kRedTileThreads) gram_reduce_tiles(const float* partial, int wgs_per_head,
+                                                                     double* g64, float* gram_out, int accumulate) {
+    const int kvh = blockIdx.y, idx = blockIdx.x * kRedTileThreads + threadIdx.x;
+    const float* src = partial + static_cast<int64_t>(kvh) * wgs_per_head * kPartialFloats + idx;
     double* g = g64 + static_cast<int64_t>(kvh) * kD * kD;
     float* go = gram_out ? gram_out + static_cast<int64_t>(kvh) * kD * kD : nullptr;
-    constexpr int kPer = 1024 / kRedThreads;
-    double sums[kPer];
+    double sum = 0.0;
+    int w = 0;
+    for (; w + 16 <= wgs_per_head; w += 16) {             // sixteen partials on their way at a time
+        float v[16];
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) sums[k] = 0.0;
-#pragma unroll 8
-    for (int w = 0; w < wgs_per_head; ++w) {
-        float v[kPer];
+        for (int u = 0; u < 16; ++u) v[u] = __builtin_nontemporal_load(src + static_cast<int64_t>(w + u) * kPartialFloats);
 #pragma unroll
-        for (int k = 0; k < kPer; ++k)
-            v[k] = __builtin_nontemporal_load(src + static_cast<int64_t>(w) * kPartialFloats + k * kRedThreads);
+        for (int u = 0; u < 16; ++u) sum += static_cast<double>(v[u]);
+    }
+    {
+        float v[15];
+        const int left = wgs_per_head - w;
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) sums[k] += static_cast<double>(v[k]);
+        for (int u = 0; u < 15; ++u)
+            v[u] = u < left ? __builtin_nontemporal_load(src + static_cast<int64_t>(w + u) * kPartialFloats) : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 15; ++u) sum += static_cast<double>(v[u]);
     }
     int a = 0, b = 0;
     {
         int c = 0;
         for (int i = 0; i < 4; ++i)
             for (int j = i; j < 4; ++j) {
-                if (c == t) { a = i; b = j; }
+                if (c == (idx >> 10)) { a = i; b = j; }
                 ++c;
             }
     }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int idx = threadIdx.x + k * kRedThreads;
-        const int e = (idx >> 6) & 15, lane = idx & 63;
-        const int nn = lane & 31;
-        const int mm = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        const int row = 4 * mm + a, col = 4 * nn + b;
-        if (a != b || row <= col) {
-            double v = sums[k];
-            if (accumulate) v += g[row * kD + col];
-            g[row * kD + col] = v;
-            g[col * kD + row] = v;
-            if (go) {
-                go[row * kD + col] = static_cast<float>(v);
-                go[col * kD + row] = static_cast<float>(v);
-            }
+    const int e = (idx >> 6) & 15, lane = idx & 63;
+    const int nn = lane & 31;
+    const int mm = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    const int row = 4 * mm + a, col = 4 * nn + b;
+    if (a != b || row <= col) {
+        double v = sum;
+        if (accumulate) v += g[row * kD + col];
+        g[row * kD + col] = v;
+        g[col * kD + row] = v;
+        if (go) {
+            go[row * kD + col] = static_cast<float>(v);
+            go[col * kD + row] = static_cast<float>(v);
         }
     }
 }
@@ -511,7 +524,7 @@ SubspacePlan plan(int64_t n_tokens, int n_kv_heads, int q_per_kv, int cus) {
     SubspacePlan pl;
     const int64_t units = q_per_kv * ((n_tokens + 15) / 16);
     int64_t per = (cus + n_kv_heads - 1) / n_kv_heads;          // one workgroup per CU in total
-    const int64_t need = (units + kGramWaves * 8 - 1) / (kGramWaves * 8);   // at least 8 chunks per wavefront
+    const int64_t need = (units + kGramWaves - 1) / kGramWaves;             // (room for) one chunk per wavefront
     if (per > need) per = need;
     if (per < 1) per = 1;
     pl.wgs_per_head = static_cast<int>(per);
@@ -580,11 +593,20 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     p.st = q_stride_token * es;
     p.n_tokens = n_tokens;
     p.q_per_kv = q_per_kv;
-    p.wgs_per_head = pl.wgs_per_head;
+    // Chunks per wavefront at least (the workspace has room for pl.wgs_per_head partials of a head, one CU each): every
+    // workgroup leaves a partial of 40 KB and pays ~5 us for reducing and writing it, so eight where that still makes 32
+    // workgroups, two where it does not, and two for fp32, whose chunk takes 5 k cycles on the matrix cores.  Gram and
+    // reduction, us at 8 | 2 | 1 chunks: fp32, 1 head of 512 tokens 34 | 16 | 14, 8 heads of 512 35 | 18 | 17, 1 x 4 heads of
+    // 4096 32 | 21 | 24; bf16, 1 head of 512 15.9 | 11.4 | 12.3, 8 of 512 16.4 | 13.0 | 14.9, 64 of 512 17.7 | 23.9 | 23.8.
+    const int64_t units = q_per_kv * ((n_tokens + 15) / 16);
+    const int64_t wide = (units + 8 * kGramWaves - 1) / (8 * kGramWaves);
+    const int64_t narrow = (units + 2 * kGramWaves - 1) / (2 * kGramWaves);
+    const int64_t want = q_dt == SQUAT_F32 || n_kv_heads * wide < 32 ? narrow : wide;
+    p.wgs_per_head = static_cast<int>(want < pl.wgs_per_head ? want : pl.wgs_per_head);
     p.chunks_per_qhead = (n_tokens + 15) / 16;
     p.units_per_head = p.chunks_per_qhead * q_per_kv;
     p.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + pl.off_partial);
-    const dim3 grid(static_cast<unsigned>(n_kv_heads) * pl.wgs_per_head);
+    const dim3 grid(static_cast<unsigned>(n_kv_heads) * p.wgs_per_head);
     switch (q_dt) {
         case SQUAT_BF16: hipLaunchKernelGGL(gram_partial_16<SQUAT_BF16>, grid, dim3(kGramWaves * kWave), kGramLdsBytes, s, p); break;
         case SQUAT_F16: hipLaunchKernelGGL(gram_partial_16<SQUAT_F16>, grid, dim3(kGramWaves * kWave), kGramLdsBytes, s, p); break;
@@ -592,11 +614,14 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     }
     int rc = check_launch();
     if (rc) return rc;
-    if (pl.wgs_per_head >= 4 && n_kv_heads <= 65535)
-        hipLaunchKernelGGL(gram_reduce_tiles, dim3(kTiles, static_cast<unsigned>(n_kv_heads)), dim3(kRedThreads), 0, s, p.partial,
-                           pl.wgs_per_head, g64, gram_out, accumulate);
+    // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head (us
+    // for Gram and reduction, per head | spread: 1 head, 2 partials 16.1 | 11.4; 32 heads, 1 partial 21.4 | 19.8 (fp32); 128
+    // heads, 2 partials 23.4 | 30.0; 256 heads, 1 partial 21.9 | 38.8: the scattered 8-byte writes)
+    if (p.wgs_per_head >= 4 || n_kv_heads <= 32)
+        hipLaunchKernelGGL(gram_reduce_tiles, dim3(kRedTileBlocks, static_cast<unsigned>(n_kv_heads)), dim3(kRedTileThreads), 0, s, p.partial,
+                           p.wgs_per_head, g64, gram_out, accumulate);
     else
-        hipLaunchKernelGGL(gram_reduce, dim3(n_kv_heads), dim3(kRedThreads), kRedLdsBytes, s, p.partial, pl.wgs_per_head,
+        hipLaunchKernelGGL(gram_reduce, dim3(n_kv_heads), dim3(kRedThreads), kRedLdsBytes, s, p.partial, p.wgs_per_head,
                            g64, gram_out, accumulate);
     return check_launch();
 }
