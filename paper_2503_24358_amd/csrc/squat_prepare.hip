@@ -49,12 +49,12 @@ __global__ void __launch_bounds__(256) zero_fill(float* p, int64_t n4) {
     if (i < n4) reinterpret_cast<f32x4*>(p)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// Large r (> 32; up to 64 with a finite lambda only for the heads the Cholesky kernel flags): one 1024-thread
+// Large r (> 32; up to 64 with a finite lambda only for the heads the elimination kernel flags): one 1024-thread
 // workgroup per (head, t) panel; intermediate products go through the global workspace.
 template <int TS>
 __global__ void __launch_bounds__(kPrepThreads) prepare_kernel(const PrepParams p, const int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (need && need[blockIdx.x / p.nsteps] == 0) return;  // done by the Cholesky kernel
+    if (need && need[blockIdx.x / p.nsteps] == 0) return;  // done by the elimination kernel
     constexpr int THREADS = kPrepThreads;
     const int r = p.r, rp = p.rp, g = p.g;
     double* S = reinterpret_cast<double*>(smem);     // rp x rp
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(kPrepThreads) prepare_kernel(const PrepParams 
 //   X = S^+ Qb = sum_i a_i (a_i . Qb) / mu_i^3   (rp x g),      W = -Qr^T X.
 __global__ void __launch_bounds__(192) prepare_wave_kernel(const PrepParams p, const int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (need && need[blockIdx.x] == 0) return;             // done by the Cholesky kernel
+    if (need && need[blockIdx.x] == 0) return;             // done by the elimination kernel
     const int r = p.r, rp = p.rp, g = p.g;
     constexpr int QLD = kD + 1;       // odd row stride: column reads across rows hit distinct LDS banks
     const int ld = rp + 2;            // padded row: teams of 4 lanes read different rows at the same column
@@ -196,169 +196,182 @@ __global__ void __launch_bounds__(192) prepare_wave_kernel(const PrepParams p, c
 }
 
 // r <= 64 and finite lambda: S = I/lambda + Qr Qr^T is positive definite with smallest eigenvalue
-// >= 1/lambda, so X = S^-1 Qb comes from a Cholesky factorisation instead of an eigen-decomposition.
-// One 512-thread workgroup per head does all panels, arranged so that no thread runs a long chain of
-// dependent LDS reads (RP = 32 or 64 rows: r rounded up; rows and columns >= r are the identity and cost nothing):
-//   - S: RP = 32: thread (i, k) accumulates the three 32-channel pieces of Q_i . Q_k side by side and sums them
-//     from the back (S_t needs the channels from t g on); RP = 64: a thread per 2 x 2 block of the upper triangle,
-//     mirrored;
-//   - Cholesky: one wavefront per panel, lane = row, the row in REGISTERS, right-looking (the column
-//     being eliminated goes through an LDS buffer of the wavefront, which every lane reads back at
-//     uniform addresses; 1 / sqrt(pivot) from the hardware approximation and two Newton steps, branch-free);
-//   - triangular solves: one wavefront per panel, lane = COLUMN of Qb with its RP unknowns in registers, so a
-//     step needs no exchange between lanes: the factor's entries are read at uniform LDS addresses, fetched ahead
-//     of their use, and the whole substitution is straight-line code;
-//   - W = -Qr^T X with a thread per 2 x 2 block of outputs and four accumulators per entry.
+// >= 1/lambda, so X = S^-1 Qb comes from Gauss-Jordan elimination of [S | Qb] without pivoting (the pivots are those of
+// the Cholesky factorisation) instead of an eigen-decomposition.  One workgroup per head, four wavefronts per panel, all
+// panels side by side; everything lives in the result layout of v_mfma_f64_16x16x4_f64 (lane (j = lane & 15, m = lane >> 4),
+// register q: row m + 4 q, column j of a 16 x 16 tile), NT row tiles, the column tiles dealt out to the wavefronts:
+//   - S: products of the rows of Qr on the matrix cores (fp32 entries of Qhat widened on the way);
+//   - four pivots a step: their columns go through LDS to every wavefront (one barrier, two buffers), every lane factors
+//     the 4 x 4 pivot block, the pivot rows are in the same wavefront for every column, and the update is one product per
+//     live 16 x 16 tile;
+//   - W = -Qr^T X: the solution's registers are the B operands as they are.
+// Bound by the chain of its steps (LDS exchange, four reciprocals, two dependent products).  us per launch, fallback launch
+// included, against the kernel it replaces (Cholesky with one wavefront a panel and a substitution with a lane per column,
+// whose factor entries were read from LDS one by one): 32 heads, g = 32: r = 16 28.3 -> 11.5, 32 30.8 -> 19.9, 40 65.8 -> 27.9, 64 83.0 -> 40.1;
+// g = 64: r = 16 24.6 -> 10.1, 40 56.8 -> 19.6; 256 heads, g = 32: r = 16 31.4 -> 13.6, 64 91.2 -> 46.4.  (One pivot a
+// step: 13.3, 24.8, 36.2, 54.6 for 32 heads, g = 32.)
 // A panel whose pivots span more than 1e9 (lambda times the largest eigenvalue of Qr Qr^T that large)
 // sets the head's flag: the eigen-route kernel, launched afterwards, redoes exactly the flagged heads.
-constexpr int kCholThreads = 512;           // 256 registers per thread: the Cholesky keeps a row of RP doubles in them
+typedef double double4v __attribute__((ext_vector_type(4)));
 
-constexpr size_t chol_lds_bytes(int rp, int nsteps, int g) {
-    // Qhat as fp32, the panels' matrices / factors, (RP = 32: the solutions,) the columns in flight, one flag;
-    // RP = 64 writes a panel's solutions over its factor, which is not needed any more by then
-    return ((static_cast<size_t>(rp) * (kD + 1) * sizeof(float) + 15) & ~size_t(15)) +
-           static_cast<size_t>(nsteps) * rp * ((rp + 1) + (rp == 32 ? g : 0) + 1) * sizeof(double) + 16;
+constexpr int kElimPanelThreads = 256;      // four wavefronts
+constexpr int kElimQLd = kD + 1;
+
+constexpr size_t elim_lds_bytes(int nt, int nsteps) {
+    // Qhat as fp32, two blocks of four columns in flight per panel, one flag
+    return ((static_cast<size_t>(16 * nt) * kElimQLd * sizeof(float) + 15) & ~size_t(15)) +
+           static_cast<size_t>(nsteps) * 2 * 4 * 16 * nt * sizeof(double) + 16;
 }
 
-template <int RP>
-__global__ void __launch_bounds__(kCholThreads) prepare_chol_kernel(const PrepParams p, int* need) {
-    static_assert(RP == 32 || RP == 64, "rows of a panel's matrix: one or two per lane pair of a wavefront");
+template <int NT>
+__global__ void __launch_bounds__(3 * kElimPanelThreads) prepare_elim_kernel(const PrepParams p, int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int r = p.r, g = p.g, nsteps = p.nsteps;
-    constexpr int QLD = kD + 1;
-    constexpr int LD = RP + 1;
-    constexpr bool kAlias = RP == 64;                     // the solutions X_t overwrite the factor of panel t
-    const int head = blockIdx.x, tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    float* Qf = reinterpret_cast<float*>(smem);                                   // [RP][129]
-    double* Sall = reinterpret_cast<double*>(smem + ((RP * QLD * sizeof(float) + 15) & ~size_t(15)));   // [nsteps][RP][LD]
-    double* Xall = kAlias ? Sall : Sall + nsteps * RP * LD;                       // [nsteps][RP][g] (aliased: at the panel's factor)
-    const int xstride = kAlias ? RP * LD : RP * g;                                // doubles between the panels' solutions
-    double* colbuf = Sall + nsteps * RP * LD + (kAlias ? 0 : nsteps * RP * g);    // [nsteps][RP] column in flight
-    int* bad = reinterpret_cast<int*>(colbuf + nsteps * RP);
+    constexpr int RP = 16 * NT;
+    const int r = p.r, g = p.g;
+    const int head = blockIdx.x, tid = threadIdx.x, threads = blockDim.x;
+    const int lane = tid & 63, mi = lane & 15, mk = lane >> 4;
+    const int panel = __builtin_amdgcn_readfirstlane(tid / kElimPanelThreads);           // t - 1
+    // the tiles of S are in the first NT of these; panels start with different SIMDs
+    const int wt = __builtin_amdgcn_readfirstlane(((tid >> 6) + panel) & 3);             // this wavefront's column tiles: wt, wt + 4
+    const int c0 = (panel + 1) * g, nrest = kD - c0;
+    const int ctiles = NT + g / 16;
+    float* Qf = reinterpret_cast<float*>(smem);                                          // [RP][129]
+    double* cols = reinterpret_cast<double*>(smem + ((RP * kElimQLd * sizeof(float) + 15) & ~size_t(15)));
+    int* bad = reinterpret_cast<int*>(cols + p.nsteps * 8 * RP);
+    cols += panel * 8 * RP;
     const float* Q = p.qhat + static_cast<int64_t>(head) * r * kD;
-    for (int idx = tid; idx < RP * kD; idx += kCholThreads)
-        Qf[(idx >> 7) * QLD + (idx & 127)] = idx < r * kD ? Q[idx] : 0.0f;
+    float* U = p.update + static_cast<int64_t>(head) * kD * kD;
+    for (int idx = tid; idx < RP * kD; idx += threads)
+        Qf[(idx >> 7) * kElimQLd + (idx & 127)] = idx < r * kD ? Q[idx] : 0.0f;
     if (tid == 0) bad[0] = 0;
     // Everything of this head's matrix outside the panels is zero: row i from the start of its own block of g
     // columns on (the panels, written at the end or by the eigen route, are the columns before it).
-    {
-        float* Uz = p.update + static_cast<int64_t>(head) * kD * kD;
-        for (int idx = tid; idx < kD * (kD / 4); idx += kCholThreads) {
-            const int row = idx / (kD / 4), col = 4 * (idx % (kD / 4));
-            if (col >= row / g * g) *reinterpret_cast<f32x4*>(Uz + row * kD + col) = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+    for (int idx = tid; idx < kD * (kD / 4); idx += threads) {
+        const int row = idx / (kD / 4), col = 4 * (idx % (kD / 4));
+        if (col >= row / g * g) *reinterpret_cast<f32x4*>(U + row * kD + col) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     __syncthreads();
 
-    // S_t[i][k] = [i == k] / lambda + sum_{c >= (t+1) g} Q[i][c] Q[k][c]   (rows / columns >= r: identity)
-    if constexpr (RP == 32) {
-        for (int e = tid; e < 1024; e += kCholThreads) {
-            const int i = e >> 5, k = e & 31;
-            const float* qi = Qf + i * QLD;
-            const float* qk = Qf + k * QLD;
-            double piece[3] = {0.0, 0.0, 0.0};                // channels 32..63, 64..95, 96..127
-#pragma unroll 8
-            for (int c = 0; c < 32; ++c) {
+    // ---- [S | Qb]
+    double a[2][NT][4];
 #pragma unroll
-                for (int b = 0; b < 3; ++b)
-                    piece[b] = fma(static_cast<double>(qi[32 * (b + 1) + c]), static_cast<double>(qk[32 * (b + 1) + c]), piece[b]);
-            }
-            const double diag = i == k ? (i < r ? p.inv_lambda : 1.0) : 0.0;
-            for (int t = 0; t < nsteps; ++t) {
-                double s = diag;
-                for (int b = (t + 1) * (g / 32) - 1; b < 3; ++b) s += piece[b];
-                Sall[(t * RP + i) * LD + k] = s;
-            }
-        }
-    } else {
-        // 2 x 2 blocks (rows 2 ti.., columns 2 tk.., ti <= tk) of the upper triangle: 528 of them, folded into a
-        // 16 x 33 rectangle of indices
-        for (int e = tid; e < 528; e += kCholThreads) {
-            const int fa = e / 33, fb = e % 33;
-            const int ti = fb > fa ? fa : 31 - fa;
-            const int tk = fb > fa ? fb - 1 : 31 - fa + fb;
-            const int i0 = 2 * ti, k0 = 2 * tk;
-            double piece[2][2][3];
+    for (int s = 0; s < 2; ++s) {
+        const int ct = wt + 4 * s;
 #pragma unroll
-            for (int q = 0; q < 12; ++q) (&piece[0][0][0])[q] = 0.0;
-            if (k0 < r) {                                 // (i0 <= k0; beyond r the rows of Qhat are zero)
-                const float* qi = Qf + i0 * QLD;
-                const float* qk = Qf + k0 * QLD;
+        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[s][ti][q] = 0.0;
+        if (s == 0 && ct < NT) {                          // uniform; (NT <= 4: the tiles of S are all in slot 0)
+            double4v acc[NT];
+#pragma unroll
+            for (int ti = 0; ti < NT; ++ti) acc[ti] = double4v{0.0, 0.0, 0.0, 0.0};
+            const float* qc = Qf + (16 * ct + mi) * kElimQLd + c0 + mk;
+            const float* qr = Qf + mi * kElimQLd + c0 + mk;
 #pragma unroll 4
-                for (int c = 0; c < 32; ++c) {
+            for (int c = 0; c < nrest; c += 4) {
+                const double bq = static_cast<double>(qc[c]);
 #pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-                        const double i_0 = static_cast<double>(qi[32 * (b + 1) + c]), i_1 = static_cast<double>(qi[QLD + 32 * (b + 1) + c]);
-                        const double k_0 = static_cast<double>(qk[32 * (b + 1) + c]), k_1 = static_cast<double>(qk[QLD + 32 * (b + 1) + c]);
-                        piece[0][0][b] = fma(i_0, k_0, piece[0][0][b]);
-                        piece[0][1][b] = fma(i_0, k_1, piece[0][1][b]);
-                        piece[1][0][b] = fma(i_1, k_0, piece[1][0][b]);
-                        piece[1][1][b] = fma(i_1, k_1, piece[1][1][b]);
-                    }
-                }
+                for (int ti = 0; ti < NT; ++ti)
+                    acc[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(qr[16 * ti * kElimQLd + c]), bq, acc[ti], 0, 0, 0);
             }
 #pragma unroll
-            for (int ia = 0; ia < 2; ++ia)
+            for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-                for (int ka = 0; ka < 2; ++ka) {
-                    const int i = i0 + ia, k = k0 + ka;
-                    const double diag = i == k ? (i < r ? p.inv_lambda : 1.0) : 0.0;
-                    for (int t = 0; t < nsteps; ++t) {
-                        double s = diag;
-                        for (int b = (t + 1) * (g / 32) - 1; b < 3; ++b) s += piece[ia][ka][b];
-                        Sall[(t * RP + i) * LD + k] = s;
-                        Sall[(t * RP + k) * LD + i] = s;
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    const int row = 16 * ti + mk + 4 * q;
+                    // rows / columns >= r: the identity
+                    a[0][ti][q] = acc[ti][q] + (row == 16 * ct + mi ? (row < r ? p.inv_lambda : 1.0) : 0.0);
                 }
+        } else if (ct < ctiles) {
+#pragma unroll
+            for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    a[s][ti][q] = static_cast<double>(Qf[(16 * ti + mk + 4 * q) * kElimQLd + (c0 - g) + 16 * (ct - NT) + mi]);
         }
     }
-    __syncthreads();
 
-    // Cholesky S = C C^T, one wavefront per panel; C goes back to LDS with 1 / C_jj on the diagonal
-    if (wave < nsteps) {
-        double* S = Sall + wave * RP * LD;
-        double* col = colbuf + wave * RP;
-        const int row = lane & (RP - 1);                  // RP = 32: lanes 32..63 mirror lanes 0..31 (same values, same addresses)
-        double a[RP];
+    // ---- elimination, four pivots at a time: rows 16 kt + 4 kq .. + 3 are register kq of the row tile kt, i.e. the four pivot
+    // rows R of a column tile are a B operand as they are.  [..] <- P^-1 R for the pivot block P, and A - C (P^-1 R) for the rest
+    double pmin = 1e300, pmax = 0.0;
 #pragma unroll
-        for (int c = 0; c < RP; ++c) a[c] = S[row * LD + c];
-        double pmin = 1e300, pmax = 0.0;
+    for (int kt = 0; kt < NT; ++kt) {
+        const bool live0 = wt >= kt && wt < ctiles, live1 = wt + 4 < ctiles;             // uniform (tiles of S before kt are done)
 #pragma unroll
-        for (int j = 0; j < RP; ++j) {
-            if (j < r) {                                  // uniform; the rows and columns from r on are the identity already
-                // column j of the trailing matrix: through the wavefront's own buffer (a wavefront's LDS accesses
-                // complete in order, so the reads see this write), read back at addresses that are the same in every lane
-                col[row] = a[j];
-                const double piv = col[j];
-                pmin = fmin(pmin, piv);
-                pmax = fmax(pmax, piv);
-                // 1 / sqrt(pivot) without the library routines' branches (with them the compiler keeps the column's
-                // loads live across the branch and spills); two Newton steps reach the last bit
-                double y = __builtin_amdgcn_rsq(piv);
+        for (int kq = 0; kq < 4; ++kq) {
+            const int k0 = 16 * kt + 4 * kq;
+            if (k0 >= r) continue;                        // uniform: the rows from r on are the identity already
+            double* col = cols + (kq & 1) * 4 * RP;       // [4 columns][row 16 t + m + 4 q at 16 t + 4 m + q]
+            if (wt == kt && (mi >> 2) == kq) {
+                double* dst = col + (mi & 3) * RP + 4 * mk;
 #pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    const double e = fma(-piv * y, y, 1.0);
-                    y = fma(0.5 * y, e, y);
+                for (int ti = 0; ti < NT; ++ti) {
+                    *reinterpret_cast<double2*>(dst + 16 * ti) = double2{a[0][ti][0], a[0][ti][1]};
+                    *reinterpret_cast<double2*>(dst + 16 * ti + 2) = double2{a[0][ti][2], a[0][ti][3]};
                 }
-                const double rs = piv > 0.0 ? y : 0.0;
-                const double lj = a[j] * rs;              // column j of C (rows > j), garbage above the diagonal
-                a[j] = row == j ? rs : lj;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            // the pivot block (its lower triangle: row k0 + i, column k0 + j)
+            const double* pb = col + 16 * kt + kq;
+            double p[4][4], cm[NT];
 #pragma unroll
-                for (int k2 = j + 1; k2 < RP; ++k2) {
-                    a[k2] = fma(-lj, col[k2] * rs, a[k2]);
-                    // (half a long column at a time, so that its loads and the row fit the registers)
-                    if (RP == 64 && k2 == j + 32) asm volatile("" ::: "memory");
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = j; i < 4; ++i) p[i][j] = pb[j * RP + 4 * i];
+#pragma unroll
+            for (int ti = 0; ti < NT; ++ti) cm[ti] = -col[mk * RP + 16 * ti + 4 * (mi & 3) + (mi >> 2)];
+            // P = L D L', every lane; then column mk of P^-1
+            double d[4], l[4][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // 1 / pivot from the hardware approximation and two Newton steps
+                const double piv = p[j][j];
+                double y = __builtin_amdgcn_rcp(piv);
+#pragma unroll
+                for (int it = 0; it < 2; ++it) y = fma(y, fma(-piv, y, 1.0), y);
+                d[j] = y;
+                if (k0 + j < r) {                         // uniform
+                    pmin = fmin(pmin, piv);
+                    pmax = fmax(pmax, piv);
                 }
-                asm volatile("" ::: "memory");            // the next step's write stays behind these reads
+#pragma unroll
+                for (int i = j + 1; i < 4; ++i) l[i][j] = p[i][j] * y;
+#pragma unroll
+                for (int j2 = j + 1; j2 < 4; ++j2)
+#pragma unroll
+                    for (int i = j2; i < 4; ++i) p[i][j2] = fma(-l[i][j], p[j2][j], p[i][j2]);
+            }
+            double x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[i] = mk == i ? 1.0 : 0.0;
+#pragma unroll
+                for (int j = 0; j < i; ++j) x[i] = fma(-l[i][j], x[j], x[i]);
+            }
+#pragma unroll
+            for (int i = 3; i >= 0; --i) {
+                x[i] *= d[i];
+#pragma unroll
+                for (int j = i + 1; j < 4; ++j) x[i] = fma(-l[j][i], x[j], x[i]);
+            }
+            const double inv_op = mi == 0 ? x[0] : (mi == 1 ? x[1] : (mi == 2 ? x[2] : (mi == 3 ? x[3] : 0.0)));
+            const double4v zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (!(s == 0 ? live0 : live1)) continue;  // uniform
+                const double4v rs = __builtin_amdgcn_mfma_f64_16x16x4f64(inv_op, a[s][kt][kq], zero, 0, 0, 0);
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti) {
+                    double4v t = {a[s][ti][0], a[s][ti][1], a[s][ti][2], a[s][ti][3]};
+                    t = __builtin_amdgcn_mfma_f64_16x16x4f64(cm[ti], rs[0], t, 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) a[s][ti][q] = t[q];
+                }
+                a[s][kt][kq] = rs[0];
             }
         }
-        if (lane < RP) {
-#pragma unroll
-            for (int c = 0; c < RP; ++c) S[row * LD + c] = c > row ? 0.0 : a[c];
-        }
-        if (lane == 0 && !(pmin > 1e-9 * pmax)) atomicOr(bad, 1);       // also catches NaN
     }
+    if ((tid & (kElimPanelThreads - 1)) == 0 && !(pmin > 1e-9 * pmax)) atomicOr(bad, 1);
     __syncthreads();
     if (bad[0]) {                                          // uniform: leave this head to the eigen route
         if (tid == 0) need[head] = 1;
@@ -366,167 +379,23 @@ __global__ void __launch_bounds__(kCholThreads) prepare_chol_kernel(const PrepPa
     }
     if (tid == 0) need[head] = 0;
 
-    // X = S^-1 Qb, one wavefront per panel, lane j = column j of Qb (g = 32: half a wavefront): the column's
-    // entries live in registers and both substitutions are straight-line code whose only memory traffic is the
-    // factor, read at addresses that are the same in every lane.  (With a lane per ROW and the unknown of every
-    // step broadcast between the lanes, the LDS crossbar bounded this phase: 26 of the kernel's 50 us.)
-    if (wave < nsteps && lane < g) {
-        const double* C = Sall + wave * RP * LD;
-        double b[RP];
+    // ---- W_t[c][j] = -sum_k Q[k][c0 + c] X[k][j]
 #pragma unroll
-        for (int k = 0; k < RP; ++k) b[k] = static_cast<double>(Qf[k * QLD + wave * g + lane]);
-        if constexpr (RP == 32) {
-            // The factor's column (row) of step k + 1 is fetched while step k computes; the fences keep the compiler
-            // from hoisting every load of the block to its top (which spills the registers).
-            double cur[32], nxt[32];
-            // forward: y_k = b_k / C_kk, then b_i -= C_ik y_k for i > k
-#pragma unroll
-            for (int i = 0; i < 32; ++i) cur[i] = C[i * LD];
-#pragma unroll
-            for (int k = 0; k < 32; ++k) {
-                if (k + 1 < 32) {
-#pragma unroll
-                    for (int i = k + 1; i < 32; ++i) nxt[i] = C[i * LD + k + 1];
-                }
-                b[k] *= cur[k];                           // the diagonal holds 1 / C_kk
-#pragma unroll
-                for (int i = k + 1; i < 32; ++i) b[i] = fma(-cur[i], b[k], b[i]);
-                asm volatile("" ::: "memory");
-#pragma unroll
-                for (int i = k + 1; i < 32; ++i) cur[i] = nxt[i];
-            }
-            // backward: x_k = y_k / C_kk, then y_i -= C_ki x_k for i < k
-#pragma unroll
-            for (int i = 0; i < 32; ++i) cur[i] = C[31 * LD + i];
-#pragma unroll
-            for (int k = 31; k >= 0; --k) {
-                if (k > 0) {
-#pragma unroll
-                    for (int i = 0; i < k; ++i) nxt[i] = C[(k - 1) * LD + i];
-                }
-                b[k] *= cur[k];
-#pragma unroll
-                for (int i = 0; i < k; ++i) b[i] = fma(-cur[i], b[k], b[i]);
-                asm volatile("" ::: "memory");
-#pragma unroll
-                for (int i = 0; i < k; ++i) cur[i] = nxt[i];
-            }
-        } else {
-            // 64 unknowns leave room for 16 entries of the factor at a time and 16 more on their way: a step's column
-            // (row) is taken in pieces of 16, the next piece (of this step or the next) fetched while one is used.
-            // Steps from r on meet zeros and the identity and are skipped (uniform).
-            constexpr int PC = 16;
-            double cur[PC], nxt[PC], dcur, dnxt = 0.0;
-            // forward: y_k = b_k / C_kk, then b_i -= C_ik y_k for i > k
-            dcur = C[0];
-#pragma unroll
-            for (int e = 0; e < PC; ++e) cur[e] = C[(1 + e) * LD];
-#pragma unroll
-            for (int k = 0; k < RP; ++k) {
-                if (k >= r) continue;                     // uniform: the unknowns from r on are zero
-                b[k] *= dcur;                             // the diagonal holds 1 / C_kk
-                if (k + 1 < RP) dnxt = C[(k + 1) * LD + k + 1];
-#pragma unroll
-                for (int pc = 0; pc < RP / PC; ++pc) {    // (a constant number of trips, so that the loop unrolls)
-                    const int i0 = k + 1 + pc * PC;
-                    if (i0 >= RP) continue;
-                    // the piece after this one: further down this column, or the head of the next
-                    if (i0 + PC < RP) {
-#pragma unroll
-                        for (int e = 0; e < PC; ++e)
-                            if (i0 + PC + e < RP) nxt[e] = C[(i0 + PC + e) * LD + k];
-                    } else if (k + 2 < RP) {
-#pragma unroll
-                        for (int e = 0; e < PC; ++e)
-                            if (k + 2 + e < RP) nxt[e] = C[(k + 2 + e) * LD + k + 1];
-                    }
-#pragma unroll
-                    for (int e = 0; e < PC; ++e)
-                        if (i0 + e < RP) b[i0 + e] = fma(-cur[e], b[k], b[i0 + e]);
-                    asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int e = 0; e < PC; ++e) cur[e] = nxt[e];
-                }
-                dcur = dnxt;
-            }
-            // backward: x_k = y_k / C_kk, then y_i -= C_ki x_k for i < k (row k of the factor, from its start); the
-            // first step that counts is r - 1, so every step fetches its own first piece and the later ones ahead
-#pragma unroll
-            for (int k = RP - 1; k >= 0; --k) {
-                if (k >= r) continue;                     // uniform
-                dcur = C[k * LD + k];
-#pragma unroll
-                for (int e = 0; e < PC; ++e)
-                    if (e < k) cur[e] = C[k * LD + e];
-                b[k] *= dcur;
-#pragma unroll
-                for (int pc = 0; pc < RP / PC; ++pc) {
-                    const int i0 = pc * PC;
-                    if (i0 >= k) continue;
-                    if (i0 + PC < k) {
-#pragma unroll
-                        for (int e = 0; e < PC; ++e)
-                            if (i0 + PC + e < k) nxt[e] = C[k * LD + i0 + PC + e];
-                    }
-#pragma unroll
-                    for (int e = 0; e < PC; ++e)
-                        if (i0 + e < k) b[i0 + e] = fma(-cur[e], b[k], b[i0 + e]);
-                    asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int e = 0; e < PC; ++e) cur[e] = nxt[e];
-                }
-            }
-        }
-        // (aliased: every lane of the wavefront is past its last read of the factor here)
-#pragma unroll
-        for (int k = 0; k < RP; ++k) Xall[wave * xstride + k * g + lane] = b[k];
-    }
-    __syncthreads();
-
-    // W_t[c][j] = -sum_k Q[k][(t+1) g + c] X_t[k][j], a thread per 2 x 2 block of outputs (two LDS reads feed
-    // four multiply-adds), the blocks of all panels dealt out in one run (1536 at g = 32: three per thread)
-    float* U = p.update + static_cast<int64_t>(head) * kD * kD;
-    const int hg = g / 2;
-    int total = 0;
-    for (int t = 0; t < nsteps; ++t) total += (kD - (t + 1) * g) * g / 4;
-    for (int q0 = tid; q0 < total; q0 += kCholThreads) {
-        int t = 0, q = q0;
-        while (q >= (kD - (t + 1) * g) * g / 4) {
-            q -= (kD - (t + 1) * g) * g / 4;
-            ++t;
-        }
-        const int c0 = (t + 1) * g;
-        const int c = 2 * (q / hg), j = 2 * (q % hg);
-        const double* X = Xall + t * xstride + j;
-        const float* Qc = Qf + c0 + c;
-        double s4[2][2][4];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) (&s4[0][0][0])[e] = 0.0;
-        auto term = [&](int k, int slot) {
-            const double qa = static_cast<double>(Qc[k * QLD]), qb = static_cast<double>(Qc[k * QLD + 1]);
-            const double2 x = *reinterpret_cast<const double2*>(X + k * g);
-            s4[0][0][slot] = fma(qa, x.x, s4[0][0][slot]);
-            s4[0][1][slot] = fma(qa, x.y, s4[0][1][slot]);
-            s4[1][0][slot] = fma(qb, x.x, s4[1][0][slot]);
-            s4[1][1][slot] = fma(qb, x.y, s4[1][1][slot]);
-        };
-        if constexpr (RP == 32) {
-#pragma unroll
-            for (int k = 0; k < 32; ++k) term(k, k & 3);
-        } else {
-            const int kmax = (r + 3) & ~3;                // rows from r on are zero on both sides
+    for (int s = 0; s < 2; ++s) {
+        const int ct = wt + 4 * s;
+        if (ct < NT || ct >= ctiles) continue;             // uniform
+        float* dst = U + (c0 - g) + 16 * (ct - NT) + mi;
 #pragma unroll 2
-            for (int k4 = 0; k4 < kmax; k4 += 4) {
+        for (int c = 0; c < nrest; c += 16) {
+            double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) term(k4 + kk, kk);
-            }
-        }
+            for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            float2 o;
-            o.x = stored_entry(-((s4[a][0][0] + s4[a][0][1]) + (s4[a][0][2] + s4[a][0][3])), p.full);
-            o.y = stored_entry(-((s4[a][1][0] + s4[a][1][1]) + (s4[a][1][2] + s4[a][1][3])), p.full);
-            *reinterpret_cast<float2*>(U + (c0 + c + a) * kD + (c0 - g) + j) = o;
+                for (int q = 0; q < 4; ++q)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(Qf[(16 * ti + 4 * q + mk) * kElimQLd + c0 + c + mi]),
+                                                               a[s][ti][q], acc, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) dst[(c0 + c + mk + 4 * q) * kD] = stored_entry(-acc[q], p.full);
         }
     }
 }
@@ -552,7 +421,7 @@ extern "C" size_t squat_prepare_workspace(int n_heads, int d, int r, int g) {
 namespace {
 
 // Bytes of the two scratch pieces a call uses: `yz` (intermediate products of the r > 32 kernel) and
-// `flags` (one int per head, written by the Cholesky kernel and read by the eigen-route kernel that follows
+// `flags` (one int per head, written by the elimination kernel and read by the eigen-route kernel that follows
 // it).  Both are fully written before they are read, so neither needs clearing.
 struct PrepScratch {
     size_t yz_bytes, flag_bytes;
@@ -572,10 +441,10 @@ int prepare_impl(const float* qhat, int n_heads, int r, float lambda, int g, uns
                  double* yz, int* flags, hipStream_t s) {
     const int nsteps = kD / g - 1;
     const bool trivial = (r == 0 || lambda == 0.0f || nsteps == 0);
-    // The Cholesky route's kernel clears its heads' matrices itself; every other route starts from a cleared tensor.
-    const bool chol_route = !trivial && r <= 64 && !isinf(lambda);
+    // The elimination kernel clears its heads' matrices itself; every other route starts from a cleared tensor.
+    const bool elim_route = !trivial && r <= 64 && !isinf(lambda);
     int rc = SQUAT_OK;
-    if (!chol_route) {
+    if (!elim_route) {
         const int64_t n4 = static_cast<int64_t>(n_heads) * kD * kD / 4;
         hipLaunchKernelGGL(zero_fill, dim3(static_cast<unsigned>((n4 + 255) / 256)), dim3(256), 0, s, update, n4);
         rc = check_launch();
@@ -595,14 +464,15 @@ int prepare_impl(const float* qhat, int n_heads, int r, float lambda, int g, uns
     p.inv_lambda = p.hard ? 0.0 : 1.0 / static_cast<double>(lambda);
     p.nprob = n_heads * nsteps;
     const int* need = nullptr;
-    if (chol_route) {
-        static std::atomic<uint64_t> chol32_done{0}, chol64_done{0};
-        if (p.rp <= 32) {
-            if ((rc = set_max_lds_once(chol32_done, reinterpret_cast<const void*>(prepare_chol_kernel<32>), 140 * 1024))) return rc;
-            hipLaunchKernelGGL(prepare_chol_kernel<32>, dim3(n_heads), dim3(kCholThreads), chol_lds_bytes(32, nsteps, g), s, p, flags);
-        } else {
-            if ((rc = set_max_lds_once(chol64_done, reinterpret_cast<const void*>(prepare_chol_kernel<64>), 140 * 1024))) return rc;
-            hipLaunchKernelGGL(prepare_chol_kernel<64>, dim3(n_heads), dim3(kCholThreads), chol_lds_bytes(64, nsteps, g), s, p, flags);
+    if (elim_route) {
+        const int nt = (r + 15) / 16;
+        const dim3 block(kElimPanelThreads * nsteps);
+        const size_t lds = elim_lds_bytes(nt, nsteps);     // 45 KB at most
+        switch (nt) {
+            case 1: hipLaunchKernelGGL(prepare_elim_kernel<1>, dim3(n_heads), block, lds, s, p, flags); break;
+            case 2: hipLaunchKernelGGL(prepare_elim_kernel<2>, dim3(n_heads), block, lds, s, p, flags); break;
+            case 3: hipLaunchKernelGGL(prepare_elim_kernel<3>, dim3(n_heads), block, lds, s, p, flags); break;
+            default: hipLaunchKernelGGL(prepare_elim_kernel<4>, dim3(n_heads), block, lds, s, p, flags); break;
         }
         rc = check_launch();
         if (rc) return rc;
