@@ -179,12 +179,17 @@ inline int64_t units_per_wave(int64_t units, int64_t sequences, int waves, int64
     return spread > most ? most : (spread < least ? least : spread);
 }
 
-// Number of compute units of the current device (256 if the query fails).
+// Number of compute units of the current device (256 if the query fails); a device is asked once per process.
 inline int device_cu_count() {
+    static std::atomic<int> known[64];
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 256;
+    std::atomic<int>& slot = known[dev & 63];
+    if (dev < 64) cus = slot.load(std::memory_order_relaxed);
+    if (cus > 0) return cus;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return 256;
+    if (dev < 64) slot.store(cus, std::memory_order_relaxed);
     return cus;
 }
 

@@ -146,14 +146,20 @@ def strerror(status: int) -> str:
     return lib().squat_strerror(int(status)).decode()
 
 
+# The handle of the current device's current stream without a Stream object around it (0.4 us against 3.1 us, a fifth of
+# what a small call costs the host).
+_device = torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(_device()) if _raw_stream is not None else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need_cuda(*ts):
