@@ -14,7 +14,32 @@ struct ResidualKeys {
     int dt;                          // squat_dtype
     int slots;
     int count;
+    // set by residual_grid: grid rows (y) from first_row on belong to these keys, a wavefront per eight of them; a grid
+    // layer (z) holds heads_y (batch, KV head) pairs
+    unsigned first_row;
+    int heads_y;
 };
+
+constexpr int kResTokens = 8;            // keys per wavefront
+constexpr int kResWaves = 4;             // wavefronts per workgroup: that of the logits kernels
+
+// The grid of a logits launch with gx workgroups for the packed keys of each of gy x gz (batch, KV head) pairs (gx = 0: no
+// packed keys), extended by the rows for the full-precision keys.  These come behind the others and not as one more
+// column: with one workgroup per pair before it, a column puts all short workgroups on every other XCD and all long ones
+// on the rest (16384 pairs of 2048 tokens and 16 full-precision keys: 530 us against 394).  False: the rows do not fit, the caller
+// launches twice (the second time with gx = 0).
+constexpr int64_t kMaxGridRows = 65535;
+
+inline bool residual_grid(ResidualKeys& r, int64_t gx, int64_t gy, int64_t gz, dim3& grid) {
+    const int64_t workgroups = (gy * ((r.count + kResTokens - 1) / kResTokens) + kResWaves - 1) / kResWaves;
+    const int64_t wide = gx > 0 ? gx : workgroups, first = gx > 0 ? gy : 0;
+    const int64_t rows = first + (workgroups + wide - 1) / wide;
+    if (rows > kMaxGridRows) return false;
+    r.first_row = static_cast<unsigned>(first);
+    r.heads_y = static_cast<int>(gy);
+    grid = dim3(static_cast<unsigned>(wide), static_cast<unsigned>(rows), static_cast<unsigned>(gz));
+    return true;
+}
 
 // 8 consecutive elements (16-byte aligned) as floats
 template <int DT>
@@ -39,46 +64,60 @@ __device__ __forceinline__ void load8(const unsigned char* p, float* out) {
     }
 }
 
-// scores[b, hq, t0 + t] = out_scale * q[b, hq, :] . rows[b, kvh, t, :] for t < count and the query heads hq of KV head kvh, by
-// one workgroup of 256 threads.  Eight lanes per token: each loads its 16 channels of the key once and meets the same
-// channels of the query heads one after the other (the buffer is read once, not once per query head); a dot product
-// is summed by three lane exchanges inside the group.  (As a launch of its own behind the logits kernel: 3.8 us more
-// per decoded token for 64 heads; as one more workgroup per head it hides behind the others, 5.2 us for both.)
-template <int QDT>
-__device__ __forceinline__ void residual_scores(const ResidualKeys& r, const unsigned char* q, int64_t qsb, int64_t qsh,
-                                                int64_t b, int kvh, int n_kv_heads, int qpk, float out_scale,
-                                                float* scores, int64_t ssb, int64_t ssh, int64_t t0) {
+// scores[b, hq, t0 + t] = out_scale * q[b, hq, :] . rows[b, kvh, t, :] for t < count and the query heads hq of KV head kvh:
+// called by every workgroup from row p.res.first_row on, each wavefront takes eight keys of one (batch, KV head).  Eight
+// lanes per key: each loads its 16 channels of the key once and meets the same channels of the query heads one after
+// the other (the buffer is read once, not once per query head); a dot product is summed by three lane exchanges
+// inside the group.  (As a launch of its own behind the logits kernel: 3.8 us more per decoded token for 64
+// heads; by the workgroups of the same launch it hides behind the others, 5.2 us for both.)
+template <int QDT, typename Params>
+__device__ __forceinline__ void residual_scores(const Params& p, int64_t t0) {
     constexpr int QES = QDT == SQUAT_F32 ? 4 : 2;
+    const ResidualKeys& r = p.res;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const unsigned i = ((blockIdx.y - r.first_row) * gridDim.x + blockIdx.x) * kResWaves + wave;
+    const unsigned chunks = static_cast<unsigned>(r.count + kResTokens - 1) / kResTokens;
+    const unsigned head = i / chunks;
+    if (head >= static_cast<unsigned>(r.heads_y)) return;                            // uniform per wavefront
+    const int64_t bh = static_cast<int64_t>(blockIdx.z) * r.heads_y + head;
+    const int64_t b = bh / p.n_kv_heads;
+    const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
     const int part = static_cast<int>(threadIdx.x) & 7;
     const int kes = r.dt == SQUAT_F32 ? 4 : 2;
-    for (int tw = static_cast<int>(threadIdx.x >> 6) * 8; tw < r.count; tw += 32) {      // uniform per wavefront
-        const int slot = tw + ((static_cast<int>(threadIdx.x) & 63) >> 3);
-        const int t = slot < r.count ? slot : r.count - 1;                               // keep the whole wavefront in the exchanges
-        const unsigned char* krow = r.rows + (((b * n_kv_heads + kvh) * r.slots + t) * kD + part * 16) * kes;
-        float ka[16];
-        if (r.dt == SQUAT_F32) {
-            load8<SQUAT_F32>(krow, ka);
-            load8<SQUAT_F32>(krow + 32, ka + 8);
-        } else if (r.dt == SQUAT_BF16) {
-            load8<SQUAT_BF16>(krow, ka);
-            load8<SQUAT_BF16>(krow + 16, ka + 8);
-        } else {
-            load8<SQUAT_F16>(krow, ka);
-            load8<SQUAT_F16>(krow + 16, ka + 8);
+    const int slot = static_cast<int>(i - head * chunks) * kResTokens + ((static_cast<int>(threadIdx.x) & 63) >> 3);
+    const int t = slot < r.count ? slot : r.count - 1;                               // keep the whole wavefront in the exchanges
+    const unsigned char* krow = r.rows + ((bh * r.slots + t) * kD + part * 16) * kes;
+    float ka[16];
+    if (r.dt == SQUAT_F32) {
+        load8<SQUAT_F32>(krow, ka);
+        load8<SQUAT_F32>(krow + 32, ka + 8);
+    } else if (r.dt == SQUAT_BF16) {
+        load8<SQUAT_BF16>(krow, ka);
+        load8<SQUAT_BF16>(krow + 16, ka + 8);
+    } else {
+        load8<SQUAT_F16>(krow, ka);
+        load8<SQUAT_F16>(krow + 16, ka + 8);
+    }
+    for (int h0 = 0; h0 < p.qpk; h0 += 4) {               // four query heads' loads in flight
+        float qa[4][16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int hq = kvh * p.qpk + (h0 + j < p.qpk ? h0 + j : p.qpk - 1);
+            const unsigned char* qrow = p.q + (b * p.qsb + hq * p.qsh) * QES + part * 16 * QES;
+            load8<QDT>(qrow, qa[j]);
+            load8<QDT>(qrow + 8 * QES, qa[j] + 8);
         }
-        for (int h = 0; h < qpk; ++h) {
-            const int hq = kvh * qpk + h;
-            const unsigned char* qrow = q + (b * qsb + hq * qsh) * QES + part * 16 * QES;
-            float qa[16];
-            load8<QDT>(qrow, qa);
-            load8<QDT>(qrow + 8 * QES, qa + 8);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (h0 + j >= p.qpk) break;                   // uniform
             float acc = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc = fmaf(qa[e], ka[e], acc);
+            for (int e = 0; e < 16; ++e) acc = fmaf(qa[j][e], ka[e], acc);
             acc += __shfl_xor(acc, 1, 64);
             acc += __shfl_xor(acc, 2, 64);
             acc += __shfl_xor(acc, 4, 64);
-            if (part == 0 && slot < r.count) scores[b * ssb + hq * ssh + t0 + slot] = out_scale * acc;
+            const int hq = kvh * p.qpk + h0 + j;
+            if (part == 0 && slot < r.count) p.scores[b * p.ssb + hq * p.ssh + t0 + slot] = p.out_scale * acc;
         }
     }
 }

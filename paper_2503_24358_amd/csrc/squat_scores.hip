@@ -63,7 +63,7 @@ struct ScoreParams {
     float out_scale;
     int units_per_wave;
     int wide_loads;                  // rows of the store are 16-byte aligned: whole units are fetched with 16-byte loads
-    ResidualKeys res;                // (RES kernels) logits of these keys by the last workgroup along x
+    ResidualKeys res;                // (RES kernels) logits of these keys by further workgroups
 };
 
 __device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi) {
@@ -71,8 +71,8 @@ __device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi) {
            (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, hi)) << 16);
 }
 
-// grid: x over slabs of kScoreWaves * units_per_wave units (RES: and one workgroup for the full-precision keys of the
-// (batch, KV head)), y / z over (batch, KV head)
+// grid: x over slabs of kScoreWaves * units_per_wave units, y / z over (batch, KV head); RES: and rows along y for the
+// full-precision keys (residual_grid)
 template <int BITS, int NG, int QDT, bool RES>
 __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const ScoreParams p) {
     constexpr int WPK = kD * BITS / 32;                   // packed words per key
@@ -87,15 +87,16 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));   // uniform: scalar loop control
     const int kb = lane >> 4;                             // K block of an operand / row block of the result
     const int col = lane & 15;                            // operand row (A) or token (B, result)
-    const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
-    const int64_t b = bh / p.n_kv_heads;
-    const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
     if constexpr (RES) {
-        if (blockIdx.x + 1 == gridDim.x) {                // uniform
-            residual_scores<QDT>(p.res, p.q, p.qsb, p.qsh, b, kvh, p.n_kv_heads, p.qpk, p.out_scale, p.scores, p.ssb, p.ssh, p.n_tokens);
+        static_assert(kScoreWaves == kResWaves);
+        if (blockIdx.y >= p.res.first_row) {              // uniform
+            residual_scores<QDT>(p, p.n_tokens);
             return;
         }
     }
+    const int64_t bh = static_cast<int64_t>(blockIdx.z) * (RES ? p.res.heads_y : static_cast<int>(gridDim.y)) + blockIdx.y;
+    const int64_t b = bh / p.n_kv_heads;
+    const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
 
     // ---- this wavefront's 16-token units; the loads of its first units are issued before anything else, so
     // that their latency overlaps the set-up of the query-side operands
@@ -513,7 +514,7 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     p.n_kv_heads = n_kv_heads;
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
-    p.res = res ? *residual : ResidualKeys{nullptr, 0, 0, 0};
+    p.res = ResidualKeys{};
     {
         const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
         p.wide_loads = (store_stride * meta_row) % 16 == 0 && aligned(scale, 16) && aligned(zero, 16);
@@ -532,7 +533,7 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     if (upw < kMinUnitsPerWave) upw = kMinUnitsPerWave;
     upw += upw & 1;                                       // even: every wavefront's range starts on a 32-token line
     p.units_per_wave = static_cast<int>(upw);
-    gx = (n_units + kScoreWaves * upw - 1) / (kScoreWaves * upw) + (res ? 1 : 0);
+    gx = (n_units + kScoreWaves * upw - 1) / (kScoreWaves * upw);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {
@@ -542,9 +543,20 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
         gz = bh / gy;
     }
     if (gx > 0x7FFFFFFF || gz > 65535) return SQUAT_E_BADSHAPE;
-    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return bits == 2 ? launch_ng<2>(128 / group, p, grid, s) : launch_ng<4>(128 / group, p, grid, s);
+    const auto launch = [&](const dim3& grid) {
+        return bits == 2 ? launch_ng<2>(128 / group, p, grid, s) : launch_ng<4>(128 / group, p, grid, s);
+    };
+    dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
+    if (!res) return launch(grid);
+    ResidualKeys tail = *residual;
+    if (!residual_grid(tail, gx, gy, gz, grid)) {         // more than 32767 rows of heads: the packed keys first
+        const int rc = launch(grid);
+        if (rc != SQUAT_OK) return rc;
+        residual_grid(tail, 0, gy, gz, grid);
+    }
+    p.res = tail;
+    return launch(grid);
 }
 
 extern "C" int squat_key_scores(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero,

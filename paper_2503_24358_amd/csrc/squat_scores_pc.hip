@@ -58,7 +58,7 @@ struct ScorePcParams {
     int qpk;
     float out_scale;
     int tiles_per_wave;
-    ResidualKeys res;                // (RES kernels) logits of these keys by the last workgroup along x
+    ResidualKeys res;                // (RES kernels) logits of these keys by further workgroups
 };
 
 __device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi) {
@@ -73,8 +73,8 @@ __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
     return v > o ? v : o;
 }
 
-// grid: x over slabs of kPcWaves * tiles_per_wave token groups (RES: and one workgroup for the full-precision keys of the
-// (batch, KV head)), y / z over (batch, KV head).
+// grid: x over slabs of kPcWaves * tiles_per_wave token groups, y / z over (batch, KV head); RES: and rows along y for the
+// full-precision keys (residual_grid)
 // NT = token groups per step.  With at most four query heads per KV head only 8 of the 16 operand rows
 // are in use, so NT = 2 gives rows 0..7 to one token group and rows 8..15 to the next one (same queries,
 // the other group's scales): the instructions that build the query-side operand then serve two groups,
@@ -95,16 +95,16 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));   // uniform: scalar loop control
     const int kb = lane >> 4;                             // K block of an operand / row block of the result
     const int col = lane & 15;                            // operand row (A) or column (B, result)
-    const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
-    const int64_t b = bh / p.n_kv_heads;
-    const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
     if constexpr (RES) {
-        if (blockIdx.x + 1 == gridDim.x) {                // uniform
-            residual_scores<QDT>(p.res, p.q, p.qsb, p.qsh, b, kvh, p.n_kv_heads, p.qpk, p.out_scale, p.scores, p.ssb, p.ssh,
-                                 static_cast<int64_t>(p.n_tiles) * 32);
+        static_assert(kPcWaves == kResWaves);
+        if (blockIdx.y >= p.res.first_row) {              // uniform
+            residual_scores<QDT>(p, static_cast<int64_t>(p.n_tiles) * 32);
             return;
         }
     }
+    const int64_t bh = static_cast<int64_t>(blockIdx.z) * (RES ? p.res.heads_y : static_cast<int>(gridDim.y)) + blockIdx.y;
+    const int64_t b = bh / p.n_kv_heads;
+    const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
 
     // ---- this wavefront's token groups (tiles_per_wave is a multiple of NT); the loads of its first steps are
     // issued before anything else, so that their latency overlaps the set-up of the query-side registers
@@ -484,7 +484,7 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     p.n_kv_heads = n_kv_heads;
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
-    p.res = res ? *residual : ResidualKeys{nullptr, 0, 0, 0};
+    p.res = ResidualKeys{};
 
     // workgroups along the sequence: about kPcWaves * aim token groups each, spread evenly
     const int64_t n_tiles = p.n_tiles;
@@ -497,7 +497,7 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     const bool two = q_per_kv <= 4;                       // two token groups per step (see the kernel)
     if (two) tpw += tpw & 1;
     p.tiles_per_wave = static_cast<int>(tpw);
-    gx = (n_tiles + kPcWaves * tpw - 1) / (kPcWaves * tpw) + (res ? 1 : 0);
+    gx = (n_tiles + kPcWaves * tpw - 1) / (kPcWaves * tpw);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {
@@ -507,10 +507,21 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
         gz = bh / gy;
     }
     if (gx > 0x7FFFFFFF || gz > 65535) return SQUAT_E_BADSHAPE;
-    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (two) return bits == 2 ? launch_dt<2, 2>(p, grid, s) : launch_dt<4, 2>(p, grid, s);
-    return bits == 2 ? launch_dt<2, 1>(p, grid, s) : launch_dt<4, 1>(p, grid, s);
+    const auto launch = [&](const dim3& grid) {
+        if (two) return bits == 2 ? launch_dt<2, 2>(p, grid, s) : launch_dt<4, 2>(p, grid, s);
+        return bits == 2 ? launch_dt<2, 1>(p, grid, s) : launch_dt<4, 1>(p, grid, s);
+    };
+    dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
+    if (!res) return launch(grid);
+    ResidualKeys tail = *residual;
+    if (!residual_grid(tail, gx, gy, gz, grid)) {         // more than 32767 rows of heads: the packed keys first
+        const int rc = launch(grid);
+        if (rc != SQUAT_OK) return rc;
+        residual_grid(tail, 0, gy, gz, grid);
+    }
+    p.res = tail;
+    return launch(grid);
 }
 
 extern "C" int squat_key_scores_per_channel(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero,

@@ -79,3 +79,29 @@ def test_logits_of_the_full_precision_tail(n, r, qdt, per_channel):
     bound = 0.5 * (np.abs(qd) @ np.abs(tail).transpose(0, 1, 3, 2))
     assert np.all(np.abs(got[..., nq:n] - want) <= 1e-5 * bound)
     assert (got[..., n:] == -5.0).all() and (got[..., :n] != -5.0).all()
+
+
+# heads: the full-precision keys' grid rows fit behind the others (several workgroups or one per head before them, three
+# grid layers of 32767 rows) or do not (32768 and a prime beyond half the limit, two layers of 35000)
+@pytest.mark.parametrize("per_channel", [False, True])
+@pytest.mark.parametrize("b,h,n", [(1, 3, 1000), (5, 40, 550), (64, 40, 40), (32768, 1, 33), (1, 32771, 33), (35000, 2, 33),
+                                   (32767, 3, 33), (32768, 1, 2)])
+def test_full_precision_tail_of_many_heads(b, h, n, per_channel):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b + h)
+    k = torch.randn((b, h, n, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((b, h, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    cache = squat.Cache(b, h, 1, 2, 32, 32, 32, (n + 31) // 32 * 32, torch.bfloat16, None, False, key_per_channel=per_channel)
+    cache.prefill(k)
+    out = torch.full((b, h, n + 1), -5.0, device="cuda")
+    cache.key_scores(q, 1.0, out=out)
+    nq = n // 32 * 32
+    if nq:
+        st = [cache.stores()["key_" + i] for i in ("codes", "scale", "zero")]
+        st = [x[:, :, :nq].contiguous() if not per_channel else x[:, :, :nq // 32].contiguous() for x in st]
+        want = squat.key_scores_per_channel(q, *st, 2, 1) if per_channel else squat.key_scores(q, *st, 2, 32, 1)
+        assert torch.equal(out[:, :, :nq], want)
+    prod = q.float()[:, :, None] * k[:, :, nq:].float()
+    err = (out[:, :, nq:n].double() - prod.double().sum(-1)).abs()
+    assert bool((err <= 1e-5 * prod.abs().double().sum(-1)).all())
+    assert bool((out[:, :, n] == -5.0).all())
