@@ -229,7 +229,7 @@ def main():
                             "unit": "GB/s", "frac": q_bytes / (d_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
         "build_subspace": {"ms": stage_ms["build_subspace"], "gram_input_GB": gram_bytes / 1e9,
                            "note": "gram (HBM-bound bf16 MFMA, see profiles/) + fp64 eigen-solver, one workgroup per "
-                                   "head (Householder tridiagonalisation, bisection, inverse iteration; latency-bound)"},
+                                   "head (Householder tridiagonalisation, Sturm counts, twisted factorisations; latency-bound)"},
         "prepare": {"ms": stage_ms["prepare"]},
     }
     out = {

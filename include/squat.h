@@ -163,8 +163,8 @@ int squat_refresh_subspace(const void* q_new, squat_dtype q_dt, int64_t n_new, i
  * A_t is its leading (t g x t g) block, B_t the block below it and H_t the
  * last g columns of A_t^{-1}.  The kernel evaluates the equivalent rank-r
  * form  -Qr^T (I/lambda + Qr Qr^T)^{-1} Qb  (Qb, Qr: the columns of Qhat in
- * and after block t) in fp64 (r <= 64 and finite lambda: by a Cholesky
- * factorisation, heads that turn out ill-conditioned and all other cases by an
+ * and after block t) in fp64 (r <= 64 and finite lambda: by block
+ * elimination, heads that turn out ill-conditioned and all other cases by an
  * eigen-decomposition).  lambda = +INFINITY selects the limit
  * -pinv(Qr) Qb (the equality constraint of Eq. (1)); lambda = 0 or r = 0
  * gives U = 0 (plain round-to-nearest).  Every entry is rounded to the nearest

@@ -4,8 +4,9 @@
 // with P = I + lambda Qhat^T Qhat, and the Woodbury identity (the paper's O(r d^2) footnote)
 // reduces this to an r x r problem:
 //     W_t = -Qr^T (I/lambda + Qr Qr^T)^{-1} Qb,     Qb = Qhat[:, blk], Qr = Qhat[:, tg:].
-// One workgroup per (head, t) works in fp64: it forms S = I/lambda + Qr Qr^T in LDS,
-// diagonalises it with the one-sided Jacobi routine (rows a_i = mu_i v_i), and applies
+// r <= 64 and finite lambda: block elimination in fp64 on the matrix cores, one workgroup per head
+// (prepare_elim_kernel).  All else, and the heads that kernel flags: one workgroup per (head, t) or per head works
+// in fp64, forms S = I/lambda + Qr Qr^T, diagonalises it with the one-sided Jacobi routine (rows a_i = mu_i v_i), and applies
 // S^+ = sum_i a_i a_i^T / mu_i^3.  lambda = +inf drops the I/lambda term and discards the
 // (numerically) zero mu_i, which yields -pinv(Qr) Qb.  By default the result is stored as fp32 numbers that
 // are exactly representable in fp16; squat_prepare_ex can store the plain fp32 rounding instead.

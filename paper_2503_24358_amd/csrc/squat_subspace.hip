@@ -12,10 +12,11 @@
 //                 workgroup, partial tiles go to the workspace.
 //   gram_reduce   sums the workgroups' partials in fp64 in a fixed order
 //                 (deterministic), un-permutes channels and mirrors;
-//   gram_reduce_tiles  the same with a workgroup per (tile, head), for
-//                 heads with many partials.
+//   gram_reduce_tiles  the same with a thread per entry, 40 workgroups per head,
+//                 for few heads and for heads with many partials.
 //   eig_tridiag_kernel  r <= 64: Householder tridiagonalisation, Sturm-count search
-//                 for the r largest eigenvalues, inverse iteration, back-transformation
+//                 for the r largest eigenvalues, twisted factorisations (inverse iteration
+//                 for close eigenvalues), back-transformation with block reflectors
 //                 (squat_tridiag.h), one workgroup per KV head; flags a head whose result
 //                 fails its own residual checks.
 //   eig_kernel    cyclic one-sided Jacobi in fp64 on the 128 x 128 Gram matrix in
