@@ -64,7 +64,7 @@ struct RopeParams {
     int qpk;
     float out_scale;
     int units_per_wave;
-    int wide_loads;                  // per-token store: rows 16-byte aligned, whole units fetched with 16-byte loads
+    int wide_loads;                  // per-token store: rows 4-byte aligned, whole units fetched with 16-byte loads
 };
 
 __device__ __forceinline__ uint32_t pack_h2(_Float16 lo, _Float16 hi) {
@@ -301,10 +301,10 @@ key_scores_rope_kernel(const RopeParams p) {
     };
     Raw ring[kEpochUnits];
     auto fetch = [&](Raw& r) {
-        r.c = RP_LOAD(reinterpret_cast<const u32x4*>(gp));
+        r.c = RP_LOAD(reinterpret_cast<const u32x4_dwords*>(gp));
         gp += gstep;
         if constexpr (BITS == 4) {
-            r.m = RP_LOAD(reinterpret_cast<const u32x4*>(mptr));
+            r.m = RP_LOAD(reinterpret_cast<const u32x4_dwords*>(mptr));
             mptr += kRopeUnit * 2 * NG;
         }
     };
@@ -827,7 +827,7 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
     p.out_scale = out_scale;
     {
         const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
-        p.wide_loads = (store_stride * meta_row) % 16 == 0 && aligned(scale, 16) && aligned(zero, 16);
+        p.wide_loads = (store_stride * meta_row) % 4 == 0;    // the bases are 8-byte aligned
     }
 
     // workgroups along the sequence: about kRopeWaves * aim units each, spread evenly
