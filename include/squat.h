@@ -571,7 +571,8 @@ int squat_cache_get_buffers(const squat_cache* cache, squat_cache_buffers* out);
 int squat_cache_prefill(squat_cache* cache, const void* k, const void* v, int64_t n_tokens,
                         int64_t stride_batch, int64_t stride_head, int64_t stride_token, squat_stream stream);
 
-/* One decoded token per sequence: k, v [n_batch, n_kv_heads, d].  SQUAT_E_BADSHAPE when a store is full. */
+/* One decoded token per sequence: k, v [n_batch, n_kv_heads, d].  SQUAT_E_BADSHAPE when a store is full.  After an error
+ * the cache is as before the call, which may be repeated. */
 int squat_cache_append(squat_cache* cache, const void* k, const void* v, int64_t stride_batch,
                        int64_t stride_head, squat_stream stream);
 

@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(256) copy_tokens_kernel(const unsigned char* s
 // each.  A decode step's bookkeeping moves a few hundred bytes per head, so it costs what its launches cost: three of
 // them (copy, quantize, copy) took 8.2 us of the GPU's time for 64 heads, this one takes 2.9.
 struct AppendParams {
-    const unsigned char *k, *v;      // v == NULL: keys only
+    const unsigned char *k, *v;      // NULL: no keys, no values
     int64_t sb, sh;                  // strides of k and v in BYTES
     unsigned char *kres, *vres;
     int slots, kslot, vslot;
@@ -133,7 +133,8 @@ __global__ void __launch_bounds__(256) append_token_kernel(const AppendParams p)
     const int64_t dst = r * p.slots * (kD * ES) + part * (16 * ES);
     u32x4 kn[NP], vn[NP];
 #pragma unroll
-    for (int e = 0; e < NP; ++e) kn[e] = *reinterpret_cast<const u32x4*>(p.k + src + 16 * e);
+    for (int e = 0; e < NP; ++e)
+        if (p.k) kn[e] = *reinterpret_cast<const u32x4*>(p.k + src + 16 * e);
     unsigned char* vslot = p.vres + dst + static_cast<int64_t>(p.vslot) * (kD * ES);
     float x[16];
     if (p.v) {
@@ -145,7 +146,8 @@ __global__ void __launch_bounds__(256) append_token_kernel(const AppendParams p)
         }
     }
 #pragma unroll
-    for (int e = 0; e < NP; ++e) *reinterpret_cast<u32x4*>(p.kres + dst + static_cast<int64_t>(p.kslot) * (kD * ES) + 16 * e) = kn[e];
+    for (int e = 0; e < NP; ++e)
+        if (p.k) *reinterpret_cast<u32x4*>(p.kres + dst + static_cast<int64_t>(p.kslot) * (kD * ES) + 16 * e) = kn[e];
     if (!p.v) return;
     if (p.evict) {
         uint32_t words[BITS / 2];
@@ -380,6 +382,11 @@ extern "C" int squat_cache_append(squat_cache* c, const void* k, const void* v, 
     const bool v_evict = f.quantize_values && c->n_vres == R;
     if (v_evict && c->n_vq + 1 > f.max_tokens) return SQUAT_E_BADSHAPE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // An append that returns an error may be repeated: nothing of it shows then.  Writing the key's slot or flushing twice
+    // does no harm, but quantizing the oldest value and giving its slot to the new one does: that launch is the last to
+    // report an error, and an error an earlier call left behind (which a launch's own check would return) is reported first.
+    int rc = check_launch();
+    if (rc) return rc;
     // key into the next residual slot; if the value ring is full its oldest token is quantized and its slot takes the new
     // token
     AppendParams p;
@@ -403,14 +410,19 @@ extern "C" int squat_cache_append(squat_cache* c, const void* k, const void* v, 
     p.n_bh = f.n_batch * f.n_kv_heads;
     const int64_t blocks = (p.n_bh * 8 + 255) / 256;
     if (blocks > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
-    if (f.bits == 2)
-        launch_append<2>(f.kv_dtype, dim3(static_cast<unsigned>(blocks)), s, p);
-    else
-        launch_append<4>(f.kv_dtype, dim3(static_cast<unsigned>(blocks)), s, p);
-    int rc = check_launch();
-    if (rc) return rc;
-    // a full buffer is quantized as one group of R tokens and emptied
+    const auto launch = [&](const AppendParams& q) {
+        if (f.bits == 2)
+            launch_append<2>(f.kv_dtype, dim3(static_cast<unsigned>(blocks)), s, q);
+        else
+            launch_append<4>(f.kv_dtype, dim3(static_cast<unsigned>(blocks)), s, q);
+        return check_launch();
+    };
     if (flush) {
+        AppendParams keys = p;
+        keys.v = nullptr;
+        rc = launch(keys);
+        if (rc) return rc;
+        // the full buffer is quantized as one group of R tokens and emptied
         const int64_t rsb = static_cast<int64_t>(f.n_kv_heads) * R * f.d, rsh = static_cast<int64_t>(R) * f.d;
         rc = f.key_per_channel
                  ? quantize_keys_pc_into(c->buf.key_residual, f.kv_dtype, f.n_batch, f.n_kv_heads, R, f.d, rsb, rsh,
@@ -419,6 +431,11 @@ extern "C" int squat_cache_append(squat_cache* c, const void* k, const void* v, 
                  : quantize_keys_into(c->buf.key_residual, f.kv_dtype, f.n_batch, f.n_kv_heads, R, f.d, rsb, rsh, f.d,
                                       c->update, 0, f.bits, f.group, f.g, c->buf.key_codes, c->buf.key_scale,
                                       c->buf.key_zero, f.max_tokens, c->n_kq, stream);
+        if (rc) return rc;
+        p.k = nullptr;
+    }
+    if (p.k || p.v) {
+        rc = launch(p);
         if (rc) return rc;
     }
     if (v_evict) {
