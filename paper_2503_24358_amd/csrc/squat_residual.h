@@ -18,26 +18,26 @@ struct ResidualKeys {
     // layer (z) holds heads_y (batch, KV head) pairs
     unsigned first_row;
     int heads_y;
+    bool taken;                      // host: a logits launch has taken these keys with it
 };
 
 constexpr int kResTokens = 8;            // keys per wavefront
 constexpr int kResWaves = 4;             // wavefronts per workgroup: that of the logits kernels
 
-// The grid of a logits launch with gx workgroups for the packed keys of each of gy x gz (batch, KV head) pairs (gx = 0: no
-// packed keys), extended by the rows for the full-precision keys.  These come behind the others and not as one more
-// column: with one workgroup per pair before it, a column puts all short workgroups on every other XCD and all long ones
-// on the rest (16384 pairs of 2048 tokens and 16 full-precision keys: 530 us against 394).  False: the rows do not fit, the caller
-// launches twice (the second time with gx = 0).
+// The grid of a logits launch with gx workgroups for the packed keys of each of gy x gz (batch, KV head) pairs, extended by
+// the rows for the full-precision keys.  These come behind the others and not as one more column: with one workgroup
+// per pair before it, a column puts all short workgroups on every other XCD and all long ones on the rest (16384 pairs
+// of 2048 tokens and 16 full-precision keys: 530 us against 394).  False: gy + ceil(ceil(gy ceil(count / 8) / 4) / gx)
+// rows are too many, these keys need a launch of their own.
 constexpr int64_t kMaxGridRows = 65535;
 
 inline bool residual_grid(ResidualKeys& r, int64_t gx, int64_t gy, int64_t gz, dim3& grid) {
     const int64_t workgroups = (gy * ((r.count + kResTokens - 1) / kResTokens) + kResWaves - 1) / kResWaves;
-    const int64_t wide = gx > 0 ? gx : workgroups, first = gx > 0 ? gy : 0;
-    const int64_t rows = first + (workgroups + wide - 1) / wide;
+    const int64_t rows = gy + (workgroups + gx - 1) / gx;
     if (rows > kMaxGridRows) return false;
-    r.first_row = static_cast<unsigned>(first);
+    r.first_row = static_cast<unsigned>(gy);
     r.heads_y = static_cast<int>(gy);
-    grid = dim3(static_cast<unsigned>(wide), static_cast<unsigned>(rows), static_cast<unsigned>(gz));
+    grid = dim3(static_cast<unsigned>(gx), static_cast<unsigned>(rows), static_cast<unsigned>(gz));
     return true;
 }
 

@@ -476,13 +476,13 @@ int launch_ng(int ng, const ScoreParams& p, dim3 grid, hipStream_t s) {
 }  // namespace
 
 // squat_key_scores over the first n_tokens tokens of a store that holds store_stride tokens per
-// (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, by the same launch.
+// (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, taken into the same
+// launch if its grid has room for them (residual->taken).
 int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                            int n_kv_heads, int64_t n_tokens, int64_t store_stride, int d, int bits, int group,
                            const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch,
                            int64_t q_stride_head, float out_scale, float* scores, int64_t s_stride_batch,
-                           int64_t s_stride_head, const ResidualKeys* residual, squat_stream stream) {
-    const bool res = residual && residual->count > 0;
+                           int64_t s_stride_head, ResidualKeys* residual, squat_stream stream) {
     if (d != kD) return SQUAT_E_BADSHAPE;
     if (bits != 2 && bits != 4) return SQUAT_E_BADSHAPE;
     if (group != 32 && group != 64 && group != 128) return SQUAT_E_BADSHAPE;
@@ -491,7 +491,7 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     if (store_stride < n_tokens) return SQUAT_E_BADSHAPE;
     if (q_dt != SQUAT_F32 && q_dt != SQUAT_F16 && q_dt != SQUAT_BF16) return SQUAT_E_BADDTYPE;
     if (!(out_scale == out_scale)) return SQUAT_E_BADVALUE;
-    if (n_batch == 0 || n_kv_heads == 0 || (n_tokens == 0 && !res)) return SQUAT_OK;
+    if (n_batch == 0 || n_kv_heads == 0 || n_tokens == 0) return SQUAT_OK;
     if (!codes || !scale || !zero || !q || !scores) return SQUAT_E_NULLPTR;
     if (q_stride_head < d || q_stride_batch < 0 || s_stride_head < n_tokens || s_stride_batch < 0) return SQUAT_E_BADSHAPE;
     if ((q_stride_head % 8) || (q_stride_batch % 8)) return SQUAT_E_ALIGN;
@@ -548,15 +548,11 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
         return bits == 2 ? launch_ng<2>(128 / group, p, grid, s) : launch_ng<4>(128 / group, p, grid, s);
     };
     dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
-    if (!res) return launch(grid);
-    ResidualKeys tail = *residual;
-    if (!residual_grid(tail, gx, gy, gz, grid)) {         // more than 32767 rows of heads: the packed keys first
-        const int rc = launch(grid);
-        if (rc != SQUAT_OK) return rc;
-        residual_grid(tail, 0, gy, gz, grid);
-    }
-    p.res = tail;
-    return launch(grid);
+    if (!residual || residual->count == 0 || !residual_grid(*residual, gx, gy, gz, grid)) return launch(grid);
+    p.res = *residual;
+    const int rc = launch(grid);
+    residual->taken = rc == SQUAT_OK;
+    return rc;
 }
 
 extern "C" int squat_key_scores(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero,

@@ -1,0 +1,35 @@
+"""Grids of squat_cache_key_scores for caches of very many heads.  A grid's y and z hold 65535 each, so packed keys of head
+counts without a divisor that suits are refused; full-precision keys alone are not bound by that.  Host side only, against
+a recorder of the launches."""
+import pytest
+
+from . import recorded
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return recorded.build(str(tmp_path_factory.mktemp("recorder")))
+
+
+CODE = """
+h = R.cache(lib, n_batch=%(b)d, n_kv_heads=%(h)d, residual=%(r)d, max_tokens=%(r)d * 4, quantize_values=0, key_per_channel=%(pc)d)
+assert lib.squat_cache_prefill(h, 0x10000, None, %(n)d, %(h)d * %(n)d * 128, %(n)d * 128, 128, None) == 0
+n0 = rec.recorded()
+rc = lib.squat_cache_key_scores(h, 0x10000, 2, %(h)d * 128, 128, 1.0, 0x20000, %(h)d * %(n)d, %(n)d, None)
+print(json.dumps(dict(rc=rc, grids=[list(rec.launch_at(i).contents.grid) for i in range(n0, rec.recorded())])))
+"""
+
+
+@pytest.mark.parametrize("pc", [0, 1])
+@pytest.mark.parametrize("b,h,n", [(1, 3, 2), (1, 65537, 2), (1, 131074, 31), (65537, 3, 31), (7, 65521, 1)])
+def test_full_precision_keys_alone(recorder, b, h, n, pc):
+    r = recorded.run(recorder, CODE % dict(b=b, h=h, n=n, r=32, pc=pc))
+    assert r["rc"] == 0 and len(r["grids"]) == 1
+    x, y, z = r["grids"][0]
+    assert y <= 65535 and z <= 65535 and x * y * z * 256 >= b * h * n * 8      # eight lanes per key
+
+
+@pytest.mark.parametrize("pc", [0, 1])
+def test_packed_keys_of_such_head_counts_stay_refused(recorder, pc):
+    r = recorded.run(recorder, CODE % dict(b=1, h=65537, n=33, r=32, pc=pc))
+    assert r["rc"] == -2 and r["grids"] == []
