@@ -515,11 +515,12 @@ extern "C" int squat_cache_key_scores(const squat_cache* c, const void* q, squat
     if (s_stride_head < c->n_kq + c->n_kres || s_stride_batch < 0 || q_stride_head < f.d || q_stride_batch < 0)
         return SQUAT_E_BADSHAPE;
     if ((q_stride_head % 8) || (q_stride_batch % 8) || !aligned(q, 16) || !aligned(scores, 4)) return SQUAT_E_ALIGN;
-    // Full-precision keys beside packed ones go into the packed keys' launch if they fit its grid; alone they have a launch
-    // of their own.
-    ResidualKeys res{static_cast<const unsigned char*>(c->buf.key_residual), static_cast<int>(f.kv_dtype), f.residual,
-                     c->n_kres};
-    ResidualKeys* beside = c->n_kq > 0 ? &res : nullptr;
+    // Full-precision keys go into the packed keys' launch or have a launch of their own.
+    const int64_t n_bh = f.n_batch * f.n_kv_heads;
+    const ResidualKeys res{static_cast<const unsigned char*>(c->buf.key_residual), static_cast<int>(f.kv_dtype), f.residual,
+                           c->n_kres, 0};
+    const bool one = c->n_kq > 0 && c->n_kres > 0 && residual_beside(n_bh, c->n_kres, f.d * elem_size(f.kv_dtype));
+    const ResidualKeys* beside = one ? &res : nullptr;
     const int rc = f.key_per_channel
                        ? key_scores_pc_from(c->buf.key_codes, c->buf.key_scale, c->buf.key_zero, f.n_batch, f.n_kv_heads,
                                             c->n_kq, f.max_tokens, f.d, f.bits, kTileTokens, q, q_dt, f.q_per_kv,
@@ -529,8 +530,8 @@ extern "C" int squat_cache_key_scores(const squat_cache* c, const void* q, squat
                                          c->n_kq, f.max_tokens, f.d, f.bits, f.group, q, q_dt, f.q_per_kv, q_stride_batch,
                                          q_stride_head, out_scale, scores, s_stride_batch, s_stride_head, beside, stream);
     if (rc) return rc;
-    if (c->n_kres == 0 || res.taken) return SQUAT_OK;
-    const int64_t total = f.n_batch * f.n_kv_heads * static_cast<int64_t>(c->n_kres);
+    if (c->n_kres == 0 || one) return SQUAT_OK;
+    const int64_t total = n_bh * c->n_kres;
     const int64_t blocks = (total * 8 + 255) / 256;          // eight lanes per buffered key
     if (blocks > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
     const dim3 grid(static_cast<unsigned>(blocks));

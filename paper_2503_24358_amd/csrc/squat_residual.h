@@ -14,31 +14,30 @@ struct ResidualKeys {
     int dt;                          // squat_dtype
     int slots;
     int count;
-    // set by residual_grid: grid rows (y) from first_row on belong to these keys, a wavefront per eight of them; a grid
-    // layer (z) holds heads_y (batch, KV head) pairs
-    unsigned first_row;
-    int heads_y;
-    bool taken;                      // host: a logits launch has taken these keys with it
+    unsigned first_row;              // grid rows (y) from this one on belong to these keys, a wavefront per eight of them
 };
 
 constexpr int kResTokens = 8;            // keys per wavefront
 constexpr int kResWaves = 4;             // wavefronts per workgroup: that of the logits kernels
 
-// The grid of a logits launch with gx workgroups for the packed keys of each of gy x gz (batch, KV head) pairs, extended by
-// the rows for the full-precision keys.  These come behind the others and not as one more column: with one workgroup
-// per pair before it, a column puts all short workgroups on every other XCD and all long ones on the rest (16384 pairs
-// of 2048 tokens and 16 full-precision keys: 530 us against 394).  False: gy + ceil(ceil(gy ceil(count / 8) / 4) / gx)
-// rows are too many, these keys need a launch of their own.
-constexpr int64_t kMaxGridRows = 65535;
+// Whether the logits of `count` full-precision keys, of `row_bytes` each, of every (batch, KV head) pair go into the packed
+// keys' launch: a launch of their own costs 2 to 3 us, but has twice the wavefronts per SIMD and so reads them at
+// 6 TB/s against 4.  The line lies where the two weigh the same, at 24 MB of keys, counted in the wavefronts' whole eights.
+// Measured (2-bit, bf16; us in one launch | in two, for 1, 4 and 8 query heads per KV head), at 4 MB, 1024 pairs of 1024
+// packed keys and 16: 13 | 15, 16 | 18, 22 | 24; 17 MB, 4096 of 1024 and 16: 46 | 48, 55 | 56, 76 | 78; 33 MB, 2048 of 256
+// and 64: 19 | 18, 23 | 22, 30 | 28; 134 MB, 4096 of 256 and 127: 50 | 42, 61 | 54, 89 | 77; 266 MB, 8192 of 1024 and
+// 127: 148 | 127, 233 | 213, 394 | 356; 33 MB as 16384 pairs of 1024 and 1: 171 | 168, 284 | 279, 518 | 505.
+inline bool residual_beside(int64_t pairs, int count, int row_bytes) {
+    constexpr int64_t kMost = int64_t(24) << 20;
+    return pairs * ((count + kResTokens - 1) / kResTokens * kResTokens) * row_bytes <= kMost;
+}
 
-inline bool residual_grid(ResidualKeys& r, int64_t gx, int64_t gy, int64_t gz, dim3& grid) {
+// The grid rows behind the gy rows of gx workgroups each that they take there.  They come behind the others and not as one
+// more column: with one workgroup per pair before it, a column puts all short workgroups on every other XCD and all
+// long ones on the rest (seen at 16384 pairs of 2048 packed keys and 16: 530 us against 394).
+inline unsigned residual_rows(const ResidualKeys& r, int64_t gx, int64_t gy) {
     const int64_t workgroups = (gy * ((r.count + kResTokens - 1) / kResTokens) + kResWaves - 1) / kResWaves;
-    const int64_t rows = gy + (workgroups + gx - 1) / gx;
-    if (rows > kMaxGridRows) return false;
-    r.first_row = static_cast<unsigned>(gy);
-    r.heads_y = static_cast<int>(gy);
-    grid = dim3(static_cast<unsigned>(gx), static_cast<unsigned>(rows), static_cast<unsigned>(gz));
-    return true;
+    return static_cast<unsigned>((workgroups + gx - 1) / gx);
 }
 
 // 8 consecutive elements (16-byte aligned) as floats
@@ -78,8 +77,8 @@ __device__ __forceinline__ void residual_scores(const Params& p, int64_t t0) {
     const unsigned i = ((blockIdx.y - r.first_row) * gridDim.x + blockIdx.x) * kResWaves + wave;
     const unsigned chunks = static_cast<unsigned>(r.count + kResTokens - 1) / kResTokens;
     const unsigned head = i / chunks;
-    if (head >= static_cast<unsigned>(r.heads_y)) return;                            // uniform per wavefront
-    const int64_t bh = static_cast<int64_t>(blockIdx.z) * r.heads_y + head;
+    if (head >= r.first_row) return;                      // uniform per wavefront
+    const int64_t bh = head;
     const int64_t b = bh / p.n_kv_heads;
     const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
     const int part = static_cast<int>(threadIdx.x) & 7;

@@ -72,7 +72,7 @@ __device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi) {
 }
 
 // grid: x over slabs of kScoreWaves * units_per_wave units, y / z over (batch, KV head); RES: and rows along y for the
-// full-precision keys (residual_grid)
+// full-precision keys (residual_rows), z = 0
 template <int BITS, int NG, int QDT, bool RES>
 __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const ScoreParams p) {
     constexpr int WPK = kD * BITS / 32;                   // packed words per key
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
             return;
         }
     }
-    const int64_t bh = static_cast<int64_t>(blockIdx.z) * (RES ? p.res.heads_y : static_cast<int>(gridDim.y)) + blockIdx.y;
+    const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
     const int64_t b = bh / p.n_kv_heads;
     const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
 
@@ -476,13 +476,13 @@ int launch_ng(int ng, const ScoreParams& p, dim3 grid, hipStream_t s) {
 }  // namespace
 
 // squat_key_scores over the first n_tokens tokens of a store that holds store_stride tokens per
-// (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, taken into the same
-// launch if its grid has room for them (residual->taken).
+// (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, by the same launch
+// (residual_beside holds).
 int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                            int n_kv_heads, int64_t n_tokens, int64_t store_stride, int d, int bits, int group,
                            const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch,
                            int64_t q_stride_head, float out_scale, float* scores, int64_t s_stride_batch,
-                           int64_t s_stride_head, ResidualKeys* residual, squat_stream stream) {
+                           int64_t s_stride_head, const ResidualKeys* residual, squat_stream stream) {
     if (d != kD) return SQUAT_E_BADSHAPE;
     if (bits != 2 && bits != 4) return SQUAT_E_BADSHAPE;
     if (group != 32 && group != 64 && group != 128) return SQUAT_E_BADSHAPE;
@@ -544,15 +544,13 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     }
     if (gx > 0x7FFFFFFF || gz > 65535) return SQUAT_E_BADSHAPE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const auto launch = [&](const dim3& grid) {
-        return bits == 2 ? launch_ng<2>(128 / group, p, grid, s) : launch_ng<4>(128 / group, p, grid, s);
-    };
     dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
-    if (!residual || residual->count == 0 || !residual_grid(*residual, gx, gy, gz, grid)) return launch(grid);
-    p.res = *residual;
-    const int rc = launch(grid);
-    residual->taken = rc == SQUAT_OK;
-    return rc;
+    if (residual) {
+        p.res = *residual;
+        p.res.first_row = static_cast<unsigned>(gy);
+        grid.y += residual_rows(*residual, gx, gy);       // (residual_beside: gz == 1, and far from 65535 rows)
+    }
+    return bits == 2 ? launch_ng<2>(128 / group, p, grid, s) : launch_ng<4>(128 / group, p, grid, s);
 }
 
 extern "C" int squat_key_scores(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero,

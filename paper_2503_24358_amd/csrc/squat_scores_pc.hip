@@ -74,7 +74,7 @@ __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
 }
 
 // grid: x over slabs of kPcWaves * tiles_per_wave token groups, y / z over (batch, KV head); RES: and rows along y for the
-// full-precision keys (residual_grid)
+// full-precision keys (residual_rows), z = 0
 // NT = token groups per step.  With at most four query heads per KV head only 8 of the 16 operand rows
 // are in use, so NT = 2 gives rows 0..7 to one token group and rows 8..15 to the next one (same queries,
 // the other group's scales): the instructions that build the query-side operand then serve two groups,
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
             return;
         }
     }
-    const int64_t bh = static_cast<int64_t>(blockIdx.z) * (RES ? p.res.heads_y : static_cast<int>(gridDim.y)) + blockIdx.y;
+    const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
     const int64_t b = bh / p.n_kv_heads;
     const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
 
@@ -445,13 +445,13 @@ int launch_dt(const ScorePcParams& p, dim3 grid, hipStream_t s) {
 }  // namespace
 
 // squat_key_scores_per_channel over the first n_tokens tokens of a store that holds store_tokens tokens
-// (a multiple of 32) per (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, taken
-// into the same launch if its grid has room for them (residual->taken).
+// (a multiple of 32) per (batch, KV head); residual (or NULL): full-precision keys whose logits follow them, by the same
+// launch (residual_beside holds).
 int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero, int64_t n_batch,
                               int n_kv_heads, int64_t n_tokens, int64_t store_tokens, int d, int bits, int group,
                               const void* q, squat_dtype q_dt, int q_per_kv, int64_t q_stride_batch,
                               int64_t q_stride_head, float out_scale, float* scores, int64_t s_stride_batch,
-                              int64_t s_stride_head, ResidualKeys* residual, squat_stream stream) {
+                              int64_t s_stride_head, const ResidualKeys* residual, squat_stream stream) {
     if (d != kD) return SQUAT_E_BADSHAPE;
     if (bits != 2 && bits != 4) return SQUAT_E_BADSHAPE;
     if (group != 32) return SQUAT_E_BADSHAPE;
@@ -507,16 +507,14 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     }
     if (gx > 0x7FFFFFFF || gz > 65535) return SQUAT_E_BADSHAPE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const auto launch = [&](const dim3& grid) {
-        if (two) return bits == 2 ? launch_dt<2, 2>(p, grid, s) : launch_dt<4, 2>(p, grid, s);
-        return bits == 2 ? launch_dt<2, 1>(p, grid, s) : launch_dt<4, 1>(p, grid, s);
-    };
     dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
-    if (!residual || residual->count == 0 || !residual_grid(*residual, gx, gy, gz, grid)) return launch(grid);
-    p.res = *residual;
-    const int rc = launch(grid);
-    residual->taken = rc == SQUAT_OK;
-    return rc;
+    if (residual) {
+        p.res = *residual;
+        p.res.first_row = static_cast<unsigned>(gy);
+        grid.y += residual_rows(*residual, gx, gy);       // (residual_beside: gz == 1, and far from 65535 rows)
+    }
+    if (two) return bits == 2 ? launch_dt<2, 2>(p, grid, s) : launch_dt<4, 2>(p, grid, s);
+    return bits == 2 ? launch_dt<2, 1>(p, grid, s) : launch_dt<4, 1>(p, grid, s);
 }
 
 extern "C" int squat_key_scores_per_channel(const uint32_t* codes, const uint16_t* scale, const uint16_t* zero,

@@ -81,12 +81,15 @@ def test_logits_of_the_full_precision_tail(n, r, qdt, per_channel):
     assert (got[..., n:] == -5.0).all() and (got[..., :n] != -5.0).all()
 
 
-# heads: the full-precision keys' grid rows fit behind the others (several workgroups or one per head before them, three
-# grid layers of 32767 rows) or do not (32768 and a prime beyond half the limit, two layers of 35000)
+# Full-precision keys beside packed ones share their launch up to 24 MiB (in whole eights per head): below, on and above
+# that line; the packed keys in one and in several grid layers (z); full-precision keys alone.
 @pytest.mark.parametrize("per_channel", [False, True])
-@pytest.mark.parametrize("b,h,n", [(1, 3, 1000), (5, 40, 550), (64, 40, 40), (32768, 1, 33), (1, 32771, 33), (35000, 2, 33),
-                                   (32767, 3, 33), (32768, 1, 2)])
-def test_full_precision_tail_of_many_heads(b, h, n, per_channel):
+@pytest.mark.parametrize("b,h,n,launches", [(1, 3, 1000, 1), (5, 40, 550, 1), (64, 40, 40, 1), (1536, 8, 40, 1),
+                                            (1536, 8, 41, 2), (12289, 1, 33, 2), (32768, 1, 33, 2), (1, 32771, 33, 2),
+                                            (35000, 2, 33, 2), (32767, 3, 33, 2), (32768, 1, 2, 1), (1, 65537, 2, 1)])
+def test_full_precision_tail_of_many_heads(b, h, n, launches, per_channel):
+    packed, eights = n // 32 * 32, (n % 32 + 7) // 8
+    assert launches == 1 + (packed > 0 and b * h * eights * 8 * 256 > 24 << 20)      # (test_logits_grids.py sees them)
     g = torch.Generator(device="cuda")
     g.manual_seed(b + h)
     k = torch.randn((b, h, n, D), generator=g, device="cuda", dtype=torch.bfloat16)

@@ -1,6 +1,7 @@
-"""Grids of squat_cache_key_scores for caches of very many heads.  A grid's y and z hold 65535 each, so packed keys of head
-counts without a divisor that suits are refused; full-precision keys alone are not bound by that.  Host side only, against
-a recorder of the launches."""
+"""Launches of squat_cache_key_scores for caches of many heads.  A grid's y and z hold 65535 each, so packed keys of head
+counts without a divisor that suits are refused; full-precision keys alone are not bound by that.  Beside packed keys up to
+24 MiB of them (in whole eights per head) are taken into the packed keys' launch.  Host side only, against a recorder of
+the launches."""
 import pytest
 
 from . import recorded
@@ -12,7 +13,7 @@ def recorder(tmp_path_factory):
 
 
 CODE = """
-h = R.cache(lib, n_batch=%(b)d, n_kv_heads=%(h)d, residual=%(r)d, max_tokens=%(r)d * 4, quantize_values=0, key_per_channel=%(pc)d)
+h = R.cache(lib, n_batch=%(b)d, n_kv_heads=%(h)d, residual=%(r)d, max_tokens=%(r)d * 4, quantize_values=0, key_per_channel=%(pc)d, kv_dtype=%(dt)d)
 assert lib.squat_cache_prefill(h, 0x10000, None, %(n)d, %(h)d * %(n)d * 128, %(n)d * 128, 128, None) == 0
 n0 = rec.recorded()
 rc = lib.squat_cache_key_scores(h, 0x10000, 2, %(h)d * 128, 128, 1.0, 0x20000, %(h)d * %(n)d, %(n)d, None)
@@ -23,7 +24,7 @@ print(json.dumps(dict(rc=rc, grids=[list(rec.launch_at(i).contents.grid) for i i
 @pytest.mark.parametrize("pc", [0, 1])
 @pytest.mark.parametrize("b,h,n", [(1, 3, 2), (1, 65537, 2), (1, 131074, 31), (65537, 3, 31), (7, 65521, 1)])
 def test_full_precision_keys_alone(recorder, b, h, n, pc):
-    r = recorded.run(recorder, CODE % dict(b=b, h=h, n=n, r=32, pc=pc))
+    r = recorded.run(recorder, CODE % dict(b=b, h=h, n=n, r=32, pc=pc, dt=2))
     assert r["rc"] == 0 and len(r["grids"]) == 1
     x, y, z = r["grids"][0]
     assert y <= 65535 and z <= 65535 and x * y * z * 256 >= b * h * n * 8      # eight lanes per key
@@ -31,5 +32,23 @@ def test_full_precision_keys_alone(recorder, b, h, n, pc):
 
 @pytest.mark.parametrize("pc", [0, 1])
 def test_packed_keys_of_such_head_counts_stay_refused(recorder, pc):
-    r = recorded.run(recorder, CODE % dict(b=1, h=65537, n=33, r=32, pc=pc))
+    r = recorded.run(recorder, CODE % dict(b=1, h=65537, n=33, r=32, pc=pc, dt=2))
     assert r["rc"] == -2 and r["grids"] == []
+
+
+@pytest.mark.parametrize("pc", [0, 1])
+@pytest.mark.parametrize("b,h,n,r,dt,launches",
+                         [(1, 3, 32, 32, 2, 1), (1, 3, 33, 32, 2, 1), (8, 1536, 40, 32, 2, 1), (8, 1536, 41, 32, 1, 2),
+                          (1, 12289, 33, 32, 2, 2), (1, 6144, 40, 32, 0, 1), (1, 6145, 40, 32, 0, 2), (96, 1, 2047, 1024, 2, 1),
+                          (97, 1, 2047, 1024, 2, 2), (65535, 3, 33, 32, 2, 2)])
+def test_full_precision_keys_beside_packed_ones(recorder, b, h, n, r, dt, launches, pc):
+    got = recorded.run(recorder, CODE % dict(b=b, h=h, n=n, r=r, pc=pc, dt=dt))
+    assert got["rc"] == 0 and len(got["grids"]) == launches
+    tail, es = n % r, 4 if dt == 0 else 2
+    eights = (tail + 7) // 8
+    assert launches == 1 + (b * h * eights * 8 * 128 * es > 24 << 20)
+    x, y, z = got["grids"][0]
+    if launches == 1:                                     # a row per head, and wavefronts (four a workgroup) for the tail behind
+        assert z == 1 and y <= 65535 and x * (y - b * h) * 4 >= b * h * eights > (x * (y - b * h) - x) * 4 - 4
+    else:
+        assert y * z == b * h
