@@ -384,14 +384,22 @@ __global__ void __launch_bounds__(kRedTileThreads) gram_reduce_tiles(const float
 #pragma unroll
         for (int u = 0; u < 16; ++u) sum += static_cast<double>(v[u]);
     }
-    {
-        float v[15];
+    if (w + 8 <= wgs_per_head) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(src + static_cast<int64_t>(w + u) * kPartialFloats);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += static_cast<double>(v[u]);
+        w += 8;
+    }
+    if (w < wgs_per_head) {
+        float v[7];
         const int left = wgs_per_head - w;
 #pragma unroll
-        for (int u = 0; u < 15; ++u)
+        for (int u = 0; u < 7; ++u)
             v[u] = u < left ? __builtin_nontemporal_load(src + static_cast<int64_t>(w + u) * kPartialFloats) : 0.0f;
 #pragma unroll
-        for (int u = 0; u < 15; ++u) sum += static_cast<double>(v[u]);
+        for (int u = 0; u < 7; ++u) sum += static_cast<double>(v[u]);
     }
     int a = 0, b = 0;
     {
@@ -594,16 +602,27 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     p.st = q_stride_token * es;
     p.n_tokens = n_tokens;
     p.q_per_kv = q_per_kv;
-    // Chunks per wavefront at least (the workspace has room for pl.wgs_per_head partials of a head, one CU each): every
-    // workgroup leaves a partial of 40 KB and pays ~5 us for reducing and writing it, so eight where that still makes 32
-    // workgroups, two where it does not, and two for fp32, whose chunk takes 5 k cycles on the matrix cores.  Gram and
-    // reduction, us at 8 | 2 | 1 chunks: fp32, 1 head of 512 tokens 34 | 16 | 14, 8 heads of 512 35 | 18 | 17, 1 x 4 heads of
-    // 4096 32 | 21 | 24; bf16, 1 head of 512 15.9 | 11.4 | 12.3, 8 of 512 16.4 | 13.0 | 14.9, 64 of 512 17.7 | 23.9 | 23.8.
+    // Chunks per wavefront at least (the workspace has room for pl.wgs_per_head partials of a head).  Every workgroup leaves
+    // a partial of 40 KB and pays ~5 us for reducing and writing it, so eight chunks, or two: for 16-bit queries where eight
+    // leave no more than 16 workgroups; for fp32, whose chunk takes 5 k cycles on the matrix cores, as far as the launch
+    // stays within one workgroup per CU (one fills a CU's LDS: more run in a second round).
+    // Gram and reduction, us at 8 | 2 chunks: bf16, 1 head of 512 tokens 12.9 | 11.3, 8 of 512 14.1 | 13.2, 16 of 512 15.8 |
+    // 15.2, 16 of 200 14.5 | 15.0, 24 of 512 17.5 | 17.4, 24 of 200 16.1 | 16.7, 32 of 512 17.7 | 19.2, 8 of 1024 14.4 | 13.2,
+    // 24 of 1024 18.0 | 18.7.  fp32, 1 head of 512 31.6 | 15.7, 8 of 512 32.7 | 17.5, 64 of 512 37.7 | 31.7; 28 heads x 4
+    // of 1024: 8 workgroups a head 40.3, 9 (one round) 41.4, 10 (two rounds) 60.1; 48 heads of 2048: 42.4, 5 a head 41.3, 6
+    // (two rounds) 57.9.
     const int64_t units = q_per_kv * ((n_tokens + 15) / 16);
     const int64_t wide = (units + 8 * kGramWaves - 1) / (8 * kGramWaves);
     const int64_t narrow = (units + 2 * kGramWaves - 1) / (2 * kGramWaves);
-    const int64_t want = q_dt == SQUAT_F32 || n_kv_heads * wide < 32 ? narrow : wide;
-    p.wgs_per_head = static_cast<int>(want < pl.wgs_per_head ? want : pl.wgs_per_head);
+    const int64_t room = pl.wgs_per_head, per_cu = kPlanCUs / n_kv_heads;
+    int64_t wgs = wide < room ? wide : room;
+    if (q_dt == SQUAT_F32) {
+        const int64_t most = narrow < per_cu ? narrow : per_cu;
+        wgs = most > wgs ? most : wgs;
+    } else if (n_kv_heads * wide <= 16) {
+        wgs = narrow < room ? narrow : room;
+    }
+    p.wgs_per_head = static_cast<int>(wgs);
     p.chunks_per_qhead = (n_tokens + 15) / 16;
     p.units_per_head = p.chunks_per_qhead * q_per_kv;
     p.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + pl.off_partial);
@@ -616,9 +635,10 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     int rc = check_launch();
     if (rc) return rc;
     // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head (us
-    // for Gram and reduction, per head | spread: 1 head, 2 partials 16.1 | 11.4; 32 heads, 1 partial 21.4 | 19.8 (fp32); 128
-    // heads, 2 partials 23.4 | 30.0; 256 heads, 1 partial 21.9 | 38.8: the scattered 8-byte writes)
-    if (p.wgs_per_head >= 4 || n_kv_heads <= 32)
+    // for Gram and reduction, per head | spread: bf16, 1 partial a head, 16 heads of 200 tokens 15.9 | 14.5, 24 of 200 16.1 |
+    // 16.1, 32 of 200 16.4 | 17.5; 2 partials, 32 of 1024 20.6 | 19.6, 36 of 1024 21.0 | 20.9, 40 of 1024 21.1 | 21.4; 256
+    // heads, 1 partial 21.9 | 38.8: the scattered 8-byte writes)
+    if (p.wgs_per_head >= 4 || n_kv_heads <= (p.wgs_per_head == 1 ? 24 : 32))
         hipLaunchKernelGGL(gram_reduce_tiles, dim3(kRedTileBlocks, static_cast<unsigned>(n_kv_heads)), dim3(kRedTileThreads), 0, s, p.partial,
                            p.wgs_per_head, g64, gram_out, accumulate);
     else

@@ -52,6 +52,10 @@ def start(recorder: str):
     lib.squat_cache_prefill.argtypes = [vp, vp, vp, i64, i64, i64, i64, vp]
     lib.squat_cache_append.argtypes = [vp, vp, vp, i64, i64, vp]
     lib.squat_cache_key_scores.argtypes = [vp, vp, ctypes.c_int, i64, i64, ctypes.c_float, vp, i64, i64, vp]
+    lib.squat_build_subspace_workspace.restype = ctypes.c_size_t
+    lib.squat_build_subspace_workspace.argtypes = [i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    lib.squat_build_subspace.argtypes = [vp, ctypes.c_int, i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, i64, i64, ctypes.c_int,
+                                         vp, vp, vp, vp, ctypes.c_size_t, vp]
     return rec, lib
 
 
