@@ -40,12 +40,15 @@ constexpr int kUnitTokens = 16;        // tokens per matrix product (MFMA N)
 constexpr int kMaxUnitsPerWave = 32;   // 16-token units a wavefront aims at (amortises its operand set-up; up to 1.5x) ...
 constexpr int kMinUnitsPerWave = 2;    // ... unless that leaves the chip idle: then the launch is spread over
 constexpr int kScoreWorkgroups = 1024; // about this many workgroups (four per CU), down to one pair of units a wavefront
+constexpr int kScoreWorkgroupsFew = 512;   // 4 bits in groups of 32: its registers leave room for three per CU
 constexpr int kScoreWaves = 4;
 // Measured (2-bit, groups of 32, 8 KV heads x 4 query heads; us with the work spread over no more workgroups than 32
 // units a wavefront give | 256 | 512 | 1024 | 2048): 1 sequence of 1024 tokens 6.1 | 3.1 | 3.0 | 3.0 | 3.0; 1 of 32768
 // 11.9 | 7.8 | 6.2 | 6.3 | 8.1; 4 of 4096 10.7 | 5.1 | 4.8 | 4.9 | 4.9; 32 of 2048 12.4 | 12.5 | 9.3 | 8.6 | 10.1;
 // 64 of 2080 16.0 | 15.8 | 15.8 | 14.7 | 16.7.  Pairs against fours of units as the least: 3.0 against 3.4, 3.4
-// against 3.9 (1 of 4096), no difference elsewhere.
+// against 3.9 (1 of 4096), no difference elsewhere.  4 bits in groups of 32 (32 units a wavefront | 512 workgroups | 768 |
+// 1024): 1 of 32768 13.9 | 7.8 | 7.8 | 9.0; 16 of 2048 13.8 | 7.8 | 7.8 | 8.9; 64 of 512 7.5 | 7.6 | 7.7 | 8.4; 64 of 1024
+// 11.4 | 11.7 | 11.7 | 12.6; 16 of 8192, 8 query heads, 22.6 | 22.9 | 23.3 | 24.1.
 
 struct ScoreParams {
     const uint32_t* codes;
@@ -524,7 +527,8 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     // Workgroups along the sequence: about kScoreWaves * aim units each, the count rounded to
     // nearest and the units then spread evenly, so that no workgroup pays the operand set-up for a sliver
     // (2080 tokens = 130 units used to run as 128 + 2 and took 60 % longer than 2048 tokens).
-    const int64_t aim = units_per_wave(n_units, n_batch * n_kv_heads, kScoreWaves, kScoreWorkgroups, kMinUnitsPerWave,
+    const int64_t aim = units_per_wave(n_units, n_batch * n_kv_heads, kScoreWaves,
+                                       bits == 4 && group == 32 ? kScoreWorkgroupsFew : kScoreWorkgroups, kMinUnitsPerWave,
                                        kMaxUnitsPerWave);
     const int64_t slab = kScoreWaves * aim;
     int64_t gx = (n_units + slab / 2) / slab;

@@ -56,6 +56,8 @@ def start(recorder: str):
     lib.squat_build_subspace_workspace.argtypes = [i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.squat_build_subspace.argtypes = [vp, ctypes.c_int, i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, i64, i64, ctypes.c_int,
                                          vp, vp, vp, vp, ctypes.c_size_t, vp]
+    lib.squat_key_scores.argtypes = [vp, vp, vp, i64, ctypes.c_int, i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, vp, ctypes.c_int,
+                                     ctypes.c_int, i64, i64, ctypes.c_float, vp, i64, i64, vp]
     return rec, lib
 
 

@@ -52,3 +52,27 @@ def test_full_precision_keys_beside_packed_ones(recorder, b, h, n, r, dt, launch
         assert z == 1 and y <= 65535 and x * (y - b * h) * 4 >= b * h * eights > (x * (y - b * h) - x) * 4 - 4
     else:
         assert y * z == b * h
+
+
+@pytest.mark.parametrize("bits,group", [(2, 32), (2, 128), (4, 32), (4, 64)])
+def test_workgroups_of_the_packed_keys(recorder, bits, group):
+    """A launch is spread over the chip as far as its workgroups are resident together: 4 bits in groups of 32 leave room for
+    three per CU, the others for four."""
+    shapes = [(b, n) for b in (1, 4, 8, 16, 64, 100, 512) for n in (33, 512, 1000, 1024, 4096, 8192, 32768)]
+    code = """
+out = []
+for b, n in %r:
+    n0 = rec.recorded()
+    assert lib.squat_key_scores(0x10000, 0x20000, 0x30000, b, 8, n, 128, %d, %d, 0x40000, 2, 4, 8 * 4 * 128, 128, 1.0, 0x50000,
+                                8 * 4 * n, n, None) == 0
+    assert rec.recorded() == n0 + 1
+    out.append(list(rec.launch_at(n0).contents.grid))
+print(json.dumps(out))
+""" % (shapes, bits, group)
+    aim = 512 if (bits, group) == (4, 32) else 1024
+    for (b, n), (x, y, z) in zip(shapes, recorded.run(recorder, code)):
+        units = -(-n // 16)
+        assert (y, z) == (8 * b, 1) and x * y <= max(1.5 * aim, 1.5 * units * y / (4 * 32) + y)
+        if units * y <= 4 * 32 * aim:                     # less work than fills the chip with full wavefronts
+            assert x * y <= 1.5 * aim or x == 1
+            assert x * y >= min(aim / 2, units * y // 8)  # (down to a pair of units a wavefront)
