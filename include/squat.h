@@ -98,7 +98,8 @@ const char* squat_strerror(int status);
  *   0 <= r <= d.  n_tokens >= 1.  The Gram products are exact for bf16/f16
  *   inputs and accumulate in fp32 within a slab of tokens, fp64 across slabs;
  *   the eigen-solver works in fp64 (r <= 64: Householder tridiagonalisation,
- *   Sturm-count search, inverse iteration, the vectors in batches of 32;
+ *   Sturm-count search, twisted factorisations (inverse iteration where
+ *   eigenvalues nearly coincide), the vectors in batches of 32;
  *   otherwise, or if that route's own checks fail for a head, cyclic
  *   one-sided Jacobi).
  * ------------------------------------------------------------------------- */

@@ -123,8 +123,9 @@ __device__ __forceinline__ void residual_scores(const Params& p, int64_t t0) {
 
 // Round-to-nearest (Section 2's quantizer, no update matrix) of one token held by a team of eight lanes (an aligned run of
 // the wavefront), 16 consecutive channels x per lane; groups of LG lanes.  The same arithmetic, instruction by instruction,
-// as the tile kernel of squat_quantize_keys runs with update = NULL on a tile of this one token, so the stored words are
-// the same whichever kernel a token meets.  words: BITS / 2 packed words of the lane's channels; sbits, zbits: its
+// as the tile kernel of squat_quantize_keys runs with update = NULL on a tile of this one token.  (A tile of more tokens
+// takes the form with the clamp for all of them if one needs it, so its words can differ from these by a code where a
+// value falls on a rounding boundary.)  words: BITS / 2 packed words of the lane's channels; sbits, zbits: its
 // group's scale and zero-point.
 template <int BITS>
 __device__ __forceinline__ void quantize_token(const float (&x)[16], int lg, uint32_t (&words)[BITS / 2], uint16_t& sbits,

@@ -193,8 +193,8 @@ __device__ __forceinline__ double tri_team_sum(double v) {
 // alpha e_1, u = A v = A x - alpha A e_1, K = beta / 2 v'u, t = u - K v, the rank-two update A - beta (v t' + t v') of
 // its registers, and the next column.  alpha and beta do not depend on the exchange and overlap the products A x.  Sums
 // over a vector are taken over the eight lanes of a team (16 entries per lane): three stages, not a wavefront's six.
-// Bound by instruction issue (one wavefront per SIMD, ~5 cycles an instruction) and the latency of the chain: 3200
-// cycles for the first steps, 1100 for the last, 98 us for the 126 of one head, against 139 us with the column, its
+// Bound by instruction issue (one wavefront per SIMD, 5.4 cycles an instruction) and the latency of the chain: 2990
+// cycles for the 556 instructions of a first step, 1200 for the 152 of a last one, 98 us for the 126 of one head, against 139 us with the column, its
 // norm, A v and v'p exchanged in turn between two barriers (of one head's 290 us in all, 32 directions).
 //
 // The copies of an entry in different lanes and wavefronts have to stay the same to the last bit: a difference d

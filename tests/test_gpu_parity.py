@@ -337,7 +337,7 @@ def _subspace_checks(q_np, r, qpk=1, scale_tol=1.0):
 
 def test_subspace_special_spectra():
     """Spectra that stress the eigen-solver (tridiagonal reduction, Sturm-count search,
-    inverse iteration): decaying, flat, rank-deficient, coincident eigenvalues, a single direction,
+    twisted factorisations, inverse iteration): decaying, flat, rank-deficient, coincident eigenvalues, a single direction,
     zero, and wildly different magnitudes across heads."""
     gen = synth.rng(1250)
     d = 128
@@ -451,8 +451,8 @@ def test_prepare_full_precision_matches_oracle(r, lam, g):
 
 @pytest.mark.parametrize("r,g", [(20, 32), (44, 32), (64, 64)])
 def test_prepare_mixed_conditioning_picks_the_route_per_head(r, g):
-    """r <= 64, finite lambda: heads whose S = I / lambda + Qr Qr^T is well conditioned take the Cholesky
-    route (large rows of full rank, or zero rows at ordinary scale); a head with zero rows AND lambda *
+    """r <= 64, finite lambda: heads whose S = I / lambda + Qr Qr^T is well conditioned take the block
+    elimination (large rows of full rank, or zero rows at ordinary scale); a head with zero rows AND lambda *
     sigma^2 ~ 1e12 (eigenvalues 1 / lambda next to sigma^2) is flagged and redone by the eigen route (the
     one-wavefront kernel up to r = 32, the workgroup-per-panel kernel beyond).  All must match the oracle;
     the flags live in the last 256-byte-aligned block of the workspace."""

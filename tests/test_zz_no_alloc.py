@@ -41,7 +41,7 @@ def _qhat(seed, H, r):
 
 
 def test_noalloc_matches_prepare_on_consecutive_calls_of_shrinking_size():
-    calls = [(_qhat(9100, 24, 32), 1e-3, 32),         # Cholesky route: one flag per head in the scratch
+    calls = [(_qhat(9100, 24, 32), 1e-3, 32),         # block elimination: one flag per head in the scratch
              (_qhat(9101, 7, 16), 1e-3, 32),          # smaller, same route: flags 7..23 are stale
              (_qhat(9102, 5, 40), 5e-4, 64),          # r > 32: intermediate products in the scratch
              (_qhat(9103, 3, 34), 1e-3, 32),          # smaller again
@@ -58,7 +58,7 @@ def test_noalloc_matches_prepare_on_consecutive_calls_of_shrinking_size():
 
 
 def test_noalloc_flagged_heads_take_the_fallback_route_through_the_static_flags():
-    """A head whose Cholesky pivots span too much is flagged (in the scratch) and redone by the eigen route;
+    """A head whose elimination pivots span too much is flagged (in the scratch) and redone by the eigen route;
     the call before it left other flags behind."""
     H, r, g, lam = 4, 20, 32, 50.0
     gen = synth.rng(1450)
