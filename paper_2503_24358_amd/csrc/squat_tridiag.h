@@ -4,11 +4,11 @@
 // eigenpairs of its Gram matrix):
 //
 //   1. Householder reduction to tridiagonal form T.  The matrix lives in the
-//      REGISTERS of four wavefronts (one per SIMD), dealt out cyclically: thread
-//      (team, lane l of the team of 8) holds rows team, 32 + team, 64 + team,
-//      96 + team at columns l, 8 + l, .., 120 + l, so the trailing block
-//      shrinks in every thread at once; per step only the product A x and the
-//      next column travel through LDS (one barrier per step).
+//      REGISTERS of four wavefronts (one per SIMD): a wavefront holds the rows of
+//      its own number modulo 4, two lanes a row, one the even, one the odd
+//      columns, so the trailing block shrinks in every wavefront at once and a
+//      product with a vector stays in the lane; per step only the product A x, the
+//      next column and one number per wavefront travel through LDS (one barrier).
 //   2. The r largest eigenvalues of T by Sturm counts (a team of threads per
 //      eigenvalue, one or two trial shifts each): the count
 //      is the number of sign changes of the three-term recurrence of the leading
@@ -38,13 +38,10 @@
 namespace squat {
 
 constexpr int kTriN = 128;
-constexpr int kTriRows = 4;             // matrix rows per thread in the reduction: one wavefront per SIMD, with all of its 512
-                                        // registers (the first steps hold ~280; capped at 256 they spilled to scratch memory,
-                                        // 10000 cycles a step instead of 3200)
-constexpr int kTriThreads = kTriN / kTriRows * 8;      // a row's 128 columns are spread over 8 lanes
-static_assert(kTriThreads == 256 && (kTriN / kTriRows) % 8 == 0, "whole wavefronts of 8 teams hold the matrix");
+constexpr int kTriThreads = 256;        // one wavefront per SIMD, with all of its 512 registers
 constexpr int kTriMaxR = 32;            // vectors the LDS plan holds
 constexpr double kTriGap = 1e-11;       // closest eigenvalues (of the spectrum's scale) whose vectors are taken from the twisted form
+constexpr double kTriTiny = 1e-290;     // |x|^2 below which a column counts as zero
 constexpr double kTriPivMin = 2.0e-19;  // smallest pivot
 constexpr double kTriBound = 3.0001;     // > the largest eigenvalue of a tridiagonal matrix with entries of at most 1
 constexpr double kTriPart = 2.0 * kTriBound / 257.0;
@@ -52,8 +49,8 @@ constexpr double kTriWidth = 4.5e-16;   // width of an eigenvalue's bracket (one
 constexpr double kTriAccept = 1e-9;     // ||T x - lambda x|| / ||T|| and |x_i . x_j| allowed before the fallback
 
 // LDS plan, in doubles
-constexpr int kTriXs = 0;               // [2][128] next column of A (double-buffered), by owner; later [128][2] (d, e^2) from the last row up
-constexpr int kTriPs = 256;             // [2][128] A x, by owner
+constexpr int kTriSs = 0;               // [2][4][64] in the reduction: the wavefronts' parts of x'A x (lanes 16 .. 31)
+constexpr int kTriXs = 0;               // [128][2] later: (d, e^2) from the last row up
 constexpr int kTriDd = 512;             // [128] diagonal of T (then normalised)
 constexpr int kTriEe = 640;             // [128] sub-diagonal (then normalised)
 constexpr int kTriBet = 768;            // [128] beta of every reflector
@@ -65,6 +62,8 @@ constexpr int kTriU0 = kTriX + 4096;    // [128][32] reciprocal pivots
 constexpr int kTriU1 = kTriU0 + 4096;
 constexpr int kTriU2 = kTriU1 + 4096;
 constexpr int kTriS = kTriU2 + 4096;    // [32][33] Gram matrix / Cholesky factor, or [8][16][17] the blocks' T factors
+constexpr int kTriPs = kTriS;           // in the reduction: [2][128] A x
+constexpr int kTriCs = kTriS + 256;     // and [2][128] the next column of A
 constexpr int kTriTLd = 17;
 constexpr int kTriLdsDoubles = kTriS + 8 * 16 * kTriTLd;
 constexpr size_t kTriLdsBytes = static_cast<size_t>(kTriLdsDoubles) * sizeof(double);
@@ -134,34 +133,21 @@ __device__ __forceinline__ double tri_readlane(double v, int src) {
     return __hiloint2double(hi, lo);
 }
 
-// 1 / sqrt(x) and 1 / x from the hardware approximations and Newton steps (short dependent chains: the
-// library routines would sit on the critical path of every Householder step).  The approximations are good
-// to 5e-8 relative (measured over 2^22 arguments across 120 binades), so two steps reach the last bit: the
-// largest relative error after one step is 4e-15, after two 2.6e-16 (reciprocal: 0 against the library's
-// division), and a third changes nothing.
+// 1 / sqrt(x) and 1 / x from the hardware approximations, good to 5e-8 relative, and one step of the series in the remaining
+// error up to its cube (short dependent chains: the library routines would sit on the critical path of every Householder
+// step).  Largest relative errors over 2^22 arguments across 120 binades: 1.4e-16 and 1.1e-16 (two Newton steps: 2.6e-16).
 __device__ __forceinline__ double tri_rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const double e = fma(-x * y, y, 1.0);
-        y = fma(0.5 * y, e, y);
-    }
-    return y;
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);                 // 1 / sqrt(x) = y (1 + e / 2 + 3 e^2 / 8 + 5 e^3 / 16 + ..)
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 __device__ __forceinline__ double tri_rcp(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) y = fma(y, fma(-x, y, 1.0), y);
-    return y;
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);                     // 1 / x = y (1 + e + e^2 + e^3 + ..)
+    return fma(y, fma(e, e, e), y);
 }
 
-// Lane roles inside a wavefront of the reduction: the eight lanes of a team differ in lane bits 5, 4 and 0 (column
-// index l), the team in bits 3..1.  Four row sums of a team then cost four row / half swaps of the wavefront and one
-// lane permute instead of three lane permutes each, and leave row r's sum in the lanes with (lane >> 4) == r.
-__device__ __forceinline__ int tri_l(int lane) { return (lane >> 4) * 2 + (lane & 1); }
-__device__ __forceinline__ int tri_team(int tid) { return (tid >> 6) * 8 + ((tid >> 1) & 7); }
-__device__ __forceinline__ int tri_lane_of(int l) { return (l >> 1) * 16 + (l & 1); }     // a lane with column index l
-
+// Sum over the two halves of a wavefront / over pairs of 16 lanes, of two numbers at once.
 __device__ __forceinline__ double tri_swap32_add(double a, double b) {      // lanes < 32: a over both halves, else b
     const auto sl = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(__double2loint(a)), static_cast<uint32_t>(__double2loint(b)), false, false);
     const auto sh = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(__double2hiint(a)), static_cast<uint32_t>(__double2hiint(b)), false, false);
@@ -174,153 +160,191 @@ __device__ __forceinline__ double tri_swap16_add(double a, double b) {      // e
     return __hiloint2double(static_cast<int>(sh[0]), static_cast<int>(sl[0])) +
            __hiloint2double(static_cast<int>(sh[1]), static_cast<int>(sl[1]));
 }
-// Sum over a team, the same bits in all of its lanes (and in every team that sums the same numbers).
-__device__ __forceinline__ double tri_team_sum(double v) {
-#pragma clang fp contract(off)                            // a product folded into one side of an addition would round differently per lane
-    v += dpp_move(v, 0);
-    v = tri_swap16_add(v, v);
-    return tri_swap32_add(v, v);
-}
 
-// Householder steps, grouped by the register CC = (k + 1) / 8 of the first column k1 = k + 1 that stays (a compile-time
-// index).  Rows and columns are dealt out cyclically: thread (team, l) holds rows team, 32 + team, 64 + team, 96 + team
-// at columns 8 c + l, c = 0 .. 15.  The trailing block then shrinks in every thread at once: registers c < CC hold
-// finished columns for every lane and groups of rows below CC / 4 finished rows (both skipped at compile time).
+// ---- multiply-adds whose first factor is one lane's number for each row of 16 lanes (v_fmac_f64 with row_newbcast; at the
+// rate of the plain one).  Eight registers of matrix columns a[8] meet the lanes 0..7 (HI: 8..15) of x; the first M of them
+// are left out.  A lane permute must not read a register in the two cycles behind the instruction that wrote it, which the
+// compiler does not see here: each block waits first.
+#define TRI_FM(D, S, A, J) "v_fmac_f64_dpp " D ", " S ", " A " row_newbcast:" #J " row_mask:0xf bank_mask:0xf\n\t"
+#define TRI_BLOCK(P0, P1, P2, P3, ...)                                   \
+    do {                                                                 \
+        if constexpr (M == 0) asm("s_nop 1\n\t" P0 P1 P2 P3 __VA_ARGS__); \
+        else if constexpr (M == 2) asm("s_nop 1\n\t" P1 P2 P3 __VA_ARGS__); \
+        else if constexpr (M == 4) asm("s_nop 1\n\t" P2 P3 __VA_ARGS__); \
+        else asm("s_nop 1\n\t" P3 __VA_ARGS__);                          \
+    } while (0)
+
+// q0 + q1 += a x
+#define TRI_MV(B0, B1, J0, J1) TRI_FM("%0", "%2", B0, J0) TRI_FM("%1", "%2", B1, J1)
+#define TRI_MV_OPS : "+v"(q0), "+v"(q1) : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7])
+template <bool HI, int M>
+__device__ __forceinline__ void tri_mv(double& q0, double& q1, double x, const double* a) {
+    if constexpr (!HI)
+        TRI_BLOCK(TRI_MV("%3", "%4", 0, 1), TRI_MV("%5", "%6", 2, 3), TRI_MV("%7", "%8", 4, 5), TRI_MV("%9", "%10", 6, 7), TRI_MV_OPS);
+    else
+        TRI_BLOCK(TRI_MV("%3", "%4", 8, 9), TRI_MV("%5", "%6", 10, 11), TRI_MV("%7", "%8", 12, 13), TRI_MV("%9", "%10", 14, 15), TRI_MV_OPS);
+}
+// a += nv u + nt v
+#define TRI_UP(B0, B1, J0, J1) TRI_FM(B0, "%8", "%10", J0) TRI_FM(B1, "%8", "%10", J1) TRI_FM(B0, "%9", "%11", J0) TRI_FM(B1, "%9", "%11", J1)
+#define TRI_UP_OPS : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]) \
+    : "v"(u), "v"(v), "v"(nv), "v"(nt)
+template <bool HI, int M>
+__device__ __forceinline__ void tri_up(double* a, double u, double v, double nv, double nt) {
+    if constexpr (!HI)
+        TRI_BLOCK(TRI_UP("%0", "%1", 0, 1), TRI_UP("%2", "%3", 2, 3), TRI_UP("%4", "%5", 4, 5), TRI_UP("%6", "%7", 6, 7), TRI_UP_OPS);
+    else
+        TRI_BLOCK(TRI_UP("%0", "%1", 8, 9), TRI_UP("%2", "%3", 10, 11), TRI_UP("%4", "%5", 12, 13), TRI_UP("%6", "%7", 14, 15), TRI_UP_OPS);
+}
+#undef TRI_FM
+#undef TRI_BLOCK
+#undef TRI_MV
+#undef TRI_MV_OPS
+#undef TRI_UP
+#undef TRI_UP_OPS
+
+// Householder steps.  Wavefront w holds the rows 4 m + w, m = lane & 31, lane (h = lane >> 5, m) the columns 2 j + h, j = 0 ..
+// 63, of its row.  The vectors of a step are kept twice: by columns (register e of lane (h, i = lane & 15): entry 32 e + 2 i +
+// h, the same in every wavefront and in both rows of 16 lanes of a half), and the entry of the lane's own row.  A product with
+// a vector by columns takes its factors by broadcast inside the rows of 16 lanes, in the instruction itself.
 //
-// A step has ONE workgroup barrier.  Every thread carries the column being eliminated, x = A[k1.., k], in both of its
-// index sets (x: its columns, xr: its rows), so A x needs no exchange; the rows' sums and column k1 of A (not yet
-// updated) go to LDS, and after the barrier every wavefront forms the rest of the step from them by itself: v = x -
-// alpha e_1, u = A v = A x - alpha A e_1, K = beta / 2 v'u, t = u - K v, the rank-two update A - beta (v t' + t v') of
-// its registers, and the next column.  alpha and beta do not depend on the exchange and overlap the products A x.  Sums
-// over a vector are taken over the eight lanes of a team (16 entries per lane): three stages, not a wavefront's six.
-// Bound by instruction issue (one wavefront per SIMD, 5.4 cycles an instruction) and the latency of the chain: 2990
-// cycles for the 556 instructions of a first step, 1200 for the 152 of a last one, 98 us for the 126 of one head, against 139 us with the column, its
-// norm, A v and v'p exchanged in turn between two barriers (of one head's 290 us in all, 32 directions).
+// A step (k1 = k + 1 is the first column that stays) has ONE workgroup barrier.  Before it: p = A x for the wavefront's rows
+// (one sum over the halves), the wavefront's part of x'A x, and |x|^2; p, that part and column k1 of A (not yet updated; one
+// half of the lanes holds it, the other writes p in the same instruction) go to LDS.  After it every wavefront forms the rest
+// by itself: v = x - alpha e_1, u = A v = p - alpha A e_1, v'u = x'p - 2 alpha p_1 + alpha^2 a_11 (which costs no second sum
+// over the lanes), K = beta / 2 v'u, t = u - K v, the rank-two update A - beta (v t' + t v') = A - beta (v u' + (u - 2 K v) v')
+// of its rows, and the next column.  alpha and beta do not depend on the exchange.
+// Bound by instruction issue (one wavefront per SIMD, four cycles an instruction, fp64 or not, dependent or not) and, with the
+// blocks getting small, by the barrier and the exchange: 300 instructions and 1800 cycles a step at the start, 150 and 950 near
+// the end, 73 us for the 126 of one head.  Before, every thread held four rows at 16 columns and 20 entries of each vector
+// (16 by columns, a copy in each of a wavefront's eight teams, and 4 by rows), the sum x'u followed the exchange, and a step was
+// 556 and 152 instructions: 99 us.  What did not help: the same with two rows a lane and the sums over the wavefronts formed
+// by the readers (79 us; LDS), all steps unrolled (same time a step, the compiler spills), the scalars in front of the barrier.
+// Writes of many lanes to one LDS address cost 200 cycles a step: every lane has a place of its own, and T stays in registers.
 //
 // The copies of an entry in different lanes and wavefronts have to stay the same to the last bit: a difference d
 // between the copies of v becomes one of d |A| in the next column, relative to its size d |A| / |x|, step after step, which
 // grows without bound where the columns are small (a nearly diagonal matrix).  Hence the same operations in the same
 // order for rows and columns, explicit fma and no contraction.
-// Entries with index <= k are zero in x, xr and in the LDS vectors (written as zeros), so finished rows and columns
-// need no masks.
-// LDS vectors are stored by owner, entry i at 4 (i mod 32) + i / 32, so that a thread's four rows are contiguous.
-__device__ __forceinline__ int tri_pos(int row) { return 4 * (row & 31) + (row >> 5); }
+// Entries with index <= k are zero in x; finished rows and the finished columns that share a block of registers with others
+// are updated too (with finite numbers: a finished row is only turned by the reflectors) and never used.
+struct TriLane {
+    int lane, wave, row, col;                             // col: 2 i + h
+    int pos[2];                                           // where this lane writes its row in an odd / even step: p or column k1
+    int rowpos;                                           // its row's place in a vector by columns
+};
 
-// Step k = 8 CC + ll - 1 (column k1 = k + 1 is register CC of the lanes l == ll, row k1 register CC / 4 of one team).
-// x, xr: the column in this thread's columns and rows, replaced by v; y, yr receive the next column.
-template <int CC>
-__device__ __forceinline__ void tri_step(double (&a)[kTriRows][16], double (&x)[16], double (&y)[16], double (&xr)[kTriRows],
-                                         double (&yr)[kTriRows], int team, int l, int tid, double* L, const int ll, const int parity) {
+// A vector by columns in LDS: entry 32 e + 2 i + h, pairs of e beside each other.
+__device__ __forceinline__ int tri_pos(int entry) { return (entry >> 6) * 64 + (entry & 31) * 2 + ((entry >> 5) & 1); }
+
+// Steps with k1 = 8 G + ll: registers 4 G + ll / 2 of the lanes with h = ll & 1 hold column k1.  xr, xc: the column, replaced by
+// the next one.
+template <int G, int S>                                   // S = ll & 1
+__device__ __forceinline__ void tri_step(double (&a)[64], double& xr, double (&xc)[4], const TriLane& id, double (&T)[3],
+                                         double* const vp, double* L, const int ll) {
 #pragma clang fp contract(off)                            // every copy of an entry is to see the same roundings (see above)
-    constexpr int R0 = CC / 4;
-    const int lane = tid & 63;
-    const int k1 = 8 * CC + ll, k = k1 - 1;
-    double* ps = L + kTriPs + parity * kTriN;             // A x
-    double* cs = L + kTriXs + parity * kTriN;             // column k + 1 of A
-    const bool own_c = l == ll, own_r = 32 * R0 + team == k1, live_r = 32 * R0 + team > k;
-    // ---- A x (four rows), |x|^2
-    double q[kTriRows], o[kTriRows], s2[2];
-    static_assert(CC < 16, "registers CC .. 15");
-    constexpr int C1 = CC + 1 < 16 ? CC + 1 : CC;
+    constexpr int R = G / 4, B0 = G / 2, M = G % 2 * 4;
+    const int k1 = 8 * G + ll, src = 32 * S + ((4 * G + (ll >> 1)) & 15);      // (a lane that holds column k1)
+    const double* ps = L + kTriPs + S * kTriN;            // A x
+    const double* cs = L + kTriCs + S * kTriN;            // column k1 of A
+    double* sp = L + kTriSs + S * 256 + 16;               // the parts of x'A x, 64 doubles apart
+    // ---- A x for the wavefront's rows
+    double q0 = 0.0, q1 = 0.0;
+    tri_mv<B0 % 2 == 1, M>(q0, q1, xc[B0 / 2], a + 8 * B0);
+    if constexpr (B0 < 7) tri_mv<(B0 + 1) % 2 == 1, 0>(q0, q1, xc[(B0 + 1) / 2 & 3], a + 8 * ((B0 + 1) & 7));
+    if constexpr (B0 < 6) tri_mv<(B0 + 2) % 2 == 1, 0>(q0, q1, xc[(B0 + 2) / 2 & 3], a + 8 * ((B0 + 2) & 7));
+    if constexpr (B0 < 5) tri_mv<(B0 + 3) % 2 == 1, 0>(q0, q1, xc[(B0 + 3) / 2 & 3], a + 8 * ((B0 + 3) & 7));
+    if constexpr (B0 < 4) tri_mv<(B0 + 4) % 2 == 1, 0>(q0, q1, xc[(B0 + 4) / 2 & 3], a + 8 * ((B0 + 4) & 7));
+    if constexpr (B0 < 3) tri_mv<(B0 + 5) % 2 == 1, 0>(q0, q1, xc[(B0 + 5) / 2 & 3], a + 8 * ((B0 + 5) & 7));
+    if constexpr (B0 < 2) tri_mv<(B0 + 6) % 2 == 1, 0>(q0, q1, xc[(B0 + 6) / 2 & 3], a + 8 * ((B0 + 6) & 7));
+    if constexpr (B0 < 1) tri_mv<(B0 + 7) % 2 == 1, 0>(q0, q1, xc[(B0 + 7) / 2 & 3], a + 8 * ((B0 + 7) & 7));
+    q0 = q0 + q1;
+    q0 = tri_swap32_add(q0, q0);
+    const double k0 = a[4 * G], k2 = a[4 * G + 1], k4 = a[4 * G + 2], k6 = a[4 * G + 3];
+    const double ck = ll < 4 ? (ll < 2 ? k0 : k2) : (ll < 6 ? k4 : k6);
+    L[id.pos[S]] = id.lane >> 5 == S ? ck : q0;
+    double s2 = xc[3] * xc[3];
 #pragma unroll
-    for (int r = 0; r < kTriRows; ++r) {
-        q[r] = o[r] = 0.0;
-        if (r < R0) continue;
-        o[r] = a[r][CC];
-        double q0 = a[r][CC] * x[CC], q1 = CC + 1 < 16 ? a[r][C1] * x[C1] : 0.0;
+    for (int e = R; e < 3; ++e) s2 = fma(xc[e], xc[e], s2);
+    double z = tri_swap16_add(s2, xr * q0);               // even rows of 16 lanes: 2 |x|^2 of the half, odd ones: x'A x
 #pragma unroll
-        for (int c = CC + 2; c < 16; ++c) {
-            if ((c - CC) & 1) q1 = fma(a[r][c], x[c], q1);
-            else q0 = fma(a[r][c], x[c], q0);
-        }
-        q[r] = CC + 1 < 16 ? q0 + q1 : q0;
-    }
-    q[R0] = live_r ? q[R0] : 0.0;
-    s2[0] = x[CC] * x[CC];
-    s2[1] = CC + 1 < 16 ? x[C1] * x[C1] : 0.0;
-#pragma unroll
-    for (int c = CC + 2; c < 16; ++c) s2[(c - CC) & 1] = fma(x[c], x[c], s2[(c - CC) & 1]);
-    if (own_c) {
-        o[R0] = live_r ? o[R0] : 0.0;
-        *reinterpret_cast<double2*>(cs + 4 * team) = double2{o[0], o[1]};
-        *reinterpret_cast<double2*>(cs + 4 * team + 2) = double2{o[2], o[3]};
-    }
-    double mine = tri_swap16_add(tri_swap32_add(q[0], q[2]), tri_swap32_add(q[1], q[3]));
-    mine += dpp_move(mine, 0);
-    ps[4 * team + (lane >> 4)] = mine;                    // (both lanes of a pair hold and write the same sum)
-    // ---- the reflector's scalars: sigma = |x|^2, alpha, beta = 2 / v'v
-    const double sigma = tri_team_sum(CC + 1 < 16 ? s2[0] + s2[1] : s2[0]);
-    const double x0 = tri_readlane(x[CC], tri_lane_of(ll));
-    // (cancellation here only matters when the rest of x is ~1e-16 |x0|^2: then the reflector is the identity to
-    // working precision either way; a tiny negative result takes the identity)
-    const bool live = sigma - x0 * x0 > 0.0;
-    const double sq = sigma * tri_rsqrt(sigma);
-    const double alpha = live ? (x0 >= 0.0 ? -sq : sq) : x0;
-    const double beta = live ? tri_rcp(fma(fabs(x0), sq, sigma)) : 0.0;
+    for (int sel = 0; sel < 4; ++sel) z += dpp_move(z, sel);
+    sp[64 * id.wave + id.lane - 16] = z;                  // (a place for every lane: writes of many lanes to one are slow)
+    const double sigma2 = tri_readlane(z, 0) + tri_readlane(z, 32), x0 = tri_readlane(xc[R], src);
     tri_lds_barrier();
-    double t[16], pr[kTriRows];
+    double p[4], c[4];
 #pragma unroll
-    for (int c = CC; c < 16; ++c) {
-        t[c] = ps[4 * (8 * (c & 3) + l) + (c >> 2)];
-        y[c] = cs[4 * (8 * (c & 3) + l) + (c >> 2)];
+    for (int e = R & 2; e < 4; e += 2) {
+        if constexpr (R == 3) {
+            p[3] = ps[64 + 2 * id.col + 1];
+            c[3] = cs[64 + 2 * id.col + 1];
+        } else {
+            const double2 pe = *reinterpret_cast<const double2*>(ps + 32 * e + 2 * id.col);
+            const double2 ce = *reinterpret_cast<const double2*>(cs + 32 * e + 2 * id.col);
+            p[e] = pe.x; p[e + 1] = pe.y;
+            c[e] = ce.x; c[e + 1] = ce.y;
+        }
     }
-    const double p1 = ps[4 * (k1 & 31) + R0], c1 = cs[4 * (k1 & 31) + R0];
+    const double pr = ps[id.rowpos], cr = cs[id.rowpos];
+    const double s0 = sp[0], s1 = sp[64], s2b = sp[128], s3 = sp[192];
+    __builtin_amdgcn_sched_barrier(0);                    // the scalars are formed while these are on their way
+    // ---- the reflector's scalars: sigma = |x|^2, al = -alpha, beta = 2 / v'v.  A column of nothing (|x| < 1e-145, of entries
+    // of at most 2) takes the identity; alpha is then of that size as well.
+    const double sg = fma(0.5, sigma2, kTriTiny);
+    const double al = copysign(sg * tri_rsqrt(sg), x0);
+    const double binv = tri_rcp(fma(fabs(x0), fabs(al), sg));
+    const double beta = sigma2 > kTriTiny ? binv : 0.0;
+    __builtin_amdgcn_sched_barrier(0);
+    // u = A v
+    double u[4];
 #pragma unroll
-    for (int r = 0; r < kTriRows; r += 2) {
-        const double2 p2 = *reinterpret_cast<const double2*>(ps + 4 * team + r);
-        const double2 c2 = *reinterpret_cast<const double2*>(cs + 4 * team + r);
-        pr[r] = p2.x; pr[r + 1] = p2.y;
-        yr[r] = c2.x; yr[r + 1] = c2.y;
-    }
+    for (int e = R; e < 4; ++e) u[e] = fma(al, c[e], p[e]);
+    const double ur = fma(al, cr, pr);
+    const double u1 = tri_readlane(u[R], src), c1 = tri_readlane(c[R], src);
+    const double vu = fma(al, fma(-al, c1, u1 + u1), (s0 + s1) + (s2b + s3));
+    const double K2 = beta * vu;                          // 2 K
+    const double v1 = x0 + al;
+    const double bv1 = -beta * v1, bt1 = -beta * fma(-K2, v1, u1);
     // v = x - alpha e_1 in place of x
-    x[CC] -= own_c ? alpha : 0.0;
-    xr[R0] -= own_r ? alpha : 0.0;
-    // reflector k (the block of the later phases is free now)
-    *reinterpret_cast<double2*>(L + kTriX + k * kTriVLd + 4 * team) = double2{xr[0], xr[1]};
-    *reinterpret_cast<double2*>(L + kTriX + k * kTriVLd + 4 * team + 2) = double2{xr[2], xr[3]};
-    // u = A v = A x - alpha A e_1;  K = beta / 2 v'u;  t = u - K v  (w = beta t)
+    const bool own = id.row == k1;
+    xr = own ? v1 : xr;
+    xc[R] = id.col == (k1 & 31) ? v1 : xc[R];
+    vp[ll * kTriVLd] = xr;                                // reflector k (the block of the later phases is free now)
+    // rank-two update, and the next column.  (What is finished gets the high half of a zero: a number below 1e-313.)
+    const double nv = -beta * xr, nt = -beta * fma(-K2, xr, ur);
+    xr = fma(xr, bt1, fma(ur, bv1, cr));
+    // the lanes of row k1 keep T's entries d_k1 and -e_k, and beta
+    T[0] = own ? xr : T[0];
+    T[1] = own ? al : T[1];
+    T[2] = own ? beta : T[2];
+    xr = __hiloint2double(id.row > k1 ? __double2hiint(xr) : 0, __double2loint(xr));
+    double vc[4];
 #pragma unroll
-    for (int c = CC; c < 16; ++c) t[c] = fma(-alpha, y[c], t[c]);
-    double t2[2] = {x[CC] * t[CC], CC + 1 < 16 ? x[C1] * t[C1] : 0.0};
-#pragma unroll
-    for (int c = CC + 2; c < 16; ++c) t2[(c - CC) & 1] = fma(x[c], t[c], t2[(c - CC) & 1]);
-    const double K = 0.5 * beta * tri_team_sum(CC + 1 < 16 ? t2[0] + t2[1] : t2[0]);
-    const double v1 = x0 - alpha, t1 = fma(-K, v1, fma(-alpha, c1, p1));
-    const double bv1 = -beta * v1, bt1 = -beta * t1;
-#pragma unroll
-    for (int c = CC; c < 16; ++c) t[c] = fma(-K, x[c], t[c]);
-    if (tid == 0) {
-        L[kTriEe + k] = alpha;
-        L[kTriBet + k] = beta;
-        L[kTriDd + k1] = fma(2.0 * bv1, t1, c1);
+    for (int e = R; e < 4; ++e) {
+        vc[e] = xc[e];
+        xc[e] = fma(xc[e], bt1, fma(u[e], bv1, c[e]));
     }
-    // rank-two update, and the next column in both index sets
-#pragma unroll
-    for (int r = R0; r < kTriRows; ++r) {
-        const double ti = fma(-K, xr[r], fma(-alpha, yr[r], pr[r]));
-        const double nw = -beta * ti, nv = -beta * xr[r];
-        yr[r] = fma(xr[r], bt1, fma(ti, bv1, yr[r]));
-#pragma unroll
-        for (int c = CC; c < 16; ++c) a[r][c] = fma(nv, t[c], fma(nw, x[c], a[r][c]));
-    }
-#pragma unroll
-    for (int c = CC; c < 16; ++c) y[c] = fma(x[c], bt1, fma(t[c], bv1, y[c]));
-    y[CC] = own_c ? 0.0 : y[CC];
-    yr[R0] = own_r ? 0.0 : yr[R0];
+    xc[R] = __hiloint2double(id.col > (k1 & 31) ? __double2hiint(xc[R]) : 0, __double2loint(xc[R]));
+    tri_up<B0 % 2 == 1, M>(a + 8 * B0, u[B0 / 2], vc[B0 / 2], nv, nt);
+    if constexpr (B0 < 7) tri_up<(B0 + 1) % 2 == 1, 0>(a + 8 * ((B0 + 1) & 7), u[(B0 + 1) / 2 & 3], vc[(B0 + 1) / 2 & 3], nv, nt);
+    if constexpr (B0 < 6) tri_up<(B0 + 2) % 2 == 1, 0>(a + 8 * ((B0 + 2) & 7), u[(B0 + 2) / 2 & 3], vc[(B0 + 2) / 2 & 3], nv, nt);
+    if constexpr (B0 < 5) tri_up<(B0 + 3) % 2 == 1, 0>(a + 8 * ((B0 + 3) & 7), u[(B0 + 3) / 2 & 3], vc[(B0 + 3) / 2 & 3], nv, nt);
+    if constexpr (B0 < 4) tri_up<(B0 + 4) % 2 == 1, 0>(a + 8 * ((B0 + 4) & 7), u[(B0 + 4) / 2 & 3], vc[(B0 + 4) / 2 & 3], nv, nt);
+    if constexpr (B0 < 3) tri_up<(B0 + 5) % 2 == 1, 0>(a + 8 * ((B0 + 5) & 7), u[(B0 + 5) / 2 & 3], vc[(B0 + 5) / 2 & 3], nv, nt);
+    if constexpr (B0 < 2) tri_up<(B0 + 6) % 2 == 1, 0>(a + 8 * ((B0 + 6) & 7), u[(B0 + 6) / 2 & 3], vc[(B0 + 6) / 2 & 3], nv, nt);
+    if constexpr (B0 < 1) tri_up<(B0 + 7) % 2 == 1, 0>(a + 8 * ((B0 + 7) & 7), u[(B0 + 7) / 2 & 3], vc[(B0 + 7) / 2 & 3], nv, nt);
 }
 
-// The steps whose first remaining column k1 = k + 1 lies in 8 CC .. 8 CC + 7, two per trip: steps with an even k1 take
-// the column from (x, xr) and leave the next in (y, yr), odd ones the other way round.
-template <int CC>
-__device__ __forceinline__ void tri_steps(double (&a)[kTriRows][16], double (&x)[16], double (&y)[16], double (&xr)[kTriRows],
-                                          double (&yr)[kTriRows], int team, int l, int tid, double* L) {
-    if constexpr (CC == 0) tri_step<CC>(a, y, x, yr, xr, team, l, tid, L, 1, 1);
+// The steps whose first remaining column k1 = k + 1 lies in 8 G .. 8 G + 7, two per trip (the LDS buffers alternate).
+template <int G>
+__device__ __forceinline__ void tri_steps(double (&a)[64], double& xr, double (&xc)[4], const TriLane& id, double (&T)[3], double* L) {
+    double* const vp = L + kTriX + (8 * G - 1) * kTriVLd + id.row;
+    if constexpr (G == 0) tri_step<G, 1>(a, xr, xc, id, T, vp, L, 1);
 #pragma nounroll
-    for (int ll = CC == 0 ? 2 : 0; ll < (CC == 15 ? 6 : 8); ll += 2) {
-        tri_step<CC>(a, x, y, xr, yr, team, l, tid, L, ll, 0);
-        tri_step<CC>(a, y, x, yr, xr, team, l, tid, L, ll + 1, 1);
+    for (int ll = G == 0 ? 2 : 0; ll < (G == 15 ? 6 : 8); ll += 2) {
+        tri_step<G, 0>(a, xr, xc, id, T, vp, L, ll);
+        tri_step<G, 1>(a, xr, xc, id, T, vp, L, ll + 1);
     }
-    if constexpr (CC == 15) tri_step<CC>(a, x, y, xr, yr, team, l, tid, L, 6, 0);
+    if constexpr (G == 15) tri_step<G, 0>(a, xr, xc, id, T, vp, L, 6);
 }
 
 // g: the matrix (row-major doubles, symmetric positive semi-definite); vws: kTriWsDoubles doubles of
@@ -330,29 +354,27 @@ __device__ __forceinline__ void tri_steps(double (&a)[kTriRows][16], double (&x)
 // the block must call it; L: kTriLdsBytes of LDS, 16-byte aligned.
 __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, int r, float* qhat, float* eig,
                                                  double* L) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int team = tri_team(tid), l = tri_l(lane);      // this thread's rows team, 32 + team, ... and columns 8 c + l
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double* misc = L + kTriMisc;
 
-    // ---- load, scale by a power of two so that the largest entry is in [1, 2)
-    double a[kTriRows][16];
+    // ---- load (a column is read as the row of the same number: 512 bytes of a wavefront's load lie side by side), scale by a
+    // power of two so that the largest entry is in [1, 2)
+    TriLane id;
+    id.lane = lane;
+    id.wave = wave;
+    id.row = 4 * (lane & 31) + wave;
+    id.col = 2 * (lane & 15) + (lane >> 5);
+    id.rowpos = tri_pos(id.row);
+    id.pos[0] = (lane >> 5 == 0 ? kTriCs : kTriPs) + id.rowpos;
+    id.pos[1] = (lane >> 5 == 1 ? kTriCs : kTriPs) + kTriN + id.rowpos;
+    double a[64], xr = g[id.row], xc[4];                  // (xr, xc: column 0)
 #pragma unroll
-    for (int r = 0; r < kTriRows; ++r) {
-        const double* src = g + (kTriN / kTriRows * r + team) * kTriN + l;
+    for (int j = 0; j < 64; ++j) a[j] = g[(2 * j + (lane >> 5)) * kTriN + id.row];
 #pragma unroll
-        for (int c = 0; c < 16; ++c) a[r][c] = src[8 * c];
-    }
-    // column 0 in this thread's columns and rows (the matrix is symmetric)
-    double x[16], y[16], xr[kTriRows], yr[kTriRows];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) y[c] = g[8 * c + l];
-#pragma unroll
-    for (int r = 0; r < kTriRows; ++r) yr[r] = g[32 * r + team];
+    for (int e = 0; e < 4; ++e) xc[e] = g[32 * e + id.col];
     double amax = 0.0;
 #pragma unroll
-    for (int r = 0; r < kTriRows; ++r)
-#pragma unroll
-        for (int c = 0; c < 16; ++c) amax = fmax(amax, fabs(a[r][c]));
+    for (int j = 0; j < 64; ++j) amax = fmax(amax, fabs(a[j]));
     amax = tri_block_max(amax, misc, tid);
     if (!(amax > 0.0) || !(amax < 1e300)) {
         // zero matrix: zero eigenvalues, zero rows (also taken for NaN / Inf input: nothing sensible exists)
@@ -365,39 +387,42 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
     const int sexp = aexp < -1000 ? -1000 : (aexp > 1000 ? 1000 : aexp);
     const double down = tri_pow2(-sexp), up = tri_pow2(sexp);
 #pragma unroll
-    for (int r = 0; r < kTriRows; ++r)
-#pragma unroll
-        for (int c = 0; c < 16; ++c) a[r][c] *= down;
+    for (int j = 0; j < 64; ++j) a[j] *= down;
 
     // ---- 1. Householder reduction
-    for (int e = tid; e < 4 * kTriN; e += kTriThreads) L[e] = 0.0;      // column and product buffers: never read uninitialised
-    __syncthreads();
+    __syncthreads();                                      // (everyone is past amax's scratch)
+    const double d0 = a[0];
+    xr = id.row > 0 ? xr * down : 0.0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) y[c] = 8 * c + l > 0 ? y[c] * down : 0.0;
-#pragma unroll
-    for (int r = 0; r < kTriRows; ++r) yr[r] = 32 * r + team > 0 ? yr[r] * down : 0.0;
-    if (tid == 0) L[kTriDd] = a[0][0];
-    tri_steps<0>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<1>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<2>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<3>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<4>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<5>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<6>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<7>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<8>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<9>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<10>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<11>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<12>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<13>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<14>(a, x, y, xr, yr, team, l, tid, L);
-    tri_steps<15>(a, x, y, xr, yr, team, l, tid, L);
-    // the last 2 x 2 block: its first diagonal entry came with the last step, the next column is e_126, and the corner
-    // is in the last team's last row
-    if (team == 31 && l == 7) {
-        L[kTriDd + kTriN - 1] = a[kTriRows - 1][15];
-        L[kTriEe + kTriN - 2] = y[15];
+    for (int e = 0; e < 4; ++e) xc[e] = 32 * e + id.col > 0 ? xc[e] * down : 0.0;
+    double T[3] = {0.0, 0.0, 0.0};
+    tri_steps<0>(a, xr, xc, id, T, L);
+    tri_steps<1>(a, xr, xc, id, T, L);
+    tri_steps<2>(a, xr, xc, id, T, L);
+    tri_steps<3>(a, xr, xc, id, T, L);
+    tri_steps<4>(a, xr, xc, id, T, L);
+    tri_steps<5>(a, xr, xc, id, T, L);
+    tri_steps<6>(a, xr, xc, id, T, L);
+    tri_steps<7>(a, xr, xc, id, T, L);
+    tri_steps<8>(a, xr, xc, id, T, L);
+    tri_steps<9>(a, xr, xc, id, T, L);
+    tri_steps<10>(a, xr, xc, id, T, L);
+    tri_steps<11>(a, xr, xc, id, T, L);
+    tri_steps<12>(a, xr, xc, id, T, L);
+    tri_steps<13>(a, xr, xc, id, T, L);
+    tri_steps<14>(a, xr, xc, id, T, L);
+    tri_steps<15>(a, xr, xc, id, T, L);
+    // T and the reflectors' beta: rows 1 .. 126 from their steps; of the last 2 x 2 block the next column is e_126, and the
+    // corner is in the last row's last column
+    if (id.row == 0) {
+        if (lane == 0) L[kTriDd] = d0;
+    } else if (id.row < kTriN - 1) {
+        L[kTriDd + id.row] = T[0];
+        L[kTriEe + id.row - 1] = -T[1];
+        L[kTriBet + id.row - 1] = T[2];
+    } else if (lane == 63) {
+        L[kTriDd + kTriN - 1] = a[63];
+        L[kTriEe + kTriN - 2] = xr;
         L[kTriEe + kTriN - 1] = 0.0;
         L[kTriBet + kTriN - 2] = 0.0;
         L[kTriBet + kTriN - 1] = 0.0;
@@ -425,13 +450,13 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             double4v acc1 = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
             for (int m = 4 * b1; m < 4 * b2; ++m) {
-                const double x = v1[tri_pos(4 * m + mk)];
+                const double x = v1[4 * m + mk];
                 acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc1, 0, 0, 0);
             }
 #pragma unroll 4
             for (int m = 4 * b2; m < kTriN / 4; ++m) {
-                const double x = v1[tri_pos(4 * m + mk)];
-                double y = v2[tri_pos(4 * m + mk)];
+                const double x = v1[4 * m + mk];
+                double y = v2[4 * m + mk];
                 y = real ? y : 0.0;
                 acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc1, 0, 0, 0);
                 acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(y, y, acc2, 0, 0, 0);
@@ -472,10 +497,10 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const double x = vk[tri_pos(16 * tile + 4 * q + mk)];
+                const double x = vk[16 * tile + 4 * q + mk];
                 dst[64 * q] = real ? x : 0.0;
                 const bool kreal = 16 * b + 4 * q + mk < kTriN - 2;
-                double y = V[(kreal ? 16 * b + 4 * q + mk : 0) * kTriVLd + tri_pos(16 * tile + mi)];
+                double y = V[(kreal ? 16 * b + 4 * q + mk : 0) * kTriVLd + 16 * tile + mi];
                 y = kreal ? y : 0.0;
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(TS[(16 * b + 4 * q + mk) * kTriTLd + mi], y, acc, 0, 0, 0);
             }
