@@ -10,11 +10,11 @@
 //      product with a vector stays in the lane; per step only the product A x, the
 //      next column and one number per wavefront travel through LDS (one barrier).
 //   2. The r largest eigenvalues of T by Sturm counts (a team of threads per
-//      eigenvalue, one or two trial shifts each): the count
+//      eigenvalue, a trial shift each): the count
 //      is the number of sign changes of the three-term recurrence of the leading
 //      principal minors, division-free, rescaled by a power of two every 8 terms;
-//      once a bracket holds one eigenvalue the trial shifts follow the zero of the
-//      line through its ends.
+//      once a bracket holds one eigenvalue the trial shifts follow the zero of a
+//      linear fraction through its ends and a third shift.
 //   3. Eigenvectors of T by twisted factorisations (eigenvalues closer than 1e-11 of
 //      the spectrum's scale: by inverse iteration with shifts made distinct by a few
 //      ulps where eigenvalues coincide: two solves per vector by Gaussian
@@ -108,17 +108,6 @@ __device__ __forceinline__ void tri_lds_wait() { __builtin_amdgcn_s_waitcnt(0xC0
 
 __device__ __forceinline__ double tri_pow2(int e) {       // 2^e, -1022 <= e <= 1023
     return __hiloint2double((e + 1023) << 20, 0);
-}
-
-// Rescales a pair of consecutive minors by a power of two (the larger one to [1, 2)); returns the exponent taken out.
-__device__ __forceinline__ int tri_rescale(double& p0, double& p1) {
-    const double m = fmax(fabs(p0), fabs(p1));
-    int ex = ((__double2hiint(m) >> 20) & 0x7FF) - 1023;
-    ex = ex > -1000 && ex < 1000 ? ex : 0;
-    const double f = tri_pow2(-ex);
-    p0 *= f;
-    p1 *= f;
-    return ex;
 }
 
 // Workgroup barrier that orders LDS traffic only (the Householder loop touches nothing else; the full
@@ -347,6 +336,67 @@ __device__ __forceinline__ void tri_steps(double (&a)[64], double& xr, double (&
     if constexpr (G == 15) tri_step<G, 0>(a, xr, xc, id, T, vp, L, 6);
 }
 
+// Eight terms of the three-term recurrence of the leading principal minors of T - x, p_{i+1} = (d_i - x) p_i - e_{i-1}^2
+// p_{i-1}, for the rows whose d_i and -e_{i-1}^2 are held by the lanes 0 .. 7 (HI: 8 .. 15) of each row of 16 lanes; nx = -x.
+// (x p_i is rounded, d_i p_i is not: an error of x by half a unit in its last place.)  PIV: piv p_i is added, so that no minor
+// vanishes against the one before it.
+#define TRI_BC " row_newbcast:"
+#define TRI_FULL " row_mask:0xf bank_mask:0xf\n\t"
+#define TRI_T0(P2, P1, P0, J, W) "v_mul_f64 " P2 ", %10, " P1 "\n\t" W "v_fmac_f64_dpp " P2 ", %11, " P1 TRI_BC #J TRI_FULL "v_fmac_f64_dpp " P2 ", %12, " P0 TRI_BC #J TRI_FULL
+#define TRI_T1(P2, P1, P0, J, W) TRI_T0(P2, P1, P0, J, W) "v_fmac_f64_e32 " P2 ", %13, " P1 "\n\t"
+#define TRI_EIGHT(T, J0, J1, J2, J3, J4, J5, J6, J7)                                                                                \
+    asm(T("%0", "%8", "%9", J0, "s_nop 0\n\t") T("%1", "%0", "%8", J1, "") T("%2", "%1", "%0", J2, "") T("%3", "%2", "%1", J3, "")  \
+        T("%4", "%3", "%2", J4, "") T("%5", "%4", "%3", J5, "") T("%6", "%5", "%4", J6, "") T("%7", "%6", "%5", J7, "")             \
+        : "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(p[4]), "=&v"(p[5]), "=&v"(p[6]), "=&v"(p[7])                    \
+        : "v"(p1), "v"(p0), "v"(nx), "v"(d), "v"(e), "v"(piv))
+template <bool HI, bool PIV>
+__device__ __forceinline__ void tri_eight(double (&p)[8], double p0, double p1, double nx, double d, double e, double piv) {
+    if constexpr (!HI && !PIV) TRI_EIGHT(TRI_T0, 0, 1, 2, 3, 4, 5, 6, 7);
+    else if constexpr (!PIV) TRI_EIGHT(TRI_T0, 8, 9, 10, 11, 12, 13, 14, 15);
+    else if constexpr (!HI) TRI_EIGHT(TRI_T1, 0, 1, 2, 3, 4, 5, 6, 7);
+    else TRI_EIGHT(TRI_T1, 8, 9, 10, 11, 12, 13, 14, 15);
+}
+#undef TRI_BC
+#undef TRI_FULL
+#undef TRI_T0
+#undef TRI_T1
+#undef TRI_EIGHT
+
+// Rescales a pair of consecutive minors by a power of two (the larger one to [1/2, 1)); returns the exponent taken out.
+__device__ __forceinline__ int tri_rescale(double& p0, double& p1) {
+    double m;
+    asm("v_max_f64 %0, |%1|, |%2|" : "=v"(m) : "v"(p0), "v"(p1));
+    const int ex = __builtin_amdgcn_frexp_exp(m);         // (0 for a zero, an infinity or a NaN)
+    p0 = __builtin_ldexp(p0, -ex);
+    p1 = __builtin_ldexp(p1, -ex);
+    return ex;
+}
+
+// Sturm count (sign changes of the minors) and last minor p1 2^ex of T - x; d, e: lane i of a row of 16 lanes holds the rows
+// 16 b + i.  Four instructions a term (with T read from LDS, one 16-byte read a term, they were eight: 46 cycles a term where
+// this takes 21 with its share of the rescaling and counting).
+__device__ __forceinline__ void tri_minors(const double (&d)[8], const double (&e)[8], double x, double& p1, int& cnt, int& ex) {
+    double p0 = 0.0;
+    uint32_t signs = 0;                                   // newest at bit 0; that of p_0 = 1 is 0
+    p1 = 1.0;
+    cnt = ex = 0;
+    auto eight = [&](int b, auto hi_tag) __attribute__((always_inline)) {
+        double p[8];
+        tri_eight<decltype(hi_tag)::value, false>(p, p0, p1, -x, d[b], e[b], 0.0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) signs = __builtin_amdgcn_alignbit(signs, static_cast<uint32_t>(__double2hiint(p[u])), 31);
+        p0 = p[6];
+        p1 = p[7];
+        ex += tri_rescale(p0, p1);
+    };
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        eight(b, std::false_type{});
+        eight(b, std::true_type{});
+        cnt += __popc((signs ^ (signs >> 1)) & 0xFFFFu);
+    }
+}
+
 // g: the matrix (row-major doubles, symmetric positive semi-definite); vws: kTriWsDoubles doubles of
 // scratch in global memory; qhat: r rows of 128 floats = sqrt(lambda_j) v_j, eigenvalues descending;
 // eig: r floats or NULL; r <= 2 kTriMaxR.  Returns (to every thread) whether the result was accepted; if not, the
@@ -436,8 +486,9 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
     // (kept in registers meanwhile they slow steps 2-4 down: 40 k cycles more in the search).  v_mfma_f64_16x16x4_f64: A lane (i = lane & 15, k = lane >> 4), B lane (j = lane & 15, k = lane >> 4), result
     // lane (j = lane & 15), register q: row (lane >> 4) + 4 q, i.e. a result is the B operand of the next product as it is.
     const int mi = lane & 15, mk = lane >> 4;
-    // [wavefront][9 (tile, block) pairs: tile 7 - wave with blocks 0 .. 7 - wave, tile `wave` with blocks 0 .. wave][8][64]
-    double* const vmine = vws + wave * kTriWsPerWave + lane;
+    // [wavefront][9 (tile, block) pairs: tile 7 - wave with blocks 0 .. 7 - wave, tile `wave` with blocks 0 .. wave]
+    // [registers 0 1, 2 3 of V', of -(V T)'][64][2]
+    double2* const vmine = reinterpret_cast<double2*>(vws + wave * kTriWsPerWave);
     {
         const double* V = L + kTriX;
         double* TS = L + kTriS;
@@ -491,26 +542,29 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             }
         }
         __syncthreads();
-        auto operands = [&](const int tile, const int b, double* dst) __attribute__((always_inline)) {
+        auto operands = [&](const int tile, const int b, double2* dst) __attribute__((always_inline)) {
             const bool real = 16 * b + mi < kTriN - 2;
             const double* vk = V + (real ? 16 * b + mi : 0) * kTriVLd;
             double4v acc = {0.0, 0.0, 0.0, 0.0};
+            double x[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const double x = vk[16 * tile + 4 * q + mk];
-                dst[64 * q] = real ? x : 0.0;
+                x[q] = vk[16 * tile + 4 * q + mk];
+                x[q] = real ? x[q] : 0.0;
                 const bool kreal = 16 * b + 4 * q + mk < kTriN - 2;
                 double y = V[(kreal ? 16 * b + 4 * q + mk : 0) * kTriVLd + 16 * tile + mi];
                 y = kreal ? y : 0.0;
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(TS[(16 * b + 4 * q + mk) * kTriTLd + mi], y, acc, 0, 0, 0);
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) dst[64 * (4 + q)] = -acc[q];
+            dst[lane] = double2{x[0], x[1]};
+            dst[64 + lane] = double2{x[2], x[3]};
+            dst[128 + lane] = double2{-acc[0], -acc[1]};
+            dst[192 + lane] = double2{-acc[2], -acc[3]};
         };
 #pragma unroll 3
         for (int e = 0; e < 9; ++e) {                         // uniform
             const bool second = e > 7 - wave;
-            operands(second ? wave : 7 - wave, second ? e - (8 - wave) : e, vmine + e * (8 * 64));
+            operands(second ? wave : 7 - wave, second ? e - (8 - wave) : e, vmine + e * (4 * 64));
         }
     }
     __syncthreads();
@@ -539,90 +593,42 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
     // a loop around one: inside a loop the compiler spills a hundred registers.)
     double lam_edge = 0.0;                                // smallest eigenvalue of the batch before
     auto batch = [&](const int joff, const int rb) __attribute__((always_inline)) -> bool {
-        // ---- 2. the rb largest eigenvalues, bracketed by Sturm counts.  A power-of-two team of threads per eigenvalue, NP
-        // trial shifts per thread, `points` in all; every round keeps the part of the bracket between two neighbouring trial
+        // ---- 2. the rb largest eigenvalues, bracketed by Sturm counts.  A power-of-two team of threads per eigenvalue, a
+        // trial shift each; every round keeps the part of the bracket between two neighbouring trial
         // shifts that holds the eigenvalue.  The trial shifts divide the bracket evenly while it holds several eigenvalues.
         // Once it holds one, the last minor (the characteristic polynomial) changes sign in it and its values at the two
-        // ends are known: the shifts then sit around the zero of the line through them, at distances that fall from 1/8 of
-        // the bracket by equal factors to 2^-31 or less, so a round gains as many digits as that estimate has and the count
-        // alone still decides.  (Even division throughout, 17 parts in 14 rounds: 75 k cycles for 16 eigenvalues, 113 k for
-        // 32; this takes 53 k and 76 k.)  A round whose line was no good (the bracket not an eighth) is followed by an even one.
-        // Sturm count, last minor (mantissa and exponent) at NP shifts per thread
-        auto minors = [&](const auto& x, auto& p1, auto& cnt, auto& ex, auto np_tag) __attribute__((always_inline)) {
-            constexpr int NP = decltype(np_tag)::value;
-            const double* de = L + kTriDe;
-            asm volatile("" ::: "memory");                    // keep the 128 LDS reads inside the round (not hoisted into registers)
-            double p0[NP];
-            uint32_t signs[NP];
+        // ends and at the next shift are known: the shifts then sit around the zero of the linear fraction (x - z) / (a x + b)
+        // through the three (of the line through the two where that falls outside), at distances that fall from 1/8 of
+        // the bracket by equal factors to 2^-27 or less, so a round gains as many digits as that estimate has and the count
+        // alone still decides.  A round whose estimate was no good (the bracket not an eighth) is followed by an even one.  5 to 7
+        // rounds for 16 eigenvalues (16 shifts each), 8 to 10 for 32 (8 shifts each): 25 k and 33 k cycles, the shared round included.
+        // (Even division throughout, 17 parts in 14 rounds: 75 k and 113 k; the zero of the line alone, 9 rounds: 53 k and 76 k with T
+        // read from LDS, 36 k and 61 k with T in lanes.)
+        double td[8], te[8];                                  // T for the counts: lane i of a row of 16 lanes holds rows 16 b + i
 #pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                p0[q] = 1.0;
-                p1[q] = de[0] - x[q];
-                // The signs of the minors are shifted into a register, newest at bit 0 (one instruction per term);
-                // a block's sign changes are then the ones of (signs ^ signs >> 1) over its terms.  The sign of
-                // p_0 = 1 is 0, so the first minor's own sign is a change.
-                signs[q] = static_cast<uint32_t>(__double2hiint(p1[q])) >> 31;
-                cnt[q] = static_cast<int>(signs[q]);
-                ex[q] = 0;
-            }
-            // blocks of 8 terms (7 in the last), the next block's (d, e^2) on their way meanwhile
-            double2 ta[8], tb[8];
-            auto fetch = [&](int b, double2 (&t)[8], auto nt_tag) __attribute__((always_inline)) {
-                constexpr int NT = decltype(nt_tag)::value;
-                tri_lds_wait();                               // (for the block about to be used)
-#pragma unroll
-                for (int u = 0; u < NT; ++u) t[u] = *reinterpret_cast<const double2*>(de + 2 * (8 * b + 1 + u));
-            };
-            auto terms = [&](const double2 (&t)[8], auto nt_tag) __attribute__((always_inline)) {
-                constexpr int NT = decltype(nt_tag)::value;
-#pragma unroll
-                for (int u = 0; u < NT; ++u)
-#pragma unroll
-                    for (int q = 0; q < NP; ++q) {
-                        const double p2 = fma(t[u].x - x[q], p1[q], -(t[u].y * p0[q]));
-                        signs[q] = __builtin_amdgcn_alignbit(signs[q], static_cast<uint32_t>(__double2hiint(p2)), 31);
-                        p0[q] = p1[q];
-                        p1[q] = p2;
-                    }
-#pragma unroll
-                for (int q = 0; q < NP; ++q) {
-                    cnt[q] += __popc((signs[q] ^ (signs[q] >> 1)) & ((1u << NT) - 1u));
-                    ex[q] += tri_rescale(p0[q], p1[q]);
-                }
-            };
-            constexpr std::integral_constant<int, 8> k8{};
-            constexpr std::integral_constant<int, 7> k7{};
-            static_assert(kTriN - 1 == 15 * 8 + 7, "15 blocks of 8 terms and one of 7");
-            fetch(0, ta, k8);
-#pragma nounroll
-            for (int b = 0; b < 14; b += 2) {
-                fetch(b + 1, tb, k8);
-                terms(ta, k8);
-                fetch(b + 2, ta, k8);
-                terms(tb, k8);
-            }
-            fetch(15, tb, k7);
-            terms(ta, k8);
-            terms(tb, k7);
-        };
+        for (int b = 0; b < 8; ++b) {
+            const double2 t = *reinterpret_cast<const double2*>(L + kTriDe + 2 * (16 * b + mi));
+            td[b] = t.x;
+            te[b] = -t.y;
+        }
         {
             // shared round: 256 shifts over [-kTriBound, kTriBound], one per thread, serve every eigenvalue
-            double x[1] = {fma(kTriPart, static_cast<double>(tid + 1), -kTriBound)}, p1[1];
-            int cnt[1], ex[1];
-            minors(x, p1, cnt, ex, std::integral_constant<int, 1>{});
-            L[kTriU0 + tid] = p1[0];
-            reinterpret_cast<int2*>(L + kTriU1)[tid] = int2{cnt[0], ex[0]};
+            const double x = fma(kTriPart, static_cast<double>(tid + 1), -kTriBound);
+            double p1;
+            int cnt, ex;
+            tri_minors(td, te, x, p1, cnt, ex);
+            L[kTriU0 + tid] = p1;
+            reinterpret_cast<int2*>(L + kTriU1)[tid] = int2{cnt, ex};
             __syncthreads();
         }
-        auto search = [&](auto np_tag, const int team_size) __attribute__((always_inline)) {
-            constexpr int NP = decltype(np_tag)::value;
-            const int j = tid / team_size, sub = tid & (team_size - 1);
-            if (j >= rb) return;
-            const int points = team_size * NP, half = points / 2, fall = 64 / points;
+        {
+            const int team_log2 = rb > 16 ? 3 : (rb > 8 ? 4 : (rb > 4 ? 5 : 6)), points = 1 << team_log2, sub = tid & (points - 1);
+            const int j = (tid >> team_log2) < rb ? tid >> team_log2 : rb - 1;     // (spare teams repeat the last: all lanes take part)
+            const int half = points / 2, fall = 64 >> team_log2;
             const double inv_parts = 1.0 / (points + 1);
             const int below_target = kTriN - 1 - (joff + j);  // eigenvalue joff + j (descending) has this many below it
-            const int lane0 = lane & ~(team_size - 1);
-            const unsigned long long team_mask = team_size == 64 ? ~0ull : ((1ull << team_size) - 1ull) << lane0;
+            const int lane0 = lane & ~(points - 1);
+            const unsigned long long team_mask = points == 64 ? ~0ull : ((1ull << points) - 1ull) << lane0;
             // first bracket: from the counts of the shared round
             int first = 0;                                    // shared shifts with count <= target (a prefix)
             const int2* shared = reinterpret_cast<const int2*>(L + kTriU1);
@@ -636,65 +642,51 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             bool known_lo = first > 0, known_hi = first < kTriThreads, stalled = false;
             double flo = L[kTriU0 + (known_lo ? first - 1 : 0)], fhi = L[kTriU0 + (known_hi ? first : 0)];
             int clo = at_lo.x, chi = at_hi.x, elo = at_lo.y, ehi = at_hi.y;
+            // a third shift next to the bracket
+            const int third = first >= 2 ? first - 2 : (first + 1 < kTriThreads ? first + 1 : first);
+            double xt = fma(kTriPart, static_cast<double>(third + 1), -kTriBound), ft = L[kTriU0 + third];
+            int et = shared[third].y;
             for (int round = 0; round < 24; ++round) {
                 if (__ballot(hi - lo > kTriWidth) == 0ull) break;
                 const double width = hi - lo, step = width * inv_parts;
                 const bool line = known_lo && known_hi && chi - clo == 1 && !stalled;
-                const int de2 = ehi - elo < -1000 ? -1000 : (ehi - elo > 1000 ? 1000 : ehi - elo);
-                const double ratio = fhi * tri_rcp(flo) * tri_pow2(de2);  // < 0
-                const double est = fma(width, tri_rcp(1.0 - ratio), lo);
-                double x[NP], p1[NP];
-                int cnt[NP], ex[NP];
-#pragma unroll
-                for (int q = 0; q < NP; ++q) {
-                    const int p = sub + q * team_size;
-                    const int away = p < half ? p : points - 1 - p;       // 0: farthest from the estimate
-                    const double d = width * tri_pow2(-3 - fall * away);
-                    const double xl = fmin(fmax(est + (p < half ? -d : d), lo), hi);
-                    x[q] = line ? xl : fma(step, static_cast<double>(p + 1), lo);
-                }
-                minors(x, p1, cnt, ex, np_tag);
+                auto scale = [](int e) __attribute__((always_inline)) { return tri_pow2(e < -1000 ? -1000 : (e > 1000 ? 1000 : e)); };
+                const double inv = tri_rcp(flo), rat_u = fhi * inv * scale(ehi - elo), rat_t = ft * inv * scale(et - elo);
+                const double ct = xt - lo;
+                double z = width * ct * (rat_u - rat_t) * tri_rcp(fma(ct * rat_t, rat_u - 1.0, width * rat_u * (1.0 - rat_t)));
+                if (!(z > 0.0 && z < width)) z = width * tri_rcp(1.0 - rat_u);     // the zero of the line (rat_u < 0)
+                const double est = lo + z;
+                const int away = sub < half ? sub : points - 1 - sub;      // 0: farthest from the estimate
+                const double dist = width * tri_pow2(-3 - fall * away);
+                const double x = line ? fmin(fmax(est + (sub < half ? -dist : dist), lo), hi) : fma(step, static_cast<double>(sub + 1), lo);
+                double p1;
+                int cnt, ex;
+                tri_minors(td, te, x, p1, cnt, ex);
                 // the team's points are ascending: those with count <= target are a prefix
-                int nb = 0;
-#pragma unroll
-                for (int q = 0; q < NP; ++q) nb += __popcll(__ballot(cnt[q] <= below_target) & team_mask);
+                const int nb = __popcll(__ballot(cnt <= below_target) & team_mask), exc = ex * 256 + cnt;
                 const int pl = nb > 0 ? nb - 1 : 0, pu = nb < points ? nb : points - 1;
-                auto pick = [&](int p, double& xo, double& fo, int& eo, int& co) __attribute__((always_inline)) {
-                    const bool second = NP > 1 && p >= team_size;
-                    const int src = lane0 + (p & (team_size - 1));
-                    double xs = __shfl(x[0], src, 64), fs = __shfl(p1[0], src, 64);
-                    int es = __shfl(ex[0], src, 64), cn = __shfl(cnt[0], src, 64);
-                    if constexpr (NP > 1) {
-                        const double x2 = __shfl(x[1], src, 64), f2 = __shfl(p1[1], src, 64);
-                        const int e2 = __shfl(ex[1], src, 64), c2 = __shfl(cnt[1], src, 64);
-                        xs = second ? x2 : xs;
-                        fs = second ? f2 : fs;
-                        es = second ? e2 : es;
-                        cn = second ? c2 : cn;
-                    }
-                    xo = xs;
-                    fo = fs;
-                    eo = es;
-                    co = cn;
+                auto pick = [&](int p, double& xo, double& fo, int& eco) __attribute__((always_inline)) {
+                    xo = __shfl(x, lane0 + p, 64);
+                    fo = __shfl(p1, lane0 + p, 64);
+                    eco = __shfl(exc, lane0 + p, 64);
                 };
-                double xl, fl, xu, fu;
-                int el, cl, eu, cu;
-                pick(pl, xl, fl, el, cl);
-                pick(pu, xu, fu, eu, cu);
-                if (nb > 0) { lo = xl; flo = fl; elo = el; clo = cl; known_lo = true; }
-                if (nb < points) { hi = xu; fhi = fu; ehi = eu; chi = cu; known_hi = true; }
+                double xl, fl, xu, fu, xa, fa, xb, fb;
+                int el, eu, ea, eb;
+                pick(pl, xl, fl, el);
+                pick(pu, xu, fu, eu);
+                // the third shift: the nearer one of those next to the new bracket
+                pick(nb >= 2 ? nb - 2 : nb + 1, xa, fa, ea);
+                pick(nb + 1 < points ? nb + 1 : nb - 2, xb, fb, eb);
+                if (nb > 0) { lo = xl; flo = fl; elo = el >> 8; clo = el & 255; known_lo = true; }
+                if (nb < points) { hi = xu; fhi = fu; ehi = eu >> 8; chi = eu & 255; known_hi = true; }
+                const bool below = lo - xa <= xb - hi && xa < lo;        // (at the ends of the range both are the same shift)
+                xt = below ? xa : xb;
+                ft = below ? fa : fb;
+                et = (below ? ea : eb) >> 8;
                 stalled = line && hi - lo > 0.125 * width;
             }
-            if (sub == 0) L[kTriLam + j] = 0.5 * (lo + hi);
-        };
-        if (rb > 16)
-            search(std::integral_constant<int, 2>{}, 8);
-        else if (rb > 8)
-            search(std::integral_constant<int, 1>{}, 16);
-        else if (rb > 4)
-            search(std::integral_constant<int, 1>{}, 32);
-        else
-            search(std::integral_constant<int, 1>{}, 64);
+            if (sub == 0 && tid >> team_log2 == j) L[kTriLam + j] = 0.5 * (lo + hi);
+        }
         __syncthreads();
         // A later batch stands on its own only if its eigenvalues are clear of the batch before (vectors of eigenvalues
         // closer than this could share a subspace, which only a joint orthonormalisation would see)
@@ -707,9 +699,9 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
         // factorisations.  With gamma_i = D+_i + D-_i - (d_i - lambda), smallest in size at row k, the vector with
         // z_k = 1 and z_i = -(e_i / D+_i) z_{i+1} above, z_i = -(e_{i-1} / D-_i) z_{i-1} below has the residual
         // |gamma_k| / |z| (Parlett and Dhillon, "Fernando's solution to Wilkinson's problem", 1997): one pass of two
-        // multiply-adds per row, and everything after it is spread over all threads (eight per vector).  The inverse
-        // iteration below, one lane per vector through two solves with a reciprocal per row, took 48 us of one head's
-        // 300; this takes ~3.  It is kept for eigenvalues closer than that, whose vectors come out of the twisted form
+        // multiply-adds per row (5 k cycles; 8.6 k with T read from LDS and every pivot compared), and everything after it is
+        // spread over all threads (eight per vector; 8 k).  The inverse iteration below, one lane per vector through two solves
+        // with a reciprocal per row, took 48 us.  It is kept for eigenvalues closer than that, whose vectors come out of the twisted form
         // nearly parallel, while it starts from independent vectors.
         bool close = false;
         {
@@ -723,44 +715,29 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
                 const double lam = L[kTriLam + (j < rb ? j : rb - 1)];
                 const double* src = L + (rising ? kTriXs : kTriDe);      // (d, e^2) in the order of the recurrence
                 double* dst = L + (rising ? kTriU1 : kTriU0) + j; // dst[32 i] = minor i + 1
-                double p0 = 1.0, p1 = src[0] - lam;
-                if (fabs(p1) < kTriPivMin) p1 = kTriPivMin;
-                dst[0] = p1;
-                double2 ta[8], tb[8];                         // the next block is on its way while one is used
-                auto fetch = [&](int b, double2 (&t)[8]) __attribute__((always_inline)) {
-                    tri_lds_wait();
+                double td2[8], te2[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const double2*>(src + 2 * (8 * b + u));
-                };
-                auto block = [&](int b, const double2 (&t)[8], auto u0_tag) __attribute__((always_inline)) {
-                    constexpr int U0 = decltype(u0_tag)::value;
+                for (int b = 0; b < 8; ++b) {
+                    const double2 t = *reinterpret_cast<const double2*>(src + 2 * (16 * b + mi));
+                    td2[b] = t.x;
+                    te2[b] = -t.y;
+                }
+                double p0 = 0.0, p1 = 1.0;
+                auto eight = [&](int b, auto hi_tag) __attribute__((always_inline)) {
+                    constexpr bool HI = decltype(hi_tag)::value;
+                    double p[8];
+                    tri_eight<HI, true>(p, p0, p1, -lam, td2[b], te2[b], kTriPivMin);
 #pragma unroll
-                    for (int u = U0; u < 8; ++u) {
-                        double p2 = fma(t[u].x - lam, p1, -(t[u].y * p0));
-                        if (fabs(p2) < kTriPivMin * fabs(p1)) p2 = kTriPivMin * p1;      // a pivot below the threshold: the threshold
-                        dst[32 * (8 * b + u)] = p2;
-                        p0 = p1;
-                        p1 = p2;
-                    }
+                    for (int u = 0; u < 8; ++u) dst[32 * (16 * b + (HI ? 8 : 0) + u)] = p[u];
+                    p0 = p[6];
+                    p1 = p[7];
                     tri_rescale(p0, p1);                      // (the stored minors keep the old scale: redone below)
                 };
-                constexpr std::integral_constant<int, 0> k0{};
-                constexpr std::integral_constant<int, 1> k1{};
-                fetch(0, ta);
-                fetch(1, tb);
-                block(0, ta, k1);
-                fetch(2, ta);
-                block(1, tb, k0);
-#pragma nounroll
-                for (int b = 2; b < 14; b += 2) {
-                    fetch(b + 1, tb);
-                    block(b, ta, k0);
-                    fetch(b + 2, ta);
-                    block(b + 1, tb, k0);
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    eight(b, std::false_type{});
+                    eight(b, std::true_type{});
                 }
-                fetch(15, tb);
-                block(14, ta, k0);
-                block(15, tb, k0);
             }
             __syncthreads();
             // thread (j, sg): rows 16 sg .. 16 sg + 15 of vector j
@@ -948,25 +925,51 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
         }
         __syncthreads();
         // ---- orthonormality: Gram matrix of the 32 columns; Cholesky-QR (twice) only if it is not the identity
-        double* S = L + kTriS;
+        // (An offset the compiler does not know: hundreds of constant addresses of S, past the reach of an LDS instruction's
+        // offset, would be formed in front of the rare paths below and spilled, 3.5 k cycles of it.)
+        int s_off = kTriS;
+        asm("" : "+v"(s_off));
+        double* S = L + s_off;
         bool ok = true;
         for (int pass = 0; pass < 3; ++pass) {
-            // wavefront (ti, tj): one 16 x 16 tile; only the rb real columns count (the padding columns are never used)
+            // every wavefront takes 32 rows of the 16 x 16 tiles (0, 0), (0, 1), (1, 1), wavefront t adds up tile t; only the rb
+            // real columns count (the padding columns are never used).  (A tile per wavefront over all rows: twice as long.)
             double dev = 0.0;
-            const int ti = wave >> 1, tj = wave & 1;
-            if (16 * ti < rb && 16 * tj < rb) {               // uniform
-                double4v acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-                for (int m = 0; m < kTriN / 4; ++m) {
-                    const double* xr2 = L + kTriX + 32 * (4 * m + mk);
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xr2[16 * ti + mi], xr2[16 * tj + mi], acc, 0, 0, 0);
+            const int tiles = rb > 16 ? 3 : 1;
+            double* part = L + kTriU0;                        // [4 wavefronts][3 tiles][4][64]
+            {
+                double4v acc[3];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) acc[t] = double4v{0.0, 0.0, 0.0, 0.0};
+                const double* xs = L + kTriX + 32 * (32 * wave + mk) + mi;
+#pragma unroll
+                for (int m = 0; m < 8; ++m) {
+                    const double x0 = xs[32 * 4 * m], x1 = xs[32 * 4 * m + 16];
+                    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, x0, acc[0], 0, 0, 0);
+                    if (tiles > 1) {                          // uniform
+                        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, x1, acc[1], 0, 0, 0);
+                        acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, x1, acc[2], 0, 0, 0);
+                    }
                 }
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    if (t < tiles) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) part[((3 * wave + t) * 4 + q) * 64 + lane] = acc[t][q];
+                    }
+            }
+            __syncthreads();
+            if (wave < tiles) {                               // uniform
+                const int ti = wave >> 1, tj = wave > 0 ? 1 : 0;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int i2 = 16 * ti + mk + 4 * q, j2 = 16 * tj + mi;
-                    S[i2 * 33 + j2] = acc[q];
+                    const double* pq = part + (4 * wave + q) * 64 + lane;
+                    const double g2 = (pq[0] + pq[768]) + (pq[1536] + pq[2304]);
+                    S[i2 * 33 + j2] = g2;
+                    if (ti != tj) S[j2 * 33 + i2] = g2;
                     if (i2 < rb && j2 < rb) {
-                        const double d2 = fabs(acc[q] - (i2 == j2 ? 1.0 : 0.0));
+                        const double d2 = fabs(g2 - (i2 == j2 ? 1.0 : 0.0));
                         dev = d2 == d2 ? fmax(dev, d2) : 1e300;
                     }
                 }
@@ -1059,19 +1062,19 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             __syncthreads();
         }
 
-        // the operands of step 5 are on their way during step 4
-        double va[4][4], ma[4][4], vb[8][4], mb[8][4];
+        // the operands of step 5 are on their way during steps 3 and 4
+        double2 va[4][2], ma[4][2], vb[8][2], mb[8][2];
 #pragma unroll
         for (int b = 0; b < 8; ++b)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 2; ++q) {
                 if (b <= 7 - wave) {                          // uniform
-                    vb[b][q] = vmine[(b * 8 + q) * 64];
-                    mb[b][q] = vmine[(b * 8 + 4 + q) * 64];
+                    vb[b][q] = vmine[(b * 4 + q) * 64 + lane];
+                    mb[b][q] = vmine[(b * 4 + 2 + q) * 64 + lane];
                 }
                 if (b < 4 && b <= wave) {
-                    va[b & 3][q] = vmine[((8 - wave + b) * 8 + q) * 64];
-                    ma[b & 3][q] = vmine[((8 - wave + b) * 8 + 4 + q) * 64];
+                    va[b & 3][q] = vmine[((8 - wave + b) * 4 + q) * 64 + lane];
+                    ma[b & 3][q] = vmine[((8 - wave + b) * 4 + 2 + q) * 64 + lane];
                 }
             }
 
@@ -1154,12 +1157,12 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
-                        for (int c = 0; c < NC; ++c) z[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(vb[b][q], xb[c][q], z[c], 0, 0, 0);
+                        for (int c = 0; c < NC; ++c) z[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q & 1 ? vb[b][q / 2].y : vb[b][q / 2].x, xb[c][q], z[c], 0, 0, 0);
                     if (on_a) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
 #pragma unroll
-                            for (int c = 0; c < NC; ++c) z[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[b & 3][q], xa[c][q], z[c], 0, 0, 0);
+                            for (int c = 0; c < NC; ++c) z[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q & 1 ? va[b & 3][q / 2].y : va[b & 3][q / 2].x, xa[c][q], z[c], 0, 0, 0);
                     }
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
@@ -1185,8 +1188,8 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
                         for (int c = 0; c < NC; ++c) {
-                            xb[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(mb[b][q], zs[c][q], xb[c], 0, 0, 0);
-                            if (on_a) xa[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[b & 3][q], zs[c][q], xa[c], 0, 0, 0);
+                            xb[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q & 1 ? mb[b][q / 2].y : mb[b][q / 2].x, zs[c][q], xb[c], 0, 0, 0);
+                            if (on_a) xa[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q & 1 ? ma[b & 3][q / 2].y : ma[b & 3][q / 2].x, zs[c][q], xa[c], 0, 0, 0);
                         }
                 }
             }
