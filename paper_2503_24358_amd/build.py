@@ -30,10 +30,11 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-# Per-file extras.  The scores kernels read every matrix-product result right away with ordinary vector
-# instructions: keep those results in the ordinary register file instead of the accumulation registers
+# Per-file extras.  The scores kernels and the block elimination read every matrix-product result right away with ordinary
+# vector instructions: keep those results in the ordinary register file instead of the accumulation registers
 # (saves one copy per result register).
-EXTRA = {"squat_scores.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+EXTRA = {"squat_prepare.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+         "squat_scores.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "squat_scores_pc.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "squat_scores_rope.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 

@@ -4,7 +4,7 @@
 // with P = I + lambda Qhat^T Qhat, and the Woodbury identity (the paper's O(r d^2) footnote)
 // reduces this to an r x r problem:
 //     W_t = -Qr^T (I/lambda + Qr Qr^T)^{-1} Qb,     Qb = Qhat[:, blk], Qr = Qhat[:, tg:].
-// r <= 64 and finite lambda: block elimination in fp64 on the matrix cores, one workgroup per head
+// r <= 64 and finite lambda: block elimination in fp64 on the matrix cores, a workgroup or more per panel
 // (prepare_elim_kernel).  All else, and the heads that kernel flags: one workgroup per (head, t) or per head works
 // in fp64, forms S = I/lambda + Qr Qr^T, diagonalises it with the one-sided Jacobi routine (rows a_i = mu_i v_i), and applies
 // S^+ = sum_i a_i a_i^T / mu_i^3.  lambda = +inf drops the I/lambda term and discards the
@@ -50,12 +50,20 @@ __global__ void __launch_bounds__(256) zero_fill(float* p, int64_t n4) {
     if (i < n4) reinterpret_cast<f32x4*>(p)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
+// A head's flag: a byte per panel from the elimination kernel, 1 when the eigen route has seen it (whoever reads it meanwhile
+// sees a number other than zero either way).
+__device__ __forceinline__ int flagged_head(int* need) {
+    const int f = *need;
+    if (f != 0 && threadIdx.x == 0) *need = 1;
+    return f;
+}
+
 // Large r (> 32; up to 64 with a finite lambda only for the heads the elimination kernel flags): one 1024-thread
 // workgroup per (head, t) panel; intermediate products go through the global workspace.
 template <int TS>
-__global__ void __launch_bounds__(kPrepThreads) prepare_kernel(const PrepParams p, const int* need) {
+__global__ void __launch_bounds__(kPrepThreads) prepare_kernel(const PrepParams p, int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (need && need[blockIdx.x / p.nsteps] == 0) return;  // done by the elimination kernel
+    if (need && flagged_head(need + blockIdx.x / p.nsteps) == 0) return;       // done by the elimination kernel
     constexpr int THREADS = kPrepThreads;
     const int r = p.r, rp = p.rp, g = p.g;
     double* S = reinterpret_cast<double*>(smem);     // rp x rp
@@ -129,9 +137,9 @@ __global__ void __launch_bounds__(kPrepThreads) prepare_kernel(const PrepParams 
 // Jacobi then needs no workgroup barrier (it is bound by synchronisation latency, not arithmetic), the
 // head's Qhat is staged once in LDS as fp32, and all intermediates stay in LDS:
 //   X = S^+ Qb = sum_i a_i (a_i . Qb) / mu_i^3   (rp x g),      W = -Qr^T X.
-__global__ void __launch_bounds__(192) prepare_wave_kernel(const PrepParams p, const int* need) {
+__global__ void __launch_bounds__(192) prepare_wave_kernel(const PrepParams p, int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (need && need[blockIdx.x] == 0) return;             // done by the elimination kernel
+    if (need && flagged_head(need + blockIdx.x) == 0) return;                  // done by the elimination kernel
     const int r = p.r, rp = p.rp, g = p.g;
     constexpr int QLD = kD + 1;       // odd row stride: column reads across rows hit distinct LDS banks
     const int ld = rp + 2;            // padded row: teams of 4 lanes read different rows at the same column
@@ -198,60 +206,75 @@ __global__ void __launch_bounds__(192) prepare_wave_kernel(const PrepParams p, c
 
 // r <= 64 and finite lambda: S = I/lambda + Qr Qr^T is positive definite with smallest eigenvalue
 // >= 1/lambda, so X = S^-1 Qb comes from Gauss-Jordan elimination of [S | Qb] without pivoting (the pivots are those of
-// the Cholesky factorisation) instead of an eigen-decomposition.  One workgroup per head, four wavefronts per panel, all
-// panels side by side; everything lives in the result layout of v_mfma_f64_16x16x4_f64 (lane (j = lane & 15, m = lane >> 4),
+// the Cholesky factorisation) instead of an eigen-decomposition.  One workgroup of four wavefronts per panel, or several that
+// share the panel's columns; everything lives in the result layout of v_mfma_f64_16x16x4_f64 (lane (j = lane & 15, m = lane >> 4),
 // register q: row m + 4 q, column j of a 16 x 16 tile), NT row tiles, the column tiles dealt out to the wavefronts:
 //   - S: products of the rows of Qr on the matrix cores (fp32 entries of Qhat widened on the way);
 //   - four pivots a step: their columns go through LDS to every wavefront (one barrier, two buffers), every lane factors
 //     the 4 x 4 pivot block, the pivot rows are in the same wavefront for every column, and the update is one product per
 //     live 16 x 16 tile;
-//   - W = -Qr^T X: the solution's registers are the B operands as they are.
-// Bound by the chain of its steps (LDS exchange, four reciprocals, two dependent products).  us per launch, fallback launch
-// included, against the kernel it replaces (Cholesky with one wavefront a panel and a substitution with a lane per column,
-// whose factor entries were read from LDS one by one): 32 heads, g = 32: r = 16 28.3 -> 11.5, 32 30.8 -> 19.9, 40 65.8 -> 27.9, 64 83.0 -> 40.1;
-// g = 64: r = 16 24.6 -> 10.1, 40 56.8 -> 19.6; 256 heads, g = 32: r = 16 31.4 -> 13.6, 64 91.2 -> 46.4.  (One pivot a
-// step: 13.3, 24.8, 36.2, 54.6 for 32 heads, g = 32.)
+//   - W = -Qr^T X: the solution's registers are the B operands as they are, through LDS to all four wavefronts.
+// Bound by the chain of its steps (LDS exchange, four reciprocals, two dependent products: 1.4 k cycles a step with one column
+// tile per wavefront, r = 40).  us per launch, fallback launch included, against all panels of a head in one workgroup (results
+// of the products in the accumulation registers, rows of Qhat 129 floats apart, four bytes a load): 32 heads, g = 32: r = 16
+// 11.5 -> 8.7, 32 19.9 -> 12.9, 40 27.8 -> 14.9, 64 40.0 -> 21.1; g = 64: r = 16 10.2 -> 8.2, 40 19.5 -> 13.5, 64 26.7 -> 19.5;
+// 256 heads: g = 32, r = 16 13.7 -> 12.8, 64 43.2 -> 40.4, g = 64, r = 40 22.8 -> 19.8.  (One pivot a step, 32 heads, g = 32, in
+// the earlier form: 13.3, 24.8, 36.2, 54.6 for r = 16, 32, 40, 64.)
 // A panel whose pivots span more than 1e9 (lambda times the largest eigenvalue of Qr Qr^T that large)
 // sets the head's flag: the eigen-route kernel, launched afterwards, redoes exactly the flagged heads.
 typedef double double4v __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));       // 16 bytes at any float's address
 
-constexpr int kElimPanelThreads = 256;      // four wavefronts
-constexpr int kElimQLd = kD + 1;
+constexpr int kElimThreads = 256;           // four wavefronts
+constexpr int kElimQLd = kD + 4;            // rows 4 banks apart: the 16 rows x 4 channels of an operand of S lie in 64 banks
 
-constexpr size_t elim_lds_bytes(int nt, int nsteps) {
-    // Qhat as fp32, two blocks of four columns in flight per panel, one flag
-    return ((static_cast<size_t>(16 * nt) * kElimQLd * sizeof(float) + 15) & ~size_t(15)) +
-           static_cast<size_t>(nsteps) * 2 * 4 * 16 * nt * sizeof(double) + 16;
+constexpr size_t elim_lds_bytes(int nt, int per) {
+    // Qhat as fp32; two blocks of four columns in flight, later the solution's tiles (50 KB at r = 64, g = 32: three workgroups
+    // on a compute unit, as many as a head has panels)
+    return static_cast<size_t>(16 * nt) * kElimQLd * sizeof(float) + static_cast<size_t>(per * 256 > 128 ? per * 256 : 128) * nt * sizeof(double);
 }
 
+// One workgroup per (head, panel t - 1, group of `per` column tiles of Qb).  need: four bytes per head, one per panel.
 template <int NT>
-__global__ void __launch_bounds__(3 * kElimPanelThreads) prepare_elim_kernel(const PrepParams p, int* need) {
+__global__ void __launch_bounds__(kElimThreads) prepare_elim_kernel(const PrepParams p, const int per, unsigned char* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int RP = 16 * NT;
     const int r = p.r, g = p.g;
-    const int head = blockIdx.x, tid = threadIdx.x, threads = blockDim.x;
+    const int head = blockIdx.x, panel = blockIdx.y, tid = threadIdx.x;
     const int lane = tid & 63, mi = lane & 15, mk = lane >> 4;
-    const int panel = __builtin_amdgcn_readfirstlane(tid / kElimPanelThreads);           // t - 1
-    // the tiles of S are in the first NT of these; panels start with different SIMDs
-    const int wt = __builtin_amdgcn_readfirstlane(((tid >> 6) + panel) & 3);             // this wavefront's column tiles: wt, wt + 4
+    const int wt = __builtin_amdgcn_readfirstlane(tid >> 6);                             // this wavefront's column tiles: wt, wt + 4
     const int c0 = (panel + 1) * g, nrest = kD - c0;
-    const int ctiles = NT + g / 16;
-    float* Qf = reinterpret_cast<float*>(smem);                                          // [RP][129]
-    double* cols = reinterpret_cast<double*>(smem + ((RP * kElimQLd * sizeof(float) + 15) & ~size_t(15)));
-    int* bad = reinterpret_cast<int*>(cols + p.nsteps * 8 * RP);
-    cols += panel * 8 * RP;
+    const int j0 = c0 - g + 16 * per * blockIdx.z;                                       // first column of Qb here
+    const int ctiles = NT + per;
+    float* Qf = reinterpret_cast<float*>(smem);                                          // [RP][132]
+    double* cols = reinterpret_cast<double*>(smem + RP * kElimQLd * sizeof(float));
+    double* Xs = cols;                                                                   // [per][4 NT][64], after the elimination
     const float* Q = p.qhat + static_cast<int64_t>(head) * r * kD;
     float* U = p.update + static_cast<int64_t>(head) * kD * kD;
-    for (int idx = tid; idx < RP * kD; idx += threads)
-        Qf[(idx >> 7) * kElimQLd + (idx & 127)] = idx < r * kD ? Q[idx] : 0.0f;
-    if (tid == 0) bad[0] = 0;
-    // Everything of this head's matrix outside the panels is zero: row i from the start of its own block of g
-    // columns on (the panels, written at the end or by the eigen route, are the columns before it).
-    for (int idx = tid; idx < kD * (kD / 4); idx += threads) {
-        const int row = idx / (kD / 4), col = 4 * (idx % (kD / 4));
-        if (col >= row / g * g) *reinterpret_cast<f32x4*>(U + row * kD + col) = f32x4{0.f, 0.f, 0.f, 0.f};
+    {
+        // all of a thread's loads before the first is used
+        f32x4 v[2 * NT];
+#pragma unroll
+        for (int i = 0; i < 2 * NT; ++i) {
+            const int idx = 4 * (tid + kElimThreads * i);
+            v[i] = *reinterpret_cast<const f32x4_any*>(Q + (idx < r * kD ? idx : 0));       // (rows from r on: zeros below)
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * NT; ++i) {
+            const int idx = 4 * (tid + kElimThreads * i);
+            *reinterpret_cast<f32x4*>(Qf + (idx >> 7) * kElimQLd + (idx & 127)) = idx < r * kD ? v[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     }
-    __syncthreads();
+    // Everything of this head's matrix outside the panels is zero: row i from the start of its own block of g
+    // columns on (the panels, written at the end or by the eigen route, are the columns before it).  The head's workgroups share it.
+    {
+        const int unit = blockIdx.y + gridDim.y * blockIdx.z, units = gridDim.y * gridDim.z;
+        for (int idx = tid + kElimThreads * unit; idx < kD * (kD / 4); idx += kElimThreads * units) {
+            const int row = idx / (kD / 4), col = 4 * (idx % (kD / 4));
+            if (col >= row / g * g) *reinterpret_cast<f32x4*>(U + row * kD + col) = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");                      // (the stores above are not waited for)
 
     // ---- [S | Qb]
     double a[2][NT][4];
@@ -268,7 +291,7 @@ __global__ void __launch_bounds__(3 * kElimPanelThreads) prepare_elim_kernel(con
             for (int ti = 0; ti < NT; ++ti) acc[ti] = double4v{0.0, 0.0, 0.0, 0.0};
             const float* qc = Qf + (16 * ct + mi) * kElimQLd + c0 + mk;
             const float* qr = Qf + mi * kElimQLd + c0 + mk;
-#pragma unroll 4
+#pragma unroll 8
             for (int c = 0; c < nrest; c += 4) {
                 const double bq = static_cast<double>(qc[c]);
 #pragma unroll
@@ -288,7 +311,7 @@ __global__ void __launch_bounds__(3 * kElimPanelThreads) prepare_elim_kernel(con
             for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    a[s][ti][q] = static_cast<double>(Qf[(16 * ti + mk + 4 * q) * kElimQLd + (c0 - g) + 16 * (ct - NT) + mi]);
+                    a[s][ti][q] = static_cast<double>(Qf[(16 * ti + mk + 4 * q) * kElimQLd + j0 + 16 * (ct - NT) + mi]);
         }
     }
 
@@ -325,11 +348,11 @@ __global__ void __launch_bounds__(3 * kElimPanelThreads) prepare_elim_kernel(con
             double d[4], l[4][4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                // 1 / pivot from the hardware approximation and two Newton steps
+                // 1 / pivot from the hardware approximation (good to 5e-8) and the series in its error up to the cube
                 const double piv = p[j][j];
                 double y = __builtin_amdgcn_rcp(piv);
-#pragma unroll
-                for (int it = 0; it < 2; ++it) y = fma(y, fma(-piv, y, 1.0), y);
+                const double e = fma(-piv, y, 1.0);
+                y = fma(y, fma(e, e, e), y);
                 d[j] = y;
                 if (k0 + j < r) {                         // uniform
                     pmin = fmin(pmin, piv);
@@ -372,32 +395,34 @@ __global__ void __launch_bounds__(3 * kElimPanelThreads) prepare_elim_kernel(con
             }
         }
     }
-    if ((tid & (kElimPanelThreads - 1)) == 0 && !(pmin > 1e-9 * pmax)) atomicOr(bad, 1);
-    __syncthreads();
-    if (bad[0]) {                                          // uniform: leave this head to the eigen route
-        if (tid == 0) need[head] = 1;
-        return;
-    }
-    if (tid == 0) need[head] = 0;
+    const int bad = __builtin_amdgcn_readfirstlane(pmin > 1e-9 * pmax ? 0 : 1);           // (every lane saw the same pivots)
+    if (blockIdx.z == 0 && tid < 4 && (tid == panel || (panel == 0 && tid >= static_cast<int>(gridDim.y))))
+        need[4 * static_cast<int64_t>(head) + tid] = tid == panel ? bad : 0;
+    if (bad) return;                                       // uniform: leave this head to the eigen route
 
-    // ---- W_t[c][j] = -sum_k Q[k][c0 + c] X[k][j]
+    // ---- W_t[c][j] = -sum_k Q[k][c0 + c] X[k][j]: the solution's tiles through LDS, (tile, 16 rows c) dealt out to the wavefronts
+    asm volatile("s_barrier" ::: "memory");                // everyone has read the last columns
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         const int ct = wt + 4 * s;
         if (ct < NT || ct >= ctiles) continue;             // uniform
-        float* dst = U + (c0 - g) + 16 * (ct - NT) + mi;
-#pragma unroll 2
-        for (int c = 0; c < nrest; c += 16) {
-            double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int ti = 0; ti < NT; ++ti)
+        for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(Qf[(16 * ti + 4 * q + mk) * kElimQLd + c0 + c + mi]),
-                                                               a[s][ti][q], acc, 0, 0, 0);
+            for (int q = 0; q < 4; ++q) Xs[((ct - NT) * 4 * NT + 4 * ti + q) * 64 + lane] = a[s][ti][q];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const int rows = nrest / 16;
+    for (int item = wt; item < per * rows; item += 4) {    // uniform
+        const int jt = item / rows, c = 16 * (item % rows);
+        const double* xs = Xs + jt * 4 * NT * 64 + lane;
+        double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) dst[(c0 + c + mk + 4 * q) * kD] = stored_entry(-acc[q], p.full);
-        }
+        for (int k = 0; k < 4 * NT; ++k)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(Qf[(4 * k + mk) * kElimQLd + c0 + c + mi]), xs[64 * k], acc, 0, 0, 0);
+        float* dst = U + j0 + 16 * jt + mi;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dst[(c0 + c + mk + 4 * q) * kD] = stored_entry(-acc[q], p.full);
     }
 }
 
@@ -464,16 +489,26 @@ int prepare_impl(const float* qhat, int n_heads, int r, float lambda, int g, uns
     p.full = (flags_arg & SQUAT_PREPARE_FULL_PRECISION) ? 1 : 0;
     p.inv_lambda = p.hard ? 0.0 : 1.0 / static_cast<double>(lambda);
     p.nprob = n_heads * nsteps;
-    const int* need = nullptr;
+    int* need = nullptr;
     if (elim_route) {
         const int nt = (r + 15) / 16;
-        const dim3 block(kElimPanelThreads * nsteps);
-        const size_t lds = elim_lds_bytes(nt, nsteps);     // 45 KB at most
+        // A workgroup per panel.  Its column tiles are the nt of S and those of Qb; the latter are split over several
+        // workgroups, each of which eliminates S for itself, until a wavefront has one tile, as far as the launch then
+        // stays within one workgroup per CU (256).
+        int per = g / 16;
+        while (per > 1 && nt + per > 4 && static_cast<int64_t>(n_heads) * nsteps * (g / 16) / (per / 2) <= 256) per /= 2;
+        const dim3 grid(n_heads, nsteps, g / 16 / per), block(kElimThreads);
+        const size_t lds = elim_lds_bytes(nt, per);        // 66 KB at most
+        unsigned char* bytes = reinterpret_cast<unsigned char*>(flags);
+        static std::atomic<uint64_t> elim_done[4];
+        const void* kernels[4] = {reinterpret_cast<const void*>(prepare_elim_kernel<1>), reinterpret_cast<const void*>(prepare_elim_kernel<2>),
+                                  reinterpret_cast<const void*>(prepare_elim_kernel<3>), reinterpret_cast<const void*>(prepare_elim_kernel<4>)};
+        if ((rc = set_max_lds_once(elim_done[nt - 1], kernels[nt - 1], static_cast<int>(elim_lds_bytes(nt, 4))))) return rc;
         switch (nt) {
-            case 1: hipLaunchKernelGGL(prepare_elim_kernel<1>, dim3(n_heads), block, lds, s, p, flags); break;
-            case 2: hipLaunchKernelGGL(prepare_elim_kernel<2>, dim3(n_heads), block, lds, s, p, flags); break;
-            case 3: hipLaunchKernelGGL(prepare_elim_kernel<3>, dim3(n_heads), block, lds, s, p, flags); break;
-            default: hipLaunchKernelGGL(prepare_elim_kernel<4>, dim3(n_heads), block, lds, s, p, flags); break;
+            case 1: hipLaunchKernelGGL(prepare_elim_kernel<1>, grid, block, lds, s, p, per, bytes); break;
+            case 2: hipLaunchKernelGGL(prepare_elim_kernel<2>, grid, block, lds, s, p, per, bytes); break;
+            case 3: hipLaunchKernelGGL(prepare_elim_kernel<3>, grid, block, lds, s, p, per, bytes); break;
+            default: hipLaunchKernelGGL(prepare_elim_kernel<4>, grid, block, lds, s, p, per, bytes); break;
         }
         rc = check_launch();
         if (rc) return rc;

@@ -1,0 +1,41 @@
+"""The update matrix's column tiles spread over workgroups: head counts on both sides of every change of the split (a launch
+of at most 256 workgroups), against one head alone, and a subspace that starts at no multiple of 16 bytes.
+
+How the columns are dealt out changes no operation of any column, so the results are the same bit for bit; one head alone
+is checked against the float64 oracle (2^-24 and the 1e-7 the elimination may lose, as at the tile edges)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import squat_oracle as O
+from paper_2503_24358_amd import squat
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("r,g,heads", [(40, 64, 64), (40, 64, 65), (40, 64, 128), (40, 64, 129), (20, 64, 128), (20, 64, 129),
+                                       (64, 32, 42), (64, 32, 43), (16, 64, 129), (64, 32, 200)])
+def test_split_of_the_columns_changes_nothing(r, g, heads):
+    rng = np.random.default_rng(r + g + heads)
+    qhat = (rng.standard_normal((heads, r, 128)) * 10.0 ** rng.uniform(-2.0, 1.0, (heads, r, 1))).astype(np.float32)
+    t = torch.from_numpy(qhat).cuda()
+    update = torch.full((heads, 128, 128), float("nan"), device="cuda")
+    squat.prepare(t, 1e-3, g, update=update, full_precision=True)
+    for h in (0, heads // 2, heads - 1):
+        alone = squat.prepare(t[h:h + 1].clone(), 1e-3, g, full_precision=True)
+        assert torch.equal(update[h], alone[0])
+        want = O.update_matrix_lowrank(qhat[h].astype(np.float64), 1e-3, g)
+        assert np.linalg.norm(alone[0].cpu().numpy() - want) <= 2e-7 * np.linalg.norm(want)
+    assert torch.isfinite(update).all()
+
+
+@pytest.mark.parametrize("r,g", [(5, 32), (40, 64)])
+def test_subspace_at_any_float(r, g):
+    rng = np.random.default_rng(r)
+    flat = torch.from_numpy(rng.standard_normal(2 * r * 128 + 4).astype(np.float32)).cuda()
+    want = squat.prepare(flat[:2 * r * 128].clone().view(2, r, 128), 1e-3, g)
+    for off in (1, 2, 3):
+        flat[off:off + 2 * r * 128] = flat[:2 * r * 128].clone() if off == 1 else flat[off - 1:off - 1 + 2 * r * 128].clone()
+        view = flat[off:off + 2 * r * 128].view(2, r, 128)
+        assert view.data_ptr() % 16 == 4 * off
+        assert torch.equal(squat.prepare(view, 1e-3, g), want)
