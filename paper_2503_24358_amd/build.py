@@ -1,9 +1,10 @@
-"""Builds libsquat.so (HIP, gfx950) in-tree with hipcc.  `python -m paper_2503_24358_amd.build`."""
+"""Builds libsquat.so (HIP, gfx950) and the native part of its Python binding in-tree with hipcc.  `python -m paper_2503_24358_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libsquat.so")
+EXT = os.path.join(PKG, "_squat_torch.so")         # the hot calls of the Python binding
 
 SOURCES = ["squat_api.cpp", "squat_quantize.hip", "squat_quantize_pc.hip", "squat_dequantize.hip",
            "squat_subspace.hip", "squat_prepare.hip", "squat_scores.hip", "squat_scores_pc.hip", "squat_scores_rope.hip",
@@ -56,9 +58,23 @@ def build(verbose: bool = True) -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + res.stderr[-4000:])
+    _build_binding()
     if verbose:
-        print("built", LIB)
+        print("built", LIB, "and", EXT)
     return LIB
+
+
+def _build_binding() -> None:
+    import torch
+    base = os.path.dirname(torch.__file__)
+    cmd = [_hipcc(), "-std=c++17", "-O2", "-fPIC", "-shared", "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(base, "include"),
+           "-I" + os.path.join(base, "include", "torch", "csrc", "api", "include"), os.path.join(CSRC, "squat_torch.cpp"), "-o", EXT,
+           "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-L" + PKG, "-l:libsquat.so", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building the Python binding failed:\n" + res.stderr[-4000:])
 
 
 if __name__ == "__main__":

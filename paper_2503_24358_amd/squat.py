@@ -1,12 +1,14 @@
-"""ctypes binding of libsquat.so -- same names and argument order as include/squat.h.
+"""Binding of libsquat.so -- same names and argument order as include/squat.h.
 
 Argument marshalling only: every step of the path runs in the library's HIP
-kernels.  PyTorch is used for device memory and the current stream.  There is
+kernels.  The calls of a decode step and of a layer's keys go through a native module
+(_squat_torch.so, csrc/squat_torch.cpp), the others through ctypes.  PyTorch is used for device memory and the current stream.  There is
 no CPU fallback: if the library is missing or no GPU is present the calls raise.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -15,6 +17,7 @@ import torch
 F32, F16, BF16 = 0, 1, 2
 _DT = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libsquat.so")
+_EXT_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_squat_torch.so")
 _lib = None
 
 SYMBOLS = ("squat_version", "squat_strerror", "squat_build_subspace_workspace",
@@ -136,6 +139,24 @@ def lib() -> ctypes.CDLL:
     L.squat_cache_key_scores_rope.argtypes = [vp, vp, i32, i64, i64, vp, i64, f32, vp, i64, i64, vp]
     _lib = L
     return L
+
+
+_native = None
+
+
+def native():
+    """Loads the native part of the binding (built with the library); raises if it is missing."""
+    global _native
+    if _native is None:
+        lib()
+        if not os.path.exists(_EXT_PATH):
+            raise RuntimeError("_squat_torch.so not found at %s: run `python -m paper_2503_24358_amd.build`" % _EXT_PATH)
+        spec = importlib.util.spec_from_file_location("_squat_torch", _EXT_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.set_error(SquatError)
+        _native = module
+    return _native
 
 
 def version() -> int:
@@ -291,29 +312,8 @@ def quantize_keys(k: torch.Tensor, update: Optional[torch.Tensor], bits: int, gr
     """squat_quantize_keys.  k: [n_batch, n_heads, n_tokens, d]; update: [n_heads, d, d] f32 shared
     across the batch, or [n_batch, n_heads, d, d], or None (plain round-to-nearest).
     Returns (codes uint32 viewed as int32 [B,H,n,d*bits/32], scale f16 [B,H,n,d/group], zero f16)."""
-    _need_cuda(k, update)
-    b, h, n, d = k.shape
-    if k.stride(3) != 1:
-        raise ValueError("k must have unit channel stride")
-    dev = k.device
-    usb = 0
-    if update is not None:
-        if update.dtype != torch.float32 or not update.is_contiguous():
-            raise ValueError("update must be dense float32")
-        if update.dim() == 4:
-            usb = update.stride(0)
-    if codes is None:
-        codes = torch.empty((b, h, n, d * bits // 32), dtype=torch.int32, device=dev)
-    if scale is None:
-        scale = torch.empty((b, h, n, d // group), dtype=torch.float16, device=dev)
-    if zero is None:
-        zero = torch.empty((b, h, n, d // group), dtype=torch.float16, device=dev)
-    rc = lib().squat_quantize_keys(_ptr(k), _DT[k.dtype], b, h, n, d, k.stride(0), k.stride(1), k.stride(2),
-                                   _ptr(update), usb, bits, group, g, _ptr(codes), _ptr(scale), _ptr(zero),
-                                   _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_quantize_keys")
-    return codes, scale, zero
+    return (_native or native()).quantize_keys(k, update, bits, group, g, codes, scale, zero,
+                                               None if stream is None else _stream(stream))
 
 
 def quantize_keys_plan(k_dtype, n_batch: int, n_heads: int, n_tokens: int, has_update: bool, update_stride_batch: int,
@@ -330,18 +330,8 @@ def quantize_keys_plan(k_dtype, n_batch: int, n_heads: int, n_tokens: int, has_u
 def dequantize_keys(codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor, bits: int, group: int,
                     out_dtype=torch.bfloat16, *, out=None, stream=None) -> torch.Tensor:
     """squat_dequantize_keys.  Dense codes/scale/zero as written by quantize_keys -> k [B,H,n,d]."""
-    _need_cuda(codes, scale, zero)
-    b, h, n, w = codes.shape
-    d = w * 32 // bits
-    if not (codes.is_contiguous() and scale.is_contiguous() and zero.is_contiguous()):
-        raise ValueError("codes/scale/zero must be dense")
-    if out is None:
-        out = torch.empty((b, h, n, d), dtype=out_dtype, device=codes.device)
-    rc = lib().squat_dequantize_keys(_ptr(codes), _ptr(scale), _ptr(zero), b, h, n, d, bits, group, _ptr(out),
-                                     _DT[out.dtype], out.stride(0), out.stride(1), out.stride(2), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_dequantize_keys")
-    return out
+    return (_native or native()).dequantize_keys(codes, scale, zero, bits, group, out_dtype, out,
+                                                 None if stream is None else _stream(stream))
 
 
 def quantize_keys_per_channel(k: torch.Tensor, update: Optional[torch.Tensor], bits: int, group: int, g: int, *,
@@ -349,52 +339,16 @@ def quantize_keys_per_channel(k: torch.Tensor, update: Optional[torch.Tensor], b
     """squat_quantize_keys_per_channel.  k: [n_batch, n_heads, n_tokens, d], n_tokens a multiple of
     group (= 32); update as for quantize_keys.
     Returns (codes uint32 viewed as int32 [B,H,n/32,d,bits], scale f16 [B,H,n/32,d], zero f16)."""
-    _need_cuda(k, update)
-    b, h, n, d = k.shape
-    if k.stride(3) != 1:
-        raise ValueError("k must have unit channel stride")
-    if group <= 0 or n % group:
-        raise ValueError("n_tokens must be a multiple of group")
-    dev = k.device
-    usb = 0
-    if update is not None:
-        if update.dtype != torch.float32 or not update.is_contiguous():
-            raise ValueError("update must be dense float32")
-        if update.dim() == 4:
-            usb = update.stride(0)
-    if codes is None:
-        codes = torch.empty((b, h, n // 32, d, bits), dtype=torch.int32, device=dev)
-    if scale is None:
-        scale = torch.empty((b, h, n // group, d), dtype=torch.float16, device=dev)
-    if zero is None:
-        zero = torch.empty((b, h, n // group, d), dtype=torch.float16, device=dev)
-    rc = lib().squat_quantize_keys_per_channel(_ptr(k), _DT[k.dtype], b, h, n, d, k.stride(0), k.stride(1),
-                                               k.stride(2), _ptr(update), usb, bits, group, g, _ptr(codes),
-                                               _ptr(scale), _ptr(zero), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_quantize_keys_per_channel")
-    return codes, scale, zero
+    return (_native or native()).quantize_keys_per_channel(k, update, bits, group, g, codes, scale, zero,
+                                                           None if stream is None else _stream(stream))
 
 
 def dequantize_keys_per_channel(codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor, bits: int,
                                 group: int, out_dtype=torch.bfloat16, *, out=None, stream=None) -> torch.Tensor:
     """squat_dequantize_keys_per_channel.  Dense codes [B,H,n/32,d,bits], scale/zero [B,H,n/group,d]
     as written by quantize_keys_per_channel -> k [B,H,n,d]."""
-    _need_cuda(codes, scale, zero)
-    b, h, tiles, d, w = codes.shape
-    if w != bits:
-        raise ValueError("codes must be [B, H, n/32, d, bits]")
-    if not (codes.is_contiguous() and scale.is_contiguous() and zero.is_contiguous()):
-        raise ValueError("codes/scale/zero must be dense")
-    n = tiles * 32
-    if out is None:
-        out = torch.empty((b, h, n, d), dtype=out_dtype, device=codes.device)
-    rc = lib().squat_dequantize_keys_per_channel(_ptr(codes), _ptr(scale), _ptr(zero), b, h, n, d, bits, group,
-                                                 _ptr(out), _DT[out.dtype], out.stride(0), out.stride(1),
-                                                 out.stride(2), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_dequantize_keys_per_channel")
-    return out
+    return (_native or native()).dequantize_keys_per_channel(codes, scale, zero, bits, group, out_dtype, out,
+                                                             None if stream is None else _stream(stream))
 
 
 def key_scores(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor, bits: int,
@@ -402,23 +356,8 @@ def key_scores(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: 
     """squat_key_scores.  q: [B, n_kv_heads*q_per_kv, d]; codes/scale/zero as written by quantize_keys
     ([B, n_kv_heads, n, ...], dense) -> scores float32 [B, n_kv_heads*q_per_kv, n] (or into `out`, whose
     last dimension may be longer than n: the logits land in its first n columns)."""
-    _need_cuda(q, codes, scale, zero)
-    b, h, n, w = codes.shape
-    d = w * 32 // bits
-    if q.dim() != 3 or q.shape[0] != b or q.shape[1] != h * q_per_kv or q.shape[2] != d or q.stride(2) != 1:
-        raise ValueError("q must be [B, n_kv_heads*q_per_kv, d] with unit channel stride")
-    if not (codes.is_contiguous() and scale.is_contiguous() and zero.is_contiguous()):
-        raise ValueError("codes/scale/zero must be dense")
-    if out is None:
-        out = torch.empty((b, h * q_per_kv, n), dtype=torch.float32, device=codes.device)
-    if out.dtype != torch.float32 or out.stride(2) != 1 or out.shape[0] != b or out.shape[1] != h * q_per_kv:
-        raise ValueError("out must be float32 [B, n_q_heads, >= n] with unit token stride")
-    rc = lib().squat_key_scores(_ptr(codes), _ptr(scale), _ptr(zero), b, h, n, d, bits, group, _ptr(q), _DT[q.dtype],
-                                q_per_kv, q.stride(0), q.stride(1), float(out_scale), _ptr(out), out.stride(0),
-                                out.stride(1), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_key_scores")
-    return out
+    return (_native or native()).key_scores(q, codes, scale, zero, bits, group, q_per_kv, None, 0, out_scale, out,
+                                            None if stream is None else _stream(stream))
 
 
 def key_scores_rope(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor, bits: int,
@@ -426,25 +365,8 @@ def key_scores_rope(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, z
                     stream=None) -> torch.Tensor:
     """squat_key_scores_rope: logits against keys stored before the rotary embedding.  Arguments as for
     key_scores plus inv_freq (float32 [64], device) and the position of token 0."""
-    b, h, n, _ = codes.shape
-    d = 128
-    if inv_freq.dtype != torch.float32 or inv_freq.numel() != 64 or not inv_freq.is_contiguous():
-        raise ValueError("inv_freq must be 64 dense float32 values")
-    _need_cuda(q, codes, inv_freq)
-    if q.dim() != 3 or q.shape[0] != b or q.shape[1] != h * q_per_kv or q.shape[2] != d or q.stride(2) != 1:
-        raise ValueError("q must be [B, n_kv_heads*q_per_kv, d] with unit channel stride")
-    if not (codes.is_contiguous() and scale.is_contiguous() and zero.is_contiguous()):
-        raise ValueError("codes/scale/zero must be dense")
-    if out is None:
-        out = torch.empty((b, h * q_per_kv, n), dtype=torch.float32, device=codes.device)
-    if out.dtype != torch.float32 or out.stride(2) != 1 or out.shape[0] != b or out.shape[1] != h * q_per_kv:
-        raise ValueError("out must be float32 [B, n_q_heads, >= n] with unit token stride")
-    rc = lib().squat_key_scores_rope(_ptr(codes), _ptr(scale), _ptr(zero), b, h, n, d, bits, group, _ptr(inv_freq),
-                                     int(pos0), _ptr(q), _DT[q.dtype], q_per_kv, q.stride(0), q.stride(1),
-                                     float(out_scale), _ptr(out), out.stride(0), out.stride(1), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_key_scores_rope")
-    return out
+    return (_native or native()).key_scores(q, codes, scale, zero, bits, group, q_per_kv, inv_freq, int(pos0), out_scale,
+                                            out, None if stream is None else _stream(stream))
 
 
 def key_scores_rope_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor,
@@ -453,28 +375,8 @@ def key_scores_rope_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: tor
     """squat_key_scores_rope_per_channel: logits against keys stored before the rotary embedding in the
     per-channel layout (codes [B, H, n/32, d, bits] int32, scale/zero [B, H, n/32, d] float16).  inv_freq:
     float32 [64] on the device; pos0: position of token 0."""
-    b, h, tiles, d, nw = codes.shape
-    n = tiles * 32
-    if nw != bits or scale.shape != (b, h, tiles, d) or zero.shape != scale.shape:
-        raise ValueError("codes [B,H,n/32,d,bits], scale/zero [B,H,n/32,d] expected")
-    if inv_freq.dtype != torch.float32 or inv_freq.numel() != 64 or not inv_freq.is_contiguous():
-        raise ValueError("inv_freq must be 64 dense float32 values")
-    _need_cuda(q, codes, inv_freq)
-    if q.dim() != 3 or q.shape[0] != b or q.shape[1] != h * q_per_kv or q.shape[2] != d or q.stride(2) != 1:
-        raise ValueError("q must be [B, n_kv_heads*q_per_kv, d] with unit channel stride")
-    if not (codes.is_contiguous() and scale.is_contiguous() and zero.is_contiguous()):
-        raise ValueError("codes/scale/zero must be dense")
-    if out is None:
-        out = torch.empty((b, h * q_per_kv, n), dtype=torch.float32, device=codes.device)
-    if out.dtype != torch.float32 or out.stride(2) != 1 or out.shape[0] != b or out.shape[1] != h * q_per_kv:
-        raise ValueError("out must be float32 [B, n_q_heads, >= n] with unit token stride")
-    rc = lib().squat_key_scores_rope_per_channel(_ptr(codes), _ptr(scale), _ptr(zero), b, h, n, d, bits, 32,
-                                                 _ptr(inv_freq), int(pos0), _ptr(q), _DT[q.dtype], q_per_kv,
-                                                 q.stride(0), q.stride(1), float(out_scale), _ptr(out),
-                                                 out.stride(0), out.stride(1), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_key_scores_rope_per_channel")
-    return out
+    return (_native or native()).key_scores_per_channel(q, codes, scale, zero, bits, 32, q_per_kv, inv_freq, int(pos0),
+                                                        out_scale, out, None if stream is None else _stream(stream))
 
 
 def key_scores_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor, bits: int,
@@ -482,24 +384,8 @@ def key_scores_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: torch.Te
     """squat_key_scores_per_channel.  q: [B, n_kv_heads*q_per_kv, d]; codes [B, H, n/32, d, bits] int32,
     scale/zero [B, H, n/32, d] float16 as written by quantize_keys_per_channel.  Returns float32
     [B, n_kv_heads*q_per_kv, n] (or fills `out`)."""
-    b, h, tiles, d, nw = codes.shape
-    n = tiles * 32
-    if nw != bits or scale.shape != (b, h, tiles, d) or zero.shape != scale.shape:
-        raise ValueError("codes [B,H,n/32,d,bits], scale/zero [B,H,n/32,d] expected")
-    if q.dim() != 3 or q.shape[0] != b or q.shape[1] != h * q_per_kv or q.shape[2] != d or q.stride(2) != 1:
-        raise ValueError("q must be [B, n_kv_heads*q_per_kv, d] with unit channel stride")
-    if not (codes.is_contiguous() and scale.is_contiguous() and zero.is_contiguous()):
-        raise ValueError("codes/scale/zero must be dense")
-    if out is None:
-        out = torch.empty((b, h * q_per_kv, n), dtype=torch.float32, device=codes.device)
-    if out.dtype != torch.float32 or out.stride(2) != 1 or out.shape[0] != b or out.shape[1] != h * q_per_kv:
-        raise ValueError("out must be float32 [B, n_q_heads, >= n] with unit token stride")
-    rc = lib().squat_key_scores_per_channel(_ptr(codes), _ptr(scale), _ptr(zero), b, h, n, d, bits, 32, _ptr(q),
-                                            _DT[q.dtype], q_per_kv, q.stride(0), q.stride(1), float(out_scale),
-                                            _ptr(out), out.stride(0), out.stride(1), _stream(stream))
-    if rc:
-        raise SquatError(rc, "squat_key_scores_per_channel")
-    return out
+    return (_native or native()).key_scores_per_channel(q, codes, scale, zero, bits, 32, q_per_kv, None, 0, out_scale,
+                                                        out, None if stream is None else _stream(stream))
 
 
 class Cache:
@@ -586,40 +472,16 @@ class Cache:
 
     def append(self, k: torch.Tensor, v: Optional[torch.Tensor] = None, stream=None):
         """k, v: [B, H, d], one decoded token per sequence."""
-        _need_cuda(k, v)
-        if v is not None and v.stride() != k.stride():
-            raise ValueError("k and v must share their strides")
-        rc = lib().squat_cache_append(self._h, _ptr(k), _ptr(v), k.stride(0), k.stride(1), _stream(stream))
-        if rc:
-            raise SquatError(rc, "squat_cache_append")
+        (_native or native()).cache_append(self._h.value, k, v, None if stream is None else _stream(stream))
 
     def key_scores(self, q: torch.Tensor, out_scale: float = 1.0, out=None, stream=None) -> torch.Tensor:
         """q: [B, H*q_per_kv, d] -> logits float32 [B, H*q_per_kv, keys cached] (quantized keys first)."""
-        _need_cuda(q)
-        cnt = self.counts()
-        n = cnt.keys_quantized + cnt.keys_residual
-        if out is None:
-            out = torch.empty((q.shape[0], q.shape[1], n), dtype=torch.float32, device=q.device)
-        rc = lib().squat_cache_key_scores(self._h, _ptr(q), _DT[q.dtype], q.stride(0), q.stride(1), float(out_scale),
-                                          _ptr(out), out.stride(0), out.stride(1), _stream(stream))
-        if rc:
-            raise SquatError(rc, "squat_cache_key_scores")
-        return out
+        return (_native or native()).cache_key_scores(self._h.value, q, None, 0, out_scale, out,
+                                                      None if stream is None else _stream(stream))
 
     def key_scores_rope(self, q: torch.Tensor, inv_freq: torch.Tensor, pos0: int = 0, out_scale: float = 1.0, out=None,
                         stream=None) -> torch.Tensor:
         """Logits against a cache of pre-RoPE keys: cache token t is rotated to position pos0 + t first.
         inv_freq: [d/2] float32 on the device."""
-        _need_cuda(q, inv_freq)
-        if inv_freq.dtype != torch.float32 or not inv_freq.is_contiguous():
-            raise ValueError("inv_freq must be dense float32")
-        cnt = self.counts()
-        n = cnt.keys_quantized + cnt.keys_residual
-        if out is None:
-            out = torch.empty((q.shape[0], q.shape[1], n), dtype=torch.float32, device=q.device)
-        rc = lib().squat_cache_key_scores_rope(self._h, _ptr(q), _DT[q.dtype], q.stride(0), q.stride(1),
-                                               _ptr(inv_freq), int(pos0), float(out_scale), _ptr(out),
-                                               out.stride(0), out.stride(1), _stream(stream))
-        if rc:
-            raise SquatError(rc, "squat_cache_key_scores_rope")
-        return out
+        return (_native or native()).cache_key_scores(self._h.value, q, inv_freq, int(pos0), out_scale, out,
+                                                      None if stream is None else _stream(stream))

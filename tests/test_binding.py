@@ -1,0 +1,79 @@
+"""The native part of the Python binding: what it refuses and with which exception, and that results land where the caller
+says (given outputs, a stream's handle or object)."""
+import pytest
+import torch
+
+from paper_2503_24358_amd import squat
+
+
+def test_refuses_without_a_device():
+    k = torch.zeros(1, 2, 32, 128)
+    with pytest.raises(ValueError):
+        squat.quantize_keys(k, None, 2, 32, 32)
+    with pytest.raises(ValueError):
+        squat.quantize_keys_per_channel(k, None, 2, 32, 32)
+    codes, meta = torch.zeros(1, 2, 32, 8, dtype=torch.int32), torch.zeros(1, 2, 32, 4, dtype=torch.float16)
+    with pytest.raises(ValueError):
+        squat.dequantize_keys(codes, meta, meta, 2, 32)
+    with pytest.raises(ValueError):
+        squat.key_scores(torch.zeros(1, 2, 128), codes, meta, meta, 2, 32, 1)
+    with pytest.raises(AttributeError):
+        squat.quantize_keys("no tensor", None, 2, 32, 32)
+    with pytest.raises(TypeError):
+        squat.native().quantize_keys(k, None, 2, 32, 32)
+    with pytest.raises(TypeError):
+        squat.native().dequantize_keys(codes, meta, meta, 2, 32, torch.float32, None)
+
+
+@pytest.mark.gpu
+def test_refusals_on_the_device():
+    k = torch.randn(1, 2, 32, 128, device="cuda")
+    with pytest.raises(KeyError):
+        squat.quantize_keys(k.double(), None, 2, 32, 32)
+    with pytest.raises(ValueError):
+        squat.quantize_keys(k[0], None, 2, 32, 32)
+    with pytest.raises(ValueError):
+        squat.quantize_keys(k, torch.zeros(2, 128, 128, device="cuda", dtype=torch.float64), 2, 32, 32)
+    with pytest.raises(TypeError):
+        squat.quantize_keys(k, None, 2.0, 32, 32)
+    with pytest.raises(squat.SquatError) as e:
+        squat.quantize_keys(k, None, 4, 16, 32)
+    assert e.value.status < 0 and "squat_quantize_keys" in str(e.value)
+    codes, scale, zero = squat.quantize_keys(k, None, 2, 32, 32)
+    with pytest.raises(ValueError):
+        squat.key_scores(k[:, :, 0, :64], codes, scale, zero, 2, 32, 1)
+    with pytest.raises(ValueError):
+        squat.key_scores(k[:, :, 0], codes[:, :, ::2], scale, zero, 2, 32, 1)
+    with pytest.raises(ZeroDivisionError):
+        squat.key_scores(k[:, :, 0], codes, scale, zero, 0, 32, 1)
+    cache = squat.Cache(1, 2, 1, 2, 32, 32, 32, 64, torch.float32)
+    with pytest.raises(squat.SquatError):
+        cache.key_scores(k[:, :, 0, 1:])               # misaligned
+    cache.append(k[:, :, 0])
+    with pytest.raises(ValueError):
+        cache.append(k[:, :, 0], k[:, :, 0].clone())    # other strides
+
+
+@pytest.mark.gpu
+def test_results_land_where_they_are_asked_for():
+    k = torch.randn(2, 3, 40, 128, device="cuda", dtype=torch.float16)
+    q = torch.randn(2, 6, 128, device="cuda", dtype=torch.bfloat16)
+    want = squat.quantize_keys(k, None, 4, 64, 64)
+    given = tuple(torch.empty_like(t) for t in want)
+    got = squat.quantize_keys(k, None, 4, 64, 64, codes=given[0], scale=given[1], zero=given[2])
+    assert all(a is b and torch.equal(b, w) for a, b, w in zip(got, given, want))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for stream in (side, side.cuda_stream):
+        out = torch.zeros(2, 6, 50, device="cuda")
+        side.wait_stream(torch.cuda.current_stream())
+        assert squat.key_scores(q, *want, 4, 64, 2, 0.5, out=out, stream=stream) is out
+        side.synchronize()
+        assert torch.equal(out[:, :, :40], squat.key_scores(q, *want, 4, 64, 2, 0.5)) and not out[:, :, 40:].any()
+    back = torch.empty(2, 3, 40, 128, device="cuda")
+    assert squat.dequantize_keys(*want, 4, 64, out=back) is back
+    assert torch.equal(back, squat.dequantize_keys(*want, 4, 64, torch.float32))
+    with torch.cuda.stream(side):
+        again = squat.dequantize_keys(*want, 4, 64, torch.float32)
+    side.synchronize()
+    assert torch.equal(again, back)
