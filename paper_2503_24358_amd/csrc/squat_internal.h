@@ -170,6 +170,20 @@ struct QuantPlan {
     int wgs_per_prob;
     int waves;
 };
+// Logits: result rows that begin on 64-byte lines are written by non-temporal stores (whole lines leave the chip once); others
+// (an odd number of tokens) by ordinary ones, whose partial lines the L2 puts together.  Per-token store, us with non-temporal |
+// ordinary stores: 64 x 8 heads x 2001 tokens, 1 query head per KV head 13.6 | 13.5, 4 18.5 | 16.2, 8 32.2 | 21.7; 32 x 32 x 2501, 4:
+// 56 | 40; 16 x 8 x 101, 4: 3.9 | 3.7; on lines (64 x 256 x 2080) 373 | 381.
+inline bool rows_on_lines(const float* scores, int64_t stride_batch, int64_t stride_head) {
+    return aligned(scores, 64) && stride_batch % 16 == 0 && stride_head % 16 == 0;
+}
+// One logit; LINES: see rows_on_lines.
+template <bool LINES>
+__device__ __forceinline__ void put_score(float* p, float v) {
+    if constexpr (LINES) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 int plan_quantize(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t n_tokens, bool has_update,
                   int64_t update_stride_batch, int group, int g, QuantPlan& out);
 int plan_quantize_pc(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t n_tokens, bool has_update,

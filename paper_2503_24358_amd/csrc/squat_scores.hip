@@ -76,7 +76,7 @@ __device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi) {
 
 // grid: x over slabs of kScoreWaves * units_per_wave units, y / z over (batch, KV head); RES: and rows along y for the
 // full-precision keys (residual_rows), z = 0
-template <int BITS, int NG, int QDT, bool RES>
+template <int BITS, int NG, int QDT, bool RES, bool LINES>
 __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const ScoreParams p) {
     constexpr int WPK = kD * BITS / 32;                   // packed words per key
     constexpr int CPG = 4 / NG;                           // 32-channel chunks per group
@@ -379,12 +379,12 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
                 held1 = s1;
             } else {
                 if (st0) {
-                    __builtin_nontemporal_store(held0, optr);
-                    __builtin_nontemporal_store(s0, optr + kUnitTokens);
+                    put_score<LINES>(optr, held0);
+                    put_score<LINES>(optr + kUnitTokens, s0);
                 }
                 if (st1) {
-                    __builtin_nontemporal_store(held1, optr + out1);
-                    __builtin_nontemporal_store(s1, optr + out1 + kUnitTokens);
+                    put_score<LINES>(optr + out1, held1);
+                    put_score<LINES>(optr + out1 + kUnitTokens, s1);
                 }
                 optr += 2 * kUnitTokens;
             }
@@ -439,20 +439,28 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
             unit_scores(s0, s1);
             const int tok = u * kUnitTokens + col;
             if (tok < n_tok) {
-                if (st0) __builtin_nontemporal_store(s0, out0 + tok);
-                if (st1) __builtin_nontemporal_store(s1, out0 + out1 + tok);
+                if (st0) put_score<LINES>(out0 + tok, s0);
+                if (st1) put_score<LINES>(out0 + out1 + tok, s1);
             }
         }
     }
 }
 
+template <int BITS, int NG, int QDT, bool RES>
+void launch_lines(const ScoreParams& p, dim3 grid, hipStream_t s) {
+    const dim3 block(kScoreWaves * kWave);
+    if (rows_on_lines(p.scores, p.ssb, p.ssh))
+        hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, RES, true>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, RES, false>), grid, block, 0, s, p);
+}
+
 template <int BITS, int NG, int QDT>
 void launch_res(const ScoreParams& p, dim3 grid, hipStream_t s) {
-    const dim3 block(kScoreWaves * kWave);
     if (p.res.rows)
-        hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, true>), grid, block, 0, s, p);
+        launch_lines<BITS, NG, QDT, true>(p, grid, s);
     else
-        hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, false>), grid, block, 0, s, p);
+        launch_lines<BITS, NG, QDT, false>(p, grid, s);
 }
 
 template <int BITS, int NG>

@@ -59,6 +59,7 @@ struct ScorePcParams {
     float out_scale;
     int tiles_per_wave;
     ResidualKeys res;                // (RES kernels) logits of these keys by further workgroups
+    int lines;                       // whole lines, or non-temporal stores pay all the same (host side)
 };
 
 __device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi) {
@@ -79,7 +80,7 @@ __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
 // are in use, so NT = 2 gives rows 0..7 to one token group and rows 8..15 to the next one (same queries,
 // the other group's scales): the instructions that build the query-side operand then serve two groups,
 // and lanes of K blocks 0, 1 find the first group's results in their registers, K blocks 2, 3 the second's.
-template <int BITS, int QDT, int NT, bool RES>
+template <int BITS, int QDT, int NT, bool RES, bool LINES>
 __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const ScorePcParams p) {
     constexpr int W = BITS;                               // packed words per channel and token group
     constexpr int TH = 16 / BITS;                         // tokens per 16-bit half of a word: 8 or 4
@@ -391,12 +392,12 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
         if (tr < t1) {
             const int64_t tok = static_cast<int64_t>(tr) * 32 + tokA;
             if (st0) {
-                __builtin_nontemporal_store(r0[0], out0 + tok);
-                __builtin_nontemporal_store(r0[1], out0 + tok + TOKB);
+                put_score<LINES>(out0 + tok, r0[0]);
+                put_score<LINES>(out0 + tok + TOKB, r0[1]);
             }
             if (st1) {
-                __builtin_nontemporal_store(r1[0], out0 + p.ssh + tok);
-                __builtin_nontemporal_store(r1[1], out0 + p.ssh + tok + TOKB);
+                put_score<LINES>(out0 + p.ssh + tok, r1[0]);
+                put_score<LINES>(out0 + p.ssh + tok + TOKB, r1[1]);
             }
         }
     };
@@ -422,13 +423,21 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
     }
 }
 
+template <int BITS, int QDT, int NT, bool RES>
+void launch_lines(const ScorePcParams& p, dim3 grid, hipStream_t s) {
+    const dim3 block(kPcWaves * kWave);
+    if (p.lines)
+        hipLaunchKernelGGL((key_scores_pc_kernel<BITS, QDT, NT, RES, true>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((key_scores_pc_kernel<BITS, QDT, NT, RES, false>), grid, block, 0, s, p);
+}
+
 template <int BITS, int QDT, int NT>
 void launch_res(const ScorePcParams& p, dim3 grid, hipStream_t s) {
-    const dim3 block(kPcWaves * kWave);
     if (p.res.rows)
-        hipLaunchKernelGGL((key_scores_pc_kernel<BITS, QDT, NT, true>), grid, block, 0, s, p);
+        launch_lines<BITS, QDT, NT, true>(p, grid, s);
     else
-        hipLaunchKernelGGL((key_scores_pc_kernel<BITS, QDT, NT, false>), grid, block, 0, s, p);
+        launch_lines<BITS, QDT, NT, false>(p, grid, s);
 }
 
 template <int BITS, int NT>
@@ -478,6 +487,11 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     p.scores = scores;
     p.ssb = s_stride_batch;
     p.ssh = s_stride_head;
+    // Rows off the lines, us with non-temporal | ordinary stores: 4 query heads per KV head, 2 MB of logits 5.8 | 5.1, 8 MB 9.8 | 10.4,
+    // 16 MB 14.9 | 16.4 or 17.0 | 16.5, 20 MB 21.8 | 19.3, 41 MB 44.3 | 33.5; 8 query heads, 8 MB 8.5 | 7.9, 41 MB 41.5 | 24.5.
+    const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
+    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) ||
+              (q_per_kv <= 4 && out_bytes > (int64_t(4) << 20) && out_bytes < (int64_t(18) << 20));
     p.n_tiles = static_cast<int>(n_tokens / 32);
     p.store_tiles = store_tokens / 32;
     p.n_kv_heads = n_kv_heads;

@@ -242,7 +242,7 @@ __device__ __forceinline__ void stage_queries(const RopeParams& p, int64_t b, in
 // as its K slots 8 kb .. 8 kb + 7 (both operands), rows = (query head, fp16 high / low part).
 // (Registers are capped at three wavefronts per SIMD: the 4-bit forms for more than four query heads per KV head
 // would otherwise take a few more and run two, 6 % slower.)
-template <int BITS, int NG, int QDT, bool WIDE>
+template <int BITS, int NG, int QDT, bool WIDE, bool LINES>
 __global__ void __launch_bounds__(kRopeWaves* kWave) __attribute__((amdgpu_waves_per_eu(3)))
 key_scores_rope_kernel(const RopeParams p) {
     constexpr int WPK = kD * BITS / 32;                   // packed words per key
@@ -477,12 +477,12 @@ key_scores_rope_kernel(const RopeParams p) {
                 held1 = s1;
             } else {
                 if (st0) {
-                    __builtin_nontemporal_store(held0, optr);
-                    __builtin_nontemporal_store(s0, optr + kRopeUnit);
+                    put_score<LINES>(optr, held0);
+                    put_score<LINES>(optr + kRopeUnit, s0);
                 }
                 if (st1) {
-                    __builtin_nontemporal_store(held1, optr + out1);
-                    __builtin_nontemporal_store(s1, optr + out1 + kRopeUnit);
+                    put_score<LINES>(optr + out1, held1);
+                    put_score<LINES>(optr + out1 + kRopeUnit, s1);
                 }
                 optr += 2 * kRopeUnit;
             }
@@ -535,8 +535,8 @@ key_scores_rope_kernel(const RopeParams p) {
             unit_scores(v, s0, s1);
             const int tok = u * kRopeUnit + col;
             if (tok < n_tok) {
-                if (st0) __builtin_nontemporal_store(s0, out0 + tok);
-                if (st1) __builtin_nontemporal_store(s1, out0 + out1 + tok);
+                if (st0) put_score<LINES>(out0 + tok, s0);
+                if (st1) put_score<LINES>(out0 + out1 + tok, s1);
             }
         }
     }
@@ -751,12 +751,20 @@ int launch_pc_dt(const RopeParams& p, dim3 grid, hipStream_t s) {
     return check_launch();
 }
 
+template <int BITS, int NG, int QDT, bool WIDE>
+void launch_lines(const RopeParams& p, dim3 grid, dim3 block, hipStream_t s) {
+    if (rows_on_lines(p.scores, p.ssb, p.ssh))
+        hipLaunchKernelGGL((key_scores_rope_kernel<BITS, NG, QDT, WIDE, true>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((key_scores_rope_kernel<BITS, NG, QDT, WIDE, false>), grid, block, 0, s, p);
+}
+
 template <int BITS, int NG, int QDT>
 void launch_wide(const RopeParams& p, dim3 grid, dim3 block, hipStream_t s) {
     if (p.qpk > 4)
-        hipLaunchKernelGGL((key_scores_rope_kernel<BITS, NG, QDT, true>), grid, block, 0, s, p);
+        launch_lines<BITS, NG, QDT, true>(p, grid, block, s);
     else
-        hipLaunchKernelGGL((key_scores_rope_kernel<BITS, NG, QDT, false>), grid, block, 0, s, p);
+        launch_lines<BITS, NG, QDT, false>(p, grid, block, s);
 }
 
 template <int BITS, int NG>
