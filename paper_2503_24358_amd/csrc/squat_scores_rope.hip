@@ -65,6 +65,7 @@ struct RopeParams {
     float out_scale;
     int units_per_wave;
     int wide_loads;                  // per-token store: rows 4-byte aligned, whole units fetched with 16-byte loads
+    bool lines;                      // per-token store: logits by non-temporal stores
 };
 
 __device__ __forceinline__ uint32_t pack_h2(_Float16 lo, _Float16 hi) {
@@ -753,7 +754,7 @@ int launch_pc_dt(const RopeParams& p, dim3 grid, hipStream_t s) {
 
 template <int BITS, int NG, int QDT, bool WIDE>
 void launch_lines(const RopeParams& p, dim3 grid, dim3 block, hipStream_t s) {
-    if (rows_on_lines(p.scores, p.ssb, p.ssh))
+    if (p.lines)
         hipLaunchKernelGGL((key_scores_rope_kernel<BITS, NG, QDT, WIDE, true>), grid, block, 0, s, p);
     else
         hipLaunchKernelGGL((key_scores_rope_kernel<BITS, NG, QDT, WIDE, false>), grid, block, 0, s, p);
@@ -837,6 +838,12 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
         const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
         p.wide_loads = (store_stride * meta_row) % 4 == 0;    // the bases are 8-byte aligned
     }
+    // Rows off the lines, us with non-temporal | ordinary stores: 4 query heads per KV head, 2 MB of logits 8.0 | 7.5, 4 MB 10.9 |
+    // 10.1 or 15.8 | 13.7, 8 MB 21.9 | 20.6, 12 MB 21.0 | 21.4 or 22.0 | 22.4, 33 MB 50.7 | 47.8; 8 query heads, 12 MB 16.0 | 15.9,
+    // 25 MB 27.8 | 24.9, 33 MB 40.4 | 33.0; 1 query head, 17 MB 78.2 | 79.5.
+    const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
+    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) ||
+              (q_per_kv <= 4 && out_bytes > (int64_t(9) << 20) && out_bytes < (int64_t(18) << 20));
 
     // workgroups along the sequence: about kRopeWaves * aim units each, spread evenly
     const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit;
