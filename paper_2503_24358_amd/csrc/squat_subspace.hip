@@ -75,6 +75,78 @@ struct GramOps<SQUAT_F16> {
     }
 };
 
+// Tiles LO .. LO + N - 1 of a wavefront's sums into LDS, and added from there.  (A tile is copied whole: parts of acc picked
+// under the two-way branches below would put it into scratch memory.)
+template <int LO, int N>
+__device__ __forceinline__ void put_tiles(const f32x16 (&acc)[kTiles], f32x4* at, int lane) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        const f32x16 a = acc[LO + t];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) at[(t * 4 + k) * kWave + lane] = f32x4{a[4 * k], a[4 * k + 1], a[4 * k + 2], a[4 * k + 3]};
+    }
+}
+template <int LO, int N>
+__device__ __forceinline__ void add_tiles(f32x16 (&acc)[kTiles], const f32x4* at, int lane) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        f32x16 a = acc[LO + t];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const f32x4 v = at[(t * 4 + k) * kWave + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[4 * k + e] += v[e];
+        }
+        acc[LO + t] = a;
+    }
+}
+template <int LO, int N>
+__device__ __forceinline__ void store_tiles(const f32x16 (&acc)[kTiles], float* dst, int lane) {
+#pragma unroll
+    for (int t = LO; t < LO + N; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dst[(t * 16 + e) * kWave + lane] = acc[t][e];
+}
+
+// The four wavefronts' sums, (0 + 2) + (1 + 3), to the workgroup's partial matrix: wavefronts 0 and 2, 1 and 3 exchange halves
+// of the ten tiles, then 0 and 1, 2 and 3 quarters, so that each adds and stores a quarter; in the second exchange a wavefront
+// writes where it has itself read in the first.  Bound by the chain of LDS accesses behind one another: with whole sums handed
+// to wavefronts 0 and 1, then to 0, 800 4-byte accesses and stores followed one another, now 60 16-byte accesses and 48
+// stores.  Gram and reduction, us before | after: fp32, 1 head of 512 tokens 15.7 | 13.1, 28 heads x 4 of 1024 40.9 | 37.3;
+// bf16, 1 head of 512 11.2 | 9.8, 8 heads x 4 of 8192 24.1 | 22.7, 256 of 512 25.7 | 24.3.
+__device__ __forceinline__ void reduce_and_store(f32x16 (&acc)[kTiles], unsigned char* smem, int wave, int lane, float* dst) {
+    constexpr int kSlot = 5 * 4 * kWave;                 // 16-byte pieces of five tiles
+    f32x4* const slots = reinterpret_cast<f32x4*>(smem);
+    if (wave < 2) put_tiles<5, 5>(acc, slots + wave * kSlot, lane);
+    else put_tiles<0, 5>(acc, slots + wave * kSlot, lane);
+    __syncthreads();
+    if (wave < 2) {
+        f32x4* mine = slots + (wave + 2) * kSlot;
+        add_tiles<0, 5>(acc, mine, lane);
+        if (wave == 0) put_tiles<3, 2>(acc, mine, lane);
+        else put_tiles<0, 3>(acc, mine, lane);
+    } else {
+        f32x4* mine = slots + (wave - 2) * kSlot;
+        add_tiles<5, 5>(acc, mine, lane);
+        if (wave == 2) put_tiles<8, 2>(acc, mine, lane);
+        else put_tiles<5, 3>(acc, mine, lane);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        add_tiles<0, 3>(acc, slots + 3 * kSlot, lane);
+        store_tiles<0, 3>(acc, dst, lane);
+    } else if (wave == 1) {
+        add_tiles<3, 2>(acc, slots + 2 * kSlot, lane);
+        store_tiles<3, 2>(acc, dst, lane);
+    } else if (wave == 2) {
+        add_tiles<5, 3>(acc, slots + kSlot, lane);
+        store_tiles<5, 3>(acc, dst, lane);
+    } else {
+        add_tiles<8, 2>(acc, slots, lane);
+        store_tiles<8, 2>(acc, dst, lane);
+    }
+}
+
 // Accumulate one workgroup's share of Q^T Q.  16-bit element types.
 template <int DT>
 __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const GramParams p) {
@@ -190,40 +262,13 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
         }
     }
 
-    // reduce the four wavefronts through LDS (two rounds), wave 0 writes the partial
-    float* red = reinterpret_cast<float*>(smem);        // [2][10][16][64]
-    auto put = [&](int slot) {
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) red[((slot * kTiles + t) * 16 + e) * 64 + lane] = acc[t][e];
-    };
-    auto add = [&](int slot) {
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[t][e] += red[((slot * kTiles + t) * 16 + e) * 64 + lane];
-    };
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) add(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave == 0) {
-        add(0);
-        float* dst = p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats;
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dst[(t * 16 + e) * 64 + lane] = acc[t][e];
-    }
+    reduce_and_store(acc, smem, wave, lane, p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats);
 }
 
 // fp32 inputs: products on the fp32 matrix cores (32x32x2), two tokens per step.
 __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const GramParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, m = lane & 31;
     const int kvh = blockIdx.x / p.wgs_per_head;
     const int wg = blockIdx.x % p.wgs_per_head;
@@ -268,33 +313,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
                         __builtin_amdgcn_mfma_f32_32x32x2f32(raw[j][a], raw[j][b], acc[tile_index(a, b)], 0, 0, 0);
     }
 
-    float* red = reinterpret_cast<float*>(smem);
-    auto put = [&](int slot) {
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) red[((slot * kTiles + t) * 16 + e) * 64 + lane] = acc[t][e];
-    };
-    auto add = [&](int slot) {
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[t][e] += red[((slot * kTiles + t) * 16 + e) * 64 + lane];
-    };
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) add(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave == 0) {
-        add(0);
-        float* dst = p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats;
-#pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dst[(t * 16 + e) * 64 + lane] = acc[t][e];
-    }
+    reduce_and_store(acc, smem, wave, lane, p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats);
 }
 
 // partial[(t*16 + e)*64 + lane] is element (row mm, col nn) of tile t = (a, b) with
@@ -603,14 +622,14 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     p.n_tokens = n_tokens;
     p.q_per_kv = q_per_kv;
     // Chunks per wavefront at least (the workspace has room for pl.wgs_per_head partials of a head).  Every workgroup leaves
-    // a partial of 40 KB and pays ~5 us for reducing and writing it, so eight chunks, or two: for 16-bit queries where eight
+    // a partial of 40 KB and pays ~2 us for reducing and writing it, so eight chunks, or two: for 16-bit queries where eight
     // leave no more than 16 workgroups; for fp32, whose chunk takes 5 k cycles on the matrix cores, as far as the launch
     // stays within one workgroup per CU (one fills a CU's LDS: more run in a second round).
-    // Gram and reduction, us at 8 | 2 chunks: bf16, 1 head of 512 tokens 12.9 | 11.3, 8 of 512 14.1 | 13.2, 16 of 512 15.8 |
-    // 15.2, 16 of 200 14.5 | 15.0, 24 of 512 17.5 | 17.4, 24 of 200 16.1 | 16.7, 32 of 512 17.7 | 19.2, 8 of 1024 14.4 | 13.2,
-    // 24 of 1024 18.0 | 18.7.  fp32, 1 head of 512 31.6 | 15.7, 8 of 512 32.7 | 17.5, 64 of 512 37.7 | 31.7; 28 heads x 4
-    // of 1024: 8 workgroups a head 40.3, 9 (one round) 41.4, 10 (two rounds) 60.1; 48 heads of 2048: 42.4, 5 a head 41.3, 6
-    // (two rounds) 57.9.
+    // Gram and reduction, us at 8 | 2 chunks: bf16, 1 head of 512 tokens 11.1 | 9.8, 8 of 512 12.7 | 11.7, 16 of 512 14.1 |
+    // 13.8, 16 of 200 13.5 | 13.9, 24 of 512 15.7 | 15.6, 24 of 200 15.0 | 15.7, 32 of 512 16.2 | 17.6, 8 of 1024 13.1 | 12.0,
+    // 24 of 1024 16.4 | 17.0.  fp32, 1 head of 512 28.4 | 13.1, 8 of 512 29.7 | 15.1, 64 of 512 34.6 | 29.3.  With a reduction
+    // that took 2 to 3 us more, fp32, 28 heads x 4 of 1024: 8 workgroups a head 40.3, 9 (one round) 41.4, 10 (two rounds) 60.1;
+    // 48 heads of 2048: 42.4, 5 a head 41.3, 6 (two rounds) 57.9.
     const int64_t units = q_per_kv * ((n_tokens + 15) / 16);
     const int64_t wide = (units + 8 * kGramWaves - 1) / (8 * kGramWaves);
     const int64_t narrow = (units + 2 * kGramWaves - 1) / (2 * kGramWaves);
@@ -635,7 +654,7 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     int rc = check_launch();
     if (rc) return rc;
     // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head (us
-    // for Gram and reduction, per head | spread: bf16, 1 partial a head, 16 heads of 200 tokens 15.9 | 14.5, 24 of 200 16.1 |
+    // for Gram and reduction, per head | spread, each 1.3 less by now: bf16, 1 partial a head, 16 heads of 200 tokens 15.9 | 14.5, 24 of 200 16.1 |
     // 16.1, 32 of 200 16.4 | 17.5; 2 partials, 32 of 1024 20.6 | 19.6, 36 of 1024 21.0 | 20.9, 40 of 1024 21.1 | 21.4; 256
     // heads, 1 partial 21.9 | 38.8: the scattered 8-byte writes)
     if (p.wgs_per_head >= 4 || n_kv_heads <= (p.wgs_per_head == 1 ? 24 : 32))
