@@ -71,6 +71,10 @@ constexpr int kTriWsPerWave = 9 * 8 * 64;              // operands of the back-t
 constexpr int kTriWsDoubles = kTriThreads / 64 * kTriWsPerWave;
 constexpr int kTriVLd = 130;            // reflector k at kTriX + 130 k in the reduction (over the vectors and factors, not in use yet);
                                         // 130: the 16 reflectors of a matrix operand fall on different banks
+constexpr int kTriTail = 96;            // first column of the reduction's last steps, on one wavefront
+constexpr int kTriTailW = kTriS + 512;  // [32][33] its matrix, [32] the column in hand
+constexpr int kTriTailLd = 33;
+static_assert(512 + 32 * kTriTailLd + 32 <= 8 * 16 * kTriTLd, "aliased blocks");
 static_assert(kTriLdsBytes <= 160 * 1024, "LDS plan exceeds a compute unit");
 static_assert((kTriN - 2) * kTriVLd <= 4 * 4096 && 32 * 33 <= 8 * 16 * kTriTLd, "aliased blocks");
 
@@ -329,11 +333,78 @@ __device__ __forceinline__ void tri_steps(double (&a)[64], double& xr, double (&
     double* const vp = L + kTriX + (8 * G - 1) * kTriVLd + id.row;
     if constexpr (G == 0) tri_step<G, 1>(a, xr, xc, id, T, vp, L, 1);
 #pragma nounroll
-    for (int ll = G == 0 ? 2 : 0; ll < (G == 15 ? 6 : 8); ll += 2) {
+    for (int ll = G == 0 ? 2 : 0; ll < 8; ll += 2) {
         tri_step<G, 0>(a, xr, xc, id, T, vp, L, ll);
         tri_step<G, 1>(a, xr, xc, id, T, vp, L, ll + 1);
     }
-    if constexpr (G == 15) tri_step<G, 0>(a, xr, xc, id, T, vp, L, 6);
+}
+
+// The last steps, k1 = 96 .. 126, on one wavefront and without LDS or barriers: with 32 columns left, lanes l and l + 32 hold row
+// 96 + rho, rho = 2 (l & 15) + (l >> 4 & 1), the lower half its even columns, the upper one the odd ones.  The sums of a row's two
+// halves are then in both of them, and a vector by rows becomes one by columns (lane (h, i): column 2 i + h, in both rows of
+// 16 lanes of the half) by one swap of rows of 16 lanes.  Everything else as above.
+template <int S>                                          // v of the lower (upper) half, in both
+__device__ __forceinline__ double tri_both(double v) {
+    const auto sl = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(__double2loint(v)), static_cast<uint32_t>(__double2loint(v)), false, false);
+    const auto sh = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(__double2hiint(v)), static_cast<uint32_t>(__double2hiint(v)), false, false);
+    return __hiloint2double(static_cast<int>(sh[S]), static_cast<int>(sl[S]));
+}
+__device__ __forceinline__ double tri_columns(double v, bool lower) {
+    const auto sl = __builtin_amdgcn_permlane16_swap(static_cast<uint32_t>(__double2loint(v)), static_cast<uint32_t>(__double2loint(v)), false, false);
+    const auto sh = __builtin_amdgcn_permlane16_swap(static_cast<uint32_t>(__double2hiint(v)), static_cast<uint32_t>(__double2hiint(v)), false, false);
+    return __hiloint2double(static_cast<int>(lower ? sh[0] : sh[1]), static_cast<int>(lower ? sl[0] : sl[1]));
+}
+template <int G, int S>                                   // k1 = 96 + 8 G + ll, S = ll & 1
+__device__ __forceinline__ void tri_tail_step(double (&a)[16], double& xr, double& xc, int lane, int rho, double (&T)[3],
+                                              double* const vp, const int ll) {
+#pragma clang fp contract(off)
+    constexpr int B0 = G / 2, M = G % 2 * 4;
+    const int at = 4 * G + (ll >> 1), src = 16 * S + at;  // column k1: registers `at` of the half S; its row: lanes src, src + 32
+    double q0 = 0.0, q1 = 0.0;
+    tri_mv<B0 == 1, M>(q0, q1, xc, a + 8 * B0);
+    if constexpr (B0 < 1) tri_mv<true, 0>(q0, q1, xc, a + 8);
+    q0 = q0 + q1;
+    const double p = tri_swap32_add(q0, q0);
+    const double k0 = a[4 * G], k2 = a[4 * G + 1], k4 = a[4 * G + 2], k6 = a[4 * G + 3];
+    const double c = tri_both<S>(ll < 4 ? (ll < 2 ? k0 : k2) : (ll < 6 ? k4 : k6));
+    double z = tri_swap16_add(xr * xr, xr * p);           // even rows of 16 lanes: |x|^2, odd ones: x'A x
+#pragma unroll
+    for (int sel = 0; sel < 4; ++sel) z += dpp_move(z, sel);
+    const double sigma2 = tri_readlane(z, 0), xax = tri_readlane(z, 16), x0 = tri_readlane(xr, src);
+    const double sg = sigma2 + kTriTiny;
+    const double al = copysign(sg * tri_rsqrt(sg), x0);
+    const double binv = tri_rcp(fma(fabs(x0), fabs(al), sg));
+    const double beta = sigma2 > kTriTiny ? binv : 0.0;
+    const double u = fma(al, c, p);
+    const double u1 = tri_readlane(u, src), c1 = tri_readlane(c, src);
+    const double vu = fma(al, fma(-al, c1, u1 + u1), xax);
+    const double K2 = beta * vu;
+    const double v1 = x0 + al;
+    const double bv1 = -beta * v1, bt1 = -beta * fma(-K2, v1, u1);
+    const bool own = (lane & 31) == src;
+    xr = own ? v1 : xr;
+    const double vc = (lane & 47) == 32 * S + at ? v1 : xc;
+    vp[ll * kTriVLd] = xr;
+    const double nv = -beta * xr, nt = -beta * fma(-K2, xr, u);
+    xr = fma(xr, bt1, fma(u, bv1, c));
+    T[0] = own ? xr : T[0];
+    T[1] = own ? al : T[1];
+    T[2] = own ? beta : T[2];
+    xr = __hiloint2double(rho > 8 * G + ll ? __double2hiint(xr) : 0, __double2loint(xr));
+    xc = tri_columns(xr, lane < 32);
+    const double uc = tri_columns(u, lane < 32);
+    tri_up<B0 == 1, M>(a + 8 * B0, uc, vc, nv, nt);
+    if constexpr (B0 < 1) tri_up<true, 0>(a + 8, uc, vc, nv, nt);
+}
+template <int G>
+__device__ __forceinline__ void tri_tail_steps(double (&a)[16], double& xr, double& xc, int lane, int rho, double (&T)[3], double* L) {
+    double* const vp = L + kTriX + (kTriTail + 8 * G - 1) * kTriVLd + kTriTail + rho;
+#pragma nounroll
+    for (int ll = 0; ll < (G == 3 ? 6 : 8); ll += 2) {
+        tri_tail_step<G, 0>(a, xr, xc, lane, rho, T, vp, ll);
+        tri_tail_step<G, 1>(a, xr, xc, lane, rho, T, vp, ll + 1);
+    }
+    if constexpr (G == 3) tri_tail_step<G, 0>(a, xr, xc, lane, rho, T, vp, 6);
 }
 
 // Eight terms of the three-term recurrence of the leading principal minors of T - x, p_{i+1} = (d_i - x) p_i - e_{i-1}^2
@@ -458,24 +529,54 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
     tri_steps<9>(a, xr, xc, id, T, L);
     tri_steps<10>(a, xr, xc, id, T, L);
     tri_steps<11>(a, xr, xc, id, T, L);
-    tri_steps<12>(a, xr, xc, id, T, L);
-    tri_steps<13>(a, xr, xc, id, T, L);
-    tri_steps<14>(a, xr, xc, id, T, L);
-    tri_steps<15>(a, xr, xc, id, T, L);
-    // T and the reflectors' beta: rows 1 .. 126 from their steps; of the last 2 x 2 block the next column is e_126, and the
-    // corner is in the last row's last column
+    // the last 32 rows to wavefront 0; meanwhile the others clear what its reflectors have above
+    {
+        double* const W = L + kTriTailW;
+        double* const X = W + 32 * kTriTailLd;
+        if ((lane & 31) >= kTriTail / 4) {
+            const int row = id.row - kTriTail;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) W[row * kTriTailLd + 2 * j + (lane >> 5)] = a[kTriTail / 2 + j];
+            X[row] = xr;                                  // (both halves have it)
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const int rho = 2 * (lane & 15) + (lane >> 4 & 1);
+            double t[16], T2[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) t[j] = W[rho * kTriTailLd + 2 * j + (lane >> 5)];
+            double x = X[rho], y = X[id.col];
+            tri_tail_steps<0>(t, x, y, lane, rho, T2, L);
+            tri_tail_steps<1>(t, x, y, lane, rho, T2, L);
+            tri_tail_steps<2>(t, x, y, lane, rho, T2, L);
+            tri_tail_steps<3>(t, x, y, lane, rho, T2, L);
+            // T and the reflectors' beta: rows up to 126 from their steps; of the last 2 x 2 block the next column is e_126, and
+            // the corner is in the last row's last column
+            const int row = kTriTail + rho;
+            if (row < kTriN - 1) {
+                L[kTriDd + row] = T2[0];
+                L[kTriEe + row - 1] = -T2[1];
+                L[kTriBet + row - 1] = T2[2];
+            } else if (lane == 63) {
+                L[kTriDd + kTriN - 1] = t[15];
+                L[kTriEe + kTriN - 2] = x;
+                L[kTriEe + kTriN - 1] = 0.0;
+                L[kTriBet + kTriN - 2] = 0.0;
+                L[kTriBet + kTriN - 1] = 0.0;
+            }
+        } else {
+            for (int e = tid - 64; e < (kTriN - 1 - kTriTail) * (kTriTail / 2); e += kTriThreads - 64) {
+                const int k = e / (kTriTail / 2), m = e % (kTriTail / 2);
+                *reinterpret_cast<double2*>(L + kTriX + (kTriTail - 1 + k) * kTriVLd + 2 * m) = double2{0.0, 0.0};
+            }
+        }
+    }
     if (id.row == 0) {
         if (lane == 0) L[kTriDd] = d0;
-    } else if (id.row < kTriN - 1) {
+    } else if (id.row < kTriTail) {
         L[kTriDd + id.row] = T[0];
         L[kTriEe + id.row - 1] = -T[1];
         L[kTriBet + id.row - 1] = T[2];
-    } else if (lane == 63) {
-        L[kTriDd + kTriN - 1] = a[63];
-        L[kTriEe + kTriN - 2] = xr;
-        L[kTriEe + kTriN - 1] = 0.0;
-        L[kTriBet + kTriN - 2] = 0.0;
-        L[kTriBet + kTriN - 1] = 0.0;
     }
     __syncthreads();
     // ---- operands of the back-transformation, while the reflectors are in LDS.  The reflectors are taken in blocks of 16,
