@@ -8,7 +8,8 @@
 //      its own number modulo 4, two lanes a row, one the even, one the odd
 //      columns, so the trailing block shrinks in every wavefront at once and a
 //      product with a vector stays in the lane; per step only the product A x, the
-//      next column and one number per wavefront travel through LDS (one barrier).
+//      next column and one number per wavefront travel through LDS (one barrier);
+//      the last 31 steps on one wavefront, without.
 //   2. The r largest eigenvalues of T by Sturm counts (a team of threads per
 //      eigenvalue, a trial shift each): the count
 //      is the number of sign changes of the three-term recurrence of the leading
@@ -207,8 +208,8 @@ __device__ __forceinline__ void tri_up(double* a, double u, double v, double nv,
 // over the lanes), K = beta / 2 v'u, t = u - K v, the rank-two update A - beta (v t' + t v') = A - beta (v u' + (u - 2 K v) v')
 // of its rows, and the next column.  alpha and beta do not depend on the exchange.
 // Bound by instruction issue (one wavefront per SIMD, four cycles an instruction, fp64 or not, dependent or not) and, with the
-// blocks getting small, by the barrier and the exchange: 300 instructions and 1800 cycles a step at the start, 150 and 950 near
-// the end, 73 us for the 126 of one head.  Before, every thread held four rows at 16 columns and 20 entries of each vector
+// blocks getting small, by the barrier and the exchange: 300 instructions and 1800 cycles a step at the start, 200 and
+// 1180 with 32 columns left, where the last steps take another form (below); 70 us for the 126 of one head.  Before, every thread held four rows at 16 columns and 20 entries of each vector
 // (16 by columns, a copy in each of a wavefront's eight teams, and 4 by rows), the sum x'u followed the exchange, and a step was
 // 556 and 152 instructions: 99 us.  What did not help: the same with two rows a lane and the sums over the wavefronts formed
 // by the readers (79 us; LDS), all steps unrolled (same time a step, the compiler spills), the scalars in front of the barrier.
@@ -343,6 +344,9 @@ __device__ __forceinline__ void tri_steps(double (&a)[64], double& xr, double (&
 // 96 + rho, rho = 2 (l & 15) + (l >> 4 & 1), the lower half its even columns, the upper one the odd ones.  The sums of a row's two
 // halves are then in both of them, and a vector by rows becomes one by columns (lane (h, i): column 2 i + h, in both rows of
 // 16 lanes of the half) by one swap of rows of 16 lanes.  Everything else as above.
+// Bound by instruction issue: 178 instructions a step, 130 at the end, against 200 and 160 with the barrier and the exchange (~300
+// cycles) on top.  Build of the subspace with them | now, us: one head 122.5 | 119.8, 8 heads x 4 131.5 | 128.5, 256 heads 151.6 |
+// 148.2.  The same from 64 columns on (a lane per row): 125; the four wavefronts' share of the products is worth their barrier there.
 template <int S>                                          // v of the lower (upper) half, in both
 __device__ __forceinline__ double tri_both(double v) {
     const auto sl = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(__double2loint(v)), static_cast<uint32_t>(__double2loint(v)), false, false);
