@@ -25,7 +25,8 @@
 //      eigenvalues) or go through Cholesky-QR (coincident ones).
 //   4. Rayleigh quotients = eigenvalues; residuals ||T x - lambda x|| checked.
 //   5. Back-transformation in blocks of 16 reflectors on the matrix cores (their
-//      operands are formed after step 1, while the reflectors are in LDS, and wait
+//      operands are formed beside the end of step 1 and after it, while the
+//      reflectors are in LDS, and wait
 //      in global memory while steps 2-4 use that LDS block).
 //
 // A matrix whose result fails the checks of step 4 (never seen with fp64, kept as
@@ -533,6 +534,91 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
     tri_steps<9>(a, xr, xc, id, T, L);
     tri_steps<10>(a, xr, xc, id, T, L);
     tri_steps<11>(a, xr, xc, id, T, L);
+    // ---- operands of the back-transformation, while the reflectors are in LDS.  The reflectors are taken in blocks of 16,
+    // H_{16 b} ... H_{16 b + 15} = I - V T V' with T upper triangular, T_mm = beta_m, T_{0..m-1, m} = -beta_m T (V'v_m).
+    // Wavefront w keeps the row tiles w and 7 - w (16 rows each) of the vectors; as the first rows of a block's
+    // reflectors are zero, tile t meets the blocks b <= t only.  Per (tile, block): V' as the A operand of V'X (4
+    // registers) and -(V T)' likewise for X - (V T)(V'X); both wait in global memory, as the lanes hold them, until step 5
+    // (kept in registers meanwhile they slow steps 2-4 down: 40 k cycles more in the search).  v_mfma_f64_16x16x4_f64: A lane (i = lane & 15, k = lane >> 4), B lane (j = lane & 15, k = lane >> 4), result
+    // lane (j = lane & 15), register q: row (lane >> 4) + 4 q, i.e. a result is the B operand of the next product as it is.
+    // The blocks 0 .. 4, whose reflectors are there by then, are the work of wavefronts 1 .. 3 beside the last steps; of the
+    // others a wavefront takes one each behind them (6 pairs of 36).  A block's T and pairs stay with one wavefront, so that no
+    // barrier stands between.  All behind the steps, 15 k cycles, against 7 k: build of the subspace, us, one head 119.9 | 116.6,
+    // 32 heads 132.8 | 129.3, 256 heads 147.4 | 145.3.
+    const int mi = lane & 15, mk = lane >> 4;
+    // [wavefront][9 (tile, block) pairs: tile 7 - wave with blocks 0 .. 7 - wave, tile `wave` with blocks 0 .. wave]
+    // [registers 0 1, 2 3 of V', of -(V T)'][64][2]
+    double2* const vmine = reinterpret_cast<double2*>(vws + wave * kTriWsPerWave);
+    auto block_operands = [&](const int bA, const int bB) __attribute__((always_inline)) {      // of one or two blocks; uniform
+        const double* V = L + kTriX;
+        double* TS = L + kTriS;
+        for (int b = bA;; b = bB) {                           // V'V
+            const bool real = 16 * b + mi < kTriN - 2;        // reflectors 126 and 127 do not exist
+            const double* v = V + (real ? 16 * b + mi : 0) * kTriVLd;
+            double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+            for (int m = 4 * b; m < kTriN / 4; ++m) {
+                double x = v[4 * m + mk];
+                x = real ? x : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) TS[(16 * b + mk + 4 * q) * kTriTLd + mi] = acc[q];
+            if (b == bB) break;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // T, a row per lane (lanes 0 .. 15: block bA, 16 .. 31: block bB)
+        {
+            const int b = (lane & 16) ? bB : bA;
+            double* S = TS + 16 * b * kTriTLd;
+            double t[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                double sum = 0.0;
+#pragma unroll
+                for (int q = 0; q < m; ++q) sum = fma(t[q], S[q * kTriTLd + m], sum);
+                const double bt = L[kTriBet + 16 * b + m];
+                t[m] = m == mi ? bt : (m > mi ? -bt * sum : 0.0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (lane < 32) {
+#pragma unroll
+                for (int m = 0; m < 16; ++m) S[mi * kTriTLd + m] = t[m];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int b = bA;; b = bB) {
+            const bool real = 16 * b + mi < kTriN - 2;
+            const double* vk = V + (real ? 16 * b + mi : 0) * kTriVLd;
+#pragma unroll 3
+            for (int tile = b; tile < 8; ++tile) {
+                const int owner = tile < 4 ? tile : 7 - tile;
+                double2* const dst = reinterpret_cast<double2*>(vws + owner * kTriWsPerWave) + (tile < 4 ? 8 - tile + b : b) * (4 * 64);
+                double4v acc = {0.0, 0.0, 0.0, 0.0};
+                double x[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[q] = vk[16 * tile + 4 * q + mk];
+                    x[q] = real ? x[q] : 0.0;
+                    const bool kreal = 16 * b + 4 * q + mk < kTriN - 2;
+                    double y = V[(kreal ? 16 * b + 4 * q + mk : 0) * kTriVLd + 16 * tile + mi];
+                    y = kreal ? y : 0.0;
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(TS[(16 * b + 4 * q + mk) * kTriTLd + mi], y, acc, 0, 0, 0);
+                }
+                dst[lane] = double2{x[0], x[1]};
+                dst[64 + lane] = double2{x[2], x[3]};
+                dst[128 + lane] = double2{-acc[0], -acc[1]};
+                dst[192 + lane] = double2{-acc[2], -acc[3]};
+            }
+            if (b == bB) break;
+        }
+    };
+
     // the last 32 rows to wavefront 0; meanwhile the others clear what its reflectors have above
     {
         double* const W = L + kTriTailW;
@@ -543,13 +629,26 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             for (int j = 0; j < 16; ++j) W[row * kTriTailLd + 2 * j + (lane >> 5)] = a[kTriTail / 2 + j];
             X[row] = xr;                                  // (both halves have it)
         }
+        // T and the reflectors' beta, of the rows before those
+        if (id.row == 0) {
+            if (lane == 0) L[kTriDd] = d0;
+        } else if (id.row < kTriTail) {
+            L[kTriDd + id.row] = T[0];
+            L[kTriEe + id.row - 1] = -T[1];
+            L[kTriBet + id.row - 1] = T[2];
+        }
         __syncthreads();
+        const int rho = 2 * (lane & 15) + (lane >> 4 & 1);
+        double t[16], x = 0.0, y = 0.0;
         if (wave == 0) {
-            const int rho = 2 * (lane & 15) + (lane >> 4 & 1);
-            double t[16], T2[3] = {0.0, 0.0, 0.0};
 #pragma unroll
             for (int j = 0; j < 16; ++j) t[j] = W[rho * kTriTailLd + 2 * j + (lane >> 5)];
-            double x = X[rho], y = X[id.col];
+            x = X[rho];
+            y = X[id.col];
+        }
+        __syncthreads();                                  // (the blocks' T factors go where W was)
+        if (wave == 0) {
+            double T2[3] = {0.0, 0.0, 0.0};
             tri_tail_steps<0>(t, x, y, lane, rho, T2, L);
             tri_tail_steps<1>(t, x, y, lane, rho, T2, L);
             tri_tail_steps<2>(t, x, y, lane, rho, T2, L);
@@ -573,105 +672,11 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
                 const int k = e / (kTriTail / 2), m = e % (kTriTail / 2);
                 *reinterpret_cast<double2*>(L + kTriX + (kTriTail - 1 + k) * kTriVLd + 2 * m) = double2{0.0, 0.0};
             }
+            block_operands(wave - 1, wave == 1 ? 0 : 6 - wave);      // 0; 1, 4; 2, 3
         }
-    }
-    if (id.row == 0) {
-        if (lane == 0) L[kTriDd] = d0;
-    } else if (id.row < kTriTail) {
-        L[kTriDd + id.row] = T[0];
-        L[kTriEe + id.row - 1] = -T[1];
-        L[kTriBet + id.row - 1] = T[2];
     }
     __syncthreads();
-    // ---- operands of the back-transformation, while the reflectors are in LDS.  The reflectors are taken in blocks of 16,
-    // H_{16 b} ... H_{16 b + 15} = I - V T V' with T upper triangular, T_mm = beta_m, T_{0..m-1, m} = -beta_m T (V'v_m).
-    // Wavefront w keeps the row tiles w and 7 - w (16 rows each) of the vectors; as the first rows of a block's
-    // reflectors are zero, tile t meets the blocks b <= t only.  Per (tile, block): V' as the A operand of V'X (4
-    // registers) and -(V T)' likewise for X - (V T)(V'X); both wait in global memory, as the lanes hold them, until step 5
-    // (kept in registers meanwhile they slow steps 2-4 down: 40 k cycles more in the search).  v_mfma_f64_16x16x4_f64: A lane (i = lane & 15, k = lane >> 4), B lane (j = lane & 15, k = lane >> 4), result
-    // lane (j = lane & 15), register q: row (lane >> 4) + 4 q, i.e. a result is the B operand of the next product as it is.
-    const int mi = lane & 15, mk = lane >> 4;
-    // [wavefront][9 (tile, block) pairs: tile 7 - wave with blocks 0 .. 7 - wave, tile `wave` with blocks 0 .. wave]
-    // [registers 0 1, 2 3 of V', of -(V T)'][64][2]
-    double2* const vmine = reinterpret_cast<double2*>(vws + wave * kTriWsPerWave);
-    {
-        const double* V = L + kTriX;
-        double* TS = L + kTriS;
-        // V'V of the blocks `wave` and 7 - wave, side by side (the second one's reflectors start further down)
-        {
-            const int b1 = wave, b2 = 7 - wave;
-            const bool real = 16 * b2 + mi < kTriN - 2;       // reflectors 126 and 127 do not exist
-            const double* v1 = V + (16 * b1 + mi) * kTriVLd;
-            const double* v2 = V + (real ? 16 * b2 + mi : 0) * kTriVLd;
-            double4v acc1 = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-            for (int m = 4 * b1; m < 4 * b2; ++m) {
-                const double x = v1[4 * m + mk];
-                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc1, 0, 0, 0);
-            }
-#pragma unroll 4
-            for (int m = 4 * b2; m < kTriN / 4; ++m) {
-                const double x = v1[4 * m + mk];
-                double y = v2[4 * m + mk];
-                y = real ? y : 0.0;
-                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc1, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(y, y, acc2, 0, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                TS[(16 * b1 + mk + 4 * q) * kTriTLd + mi] = acc1[q];
-                TS[(16 * b2 + mk + 4 * q) * kTriTLd + mi] = acc2[q];
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // T, a row per lane (lanes 0 .. 15: block `wave`, 16 .. 31: block 7 - wave)
-        {
-            const int b = (lane & 16) ? 7 - wave : wave;
-            double* S = TS + 16 * b * kTriTLd;
-            double t[16];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                double sum = 0.0;
-#pragma unroll
-                for (int q = 0; q < m; ++q) sum = fma(t[q], S[q * kTriTLd + m], sum);
-                const double bt = L[kTriBet + 16 * b + m];
-                t[m] = m == mi ? bt : (m > mi ? -bt * sum : 0.0);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (lane < 32) {
-#pragma unroll
-                for (int m = 0; m < 16; ++m) S[mi * kTriTLd + m] = t[m];
-            }
-        }
-        __syncthreads();
-        auto operands = [&](const int tile, const int b, double2* dst) __attribute__((always_inline)) {
-            const bool real = 16 * b + mi < kTriN - 2;
-            const double* vk = V + (real ? 16 * b + mi : 0) * kTriVLd;
-            double4v acc = {0.0, 0.0, 0.0, 0.0};
-            double x[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                x[q] = vk[16 * tile + 4 * q + mk];
-                x[q] = real ? x[q] : 0.0;
-                const bool kreal = 16 * b + 4 * q + mk < kTriN - 2;
-                double y = V[(kreal ? 16 * b + 4 * q + mk : 0) * kTriVLd + 16 * tile + mi];
-                y = kreal ? y : 0.0;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(TS[(16 * b + 4 * q + mk) * kTriTLd + mi], y, acc, 0, 0, 0);
-            }
-            dst[lane] = double2{x[0], x[1]};
-            dst[64 + lane] = double2{x[2], x[3]};
-            dst[128 + lane] = double2{-acc[0], -acc[1]};
-            dst[192 + lane] = double2{-acc[2], -acc[3]};
-        };
-#pragma unroll 3
-        for (int e = 0; e < 9; ++e) {                         // uniform
-            const bool second = e > 7 - wave;
-            operands(second ? wave : 7 - wave, second ? e - (8 - wave) : e, vmine + e * (4 * 64));
-        }
-    }
+    if (wave < 3) block_operands(5 + wave, 5 + wave);
     __syncthreads();
 
     // ---- normalise T to max |entry| = 1
