@@ -245,12 +245,12 @@ PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// q, codes, scale, zero, bits, group, q_per_kv, inv_freq (None: keys as they are), pos0, out_scale, out, stream
-template <bool PC>
+// q, codes, scale, zero, bits, group, q_per_kv, inv_freq, pos0, out_scale, out, stream; without rope inv_freq and pos0 are not looked
+// at.  (Two functions and not one that goes by inv_freq: a caller who lacks the frequencies gets an error, no unrotated logits.)
+template <bool PC, bool rope>
 PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded(n, 12, [&]() -> PyObject* {
         const at::Tensor &q = tensor(a[0]), &codes = tensor(a[1]), &scale = tensor(a[2]), &zero = tensor(a[3]);
-        const bool rope = a[7] != Py_None;
         const int bits = small(a[4]), group = small(a[5]), qpk = small(a[6]);
         if (!PC && !rope) {
             need_device(q);
@@ -265,7 +265,7 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (PC && (codes.size(4) != bits || scale.sizes() != at::IntArrayRef({b, h, codes.size(2), d}) || zero.sizes() != scale.sizes()))
             raise(PyExc_ValueError, "codes [B,H,n/32,d,bits], scale/zero [B,H,n/32,d] expected");
         const float* freq = nullptr;
-        if (rope) {
+        if constexpr (rope) {
             const at::Tensor& f = tensor(a[7]);
             if (f.scalar_type() != at::kFloat || f.numel() != 64 || !f.is_contiguous())
                 raise(PyExc_ValueError, "inv_freq must be 64 dense float32 values");
@@ -282,7 +282,7 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (out.scalar_type() != at::kFloat || out.stride(2) != 1 || out.size(0) != b || out.size(1) != h * qpk)
             raise(PyExc_ValueError, "out must be float32 [B, n_q_heads, >= n] with unit token stride");
         const squat_dtype dt = dtype(a[0], q);
-        const long long pos0 = integer(a[8]);
+        const long long pos0 = rope ? integer(a[8]) : 0;
         const float out_scale = number(a[9]);
         const squat_stream s = stream(a[11]);
         const auto* cp = pointer<const uint32_t>(codes);
@@ -292,7 +292,7 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         float* op = pointer<float>(out);
         const int64_t q0 = q.stride(0), q1 = q.stride(1), o0 = out.stride(0), o1 = out.stride(1);
         const int hi = static_cast<int>(h), di = static_cast<int>(d);
-        if (rope)
+        if constexpr (rope)
             call(PC ? "squat_key_scores_rope_per_channel" : "squat_key_scores_rope", [&] {
                 return (PC ? squat_key_scores_rope_per_channel : squat_key_scores_rope)(cp, sp, zp, b, hi, tokens, di, bits, group, freq, pos0,
                                                                                        qp, dt, qpk, q0, q1, out_scale, op, o0, o1, s);
@@ -333,15 +333,15 @@ PyObject* cache_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// handle, q, inv_freq (None: keys as they are), pos0, out_scale, out, stream
+// handle, q, inv_freq, pos0, out_scale, out, stream; without rope inv_freq and pos0 are not looked at
+template <bool rope>
 PyObject* cache_key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded(n, 7, [&]() -> PyObject* {
-        squat_cache* c = cache(a[0]);
         const at::Tensor& q = tensor(a[1]);
         need_device(q);
-        const bool rope = a[2] != Py_None;
+        squat_cache* c = cache(a[0]);
         const float* freq = nullptr;
-        if (rope) {
+        if constexpr (rope) {
             const at::Tensor& f = tensor(a[2]);
             need_device(f);
             if (f.scalar_type() != at::kFloat || !f.is_contiguous()) raise(PyExc_ValueError, "inv_freq must be dense float32");
@@ -357,13 +357,13 @@ PyObject* cache_key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
             out = tensor(a[5]);
         }
         const squat_dtype dt = dtype(a[1], q);
-        const long long pos0 = integer(a[3]);
+        const long long pos0 = rope ? integer(a[3]) : 0;
         const float out_scale = number(a[4]);
         const squat_stream s = stream(a[6]);
         const void* qp = pointer<void>(q);
         float* op = pointer<float>(out);
         const int64_t q0 = q.stride(0), q1 = q.stride(1), o0 = out.stride(0), o1 = out.stride(1);
-        if (rope)
+        if constexpr (rope)
             call("squat_cache_key_scores_rope", [&] { return squat_cache_key_scores_rope(c, qp, dt, q0, q1, freq, pos0, out_scale, op, o0, o1, s); });
         else
             call("squat_cache_key_scores", [&] { return squat_cache_key_scores(c, qp, dt, q0, q1, out_scale, op, o0, o1, s); });
@@ -383,10 +383,13 @@ PyMethodDef methods[] = {
     SQUAT_FAST("quantize_keys_per_channel", quantize<true>),
     SQUAT_FAST("dequantize_keys", dequantize<false>),
     SQUAT_FAST("dequantize_keys_per_channel", dequantize<true>),
-    SQUAT_FAST("key_scores", key_scores<false>),
-    SQUAT_FAST("key_scores_per_channel", key_scores<true>),
+    SQUAT_FAST("key_scores", (key_scores<false, false>)),
+    SQUAT_FAST("key_scores_per_channel", (key_scores<true, false>)),
+    SQUAT_FAST("key_scores_rope", (key_scores<false, true>)),
+    SQUAT_FAST("key_scores_rope_per_channel", (key_scores<true, true>)),
     SQUAT_FAST("cache_append", cache_append),
-    SQUAT_FAST("cache_key_scores", cache_key_scores),
+    SQUAT_FAST("cache_key_scores", cache_key_scores<false>),
+    SQUAT_FAST("cache_key_scores_rope", cache_key_scores<true>),
     {"set_error", set_error, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 

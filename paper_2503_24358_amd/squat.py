@@ -365,8 +365,8 @@ def key_scores_rope(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, z
                     stream=None) -> torch.Tensor:
     """squat_key_scores_rope: logits against keys stored before the rotary embedding.  Arguments as for
     key_scores plus inv_freq (float32 [64], device) and the position of token 0."""
-    return (_native or native()).key_scores(q, codes, scale, zero, bits, group, q_per_kv, inv_freq, int(pos0), out_scale,
-                                            out, None if stream is None else _stream(stream))
+    return (_native or native()).key_scores_rope(q, codes, scale, zero, bits, group, q_per_kv, inv_freq, int(pos0), out_scale,
+                                                 out, None if stream is None else _stream(stream))
 
 
 def key_scores_rope_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor,
@@ -375,8 +375,8 @@ def key_scores_rope_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: tor
     """squat_key_scores_rope_per_channel: logits against keys stored before the rotary embedding in the
     per-channel layout (codes [B, H, n/32, d, bits] int32, scale/zero [B, H, n/32, d] float16).  inv_freq:
     float32 [64] on the device; pos0: position of token 0."""
-    return (_native or native()).key_scores_per_channel(q, codes, scale, zero, bits, 32, q_per_kv, inv_freq, int(pos0),
-                                                        out_scale, out, None if stream is None else _stream(stream))
+    return (_native or native()).key_scores_rope_per_channel(q, codes, scale, zero, bits, 32, q_per_kv, inv_freq, int(pos0),
+                                                             out_scale, out, None if stream is None else _stream(stream))
 
 
 def key_scores_per_channel(q: torch.Tensor, codes: torch.Tensor, scale: torch.Tensor, zero: torch.Tensor, bits: int,
@@ -483,5 +483,5 @@ class Cache:
                         stream=None) -> torch.Tensor:
         """Logits against a cache of pre-RoPE keys: cache token t is rotated to position pos0 + t first.
         inv_freq: [d/2] float32 on the device."""
-        return (_native or native()).cache_key_scores(self._h.value, q, inv_freq, int(pos0), out_scale, out,
-                                                      None if stream is None else _stream(stream))
+        return (_native or native()).cache_key_scores_rope(self._h.value, q, inv_freq, int(pos0), out_scale, out,
+                                                           None if stream is None else _stream(stream))

@@ -25,6 +25,37 @@ def test_refuses_without_a_device():
         squat.native().dequantize_keys(codes, meta, meta, 2, 32, torch.float32, None)
 
 
+def _stores(device="cpu"):
+    """(q, per-token store, per-channel store) of one sequence, two heads, 32 tokens."""
+    q = torch.zeros(1, 2, 128, device=device)
+    per_token = (torch.zeros(1, 2, 32, 8, dtype=torch.int32, device=device),
+                 *(torch.zeros(1, 2, 32, 4, dtype=torch.float16, device=device) for _ in range(2)))
+    per_channel = (torch.zeros(1, 2, 1, 128, 2, dtype=torch.int32, device=device),
+                   *(torch.zeros(1, 2, 1, 128, dtype=torch.float16, device=device) for _ in range(2)))
+    return q, per_token, per_channel
+
+
+def test_rotary_logits_need_their_frequencies():
+    q, per_token, per_channel = _stores()
+    with pytest.raises(AttributeError):
+        squat.key_scores_rope(q, *per_token, 2, 32, 1, None)
+    with pytest.raises(AttributeError):
+        squat.key_scores_rope_per_channel(q, *per_channel, 2, 1, None)
+
+
+@pytest.mark.gpu
+def test_rotary_logits_need_their_frequencies_on_the_device():
+    q, per_token, per_channel = _stores("cuda")
+    with pytest.raises(AttributeError):
+        squat.key_scores_rope(q, *per_token, 2, 32, 1, None)
+    with pytest.raises(AttributeError):
+        squat.key_scores_rope_per_channel(q, *per_channel, 2, 1, None)
+    cache = squat.Cache(1, 2, 1, 2, 32, 32, 32, 64, torch.float32)
+    cache.append(q)
+    with pytest.raises(AttributeError):
+        cache.key_scores_rope(q, None)
+
+
 @pytest.mark.gpu
 def test_refusals_on_the_device():
     k = torch.randn(1, 2, 32, 128, device="cuda")
