@@ -89,6 +89,11 @@ void need_device(const at::Tensor& t) {
     if (!t.is_cuda()) raise(PyExc_ValueError, "libsquat takes device tensors only");
 }
 
+// Device memory, or pinned host memory, which kernels reach as well (where calls have taken that before).
+void need_reachable(const at::Tensor& t) {
+    if (!t.is_cuda() && !t.is_pinned()) raise(PyExc_ValueError, "libsquat takes device tensors only (here: or pinned host memory)");
+}
+
 template <typename T>
 T* pointer(const at::Tensor& t) {
     return static_cast<T*>(t.data_ptr());
@@ -105,7 +110,12 @@ at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& l
 }
 
 at::Tensor given_or_empty(PyObject* o, at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
-    return o == Py_None ? empty(shape, type, like) : tensor(o);
+    if (o == Py_None) {
+        need_device(like);
+        return empty(shape, type, like);
+    }
+    need_reachable(tensor(o));
+    return tensor(o);
 }
 
 PyObject* three(const at::Tensor& a, const at::Tensor& b, const at::Tensor& c) {
@@ -222,6 +232,7 @@ PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
             out = empty({b, h, tokens, d}, reinterpret_cast<THPDtype*>(a[5])->scalar_type, codes);
         } else {
             out = tensor(a[6]);
+            need_reachable(out);
         }
         PyObject* wrapped = a[6] == Py_None ? THPVariable_Wrap(out) : Py_NewRef(a[6]);
         if (!wrapped) throw Raised{};
@@ -252,12 +263,11 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded(n, 12, [&]() -> PyObject* {
         const at::Tensor &q = tensor(a[0]), &codes = tensor(a[1]), &scale = tensor(a[2]), &zero = tensor(a[3]);
         const int bits = small(a[4]), group = small(a[5]), qpk = small(a[6]);
-        if (!PC && !rope) {
-            need_device(q);
-            need_device(codes);
-            need_device(scale);
-            need_device(zero);
-        }
+        if constexpr (rope) need_device(tensor(a[7]));
+        (PC && !rope ? need_reachable : need_device)(q);
+        (PC && !rope ? need_reachable : need_device)(codes);
+        (PC || rope ? need_reachable : need_device)(scale);
+        (PC || rope ? need_reachable : need_device)(zero);
         need_dims(codes, PC ? 5 : 4);
         const int64_t b = codes.size(0), h = codes.size(1);
         const int64_t tokens = PC ? codes.size(2) * 32 : codes.size(2);
@@ -269,9 +279,6 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
             const at::Tensor& f = tensor(a[7]);
             if (f.scalar_type() != at::kFloat || f.numel() != 64 || !f.is_contiguous())
                 raise(PyExc_ValueError, "inv_freq must be 64 dense float32 values");
-            need_device(q);
-            need_device(codes);
-            need_device(f);
             freq = pointer<const float>(f);
         }
         if (q.dim() != 3 || q.size(0) != b || q.size(1) != h * qpk || q.size(2) != d || q.stride(2) != 1)
@@ -355,6 +362,7 @@ PyObject* cache_key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
             out = empty({q.size(0), q.size(1), counts.keys_quantized + counts.keys_residual}, at::kFloat, q);
         } else {
             out = tensor(a[5]);
+            need_reachable(out);
         }
         const squat_dtype dt = dtype(a[1], q);
         const long long pos0 = rope ? integer(a[3]) : 0;

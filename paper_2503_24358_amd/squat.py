@@ -189,6 +189,13 @@ def _need_cuda(*ts):
             raise ValueError("libsquat takes device tensors only")
 
 
+def _need_reachable(*ts):
+    """Device memory, or pinned host memory, which kernels reach as well: outputs and workspaces a caller brings along."""
+    for t in ts:
+        if t is not None and not t.is_cuda and not t.is_pinned():
+            raise ValueError("libsquat takes device tensors only (here: or pinned host memory)")
+
+
 def _ws(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
@@ -202,6 +209,7 @@ def build_subspace(q: torch.Tensor, q_per_kv: int, r: int, *, want_eig: bool = T
     """squat_build_subspace.  q: [n_kv_heads*q_per_kv, n_tokens, d] (last dim contiguous).
     Returns (qhat [n_kv, r, d] f32, eig [n_kv, r] f32 or None, gram [n_kv, d, d] f32 or None)."""
     _need_cuda(q)
+    _need_reachable(qhat, eig, gram, ws)
     hq, n, d = q.shape
     if q.stride(2) != 1 or hq % q_per_kv:
         raise ValueError("q must be [heads, tokens, d] with unit channel stride")
@@ -229,6 +237,7 @@ def refresh_subspace(gram_state: torch.Tensor, q_per_kv: int, r: int, iterations
     [n_kv_heads*q_per_kv, n_new, d] or None; qhat_prev: float32 [n_kv_heads, r_prev, d] or None (cold start).
     Returns (qhat [n_kv, r, d] f32, eig [n_kv, r] f32, residual [n_kv] f32)."""
     _need_cuda(gram_state, q_new, qhat_prev)
+    _need_reachable(qhat, eig, residual, ws)
     n_kv, d, _ = gram_state.shape
     if gram_state.dtype != torch.float64 or not gram_state.is_contiguous():
         raise ValueError("gram_state must be dense float64 [n_kv_heads, d, d]")
@@ -273,6 +282,7 @@ def prepare(qhat: torch.Tensor, lam: float, g: int, *, update=None, ws=None, str
     """squat_prepare (squat_prepare_ex with SQUAT_PREPARE_FULL_PRECISION when full_precision is set).
     qhat: [n_heads, r, d] f32 dense -> update [n_heads, d, d] f32."""
     _need_cuda(qhat)
+    _need_reachable(update, ws)
     if qhat.dtype != torch.float32 or not qhat.is_contiguous():
         raise ValueError("qhat must be dense float32")
     h, r, d = qhat.shape
@@ -405,6 +415,7 @@ class Cache:
         self.arena = torch.empty(nbytes, dtype=torch.uint8, device=device)
         if update is not None and (update.dtype != torch.float32 or not update.is_contiguous()):
             raise ValueError("update must be dense float32")
+        _need_reachable(self.arena, update)
         self.update = update
         handle = ctypes.c_void_p()
         rc = lib().squat_cache_create(ctypes.byref(self.cfg), _ptr(self.arena), nbytes, _ptr(update), ctypes.byref(handle))

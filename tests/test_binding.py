@@ -35,6 +35,72 @@ def _stores(device="cpu"):
     return q, per_token, per_channel
 
 
+def test_logits_refuse_host_stores():
+    """(The store a call reads; a host `out` beside device inputs is refused on the device, below.)"""
+    q, per_token, per_channel = _stores()
+    inv = torch.ones(64)
+    with pytest.raises(ValueError):
+        squat.key_scores_per_channel(q, *per_channel, 2, 1)
+    with pytest.raises(ValueError):
+        squat.key_scores_rope(q, *per_token, 2, 32, 1, inv)
+    with pytest.raises(ValueError):
+        squat.key_scores_rope_per_channel(q, *per_channel, 2, 1, inv)
+
+
+def _host_or_pinned(t, pinned):
+    return torch.empty(t.shape, dtype=t.dtype, pin_memory=pinned)
+
+
+@pytest.mark.gpu
+def test_host_memory_is_refused_pinned_memory_taken():
+    """No launch sees a host pointer it cannot reach: every output, workspace and part of a store that used to go unchecked."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    k = torch.randn(1, 2, 32, 128, generator=g, device="cuda")
+    q = torch.randn(1, 2, 128, generator=g, device="cuda")
+    inv = torch.ones(64, device="cuda")
+    per_token, per_channel = squat.quantize_keys(k, None, 2, 32, 32), squat.quantize_keys_per_channel(k, None, 2, 32, 32)
+    cache = squat.Cache(1, 2, 1, 2, 32, 32, 32, 64, torch.float32)
+    cache.append(q)
+    qhat = torch.randn(2, 4, 128, generator=g, device="cuda")
+    names = ("codes", "scale", "zero")
+    calls = [(lambda i=i, f=f, **kw: f(k, None, 2, 32, 32, **kw)[i], n) for f in (squat.quantize_keys, squat.quantize_keys_per_channel)
+             for i, n in enumerate(names)]
+    calls += [(lambda **kw: squat.dequantize_keys(*per_token, 2, 32, torch.float32, **kw), "out"),
+              (lambda **kw: squat.dequantize_keys_per_channel(*per_channel, 2, 32, torch.float32, **kw), "out"),
+              (lambda **kw: squat.key_scores(q, *per_token, 2, 32, 1, **kw), "out"),
+              (lambda **kw: squat.key_scores_rope(q, *per_token, 2, 32, 1, inv, **kw), "out"),
+              (lambda **kw: squat.key_scores_per_channel(q, *per_channel, 2, 1, **kw), "out"),
+              (lambda **kw: squat.key_scores_rope_per_channel(q, *per_channel, 2, 1, inv, **kw), "out"),
+              (lambda **kw: cache.key_scores(q, **kw), "out"),
+              (lambda **kw: cache.key_scores_rope(q, inv, **kw), "out"),
+              (lambda **kw: squat.build_subspace(q.view(2, 1, 128), 1, 1, **kw)[0], "qhat"),
+              (lambda **kw: squat.prepare(qhat, 1e-3, 32, **kw), "update")]
+    for call, name in calls:
+        want = call()
+        with pytest.raises(ValueError):
+            call(**{name: _host_or_pinned(want, False)})
+        got = call(**{name: _host_or_pinned(want, True)})
+        torch.cuda.synchronize()
+        assert not got.is_cuda and torch.equal(got, want.cpu())
+    for i in range(3):
+        for logits, store in ((lambda *s: squat.key_scores_rope(q, *s, 2, 32, 1, inv), per_token),
+                              (lambda *s: squat.key_scores_per_channel(q, *s, 2, 1), per_channel),
+                              (lambda *s: squat.key_scores_rope_per_channel(q, *s, 2, 1, inv), per_channel)):
+            with pytest.raises(ValueError):
+                logits(*[t.cpu() if j == i else t for j, t in enumerate(store)])
+    with pytest.raises(ValueError):
+        squat.key_scores_per_channel(q.cpu(), *per_channel, 2, 1)
+    want, pinned = squat.key_scores_per_channel(q, *per_channel, 2, 1), [t.cpu().pin_memory() for t in per_channel]
+    with pytest.raises(ValueError):                    # (where would the logits lie?)
+        squat.key_scores_per_channel(q, *pinned, 2, 1)
+    assert torch.equal(squat.key_scores_per_channel(q, *pinned, 2, 1, out=torch.empty_like(want)), want)
+    with pytest.raises(ValueError):
+        squat.prepare(qhat, 1e-3, 32, ws=torch.empty(1 << 20, dtype=torch.uint8))
+    with pytest.raises(ValueError):
+        squat.Cache(1, 2, 1, 2, 32, 32, 32, 64, torch.float32, update=torch.zeros(2, 128, 128))
+
+
 def test_rotary_logits_need_their_frequencies():
     q, per_token, per_channel = _stores()
     with pytest.raises(AttributeError):
