@@ -43,9 +43,17 @@ const at::Tensor& tensor(PyObject* o) {
     return THPVariable_Unpack(o);
 }
 
+// An int, or what stands for one (numpy's, a tensor of one: __index__), as ctypes takes it in the calls that go through it.
 long long integer(PyObject* o) {
-    if (!PyLong_Check(o)) raise(PyExc_TypeError, "an int is needed");
-    const long long v = PyLong_AsLongLong(o);
+    long long v;
+    if (PyLong_Check(o)) {
+        v = PyLong_AsLongLong(o);
+    } else {
+        PyObject* i = PyNumber_Index(o);
+        if (!i) throw Raised{};
+        v = PyLong_AsLongLong(i);
+        Py_DECREF(i);
+    }
     if (v == -1 && PyErr_Occurred()) throw Raised{};
     return v;
 }

@@ -1,5 +1,6 @@
 """The native part of the Python binding: what it refuses and with which exception, and that results land where the caller
 says (given outputs, a stream's handle or object)."""
+import numpy as np
 import pytest
 import torch
 
@@ -107,6 +108,43 @@ def test_rotary_logits_need_their_frequencies():
         squat.key_scores_rope(q, *per_token, 2, 32, 1, None)
     with pytest.raises(AttributeError):
         squat.key_scores_rope_per_channel(q, *per_channel, 2, 1, None)
+
+
+INTS = (np.int64, np.int32, np.uint8, torch.tensor)
+
+
+@pytest.mark.parametrize("kind", INTS)
+def test_what_stands_for_an_int_is_taken(kind):
+    """(Taken: the next check, for a device tensor, is the one that refuses.)"""
+    q, per_token, per_channel = _stores()
+    bits, group, qpk = kind(2), kind(32), kind(1)
+    inv = torch.ones(64)
+    for call in (lambda b: squat.key_scores(q, *per_token, b, group, qpk), lambda b: squat.key_scores_per_channel(q, *per_channel, b, qpk),
+                 lambda b: squat.key_scores_rope(q, *per_token, b, group, qpk, inv),
+                 lambda b: squat.key_scores_rope_per_channel(q, *per_channel, b, qpk, inv)):
+        with pytest.raises(ValueError):
+            call(bits)
+        with pytest.raises(TypeError):
+            call(2.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", INTS)
+def test_what_stands_for_an_int_gives_the_same(kind):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    k = torch.randn(1, 2, 32, 128, generator=g, device="cuda")
+    q = torch.randn(1, 2, 128, generator=g, device="cuda")
+    inv = torch.rand(64, generator=g, device="cuda")
+
+    def every_call(n):
+        a = squat.quantize_keys(k, None, n(2), n(32), n(32))
+        b = squat.quantize_keys_per_channel(k, None, n(2), n(32), n(32))
+        return (*a, *b, squat.dequantize_keys(*a, n(2), n(32)), squat.dequantize_keys_per_channel(*b, n(2), n(32)),
+                squat.key_scores(q, *a, n(2), n(32), n(1)), squat.key_scores_per_channel(q, *b, n(2), n(1)),
+                squat.key_scores_rope(q, *a, n(2), n(32), n(1), inv, n(3)),
+                squat.key_scores_rope_per_channel(q, *b, n(2), n(1), inv, n(3)))
+    assert all(torch.equal(x, y) for x, y in zip(every_call(kind), every_call(int)))
 
 
 @pytest.mark.gpu
