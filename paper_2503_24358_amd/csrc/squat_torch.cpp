@@ -219,7 +219,7 @@ int64_t channels(int64_t words, int bits) {
     return words * 32 / bits;
 }
 
-// codes, scale, zero, bits, group, out_dtype (a tensor's, or None with out), out, stream
+// codes, scale, zero, bits, group, out_dtype (of an output made here; None: torch's default), out, stream
 template <bool PC>
 PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded(n, 8, [&]() -> PyObject* {
@@ -236,8 +236,9 @@ PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         need_dense_store(codes, scale, zero);
         at::Tensor out;
         if (a[6] == Py_None) {
-            if (!THPDtype_Check(a[5])) raise(PyExc_TypeError, "out_dtype must be a torch.dtype");
-            out = empty({b, h, tokens, d}, reinterpret_cast<THPDtype*>(a[5])->scalar_type, codes);
+            if (a[5] != Py_None && !THPDtype_Check(a[5])) raise(PyExc_TypeError, "out_dtype must be a torch.dtype");
+            const at::ScalarType type = a[5] == Py_None ? at::get_default_dtype_as_scalartype() : reinterpret_cast<THPDtype*>(a[5])->scalar_type;
+            out = empty({b, h, tokens, d}, type, codes);
         } else {
             out = tensor(a[6]);
             need_reachable(out);

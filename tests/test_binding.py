@@ -190,6 +190,18 @@ def test_refusals_on_the_device():
 
 
 @pytest.mark.gpu
+def test_output_type_left_to_torch():
+    k = torch.randn(1, 2, 32, 128, device="cuda")
+    per_token, per_channel = squat.quantize_keys(k, None, 2, 32, 32), squat.quantize_keys_per_channel(k, None, 2, 32, 32)
+    for call in (lambda t: squat.dequantize_keys(*per_token, 2, 32, t), lambda t: squat.dequantize_keys_per_channel(*per_channel, 2, 32, t)):
+        assert torch.equal(call(None), call(torch.float32))
+        with pytest.raises(TypeError):
+            call("float32")
+        with pytest.raises(KeyError):
+            call(torch.float64)
+
+
+@pytest.mark.gpu
 def test_results_land_where_they_are_asked_for():
     k = torch.randn(2, 3, 40, 128, device="cuda", dtype=torch.float16)
     q = torch.randn(2, 6, 128, device="cuda", dtype=torch.bfloat16)
