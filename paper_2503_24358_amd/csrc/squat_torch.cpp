@@ -294,7 +294,6 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
             raise(PyExc_ValueError, "q must be [B, n_kv_heads*q_per_kv, d] with unit channel stride");
         need_dense_store(codes, scale, zero);
         const at::Tensor out = given_or_empty(a[10], {b, h * qpk, tokens}, at::kFloat, codes);
-        need_dims(out, 3);
         if (out.scalar_type() != at::kFloat || out.stride(2) != 1 || out.size(0) != b || out.size(1) != h * qpk)
             raise(PyExc_ValueError, "out must be float32 [B, n_q_heads, >= n] with unit token stride");
         const squat_dtype dt = dtype(a[0], q);

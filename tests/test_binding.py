@@ -202,6 +202,22 @@ def test_output_type_left_to_torch():
 
 
 @pytest.mark.gpu
+def test_logits_into_more_dimensions():
+    """The first three count: rows of tokens with a dimension of one behind them are a place like any other."""
+    k = torch.randn(2, 2, 32, 128, device="cuda")
+    q = torch.randn(2, 2, 128, device="cuda")
+    inv = torch.ones(64, device="cuda")
+    per_token, per_channel = squat.quantize_keys(k, None, 2, 32, 32), squat.quantize_keys_per_channel(k, None, 2, 32, 32)
+    for call in (lambda **kw: squat.key_scores(q, *per_token, 2, 32, 1, **kw), lambda **kw: squat.key_scores_per_channel(q, *per_channel, 2, 1, **kw),
+                 lambda **kw: squat.key_scores_rope(q, *per_token, 2, 32, 1, inv, **kw),
+                 lambda **kw: squat.key_scores_rope_per_channel(q, *per_channel, 2, 1, inv, **kw)):
+        out = torch.empty(2, 2, 32, 1, device="cuda")
+        assert call(out=out) is out and torch.equal(out[..., 0], call())
+        with pytest.raises(IndexError):
+            call(out=torch.empty(4, 32, device="cuda"))
+
+
+@pytest.mark.gpu
 def test_results_land_where_they_are_asked_for():
     k = torch.randn(2, 3, 40, 128, device="cuda", dtype=torch.float16)
     q = torch.randn(2, 6, 128, device="cuda", dtype=torch.bfloat16)
