@@ -64,9 +64,12 @@ int small(PyObject* o) {
     return static_cast<int>(v);
 }
 
-float number(PyObject* o) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+float number(PyObject* o) {                // whatever float() takes
+    if (PyFloat_CheckExact(o)) return static_cast<float>(PyFloat_AS_DOUBLE(o));
+    PyObject* f = PyNumber_Float(o);
+    if (!f) throw Raised{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return static_cast<float>(v);
 }
 

@@ -218,6 +218,22 @@ def test_logits_into_more_dimensions():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("half", ["0.5", np.float32(0.5), torch.tensor(0.5), np.array(0.5)])
+def test_scale_is_what_float_takes(half):
+    k = torch.randn(2, 2, 32, 128, device="cuda")
+    q = torch.randn(2, 2, 128, device="cuda")
+    store = squat.quantize_keys(k, None, 2, 32, 32)
+    cache = squat.Cache(2, 2, 1, 2, 32, 32, 32, 64, torch.float32)
+    cache.append(k[:, :, 0])
+    for call in (lambda s: squat.key_scores(q, *store, 2, 32, 1, s), lambda s: cache.key_scores(q, s)):
+        assert torch.equal(call(half), call(0.5))
+        with pytest.raises(ValueError):
+            call("half")
+        with pytest.raises(TypeError):
+            call(None)
+
+
+@pytest.mark.gpu
 def test_results_land_where_they_are_asked_for():
     k = torch.randn(2, 3, 40, 128, device="cuda", dtype=torch.float16)
     q = torch.randn(2, 6, 128, device="cuda", dtype=torch.bfloat16)
