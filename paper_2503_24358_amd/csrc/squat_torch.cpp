@@ -190,13 +190,14 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (u.dim() == 4) usb = u.stride(0);
             update = pointer<const float>(u);
         }
-        if (group == 0) raise(PyExc_ZeroDivisionError, "integer division or modulo by zero");
+        if (group == 0 && (a[6] == Py_None || a[7] == Py_None)) raise(PyExc_ZeroDivisionError, "integer division or modulo by zero");
+        const int per = group == 0 ? 1 : group;          // (outputs given: the library refuses the group)
         const at::Tensor codes = PC ? given_or_empty(a[5], {b, h, tokens / 32, d, bits}, at::kInt, k)
                                     : given_or_empty(a[5], {b, h, tokens, d * bits / 32}, at::kInt, k);
-        const at::Tensor scale = PC ? given_or_empty(a[6], {b, h, tokens / group, d}, at::kHalf, k)
-                                    : given_or_empty(a[6], {b, h, tokens, d / group}, at::kHalf, k);
-        const at::Tensor zero = PC ? given_or_empty(a[7], {b, h, tokens / group, d}, at::kHalf, k)
-                                   : given_or_empty(a[7], {b, h, tokens, d / group}, at::kHalf, k);
+        const at::Tensor scale = PC ? given_or_empty(a[6], {b, h, tokens / per, d}, at::kHalf, k)
+                                    : given_or_empty(a[6], {b, h, tokens, d / per}, at::kHalf, k);
+        const at::Tensor zero = PC ? given_or_empty(a[7], {b, h, tokens / per, d}, at::kHalf, k)
+                                   : given_or_empty(a[7], {b, h, tokens, d / per}, at::kHalf, k);
         const squat_dtype dt = dtype(a[0], k);
         const squat_stream s = stream(a[8]);
         const void* kp = pointer<void>(k);

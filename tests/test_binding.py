@@ -234,6 +234,16 @@ def test_scale_is_what_float_takes(half):
 
 
 @pytest.mark.gpu
+def test_a_group_of_none():
+    k = torch.randn(1, 2, 32, 128, device="cuda")
+    codes, scale, zero = squat.quantize_keys(k, None, 2, 32, 32)
+    with pytest.raises(ZeroDivisionError):               # (no shape for the outputs)
+        squat.quantize_keys(k, None, 2, 0, 32)
+    with pytest.raises(squat.SquatError):                # the library's answer
+        squat.quantize_keys(k, None, 2, 0, 32, codes=codes, scale=scale, zero=zero)
+
+
+@pytest.mark.gpu
 def test_results_land_where_they_are_asked_for():
     k = torch.randn(2, 3, 40, 128, device="cuda", dtype=torch.float16)
     q = torch.randn(2, 6, 128, device="cuda", dtype=torch.bfloat16)
