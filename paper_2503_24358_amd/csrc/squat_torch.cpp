@@ -325,7 +325,8 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-squat_cache* cache(PyObject* o) {
+squat_cache* cache(PyObject* o) {            // None (a destroyed cache): the library refuses it
+    if (o == Py_None) return nullptr;
     void* p = PyLong_AsVoidPtr(o);
     if (!p && PyErr_Occurred()) throw Raised{};
     return static_cast<squat_cache*>(p);

@@ -483,16 +483,16 @@ class Cache:
 
     def append(self, k: torch.Tensor, v: Optional[torch.Tensor] = None, stream=None):
         """k, v: [B, H, d], one decoded token per sequence."""
-        (_native or native()).cache_append(self._h.value, k, v, None if stream is None else _stream(stream))
+        (_native or native()).cache_append(self._h and self._h.value, k, v, None if stream is None else _stream(stream))
 
     def key_scores(self, q: torch.Tensor, out_scale: float = 1.0, out=None, stream=None) -> torch.Tensor:
         """q: [B, H*q_per_kv, d] -> logits float32 [B, H*q_per_kv, keys cached] (quantized keys first)."""
-        return (_native or native()).cache_key_scores(self._h.value, q, None, 0, out_scale, out,
+        return (_native or native()).cache_key_scores(self._h and self._h.value, q, None, 0, out_scale, out,
                                                       None if stream is None else _stream(stream))
 
     def key_scores_rope(self, q: torch.Tensor, inv_freq: torch.Tensor, pos0: int = 0, out_scale: float = 1.0, out=None,
                         stream=None) -> torch.Tensor:
         """Logits against a cache of pre-RoPE keys: cache token t is rotated to position pos0 + t first.
         inv_freq: [d/2] float32 on the device."""
-        return (_native or native()).cache_key_scores_rope(self._h.value, q, inv_freq, int(pos0), out_scale, out,
+        return (_native or native()).cache_key_scores_rope(self._h and self._h.value, q, inv_freq, int(pos0), out_scale, out,
                                                            None if stream is None else _stream(stream))

@@ -244,6 +244,17 @@ def test_a_group_of_none():
 
 
 @pytest.mark.gpu
+def test_a_destroyed_cache():
+    q = torch.randn(1, 2, 128, device="cuda")
+    cache = squat.Cache(1, 2, 1, 2, 32, 32, 32, 64, torch.float32)
+    cache.append(q)
+    cache.__del__()
+    for call in (lambda: cache.append(q), lambda: cache.key_scores(q), lambda: cache.key_scores_rope(q, torch.ones(64, device="cuda"))):
+        with pytest.raises(squat.SquatError):
+            call()
+
+
+@pytest.mark.gpu
 def test_results_land_where_they_are_asked_for():
     k = torch.randn(2, 3, 40, 128, device="cuda", dtype=torch.float16)
     q = torch.randn(2, 6, 128, device="cuda", dtype=torch.bfloat16)
