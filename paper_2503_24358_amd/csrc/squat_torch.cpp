@@ -116,7 +116,14 @@ void need_dims(const at::Tensor& t, int64_t dims) {
     throw Raised{};
 }
 
+// Leaves the interpreter to other threads for as long as it lives.
+struct Free {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~Free() { PyEval_RestoreThread(state); }
+};
+
 at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
+    const Free free;                       // (an allocator that has to grow or to give back memory waits for the device)
     return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
 }
 
@@ -144,13 +151,14 @@ PyObject* three(const at::Tensor& a, const at::Tensor& b, const at::Tensor& c) {
     return out;
 }
 
-// The C call, with the interpreter free for other threads meanwhile.
+// The C call, with the interpreter free as well.
 template <typename F>
 void call(const char* where, F&& f) {
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f();
-    Py_END_ALLOW_THREADS
+    {
+        const Free free;
+        rc = f();
+    }
     check(rc, where);
 }
 

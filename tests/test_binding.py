@@ -1,5 +1,9 @@
 """The native part of the Python binding: what it refuses and with which exception, and that results land where the caller
 says (given outputs, a stream's handle or object)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -252,6 +256,51 @@ def test_a_destroyed_cache():
     for call in (lambda: cache.append(q), lambda: cache.key_scores(q), lambda: cache.key_scores_rope(q, torch.ones(64, device="cuda"))):
         with pytest.raises(squat.SquatError):
             call()
+
+
+ALLOCATOR = """
+extern int PyGILState_Check(void);
+static void* block;
+static int asked, held;
+void lend(void* p) { block = p; }
+int times_asked(void) { return asked; }
+int times_held(void) { return held; }
+void* get(long size, int device, void* stream) { ++asked; held += PyGILState_Check(); return block; }
+void put(void* p, long size, int device, void* stream) {}
+"""
+
+
+# Lent: the memory 2 MiB into a tensor, an address that torch's own table of blocks does not hold.
+ALLOCATING = """
+import ctypes, os, sys, torch
+sys.path.insert(0, sys.argv[2])
+from paper_2503_24358_amd import squat
+lib = ctypes.CDLL(sys.argv[1])
+block = torch.zeros(66 << 20, dtype=torch.uint8, device="cuda")
+lib.lend(ctypes.c_void_p(block.data_ptr() + (2 << 20)))
+allocator = torch.cuda.memory.CUDAPluggableAllocator(sys.argv[1], "get", "put")
+k = torch.randn(1, 2, 32, 128, device="cuda")
+want = squat.quantize_keys(k, None, 2, 32, 32)
+pool = torch.cuda.MemPool(allocator.allocator())
+with torch.cuda.use_mem_pool(pool):
+    got = squat.quantize_keys(k, None, 2, 32, 32)
+torch.cuda.synchronize()
+lent = all(block.data_ptr() <= t.data_ptr() < block.data_ptr() + block.numel() for t in got)
+print(lib.times_asked(), lib.times_held(), lent, all(torch.equal(a, b) for a, b in zip(got, want)), flush=True)
+os._exit(0)                                              # (lent memory is nothing for torch to clean up)
+"""
+
+
+@pytest.mark.gpu
+def test_outputs_are_allocated_with_the_interpreter_free(tmp_path):
+    """torch's allocator grows through a function that looks whether the calling thread holds the interpreter."""
+    (tmp_path / "allocator.c").write_text(ALLOCATOR)
+    so = str(tmp_path / "allocator.so")
+    subprocess.run(["cc", "-O1", "-shared", "-fPIC", str(tmp_path / "allocator.c"), "-o", so], check=True)
+    root = os.path.dirname(os.path.dirname(squat.__file__))
+    p = subprocess.run([sys.executable, "-c", ALLOCATING, so, root], capture_output=True, text=True, timeout=100)
+    assert p.returncode == 0, p.stderr
+    assert p.stdout.split() == ["1", "0", "True", "True"]
 
 
 @pytest.mark.gpu
