@@ -838,12 +838,14 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
         const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
         p.wide_loads = (store_stride * meta_row) % 4 == 0;    // the bases are 8-byte aligned
     }
-    // Rows off the lines, us with non-temporal | ordinary stores: 4 query heads per KV head, 2 MB of logits 8.0 | 7.5, 4 MB 10.9 |
-    // 10.1 or 15.8 | 13.7, 8 MB 21.9 | 20.6, 12 MB 21.0 | 21.4 or 22.0 | 22.4, 33 MB 50.7 | 47.8; 8 query heads, 12 MB 16.0 | 15.9,
-    // 25 MB 27.8 | 24.9, 33 MB 40.4 | 33.0; 1 query head, 17 MB 78.2 | 79.5.
+    // Rows off the lines: ordinary stores, except for 5 to 18 MB of logits.  us with non-temporal | ordinary stores, 2 bits, heads of
+    // about 2050 tokens (medians of 15 graphs of 20 calls on four sets of buffers in turn; their spread is 1 %, 3 % from 16 MB on):
+    // 8 query heads per KV head, 2 MB 9.0 | 8.6, 4 MB 11.5 | 11.3, 5.6 MB 11.6 | 11.8, 8 MB 14.4 | 15.1, 11 MB 17.7 | 18.9, 16 MB 20.6 |
+    // 21.8, 18 MB 26.3 | 27.5 (rows of 12289 tokens: 22.2 | 22.0), 22 MB 31.0 | 31.7 (of 11265: 26.3 | 25.2), 30 MB 35.6 | 33.0, 45 MB
+    // 54.8 | 43.0; 4 query heads, 2 MB 10.0 | 9.7, 4 MB 12.6 | 12.7, 5.6 MB 15.8 | 16.3, 8 MB 17.9 | 18.5, 16 MB 28.1 | 28.9, 22 MB 36.9 |
+    // 37.9 (4 bits: 0.93 as long), 30 MB 51.1 | 49.0; 1 query head, 0.99 to 1.025 throughout.
     const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
-    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) ||
-              (q_per_kv <= 4 && out_bytes > (int64_t(9) << 20) && out_bytes < (int64_t(18) << 20));
+    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) || (out_bytes > (int64_t(5) << 20) && out_bytes < (int64_t(18) << 20));
 
     // workgroups along the sequence: about kRopeWaves * aim units each, spread evenly
     const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit;
