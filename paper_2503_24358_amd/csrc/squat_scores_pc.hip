@@ -487,11 +487,16 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     p.scores = scores;
     p.ssb = s_stride_batch;
     p.ssh = s_stride_head;
-    // Rows off the lines, us with non-temporal | ordinary stores: 4 query heads per KV head, 2 MB of logits 5.8 | 5.1, 8 MB 9.8 | 10.4,
-    // 16 MB 14.9 | 16.4 or 17.0 | 16.5, 20 MB 21.8 | 19.3, 41 MB 44.3 | 33.5; 8 query heads, 8 MB 8.5 | 7.9, 41 MB 41.5 | 24.5.
+    // Rows off the lines: ordinary stores, except for 2.5 (4 bits: 4) to 18 MB of logits of up to 4 query heads per KV head.  us with
+    // non-temporal | ordinary stores, 2 bits, heads of about 2050 tokens (medians of 15 graphs of 20 calls on four sets of buffers in
+    // turn; their spread is 1 to 4 %): 1 query head, 1 MB 7.03 | 6.98, 2 MB 9.6 | 9.8, 2.8 MB 13.7 | 14.2, 4 MB 14.6 | 15.5, 8 MB 25.6 |
+    // 27.5, 18 MB 53.2 | 55.3, 30 MB 86.6 | 86.4; 4 query heads, 1 MB 4.4 | 4.0, 2 MB 5.6 | 5.2, 2.8 MB 6.9 | 7.1, 4 MB 7.1 | 7.6, 8 MB
+    // 10.3 | 11.3, 11 MB 14.5 | 16.1, 16 MB 18.2 | 18.4 (rows of 11904 tokens: 22.2 | 21.2), 18 MB 22.6 | 22.0, 30 MB 32.7 | 29.0, 45 MB
+    // 48.0 | 41.8; 8 query heads, ordinary stores 0.90 to 0.94 as long up to 2.8 MB, 0.98 at 4 to 6 MB, 1.01 at 8, 0.57 at 45.  With 4 bits
+    // 0.95 to 1.03 as long from 2 to 22 MB, 1 to 4 query heads.
     const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
     p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) ||
-              (q_per_kv <= 4 && out_bytes > (int64_t(4) << 20) && out_bytes < (int64_t(18) << 20));
+              (q_per_kv <= 4 && out_bytes > (int64_t(bits == 2 ? 5 : 8) << 19) && out_bytes < (int64_t(18) << 20));
     p.n_tiles = static_cast<int>(n_tokens / 32);
     p.store_tiles = store_tokens / 32;
     p.n_kv_heads = n_kv_heads;

@@ -45,3 +45,12 @@ def test_rotary(recorder, bits, qpk):
     shapes = [s for m in sizes for s in _shapes(m, qpk)]
     got = recorded.run(recorder, CODE % (("squat_key_scores_rope", bits, True), shapes))
     assert got == [5 < m < 18 for m in sizes for _ in range(2)]
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("qpk", [1, 4, 8])
+def test_per_channel(recorder, bits, qpk):
+    sizes = (1, 2.25, 2.75, 3.75, 4.25, 8, 17.5, 18.5, 45)
+    shapes = [s for m in sizes for s in _shapes(m, qpk)]
+    got = recorded.run(recorder, CODE % (("squat_key_scores_per_channel", bits, False), shapes))
+    assert got == [qpk <= 4 and (2.5 if bits == 2 else 4) < m < 18 for m in sizes for _ in range(2)]
