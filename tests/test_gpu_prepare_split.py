@@ -39,3 +39,28 @@ def test_subspace_at_any_float(r, g):
         view = flat[off:off + 2 * r * 128].view(2, r, 128)
         assert view.data_ptr() % 16 == 4 * off
         assert torch.equal(squat.prepare(view, 1e-3, g), want)
+
+
+@pytest.mark.parametrize("r,rank", [(8, 2), (40, 20)])
+def test_one_ill_conditioned_panel_is_enough(r, rank):
+    """A panel whose own problem spans 1 / lambda to lambda sigma^2 (~1e12) sends its head to the eigen route: the last of three
+    alone, the first alone, none (the pivots of the others span 5e3 at most; the flags are the last 256 bytes of the workspace).
+    Entries are on the fp16 grid: half a step of it, and 3e-4 of the norm for the few at its midpoints."""
+    rng = np.random.default_rng(r)
+    qhat = np.zeros((3, r, 128))
+    qhat[0] = rng.standard_normal((r, 128))
+    qhat[0, rank:, 96:] = 0.0                            # the panel over columns 96 .. 127
+    qhat[1, :rank, 32:64] = rng.standard_normal((rank, 32))
+    # the one over columns 32 .. 127; the next panel is lambda times what stands here times 3e4, 771 at most, where 1e-7 gave
+    # 7.4e4: the fp16 grid ends at 65504 (the oracle's entries are within 5e-12 of 80-bit ones)
+    qhat[1, :, 64:] = 1e-9 * rng.standard_normal((r, 64))
+    qhat[2] = 1e-4 * rng.standard_normal((r, 128))
+    qhat = (3e4 * qhat).astype(np.float32)
+    nbytes = squat.prepare_workspace(3, 128, r, 32)
+    ws = torch.full((nbytes,), 0x55, dtype=torch.uint8, device="cuda")
+    got = squat.prepare(torch.from_numpy(qhat).cuda(), 50.0, 32, ws=ws).cpu().numpy().astype(np.float64)
+    assert ws[nbytes - 256:].view(torch.int32)[:3].tolist() == [1, 1, 0]
+    for h in range(3):
+        want = O.update_matrix_lowrank(qhat[h].astype(np.float64), 50.0, 32)
+        assert np.all(np.abs(got[h] - want) <= 2.0 ** -11 * np.abs(want) + 2.0 ** -24)
+        assert np.linalg.norm(got[h] - want) <= 3e-4 * np.linalg.norm(want)
