@@ -214,12 +214,11 @@ __global__ void __launch_bounds__(192) prepare_wave_kernel(const PrepParams p, i
 //     the 4 x 4 pivot block, the pivot rows are in the same wavefront for every column, and the update is one product per
 //     live 16 x 16 tile;
 //   - W = -Qr^T X: the solution's registers are the B operands as they are, through LDS to all four wavefronts.
-// Bound by the chain of its steps (LDS exchange, four reciprocals, two dependent products: 1.4 k cycles a step with one column
-// tile per wavefront, r = 40).  us per launch, fallback launch included, against all panels of a head in one workgroup (results
-// of the products in the accumulation registers, rows of Qhat 129 floats apart, four bytes a load): 32 heads, g = 32: r = 16
-// 11.5 -> 8.7, 32 19.9 -> 12.9, 40 27.8 -> 14.9, 64 40.0 -> 21.1; g = 64: r = 16 10.2 -> 8.2, 40 19.5 -> 13.5, 64 26.7 -> 19.5;
-// 256 heads: g = 32, r = 16 13.7 -> 12.8, 64 43.2 -> 40.4, g = 64, r = 40 22.8 -> 19.8.  (One pivot a step, 32 heads, g = 32, in
-// the earlier form: 13.3, 24.8, 36.2, 54.6 for r = 16, 32, 40, 64.)
+// Bound by the chain of its steps (LDS exchange, four reciprocals, two dependent products): 32 heads, r = 40, g = 64, one column
+// tile per wavefront, 2.6 k cycles for loading, 4.9 k for S, 14.8 k for ten steps, 2.5 k for W.  us per
+// launch, fallback launch included, against all panels of a head in one workgroup (results of the products in the
+// accumulation registers, rows of Qhat 129 floats apart, four bytes a load): 32 heads, g = 32: r = 16 11.5 -> 8.7, 32 19.9 -> 12.9, 40 27.8 -> 14.9, 64 40.0 -> 21.1; g = 64: r = 16 10.2 -> 8.2, 40 19.5 -> 13.5, 64 26.7 -> 19.5;
+// 256 heads: g = 32, r = 16 13.7 -> 12.8, 64 43.2 -> 40.4, g = 64, r = 40 22.8 -> 19.8.
 // A panel whose pivots span more than 1e9 (lambda times the largest eigenvalue of Qr Qr^T that large)
 // sets the head's flag: the eigen-route kernel, launched afterwards, redoes exactly the flagged heads.
 typedef double double4v __attribute__((ext_vector_type(4)));

@@ -625,11 +625,11 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     // a partial of 40 KB and pays ~2 us for reducing and writing it, so eight chunks, or two: for 16-bit queries where eight
     // leave no more than 16 workgroups; for fp32, whose chunk takes 5 k cycles on the matrix cores, as far as the launch
     // stays within one workgroup per CU (one fills a CU's LDS: more run in a second round).
-    // Gram and reduction, us at 8 | 2 chunks: bf16, 1 head of 512 tokens 11.1 | 9.8, 8 of 512 12.7 | 11.7, 16 of 512 14.1 |
-    // 13.8, 16 of 200 13.5 | 13.9, 24 of 512 15.7 | 15.6, 24 of 200 15.0 | 15.7, 32 of 512 16.2 | 17.6, 8 of 1024 13.1 | 12.0,
-    // 24 of 1024 16.4 | 17.0.  fp32, 1 head of 512 28.4 | 13.1, 8 of 512 29.7 | 15.1, 64 of 512 34.6 | 29.3.  With a reduction
-    // that took 2 to 3 us more, fp32, 28 heads x 4 of 1024: 8 workgroups a head 40.3, 9 (one round) 41.4, 10 (two rounds) 60.1;
-    // 48 heads of 2048: 42.4, 5 a head 41.3, 6 (two rounds) 57.9.
+    // Gram and reduction, us at 8 | 2 chunks (graphs of such calls): bf16, 1 head of 512 tokens 11.0 | 9.8, 8 of 512 11.8 | 11.0, 16 of
+    // 512 12.9 | 12.4, 16 of 200 11.8 | 12.1, 24 of 512 14.1 | 13.9, 24 of 200 12.9 | 13.2, 32 of 512 15.6 | 16.4, 8 of 1024 12.5 |
+    // 11.3, 24 of 1024 14.8 | 16.3.  fp32, 1 head of 512 28.3 | 13.0, 8 of 512 28.9 | 14.3, 64 of 512 33.7 | 25.6; 28 heads x 4 of
+    // 1024: 8 workgroups a head 34.4, 9 (one round) 35.4, 10 (two rounds) 51.9; 48 heads of 2048: 4 a head 36.3, 5 35.0, 6 (two
+    // rounds) 49.1.
     const int64_t units = q_per_kv * ((n_tokens + 15) / 16);
     const int64_t wide = (units + 8 * kGramWaves - 1) / (8 * kGramWaves);
     const int64_t narrow = (units + 2 * kGramWaves - 1) / (2 * kGramWaves);
@@ -653,10 +653,11 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     }
     int rc = check_launch();
     if (rc) return rc;
-    // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head (us
-    // for Gram and reduction, per head | spread, each 1.3 less by now: bf16, 1 partial a head, 16 heads of 200 tokens 15.9 | 14.5, 24 of 200 16.1 |
-    // 16.1, 32 of 200 16.4 | 17.5; 2 partials, 32 of 1024 20.6 | 19.6, 36 of 1024 21.0 | 20.9, 40 of 1024 21.1 | 21.4; 256
-    // heads, 1 partial 21.9 | 38.8: the scattered 8-byte writes)
+    // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head, which has its
+    // row of results to itself (the others write 8 bytes here and there).  Gram and reduction, us per head | spread (graphs of such
+    // calls): bf16, 1 partial a head, 16 heads of 200 tokens 15.8 | 12.3, 24 14.1 | 13.0, 32 14.2 | 14.1, 40 14.5 | 15.3, 64 15.3 |
+    // 19.4, 256 of 512 21.3 | 37.4; 2 partials, 32 of 1024 18.2 | 16.4, 40 18.8 | 17.7, 48 19.5 | 19.3, 64 20.2 | 21.8.  (The lines are a
+    // little low: 32 and 48 would do.)
     if (p.wgs_per_head >= 4 || n_kv_heads <= (p.wgs_per_head == 1 ? 24 : 32))
         hipLaunchKernelGGL(gram_reduce_tiles, dim3(kRedTileBlocks, static_cast<unsigned>(n_kv_heads)), dim3(kRedTileThreads), 0, s, p.partial,
                            p.wgs_per_head, g64, gram_out, accumulate);

@@ -210,7 +210,8 @@ __device__ __forceinline__ void tri_up(double* a, double u, double v, double nv,
 // of its rows, and the next column.  alpha and beta do not depend on the exchange.
 // Bound by instruction issue (one wavefront per SIMD, four cycles an instruction, fp64 or not, dependent or not) and, with the
 // blocks getting small, by the barrier and the exchange: 300 instructions and 1800 cycles a step at the start, 200 and
-// 1180 with 32 columns left, where the last steps take another form (below); 70 us for the 126 of one head.  Before, every thread held four rows at 16 columns and 20 entries of each vector
+// 1180 with 32 columns left, where the last steps take another form (below); of one head 61 us for these 95, 10.6 for the last 31 and
+// the hand-over to them.  Before, every thread held four rows at 16 columns and 20 entries of each vector
 // (16 by columns, a copy in each of a wavefront's eight teams, and 4 by rows), the sum x'u followed the exchange, and a step was
 // 556 and 152 instructions: 99 us.  What did not help: the same with two rows a lane and the sums over the wavefronts formed
 // by the readers (79 us; LDS), all steps unrolled (same time a step, the compiler spills), the scalars in front of the barrier.
@@ -711,7 +712,7 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
         // through the three (of the line through the two where that falls outside), at distances that fall from 1/8 of
         // the bracket by equal factors to 2^-27 or less, so a round gains as many digits as that estimate has and the count
         // alone still decides.  A round whose estimate was no good (the bracket not an eighth) is followed by an even one.  5 to 7
-        // rounds for 16 eigenvalues (16 shifts each), 8 to 10 for 32 (8 shifts each): 25 k and 33 k cycles, the shared round included.
+        // rounds for 16 eigenvalues (16 shifts each), 8 to 10 for 32 (8 shifts each): 26 k and 34 k cycles, the shared round included.
         // (Even division throughout, 17 parts in 14 rounds: 75 k and 113 k; the zero of the line alone, 9 rounds: 53 k and 76 k with T
         // read from LDS, 36 k and 61 k with T in lanes.)
         double td[8], te[8];                                  // T for the counts: lane i of a row of 16 lanes holds rows 16 b + i
@@ -1240,7 +1241,8 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
         // 16 vectors.  A wavefront's part of V'X over its own rows goes to LDS, every wavefront adds up the parts (in the same
         // order) and applies the product to its rows.  One barrier per block: 144 products of 64 cycles and eight exchanges
         // per wavefront for 32 vectors.  (One reflector after the other, with a dot product over 16 lanes each, took 55 k
-        // cycles for 16 vectors and 90 k for 32, and the reflectors a trip through global memory; this takes 14 k and 26 k.)
+        // cycles for 16 vectors and 90 k for 32, and the reflectors a trip through global memory; this takes 15 k and 32 k
+        // with the output.)
         auto back = [&](auto nc_tag) __attribute__((always_inline)) {
             constexpr int NC = decltype(nc_tag)::value;
             const int tb = 7 - wave;
