@@ -122,15 +122,16 @@ struct Free {
     ~Free() { PyEval_RestoreThread(state); }
 };
 
+// To be called with the interpreter free, as torch.empty does: an allocator that has to grow or to give back memory waits for the device.
 at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
-    const Free free;                       // (an allocator that has to grow or to give back memory waits for the device)
     return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
 }
 
-at::Tensor given_or_empty(PyObject* o, at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
+// An output: the caller's, or none yet (None: made beside `like` by the call that fills it).
+at::Tensor given(PyObject* o, const at::Tensor& like) {
     if (o == Py_None) {
         need_device(like);
-        return empty(shape, type, like);
+        return {};
     }
     need_reachable(tensor(o));
     return tensor(o);
@@ -151,7 +152,7 @@ PyObject* three(const at::Tensor& a, const at::Tensor& b, const at::Tensor& c) {
     return out;
 }
 
-// The C call, with the interpreter free as well.
+// The C call, with the interpreter free; f makes its outputs before it, so that the interpreter is left and taken once a call.
 template <typename F>
 void call(const char* where, F&& f) {
     int rc;
@@ -200,20 +201,18 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         }
         if (group == 0 && (a[6] == Py_None || a[7] == Py_None)) raise(PyExc_ZeroDivisionError, "integer division or modulo by zero");
         const int per = group == 0 ? 1 : group;          // (outputs given: the library refuses the group)
-        const at::Tensor codes = PC ? given_or_empty(a[5], {b, h, tokens / 32, d, bits}, at::kInt, k)
-                                    : given_or_empty(a[5], {b, h, tokens, d * bits / 32}, at::kInt, k);
-        const at::Tensor scale = PC ? given_or_empty(a[6], {b, h, tokens / per, d}, at::kHalf, k)
-                                    : given_or_empty(a[6], {b, h, tokens, d / per}, at::kHalf, k);
-        const at::Tensor zero = PC ? given_or_empty(a[7], {b, h, tokens / per, d}, at::kHalf, k)
-                                   : given_or_empty(a[7], {b, h, tokens, d / per}, at::kHalf, k);
+        at::Tensor codes = given(a[5], k), scale = given(a[6], k), zero = given(a[7], k);
         const squat_dtype dt = dtype(a[0], k);
         const squat_stream s = stream(a[8]);
         const void* kp = pointer<void>(k);
-        auto* cp = pointer<uint32_t>(codes);
-        auto* sp = pointer<uint16_t>(scale);
-        auto* zp = pointer<uint16_t>(zero);
         const int64_t s0 = k.stride(0), s1 = k.stride(1), s2 = k.stride(2);
         call(PC ? "squat_quantize_keys_per_channel" : "squat_quantize_keys", [&] {
+            if (!codes.defined()) codes = PC ? empty({b, h, tokens / 32, d, bits}, at::kInt, k) : empty({b, h, tokens, d * bits / 32}, at::kInt, k);
+            if (!scale.defined()) scale = PC ? empty({b, h, tokens / per, d}, at::kHalf, k) : empty({b, h, tokens, d / per}, at::kHalf, k);
+            if (!zero.defined()) zero = PC ? empty({b, h, tokens / per, d}, at::kHalf, k) : empty({b, h, tokens, d / per}, at::kHalf, k);
+            auto* cp = pointer<uint32_t>(codes);
+            auto* sp = pointer<uint16_t>(scale);
+            auto* zp = pointer<uint16_t>(zero);
             return (PC ? squat_quantize_keys_per_channel : squat_quantize_keys)(
                 kp, dt, b, static_cast<int>(h), tokens, static_cast<int>(d), s0, s1, s2, update, usb, bits, group, g, cp, sp, zp, s);
         });
@@ -250,6 +249,7 @@ PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (a[6] == Py_None) {
             if (a[5] != Py_None && !THPDtype_Check(a[5])) raise(PyExc_TypeError, "out_dtype must be a torch.dtype");
             const at::ScalarType type = a[5] == Py_None ? at::get_default_dtype_as_scalartype() : reinterpret_cast<THPDtype*>(a[5])->scalar_type;
+            const Free free;
             out = empty({b, h, tokens, d}, type, codes);
         } else {
             out = tensor(a[6]);
@@ -305,8 +305,8 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (q.dim() != 3 || q.size(0) != b || q.size(1) != h * qpk || q.size(2) != d || q.stride(2) != 1)
             raise(PyExc_ValueError, "q must be [B, n_kv_heads*q_per_kv, d] with unit channel stride");
         need_dense_store(codes, scale, zero);
-        const at::Tensor out = given_or_empty(a[10], {b, h * qpk, tokens}, at::kFloat, codes);
-        if (out.scalar_type() != at::kFloat || out.stride(2) != 1 || out.size(0) != b || out.size(1) != h * qpk)
+        at::Tensor out = given(a[10], codes);
+        if (out.defined() && (out.scalar_type() != at::kFloat || out.stride(2) != 1 || out.size(0) != b || out.size(1) != h * qpk))
             raise(PyExc_ValueError, "out must be float32 [B, n_q_heads, >= n] with unit token stride");
         const squat_dtype dt = dtype(a[0], q);
         const long long pos0 = rope ? integer(a[8]) : 0;
@@ -316,18 +316,23 @@ PyObject* key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const auto* sp = pointer<const uint16_t>(scale);
         const auto* zp = pointer<const uint16_t>(zero);
         const void* qp = pointer<void>(q);
-        float* op = pointer<float>(out);
-        const int64_t q0 = q.stride(0), q1 = q.stride(1), o0 = out.stride(0), o1 = out.stride(1);
+        const int64_t q0 = q.stride(0), q1 = q.stride(1);
         const int hi = static_cast<int>(h), di = static_cast<int>(d);
+        auto make = [&] {
+            if (!out.defined()) out = empty({b, h * qpk, tokens}, at::kFloat, codes);
+        };
         if constexpr (rope)
             call(PC ? "squat_key_scores_rope_per_channel" : "squat_key_scores_rope", [&] {
-                return (PC ? squat_key_scores_rope_per_channel : squat_key_scores_rope)(cp, sp, zp, b, hi, tokens, di, bits, group, freq, pos0,
-                                                                                       qp, dt, qpk, q0, q1, out_scale, op, o0, o1, s);
+                make();
+                return (PC ? squat_key_scores_rope_per_channel : squat_key_scores_rope)(
+                    cp, sp, zp, b, hi, tokens, di, bits, group, freq, pos0, qp, dt, qpk, q0, q1, out_scale, pointer<float>(out), out.stride(0),
+                    out.stride(1), s);
             });
         else
             call(PC ? "squat_key_scores_per_channel" : "squat_key_scores", [&] {
+                make();
                 return (PC ? squat_key_scores_per_channel : squat_key_scores)(cp, sp, zp, b, hi, tokens, di, bits, group, qp, dt, qpk, q0, q1,
-                                                                             out_scale, op, o0, o1, s);
+                                                                             out_scale, pointer<float>(out), out.stride(0), out.stride(1), s);
             });
         return a[10] == Py_None ? THPVariable_Wrap(out) : Py_NewRef(a[10]);
     });
@@ -380,7 +385,6 @@ PyObject* cache_key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor out;
         if (a[5] == Py_None) {
             if (q.dim() < 2) raise(PyExc_IndexError, "q must be [B, H*q_per_kv, d]");
-            out = empty({q.size(0), q.size(1), counts.keys_quantized + counts.keys_residual}, at::kFloat, q);
         } else {
             out = tensor(a[5]);
             need_reachable(out);
@@ -390,12 +394,14 @@ PyObject* cache_key_scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const float out_scale = number(a[4]);
         const squat_stream s = stream(a[6]);
         const void* qp = pointer<void>(q);
-        float* op = pointer<float>(out);
-        const int64_t q0 = q.stride(0), q1 = q.stride(1), o0 = out.stride(0), o1 = out.stride(1);
-        if constexpr (rope)
-            call("squat_cache_key_scores_rope", [&] { return squat_cache_key_scores_rope(c, qp, dt, q0, q1, freq, pos0, out_scale, op, o0, o1, s); });
-        else
-            call("squat_cache_key_scores", [&] { return squat_cache_key_scores(c, qp, dt, q0, q1, out_scale, op, o0, o1, s); });
+        const int64_t q0 = q.stride(0), q1 = q.stride(1);
+        call(rope ? "squat_cache_key_scores_rope" : "squat_cache_key_scores", [&] {
+            if (!out.defined()) out = empty({q.size(0), q.size(1), counts.keys_quantized + counts.keys_residual}, at::kFloat, q);
+            float* op = pointer<float>(out);
+            const int64_t o0 = out.stride(0), o1 = out.stride(1);
+            if constexpr (rope) return squat_cache_key_scores_rope(c, qp, dt, q0, q1, freq, pos0, out_scale, op, o0, o1, s);
+            else return squat_cache_key_scores(c, qp, dt, q0, q1, out_scale, op, o0, o1, s);
+        });
         return a[5] == Py_None ? THPVariable_Wrap(out) : Py_NewRef(a[5]);
     });
 }
