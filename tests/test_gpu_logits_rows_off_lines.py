@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("rope", [False, True])
 @pytest.mark.parametrize("per_channel", [False, True])
-@pytest.mark.parametrize("b,h,qpk,n", [(1, 1, 1, 32), (2, 3, 4, 96), (2, 3, 8, 992), (16, 8, 4, 2496), (32, 8, 4, 2496), (64, 8, 4, 2496), (3, 2, 5, 1504)])
+@pytest.mark.parametrize("b,h,qpk,n", [(1, 1, 1, 32), (2, 3, 4, 96), (2, 3, 8, 992), (16, 8, 4, 2496), (32, 8, 4, 2496), (64, 8, 4, 2496), (16, 8, 8, 1504), (3, 2, 5, 1504)])
 def test_rows_on_and_off_the_lines_agree(b, h, qpk, n, per_channel, rope):
     g = torch.Generator(device="cuda")
     g.manual_seed(b + n)
