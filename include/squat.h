@@ -272,8 +272,8 @@ int squat_quantize_keys(const void* k, squat_dtype k_dt, int64_t n_batch, int n_
  * tiles of 32 consecutive tokens of one (batch entry, head).  The tiles that
  * share an update matrix (a head's, over the whole batch, or one batch
  * entry's when update_stride_batch != 0) form a "problem"; each problem gets
- * workgroups_per_problem persistent workgroups (as many as fill the device
- * once, at most one per tile) whose wavefronts take tiles
+ * workgroups_per_problem persistent workgroups (as many as the device holds
+ * at once, rounded down; at least one, at most one per tile) whose wavefronts take tiles
  *     w, w + S, w + 2 S, ...     (w = wavefront_in_workgroup *
  *     workgroups_per_problem + workgroup_in_problem,
  *     S = workgroups_per_problem * wavefronts_per_workgroup)

@@ -33,8 +33,6 @@ constexpr int NT = kD / 32;          // 32-channel tiles per key
 __host__ __device__ constexpr int waves_for(int dt, int gt, int bt) {
     return dt == SQUAT_F32 ? 6 : ((bt == 2 || (gt == 4 && bt == 1)) ? 8 : 12);
 }
-constexpr int kWgsPerCU = 1;
-
 struct QuantParams {
     const unsigned char* k;
     int64_t sb, sh, st;              // key strides in BYTES
@@ -108,7 +106,7 @@ __device__ __forceinline__ void split8(const float* v, half8& hi, half8& lo) {
 }
 
 template <int BITS, int GT, int BT, int DT>
-__global__ void __launch_bounds__(waves_for(DT, GT, BT) * kWave, kWgsPerCU) quantize_kernel(const QuantParams p) {
+__global__ void __launch_bounds__(waves_for(DT, GT, BT) * kWave, 1) quantize_kernel(const QuantParams p) {
     constexpr int kWaves = waves_for(DT, GT, BT);
     constexpr int ES = Elem<DT>::size;
     constexpr int ROWB = kD * ES;                 // bytes of one key
@@ -498,14 +496,7 @@ int squat::plan_quantize(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t
     const int bt = has_update ? g / 32 : 4;      // no update matrix: one block, plain round-to-nearest
     if (!(gt % bt == 0 || bt % gt == 0)) return SQUAT_E_BADSHAPE;
     out.waves = waves_for(k_dt, gt, bt);
-    const int64_t target = kWgsPerCU * static_cast<int64_t>(device_cu_count());   // fill every CU once
-    int64_t per = (target + out.n_prob - 1) / out.n_prob;
-    const int64_t need = out.units_per_prob;     // at least one tile per workgroup
-    if (per > need) per = need;
-    if (per < 1) per = 1;
-    if (out.n_prob * per > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
-    out.wgs_per_prob = static_cast<int>(per);
-    return SQUAT_OK;
+    return spread_problems(out);
 }
 
 // squat_quantize_keys with the outputs placed at tokens out_offset .. of a store that holds out_stride

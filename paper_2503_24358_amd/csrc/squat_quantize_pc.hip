@@ -511,13 +511,7 @@ int squat::plan_quantize_pc(squat_dtype k_dt, int64_t n_batch, int n_heads, int6
     if (out.units_per_prob >= (int64_t(1) << 31) || out.tiles_per_seq >= (int64_t(1) << 31)) return SQUAT_E_BADSHAPE;
     const int bt = has_update ? g / 32 : 4;      // no update matrix: one block, plain round-to-nearest
     out.waves = pc_waves_for(k_dt, bt);
-    int64_t per = (static_cast<int64_t>(device_cu_count()) + out.n_prob - 1) / out.n_prob;     // fill every CU once
-    const int64_t need = out.units_per_prob;     // at least one tile per workgroup
-    if (per > need) per = need;
-    if (per < 1) per = 1;
-    if (out.n_prob * per > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
-    out.wgs_per_prob = static_cast<int>(per);
-    return SQUAT_OK;
+    return spread_problems(out);
 }
 
 // squat_quantize_keys_per_channel into a store that holds out_stride tokens per (batch, head), starting at
