@@ -41,9 +41,11 @@ struct GramParams {
     int64_t n_tokens;
     int q_per_kv;
     int wgs_per_head;
+    unsigned idle;               // FEWER: workgroups at the front of the grid that have no share
     int64_t chunks_per_qhead;    // ceil(n_tokens / 16)
     int64_t units_per_head;      // q_per_kv * chunks_per_qhead
     int64_t step_qh, step_c;     // from a wavefront's unit to its next one: query heads, chunks
+    int64_t pause;               // FEWER, > 0: the sums over the units before this one are put aside (all of LDS), see run_gram
     float* partial;              // [n_kv_heads][wgs_per_head][10][1024]
 };
 
@@ -148,45 +150,20 @@ __device__ __forceinline__ void reduce_and_store(f32x16 (&acc)[kTiles], unsigned
     }
 }
 
-// Position of a unit (chunk of 16 tokens of one query head), kept in scalar registers and advanced
-// without a division: the units of a wavefront lie all wavefronts of the head's workgroups apart.
-struct GramCursor {
-    int64_t u, qh, c;            // unit, its query head, its chunk inside the query head
-    __device__ __forceinline__ GramCursor(const GramParams& p, int wg, int wave) {
-        u = static_cast<int64_t>(wg) * kGramWaves + wave;
-        qh = u / p.chunks_per_qhead;
-        c = u - qh * p.chunks_per_qhead;
-    }
-    __device__ __forceinline__ void advance(const GramParams& p) {
-        const int64_t by = static_cast<int64_t>(p.wgs_per_head) * kGramWaves;
-        u += by;
-        c += by;
-        while (c >= p.chunks_per_qhead) {     // wave-uniform
-            c -= p.chunks_per_qhead;
-            ++qh;
-        }
-    }
-    // The same without a loop (for 16-bit queries the loop is the faster: 256 x 4 heads of 32768 tokens 1352 | 1371 us).
-    __device__ __forceinline__ void advance_at_once(const GramParams& p) {
-        u += static_cast<int64_t>(p.wgs_per_head) * kGramWaves;
-        qh += p.step_qh;
-        c += p.step_c;
-        if (c >= p.chunks_per_qhead) {        // wave-uniform
-            c -= p.chunks_per_qhead;
-            ++qh;
-        }
-    }
-};
-
 // Accumulate one workgroup's share of Q^T Q.  16-bit element types.
-template <int DT>
+template <int DT, bool FEWER>
 __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const GramParams p) {
     typedef typename GramOps<DT>::op_t op_t;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, m = lane & 31;
-    const int kvh = blockIdx.x / p.wgs_per_head;
-    const int wg = blockIdx.x % p.wgs_per_head;
+    unsigned block = blockIdx.x;
+    if constexpr (FEWER) {
+        if (block < p.idle) return;
+        block -= p.idle;
+    }
+    const int kvh = block / p.wgs_per_head;
+    const int wg = block % p.wgs_per_head;
 
     f32x16 acc[kTiles];
 #pragma unroll
@@ -194,10 +171,29 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
 
+    const int64_t ustride = static_cast<int64_t>(p.wgs_per_head) * kGramWaves;
     const int64_t cpq = p.chunks_per_qhead;
     const int64_t last_unit = p.units_per_head - 1;
-    GramCursor ci(p, wg, wave);  // next unit to load
-    GramCursor cc = ci;          // next unit to multiply
+
+    // Position of a unit (chunk of 16 tokens of one query head), kept in scalar registers and advanced
+    // without a division: units of a wavefront are `ustride` apart.
+    struct Cursor {
+        int64_t u, qh, c;        // unit, its query head, its chunk inside the query head
+    };
+    auto advance = [&](Cursor& k) {
+        k.u += ustride;
+        k.c += ustride;
+        while (k.c >= cpq) {     // wave-uniform
+            k.c -= cpq;
+            ++k.qh;
+        }
+    };
+    Cursor ci;                   // next unit to load
+    ci.u = static_cast<int64_t>(wg) * kGramWaves + wave;
+    ci.qh = ci.u / cpq;
+    ci.c = ci.u - ci.qh * cpq;
+    Cursor cc = ci;              // next unit to multiply
+    f32x4* const aside = reinterpret_cast<f32x4*>(smem) + wave * (kTiles * 4 * kWave);
 
     // Lane (hh, m) loads bytes 8 m .. 8 m + 7 of rows 8 hh + j, j = 0..7, of a chunk: one 32-bit offset per
     // row from the chunk's (scalar) base address.
@@ -211,7 +207,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
     // row; both are discarded below by wave-uniform tests, so the load stream stays straight-line.
     constexpr int kDepth = 4;
     u32x2 raw[kDepth][8];
-    auto issue = [&](const GramCursor& k, u32x2* dst) {
+    auto issue = [&](const Cursor& k, u32x2* dst) {
         const bool past = k.u > last_unit;
         const int64_t qh = past ? p.q_per_kv - 1 : k.qh;
         const int64_t tokc = (past ? cpq - 1 : k.c) * 16;
@@ -230,7 +226,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
             }
         }
     };
-    auto consume = [&](const GramCursor& k, u32x2* src) {
+    auto consume = [&](const Cursor& k, u32x2* src) {
         if (k.u > last_unit) return;                     // wave-uniform
         const int64_t tokc = k.c * 16;
         if (tokc + 16 > p.n_tokens) {                    // ragged last chunk of a query head (wave-uniform)
@@ -262,18 +258,32 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
 #pragma unroll
         for (int i = 0; i < kDepth; ++i) {
             issue(ci, raw[i]);
-            ci.advance(p);
+            advance(ci);
         }
-        while (cc.u <= last_unit) {
+        int64_t end = FEWER && p.pause > 0 ? p.pause : last_unit + 1;
+        for (;;) {
+            while (cc.u < end) {
 #pragma unroll
-            for (int i = 0; i < kDepth; ++i) {
-                consume(cc, raw[i]);
-                cc.advance(p);
-                issue(ci, raw[i]);
-                ci.advance(p);
+                for (int i = 0; i < kDepth; ++i) {
+                    consume(cc, raw[i]);
+                    advance(cc);
+                    issue(ci, raw[i]);
+                    advance(ci);
+                }
             }
+            if (!FEWER || end > last_unit) break;
+            end = last_unit + 1;
+            put_tiles<0, kTiles>(acc, aside, lane);
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
         }
+        if constexpr (FEWER)
+            if (p.pause > 0) add_tiles<0, kTiles>(acc, aside, lane);
     }
+    if constexpr (FEWER)
+        if (p.pause > 0) __syncthreads();                // the places below are others' as well
 
     reduce_and_store(acc, smem, wave, lane, p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats);
 }
@@ -281,12 +291,18 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
 // fp32 inputs: products on the fp32 matrix cores (32x32x2), two tokens per step.
 // Bound by the matrix cores: 80 products of 64 cycles a chunk.  Positions kept as above, loads without conditions and two chunks
 // in flight (a division and a test per load, one chunk, before): 32 x 4 heads of 8192 tokens 202 -> 165 us (137 at 2.4 GHz).
+template <bool FEWER>
 __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const GramParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, m = lane & 31;
-    const int kvh = blockIdx.x / p.wgs_per_head;
-    const int wg = blockIdx.x % p.wgs_per_head;
+    unsigned block = blockIdx.x;
+    if constexpr (FEWER) {
+        if (block < p.idle) return;
+        block -= p.idle;
+    }
+    const int kvh = block / p.wgs_per_head;
+    const int wg = block % p.wgs_per_head;
 
     f32x16 acc[kTiles];
 #pragma unroll
@@ -296,8 +312,24 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
 
     const int64_t cpq = p.chunks_per_qhead;
     const int64_t last_unit = p.units_per_head - 1;
-    GramCursor ci(p, wg, wave);  // next unit to load
-    GramCursor cc = ci;          // next unit to multiply
+    struct Cursor {
+        int64_t u, qh, c;        // unit, its query head, its chunk inside the query head
+    };
+    auto advance = [&](Cursor& k) {                      // (for 16-bit queries the loop above is the faster)
+        k.u += static_cast<int64_t>(p.wgs_per_head) * kGramWaves;
+        k.qh += p.step_qh;
+        k.c += p.step_c;
+        if (k.c >= cpq) {        // wave-uniform
+            k.c -= cpq;
+            ++k.qh;
+        }
+    };
+    Cursor ci;                   // next unit to load
+    ci.u = static_cast<int64_t>(wg) * kGramWaves + wave;
+    ci.qh = ci.u / cpq;
+    ci.c = ci.u - ci.qh * cpq;
+    Cursor cc = ci;              // next unit to multiply
+    f32x4* const aside = reinterpret_cast<f32x4*>(smem) + wave * (kTiles * 4 * kWave);
 
     // Lane (hh, m) loads channels 4 m .. 4 m + 3 of rows 2 j + hh, j = 0..7, of a chunk; otherwise as for 16-bit queries.
     const uint32_t st32 = static_cast<uint32_t>(p.st);
@@ -306,7 +338,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
     for (int j = 0; j < 8; ++j) voff[j] = static_cast<uint32_t>(2 * j + hh) * st32 + static_cast<uint32_t>(m) * 16u;
     constexpr int kDepth = 2;    // chunks in flight per wavefront (8 KB each)
     f32x4 raw[kDepth][8];
-    auto issue = [&](const GramCursor& k, f32x4* dst) {
+    auto issue = [&](const Cursor& k, f32x4* dst) {
         const bool past = k.u > last_unit;
         const int64_t qh = past ? p.q_per_kv - 1 : k.qh;
         const int64_t tokc = (past ? cpq - 1 : k.c) * 16;
@@ -324,7 +356,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
             }
         }
     };
-    auto consume = [&](const GramCursor& k, f32x4* src) {
+    auto consume = [&](const Cursor& k, f32x4* src) {
         if (k.u > last_unit) return;                     // wave-uniform
         const int64_t tokc = k.c * 16;
         if (tokc + 16 > p.n_tokens) {                    // ragged last chunk of a query head (wave-uniform)
@@ -346,18 +378,32 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
 #pragma unroll
         for (int i = 0; i < kDepth; ++i) {
             issue(ci, raw[i]);
-            ci.advance_at_once(p);
+            advance(ci);
         }
-        while (cc.u <= last_unit) {
+        int64_t end = FEWER && p.pause > 0 ? p.pause : last_unit + 1;
+        for (;;) {
+            while (cc.u < end) {
 #pragma unroll
-            for (int i = 0; i < kDepth; ++i) {
-                consume(cc, raw[i]);
-                cc.advance_at_once(p);
-                issue(ci, raw[i]);
-                ci.advance_at_once(p);
+                for (int i = 0; i < kDepth; ++i) {
+                    consume(cc, raw[i]);
+                    advance(cc);
+                    issue(ci, raw[i]);
+                    advance(ci);
+                }
             }
+            if (!FEWER || end > last_unit) break;
+            end = last_unit + 1;
+            put_tiles<0, kTiles>(acc, aside, lane);
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
         }
+        if constexpr (FEWER)
+            if (p.pause > 0) add_tiles<0, kTiles>(acc, aside, lane);
     }
+    if constexpr (FEWER)
+        if (p.pause > 0) __syncthreads();                // the places below are others' as well
 
     reduce_and_store(acc, smem, wave, lane, p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats);
 }
@@ -626,19 +672,34 @@ namespace {
 
 constexpr size_t kEigLdsBytes = kD * kEigLd * sizeof(double) + kD * sizeof(double) + kD * sizeof(int) + 16;
 constexpr size_t kGramLdsBytes = 2 * kPartialFloats * sizeof(float);      // 80 KB
+constexpr size_t kGramLdsMost = kGramWaves * kPartialFloats * sizeof(float);   // 160 KB: a wavefront's sums each
+
+struct GramKernels {
+    void (*bf16)(GramParams);
+    void (*f16)(GramParams);
+    void (*f32)(GramParams);
+};
+GramKernels gram_kernels(bool fewer) {
+    return fewer ? GramKernels{gram_partial_16<SQUAT_BF16, true>, gram_partial_16<SQUAT_F16, true>, gram_partial_f32<true>}
+                 : GramKernels{gram_partial_16<SQUAT_BF16, false>, gram_partial_16<SQUAT_F16, false>, gram_partial_f32<false>};
+}
 
 int raise_lds_limits() {
     // one flag per kernel: a failed call is retried by the next launch, a raced one only repeated
-    static std::atomic<uint64_t> done[7];
-    const struct { const void* kernel; size_t bytes; } limits[7] = {
-        {reinterpret_cast<const void*>(gram_partial_16<SQUAT_BF16>), kGramLdsBytes},
-        {reinterpret_cast<const void*>(gram_partial_16<SQUAT_F16>), kGramLdsBytes},
-        {reinterpret_cast<const void*>(gram_partial_f32), kGramLdsBytes},
+    static std::atomic<uint64_t> done[10];
+    const GramKernels g[2] = {gram_kernels(false), gram_kernels(true)};
+    const struct { const void* kernel; size_t bytes; } limits[10] = {
+        {reinterpret_cast<const void*>(g[0].bf16), kGramLdsBytes},
+        {reinterpret_cast<const void*>(g[0].f16), kGramLdsBytes},
+        {reinterpret_cast<const void*>(g[0].f32), kGramLdsBytes},
+        {reinterpret_cast<const void*>(g[1].bf16), kGramLdsMost},
+        {reinterpret_cast<const void*>(g[1].f16), kGramLdsMost},
+        {reinterpret_cast<const void*>(g[1].f32), kGramLdsMost},
         {reinterpret_cast<const void*>(eig_kernel), kEigLdsBytes},
         {reinterpret_cast<const void*>(eig_tridiag_kernel), static_cast<size_t>(kTriLdsBytes)},
         {reinterpret_cast<const void*>(gram_reduce), static_cast<size_t>(kRedLdsBytes)},
         {reinterpret_cast<const void*>(subspace_iter_kernel), static_cast<size_t>(kItLdsBytes)}};
-    for (int i = 0; i < 7; ++i)
+    for (int i = 0; i < 10; ++i)
         if (int rc = set_max_lds_once(done[i], limits[i].kernel, static_cast<int>(limits[i].bytes))) return rc;
     return SQUAT_OK;
 }
@@ -687,18 +748,26 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     } else if (n_kv_heads * wide <= 16) {
         wgs = narrow < room ? narrow : room;
     }
-    p.wgs_per_head = static_cast<int>(wgs);
+    // Up to 128 heads: where that makes a few workgroups more than compute units, a head keeps as many as all hold at once, and the
+    // rest of the grid, at its front, leaves at once; in a second round those few would read their share alone.  Build of the
+    // subspace, us, two rounds | one, 2^20 queries: bf16, 7 heads 187 | 160, 48 193 | 170; fp32, 7 heads 469 | 280, 48 442 | 299.  (More heads
+    // than 128 would come down to one workgroup each: 130 bf16 199 | 197, 200 194 | 183, fp32 367 | 339, with longer sums.)
+    p.wgs_per_head = static_cast<int>(wgs > per_cu && per_cu > 1 ? per_cu : wgs);
+    p.idle = static_cast<unsigned>(n_kv_heads) * static_cast<unsigned>(wgs - p.wgs_per_head);
     p.chunks_per_qhead = (n_tokens + 15) / 16;
     p.units_per_head = p.chunks_per_qhead * q_per_kv;
     p.step_qh = static_cast<int64_t>(p.wgs_per_head) * kGramWaves / p.chunks_per_qhead;
     p.step_c = static_cast<int64_t>(p.wgs_per_head) * kGramWaves % p.chunks_per_qhead;
+    // The fewer workgroups' sums are longer, by up to a half; each is then made of two (workgroups of a head, 2-norm of the error of Qhat,
+    // before | fewer | of two sums: 48 heads x 4 of 2000 tokens, r = 16, bf16 3.4e-8 | 3.6e-8 | 3.1e-8, fp32 5.7e-8 | 6.6e-8 | 4.3e-8; 100 x 4,
+    // bf16 4.7e-8 | 6.3e-8 | 4.3e-8).
+    const bool halves = p.idle > 0 && p.wgs_per_head < 16;
+    p.pause = halves ? p.units_per_head / 2 : 0;
+    const size_t lds = halves ? kGramLdsMost : kGramLdsBytes;
     p.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + pl.off_partial);
-    const dim3 grid(static_cast<unsigned>(n_kv_heads) * p.wgs_per_head);
-    switch (q_dt) {
-        case SQUAT_BF16: hipLaunchKernelGGL(gram_partial_16<SQUAT_BF16>, grid, dim3(kGramWaves * kWave), kGramLdsBytes, s, p); break;
-        case SQUAT_F16: hipLaunchKernelGGL(gram_partial_16<SQUAT_F16>, grid, dim3(kGramWaves * kWave), kGramLdsBytes, s, p); break;
-        default: hipLaunchKernelGGL(gram_partial_f32, grid, dim3(kGramWaves * kWave), kGramLdsBytes, s, p); break;
-    }
+    const dim3 grid(static_cast<unsigned>(n_kv_heads) * p.wgs_per_head + p.idle);
+    const GramKernels k = gram_kernels(p.idle > 0);
+    hipLaunchKernelGGL(q_dt == SQUAT_BF16 ? k.bf16 : q_dt == SQUAT_F16 ? k.f16 : k.f32, grid, dim3(kGramWaves * kWave), lds, s, p);
     int rc = check_launch();
     if (rc) return rc;
     // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head, which has its
@@ -706,7 +775,7 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     // calls): bf16, 1 partial a head, 16 heads of 200 tokens 15.8 | 12.3, 24 14.1 | 13.0, 32 14.2 | 14.1, 40 14.5 | 15.3, 64 15.3 |
     // 19.4, 256 of 512 21.3 | 37.4; 2 partials, 32 of 1024 18.2 | 16.4, 40 18.8 | 17.7, 48 19.5 | 19.3, 64 20.2 | 21.8.  (The lines are a
     // little low: 32 and 48 would do.)
-    if (p.wgs_per_head >= 4 || n_kv_heads <= (p.wgs_per_head == 1 ? 24 : 32))
+    if (wgs >= 4 || n_kv_heads <= (wgs == 1 ? 24 : 32))
         hipLaunchKernelGGL(gram_reduce_tiles, dim3(kRedTileBlocks, static_cast<unsigned>(n_kv_heads)), dim3(kRedTileThreads), 0, s, p.partial,
                            p.wgs_per_head, g64, gram_out, accumulate);
     else
