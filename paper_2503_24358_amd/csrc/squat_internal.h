@@ -168,6 +168,7 @@ struct QuantPlan {
     int64_t tiles_per_seq;
     int64_t units_per_prob;
     int wgs_per_prob;
+    int wgs_to_fill;         // the same without the bound by what the device holds at once
     int waves;
 };
 // Logits: result rows that begin on 64-byte lines are written by non-temporal stores (whole lines leave the chip once; 64 x 256 x 2080
@@ -220,14 +221,15 @@ inline int device_cu_count() {
 // least one and at most one per tile.  Rounded down: where rounding up makes a launch of 257 to 300 workgroups, the few beyond 256
 // start when the others have ended and read their share alone.  Up | down, us, 2 bits, bf16, groups of 32, 16384 tiles in all: 3 heads
 // 59.8 | 42.7, 7 58.7 | 42.1, 40 57.3 | 41.8, 56 59.0 | 44.9, 98 54.3 | 44.2, 200 48.5 | 46.8; 4096 tiles: 7 heads 22.0 | 14.5,
-// 40 22.8 | 14.9, 130 22.5 | 17.8; per channel, 4 bits, g = 64, 40 heads 56.8 | 42.9; fp32, 7 heads 45.2 | 31.9.  (Up to a quarter of
+// 40 22.8 | 14.9, 130 22.5 | 17.8; 16 tiles a head, 24 heads 9.6 | 6.1, 56 11.4 | 7.1; per channel, 4 bits, g = 64, 40 heads 56.8 | 42.9; fp32, 7 heads 45.2 | 31.9.  (Up to a quarter of
 // the compute units stay idle so, 98 heads x 2; the launch is bound by the memory, which the others keep busy.)
 inline int spread_problems(QuantPlan& plan) {
-    int64_t per = static_cast<int64_t>(device_cu_count()) / plan.n_prob;
-    if (per > plan.units_per_prob) per = plan.units_per_prob;
-    if (per < 1) per = 1;
-    if (plan.n_prob * per > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
-    plan.wgs_per_prob = static_cast<int>(per);
+    const int64_t cus = device_cu_count(), tiles = plan.units_per_prob;
+    const auto within = [tiles](int64_t wgs) { return wgs > tiles ? tiles : (wgs < 1 ? 1 : wgs); };
+    const int64_t fill = within((cus + plan.n_prob - 1) / plan.n_prob), held = within(cus / plan.n_prob);
+    if (plan.n_prob * fill > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
+    plan.wgs_per_prob = static_cast<int>(held);
+    plan.wgs_to_fill = static_cast<int>(fill);
     return SQUAT_OK;
 }
 
