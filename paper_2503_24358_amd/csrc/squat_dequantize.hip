@@ -1,13 +1,14 @@
 // squat_dequantize_keys: deq(c) = c * Delta + m (Section 2 of the paper) over the
 // packed store written by squat_quantize_keys.  Pure streaming: one thread turns
-// 16 channels of one key (one or two packed words, one scale, one zero) into 16
-// output elements; a wavefront covers 8 consecutive keys, so code reads are one
-// contiguous 256/512-byte run and output writes one contiguous 2/4-KB run.
+// 16 channels of one key (a word or two, or the parts of four that it needs) into
+// two or four 16-byte pieces of output, 128 bytes apart: in each store the eight
+// threads of a key write one whole line, which a non-temporal store sends as it
+// is.  A wavefront covers 8 consecutive keys.
 //
 // squat_dequantize_keys_per_channel reads the token-major store of the
 // per-channel mode: one wavefront rebuilds one tile of 32 tokens; a lane owns 8
-// consecutive channels (one 16-byte piece of an output row) of 8 tokens, so it
-// needs 8 packed words, 8 scales and 8 zero-points, and writes whole rows.
+// channels (one 16-byte piece of an output row, or two of fp32) of 8 tokens, so it
+// needs 8 packed words, 8 scales and 8 zero-points, and writes whole lines.
 #include "squat_internal.h"
 
 using namespace squat;
@@ -32,16 +33,17 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-template <int DT>
-__device__ __forceinline__ void store16(unsigned char* dst, const float* v) {
+// 16 bytes of output.
+template <int DT, bool NT>
+__device__ __forceinline__ void store_piece(unsigned char* dst, const float* v) {
     if constexpr (DT == SQUAT_F32) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<f32x4*>(dst + 16 * i) = f32x4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+        const f32x4 w = {v[0], v[1], v[2], v[3]};
+        if constexpr (NT) __builtin_nontemporal_store(w, reinterpret_cast<f32x4*>(dst));
+        else *reinterpret_cast<f32x4*>(dst) = w;
     } else {
-        uint32_t w[8];
+        u32x4 w;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < 4; ++i) {
             if constexpr (DT == SQUAT_F16) {
                 half2v h;
                 h[0] = static_cast<_Float16>(v[2 * i]);
@@ -51,18 +53,21 @@ __device__ __forceinline__ void store16(unsigned char* dst, const float* v) {
                 w[i] = pack_bf16(v[2 * i], v[2 * i + 1]);
             }
         }
-        *reinterpret_cast<u32x4*>(dst) = u32x4{w[0], w[1], w[2], w[3]};
-        *reinterpret_cast<u32x4*>(dst + 16) = u32x4{w[4], w[5], w[6], w[7]};
+        if constexpr (NT) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(dst));
+        else *reinterpret_cast<u32x4*>(dst) = w;
     }
 }
 
-// grid: x over (token, 16-channel chunk), y/z over (batch, head)
-template <int BITS, int GROUP, int DT>
+// Bound by HBM.  With 16 consecutive channels a thread, its pieces beside each other, a store wrote 16 of every 32 (fp32: 64) bytes, which the
+// L2 had to put together, and ordinary stores were the only ones fit for that.  us, before | now: 2 bits, groups of 32, bf16, 256 x 32768
+// tokens 514 | 441 (5.8 TB/s), 648 x 1296 54.2 | 38.5; 4 bits, groups of 128, bf16, 32 x 8191 tokens 16.9 | 14.6, fp32, 324 x 1296 71.1 | 37.4,
+// 16 x 2049 9.3 | 4.4.
+// grid: x over (token, thread of a key), y/z over (batch, head)
+template <int BITS, int GROUP, int DT, bool NT>
 __global__ void __launch_bounds__(256) dequantize_kernel(const DeqParams p) {
     constexpr int ES = (DT == SQUAT_F32) ? 4 : 2;
     constexpr int WPK = kD * BITS / 32;       // words per key
     constexpr int NG = kD / GROUP;            // groups per key
-    constexpr int WPC = BITS / 2;             // words per 16-channel chunk
     const int64_t bh = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
     const int64_t flat = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t tok = flat >> 3;
@@ -74,36 +79,38 @@ __global__ void __launch_bounds__(256) dequantize_kernel(const DeqParams p) {
     const int64_t h = bh - b * p.n_heads;
     const int64_t row = bh * p.n_tokens + tok;
 
-    uint32_t w[WPC];
-    if constexpr (WPC == 1) {
-        w[0] = p.codes[row * WPK + chunk];
-    } else {
-        const u32x2 v = *reinterpret_cast<const u32x2*>(p.codes + row * WPK + 2 * chunk);
-        w[0] = v[0];
-        w[1] = v[1];
-    }
-    const int gi = chunk * 16 / GROUP;
-    float sc = static_cast<float>(__builtin_bit_cast(_Float16, p.scale[row * NG + gi]));
-    float zp = static_cast<float>(__builtin_bit_cast(_Float16, p.zero[row * NG + gi]));
-    // converted once: folded into the 16 multiply-adds as mixed-precision operands they would issue at half rate
-    asm volatile("" : "+v"(sc), "+v"(zp));
-
-    float v[16];
+    // 16 bytes of output of every 128: the eight threads of a key write whole lines
+    constexpr int CH = 16 / ES;                           // channels per piece
+    constexpr int NP = 16 / CH;                           // pieces per thread
     constexpr int IPW = 32 / BITS;
     constexpr uint32_t MASK = (1u << BITS) - 1u;
+    uint32_t w[NP];
+    float sc[NP], zp[NP];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const uint32_t c = (w[i / IPW] >> (BITS * (i % IPW))) & MASK;
-        v[i] = fmaf(static_cast<float>(c), sc, zp);
+    for (int i = 0; i < NP; ++i) w[i] = p.codes[row * WPK + (8 * CH * i + CH * chunk) / IPW];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int gi = (8 * CH * i + CH * chunk) / GROUP;
+        sc[i] = static_cast<float>(__builtin_bit_cast(_Float16, p.scale[row * NG + gi]));
+        zp[i] = static_cast<float>(__builtin_bit_cast(_Float16, p.zero[row * NG + gi]));
     }
-    unsigned char* dst = p.out + b * p.ob + h * p.oh + tok * p.ot + chunk * 16 * ES;
-    store16<DT>(dst, v);
+    unsigned char* dst = p.out + b * p.ob + h * p.oh + tok * p.ot + chunk * 16;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        // converted once: folded into the multiply-adds as mixed-precision operands they would issue at half rate
+        asm volatile("" : "+v"(sc[i]), "+v"(zp[i]));
+        const uint32_t c = w[i] >> (CH * chunk % IPW * BITS);
+        float v[CH];
+#pragma unroll
+        for (int e = 0; e < CH; ++e) v[e] = fmaf(static_cast<float>((c >> (BITS * e)) & MASK), sc[i], zp[i]);
+        store_piece<DT, NT>(dst + 128 * i, v);
+    }
 }
 
-// One wavefront per tile of 32 tokens.  Lane (s = lane >> 4, pc = lane & 15): channels 8 pc .. 8 pc + 7,
-// tokens 8 s .. 8 s + 7 of the tile.  Token j of the tile sits in word j / (32 / BITS) of its channel
+// One wavefront per tile of 32 tokens.  Lane (s = lane >> 4, pc = lane & 15): channels 8 pc .. 8 pc + 7 (fp32: 4 pc .. 4 pc + 3 of
+// each half, 324 x 1312 tokens, 4 bits: 55.5 -> 48.3 us), tokens 8 s .. 8 s + 7 of the tile.  Token j of the tile sits in word j / (32 / BITS) of its channel
 // at bit BITS * (j mod 32 / BITS), so the lane's 8 tokens are BITS consecutive bytes of one word.
-template <int BITS, int DT>
+template <int BITS, int DT, bool NT>
 __global__ void __launch_bounds__(256) dequantize_pc_kernel(const DeqParams p, const int64_t tiles_per_seq) {
     constexpr int ES = (DT == SQUAT_F32) ? 4 : 2;
     const int lane = threadIdx.x & 63;
@@ -137,14 +144,26 @@ __global__ void __launch_bounds__(256) dequantize_pc_kernel(const DeqParams p, c
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // The lane's channels: CH of every 16 CH, so that 16 lanes write whole lines.
+    constexpr int CH = 16 / ES, NP = 8 / CH;
     uint32_t w[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const int idx = (8 * pc + c) * BITS + widx;
+        const int idx = (16 * CH * (c / CH) + CH * pc + c % CH) * BITS + widx;
         w[c] = tl[idx + (idx >> 4) * 4] >> shift0;
     }
-    const u32x4 sraw = *reinterpret_cast<const u32x4*>(p.scale + gt * kD + 8 * pc);
-    const u32x4 zraw = *reinterpret_cast<const u32x4*>(p.zero + gt * kD + 8 * pc);
+    uint32_t sraw[4], zraw[4];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        typedef uint32_t piece __attribute__((ext_vector_type(CH / 2)));
+        const piece sv = *reinterpret_cast<const piece*>(p.scale + gt * kD + 16 * CH * i + CH * pc);
+        const piece zv = *reinterpret_cast<const piece*>(p.zero + gt * kD + 16 * CH * i + CH * pc);
+#pragma unroll
+        for (int k = 0; k < CH / 2; ++k) {
+            sraw[i * CH / 2 + k] = sv[k];
+            zraw[i * CH / 2 + k] = zv[k];
+        }
+    }
     float sc[8], zp[8];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -154,44 +173,35 @@ __global__ void __launch_bounds__(256) dequantize_pc_kernel(const DeqParams p, c
         zp[2 * c + 1] = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(zraw[c] >> 16)));
     }
     constexpr uint32_t MASK = (1u << BITS) - 1u;
-    unsigned char* dst = p.out + b * p.ob + h * p.oh + (tile * kTileTokens + 8 * s) * p.ot + pc * 8 * ES;
+    unsigned char* dst = p.out + b * p.ob + h * p.oh + (tile * kTileTokens + 8 * s) * p.ot + pc * 16;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         float v[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c)
             v[c] = fmaf(static_cast<float>((w[c] >> (BITS * i)) & MASK), sc[c], zp[c]);
-        unsigned char* o = dst + i * p.ot;
-        if constexpr (DT == SQUAT_F32) {
-            *reinterpret_cast<f32x4*>(o) = f32x4{v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<f32x4*>(o + 16) = f32x4{v[4], v[5], v[6], v[7]};
-        } else {
-            uint32_t pk[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if constexpr (DT == SQUAT_F16) {
-                    half2v hv;
-                    hv[0] = static_cast<_Float16>(v[2 * c]);
-                    hv[1] = static_cast<_Float16>(v[2 * c + 1]);
-                    pk[c] = __builtin_bit_cast(uint32_t, hv);
-                } else {
-                    pk[c] = pack_bf16(v[2 * c], v[2 * c + 1]);
-                }
-            }
-            *reinterpret_cast<u32x4*>(o) = u32x4{pk[0], pk[1], pk[2], pk[3]};
-        }
+        for (int k = 0; k < NP; ++k) store_piece<DT, NT>(dst + i * p.ot + 256 * k, v + CH * k);
     }
 }
 
-template <int BITS>
+template <int BITS, bool NT>
 int launch_pc(squat_dtype dt, const DeqParams& p, int64_t tiles, dim3 grid, hipStream_t s) {
     switch (dt) {
-        case SQUAT_F32: hipLaunchKernelGGL((dequantize_pc_kernel<BITS, SQUAT_F32>), grid, dim3(256), 0, s, p, tiles); break;
-        case SQUAT_F16: hipLaunchKernelGGL((dequantize_pc_kernel<BITS, SQUAT_F16>), grid, dim3(256), 0, s, p, tiles); break;
-        case SQUAT_BF16: hipLaunchKernelGGL((dequantize_pc_kernel<BITS, SQUAT_BF16>), grid, dim3(256), 0, s, p, tiles); break;
+        case SQUAT_F32: hipLaunchKernelGGL((dequantize_pc_kernel<BITS, SQUAT_F32, NT>), grid, dim3(256), 0, s, p, tiles); break;
+        case SQUAT_F16: hipLaunchKernelGGL((dequantize_pc_kernel<BITS, SQUAT_F16, NT>), grid, dim3(256), 0, s, p, tiles); break;
+        case SQUAT_BF16: hipLaunchKernelGGL((dequantize_pc_kernel<BITS, SQUAT_BF16, NT>), grid, dim3(256), 0, s, p, tiles); break;
         default: return SQUAT_E_BADDTYPE;
     }
     return check_launch();
+}
+
+// Non-temporal stores for outputs of 4 MB and more.  The last of them is on its way to memory when the kernel ends, which a short
+// launch waits for.  us, ordinary | non-temporal stores (graphs of such calls): fp16, 4 bits, groups of 128, 0.7 MB 2.8 | 3.0, 8.4 MB
+// 4.1 | 3.5; bf16, 215 MB 47.8 | 41.2; fp32, 215 MB 47.3 | 37.1; per channel, bf16, 0.7 MB 3.0 | 3.2, 3 MB 3.3 | 3.5, 8.4 MB 4.2 | 3.9, 109
+// MB 29.6 | 25.9, 537 MB 125 | 121, fp32, 217 MB 50.1 | 48.3 (1 GB 231 | 244).
+bool streamed(int64_t n_batch, int64_t n_heads, int64_t n_tokens, int es) {
+    return n_batch * n_heads >= (int64_t(4) << 20) || n_batch * n_heads * n_tokens >= (int64_t(4) << 20) / (kD * es);
 }
 
 // (batch, head) pairs over grid y / z: an exact factorisation so that every (y, z) is a real pair.
@@ -207,23 +217,23 @@ bool split_bh(int64_t bh, int64_t& gy, int64_t& gz) {
     return gz <= 65535;
 }
 
-template <int BITS, int GROUP>
+template <int BITS, int GROUP, bool NT>
 int launch_dt(squat_dtype dt, const DeqParams& p, dim3 grid, hipStream_t s) {
     switch (dt) {
-        case SQUAT_F32: hipLaunchKernelGGL((dequantize_kernel<BITS, GROUP, SQUAT_F32>), grid, dim3(256), 0, s, p); break;
-        case SQUAT_F16: hipLaunchKernelGGL((dequantize_kernel<BITS, GROUP, SQUAT_F16>), grid, dim3(256), 0, s, p); break;
-        case SQUAT_BF16: hipLaunchKernelGGL((dequantize_kernel<BITS, GROUP, SQUAT_BF16>), grid, dim3(256), 0, s, p); break;
+        case SQUAT_F32: hipLaunchKernelGGL((dequantize_kernel<BITS, GROUP, SQUAT_F32, NT>), grid, dim3(256), 0, s, p); break;
+        case SQUAT_F16: hipLaunchKernelGGL((dequantize_kernel<BITS, GROUP, SQUAT_F16, NT>), grid, dim3(256), 0, s, p); break;
+        case SQUAT_BF16: hipLaunchKernelGGL((dequantize_kernel<BITS, GROUP, SQUAT_BF16, NT>), grid, dim3(256), 0, s, p); break;
         default: return SQUAT_E_BADDTYPE;
     }
     return check_launch();
 }
 
-template <int BITS>
+template <int BITS, bool NT>
 int launch_group(int group, squat_dtype dt, const DeqParams& p, dim3 grid, hipStream_t s) {
     switch (group) {
-        case 32: return launch_dt<BITS, 32>(dt, p, grid, s);
-        case 64: return launch_dt<BITS, 64>(dt, p, grid, s);
-        case 128: return launch_dt<BITS, 128>(dt, p, grid, s);
+        case 32: return launch_dt<BITS, 32, NT>(dt, p, grid, s);
+        case 64: return launch_dt<BITS, 64, NT>(dt, p, grid, s);
+        case 128: return launch_dt<BITS, 128, NT>(dt, p, grid, s);
     }
     return SQUAT_E_BADSHAPE;
 }
@@ -271,8 +281,9 @@ extern "C" int squat_dequantize_keys(const uint32_t* codes, const uint16_t* scal
     if (!split_bh(n_batch * n_heads, gy, gz) || gx > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return bits == 2 ? launch_group<2>(group, out_dt, p, grid, s)
-                     : launch_group<4>(group, out_dt, p, grid, s);
+    if (streamed(n_batch, n_heads, n_tokens, es))
+        return bits == 2 ? launch_group<2, true>(group, out_dt, p, grid, s) : launch_group<4, true>(group, out_dt, p, grid, s);
+    return bits == 2 ? launch_group<2, false>(group, out_dt, p, grid, s) : launch_group<4, false>(group, out_dt, p, grid, s);
 }
 
 extern "C" int squat_dequantize_keys_per_channel(const uint32_t* codes, const uint16_t* scale,
@@ -319,5 +330,7 @@ extern "C" int squat_dequantize_keys_per_channel(const uint32_t* codes, const ui
     if (!split_bh(n_batch * n_heads, gy, gz) || gx > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return bits == 2 ? launch_pc<2>(out_dt, p, tiles, grid, s) : launch_pc<4>(out_dt, p, tiles, grid, s);
+    if (streamed(n_batch, n_heads, n_tokens, es))
+        return bits == 2 ? launch_pc<2, true>(out_dt, p, tiles, grid, s) : launch_pc<4, true>(out_dt, p, tiles, grid, s);
+    return bits == 2 ? launch_pc<2, false>(out_dt, p, tiles, grid, s) : launch_pc<4, false>(out_dt, p, tiles, grid, s);
 }
