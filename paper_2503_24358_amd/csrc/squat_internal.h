@@ -40,6 +40,18 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // number of tokens per head so; word by word against this, 2-bit, groups of 32, GQA 4, us: 64 x 8 x 2081 tokens 33.9 ->
 // 19.5, 32 x 32 x 4097 130.6 -> 83.3, 1 x 8 x 32767 10.2 -> 8.3; rotary keys 62.1 -> 28.4, 223 -> 99, 18.0 -> 12.1.
 typedef uint32_t u32x4_dwords __attribute__((ext_vector_type(4), aligned(4)));
+// At a multiple of 2 (compute on gfx950 runs with unaligned access on): groups of 128, whose scales are 2 bytes a token.  Word by word against
+// this, us: 2 bits, 252 x 10541 tokens, 2 query heads 52.2 -> 34.6, rotary keys 91.8 -> 59.0, 4 bits 91.5 -> 55.2 and 94.8 -> 69.1; 64 x 8 x
+// 2081, 4 query heads 28.7 -> 20.6, rotary keys 61.1 -> 30.9; 1 x 8 x 32767, 8 query heads, rotary keys 20.2 -> 14.5.
+typedef uint32_t u32x4_halves __attribute__((ext_vector_type(4), aligned(2)));
+template <int NG>                                         // groups per key
+struct StorePiece {
+    typedef u32x4_dwords type;
+};
+template <>
+struct StorePiece<1> {
+    typedef u32x4_halves type;
+};
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float as_f32(uint32_t u) { return __builtin_bit_cast(float, u); }

@@ -65,7 +65,6 @@ struct ScoreParams {
     int qpk;
     float out_scale;
     int units_per_wave;
-    int wide_loads;                  // rows of the store are 4-byte aligned: whole units are fetched with 16-byte loads
     ResidualKeys res;                // (RES kernels) logits of these keys by further workgroups
 };
 
@@ -124,8 +123,7 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
     // contiguous over the wavefront, kDepth units in flight.  Lanes left over after the codes and the metadata
     // repeat a neighbour's load and drop it into a spare LDS slot: no lane tests in the loop.
     const int n_full = n_tok / kUnitTokens;
-    int nf = 0;
-    if (p.wide_loads) nf = max(min(u1, n_full) - u0, 0) & ~1;
+    const int nf = max(min(u1, n_full) - u0, 0) & ~1;
     const int uf = u0 + nf;
     const int ml = BITS == 2 ? (lane - 32) & 31 : lane;   // index among the lanes that may load metadata
     const int mm = ml & (2 * MP - 1);
@@ -148,11 +146,12 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
         u32x4 m;
     };
     Raw ring[kDepth];
+    typedef typename StorePiece<NG>::type piece;
     auto fetch = [&](Raw& r) {
-        r.c = SC_LOAD(reinterpret_cast<const u32x4_dwords*>(gp));
+        r.c = SC_LOAD(reinterpret_cast<const piece*>(gp));
         gp += gstep;
         if constexpr (BITS == 4) {
-            r.m = SC_LOAD(reinterpret_cast<const u32x4_dwords*>(mptr));
+            r.m = SC_LOAD(reinterpret_cast<const piece*>(mptr));
             mptr += kUnitTokens * 2 * NG;
         }
     };
@@ -405,9 +404,8 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
         }
     }
 
-    // ---- what is left: a single unit after the pairs, the ragged end of the sequence, or everything when the
-    // store's rows are not aligned for the wide loads.  Every lane fetches for itself; rows past the end of the
-    // keys re-read the last key and are not stored.
+    // ---- what is left: a single unit after the pairs and the ragged end of the sequence.  Every lane fetches for
+    // itself; rows past the end of the keys re-read the last key and are not stored.
     {
         const int sl = BITS == 2 ? lane - 32 : lane;          // index among the lanes that load metadata
         const bool is_c = lane < CL, is_m = sl >= 0 && sl < 32;
@@ -526,10 +524,6 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
     p.res = ResidualKeys{};
-    {
-        const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
-        p.wide_loads = (store_stride * meta_row) % 4 == 0;    // the bases are 8-byte aligned
-    }
 
     const int64_t n_units = (n_tokens + kUnitTokens - 1) / kUnitTokens;
     // Workgroups along the sequence: about kScoreWaves * aim units each, the count rounded to

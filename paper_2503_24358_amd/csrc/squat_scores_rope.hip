@@ -64,7 +64,6 @@ struct RopeParams {
     int qpk;
     float out_scale;
     int units_per_wave;
-    int wide_loads;                  // per-token store: rows 4-byte aligned, whole units fetched with 16-byte loads
     bool lines;                      // per-token store: logits by non-temporal stores
 };
 
@@ -278,8 +277,7 @@ key_scores_rope_kernel(const RopeParams p) {
     constexpr int SPARE = META0 + 256;
     constexpr int TILE = SPARE + kWave * 16;
     const int n_full = n_tok / kRopeUnit;
-    int nf = 0;
-    if (p.wide_loads) nf = max(min(u1, n_full) - u0, 0) & ~1;
+    const int nf = max(min(u1, n_full) - u0, 0) & ~1;
     const int uf = u0 + nf;
     const int ml = BITS == 2 ? (lane - 32) & 31 : lane;   // index among the lanes that may load metadata
     const int mm = ml & (2 * MP - 1);
@@ -301,11 +299,12 @@ key_scores_rope_kernel(const RopeParams p) {
         u32x4 m;
     };
     Raw ring[kEpochUnits];
+    typedef typename StorePiece<NG>::type piece;
     auto fetch = [&](Raw& r) {
-        r.c = RP_LOAD(reinterpret_cast<const u32x4_dwords*>(gp));
+        r.c = RP_LOAD(reinterpret_cast<const piece*>(gp));
         gp += gstep;
         if constexpr (BITS == 4) {
-            r.m = RP_LOAD(reinterpret_cast<const u32x4_dwords*>(mptr));
+            r.m = RP_LOAD(reinterpret_cast<const piece*>(mptr));
             mptr += kRopeUnit * 2 * NG;
         }
     };
@@ -500,9 +499,8 @@ key_scores_rope_kernel(const RopeParams p) {
         }
     }
 
-    // ---- what is left: a single unit after the pairs, the ragged end of the sequence, or everything when the
-    // store's rows are not aligned for the wide loads.  Every lane fetches for itself; rows past the end of the
-    // keys re-read the last key and are not stored.
+    // ---- what is left: a single unit after the pairs and the ragged end of the sequence.  Every lane fetches for
+    // itself; rows past the end of the keys re-read the last key and are not stored.
     {
         const int sl = BITS == 2 ? lane - 32 : lane;          // index among the lanes that load metadata
         const bool is_c = lane < CL, is_m = sl >= 0 && sl < 32;
@@ -834,10 +832,6 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
     p.n_kv_heads = n_kv_heads;
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
-    {
-        const int64_t meta_row = 2 * (128 / group);       // bytes of scales (or zero-points) per key
-        p.wide_loads = (store_stride * meta_row) % 4 == 0;    // the bases are 8-byte aligned
-    }
     // Rows off the lines: ordinary stores, except for 5 to 18 MB of logits.  us with non-temporal | ordinary stores, 2 bits, heads of
     // about 2050 tokens (medians of 15 graphs of 20 calls on four sets of buffers in turn; their spread is 1 %, 3 % from 16 MB on):
     // 8 query heads per KV head, 2 MB 9.0 | 8.6, 4 MB 11.5 | 11.3, 5.6 MB 11.6 | 11.8, 8 MB 14.4 | 15.1, 11 MB 17.7 | 18.9, 16 MB 20.6 |
@@ -937,7 +931,6 @@ int squat::key_scores_pc_rope_from(const uint32_t* codes, const uint16_t* scale,
     int64_t tpw = (n_tiles + kRopeWaves * gx - 1) / (kRopeWaves * gx);
     if (tpw < kRopeMinUnitsPerWave / 2) tpw = kRopeMinUnitsPerWave / 2;
     tpw += tpw & 1;                                       // whole epochs of two tiles
-    p.wide_loads = 0;
     p.units_per_wave = static_cast<int>(tpw);
     gx = (n_tiles + kRopeWaves * tpw - 1) / (kRopeWaves * tpw);
     const int64_t bh = n_batch * n_kv_heads;
