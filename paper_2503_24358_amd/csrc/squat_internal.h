@@ -149,6 +149,36 @@ int key_scores_pc_rope_from(const uint32_t* codes, const uint16_t* scale, const 
                             int64_t s_stride_batch, int64_t s_stride_head, squat_stream stream);
 
 #if defined(__HIPCC__)
+// Logits: 4 consecutive channels of a query head, thread by thread over the KV head's queries (256 threads, 8 x 128 values).  Asked for in
+// front of the first keys: loads come back in order, so that what is needed first is not behind the keys, which come from
+// memory.
+template <int QDT>
+struct QueryPiece {
+    u32x4 raw;
+    int row, ch;
+    bool live;                                            // a row of this KV head
+    template <class Params>
+    __device__ __forceinline__ QueryPiece(const Params& p, int64_t b, int kvh) {
+        const int e0 = 4 * static_cast<int>(threadIdx.x);
+        row = e0 / kD;
+        ch = e0 % kD;
+        live = row < p.qpk;
+        // (a row of another head's place reads the last one; a load under a condition would be waited for there)
+        const int64_t off = b * p.qsb + (static_cast<int64_t>(kvh) * p.qpk + (live ? row : p.qpk - 1)) * p.qsh + ch;
+        if constexpr (QDT == SQUAT_F32) {
+            raw = *reinterpret_cast<const u32x4*>(p.q + off * 4);
+        } else {
+            const u32x2 t = *reinterpret_cast<const u32x2*>(p.q + off * 2);
+            raw = u32x4{t[0], t[1], 0u, 0u};
+        }
+    }
+    __device__ __forceinline__ float value(int i) const {
+        if constexpr (QDT == SQUAT_F32) return as_f32(raw[i]);
+        const uint32_t h = (i & 1) ? (raw[i >> 1] >> 16) : (raw[i >> 1] & 0xFFFFu);
+        return QDT == SQUAT_BF16 ? as_f32(h << 16) : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h)));
+    }
+};
+
 // cos and sin of position * freq: the product is reduced to a fraction of a turn in fp64 first
 __device__ __forceinline__ void turn_sincos(double position, float freq, float& c, float& s) {
     const double turns = position * static_cast<double>(freq) * 0.15915494309189535;   // / (2 pi)

@@ -145,6 +145,7 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
         u32x4 c;
         u32x4 m;
     };
+    const QueryPiece<QDT> qp(p, b, kvh);
     Raw ring[kDepth];
     typedef typename StorePiece<NG>::type piece;
     auto fetch = [&](Raw& r) {
@@ -166,27 +167,9 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
     // lane: vector-memory instructions are what this kernel runs out of first)
     constexpr int QLD = kD + 1;                           // row stride in floats (odd: spreads the banks)
     __shared__ float qlds[8 * QLD];
-    {
-        const int e0 = 4 * static_cast<int>(threadIdx.x);            // 4 consecutive channels of one query head
-        const int qrow = e0 / kD, qch = e0 % kD;
-        if (qrow < p.qpk) {
-            const int64_t qoff = b * p.qsb + (static_cast<int64_t>(kvh) * p.qpk + qrow) * p.qsh + qch;
-            float v[4];
-            if constexpr (QDT == SQUAT_F32) {
-                const f32x4 t = *reinterpret_cast<const f32x4*>(p.q + qoff * 4);
-                v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
-            } else {
-                const u32x2 t = *reinterpret_cast<const u32x2*>(p.q + qoff * 2);
+    if (qp.live) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t raw = (i & 1) ? (t[i >> 1] >> 16) : (t[i >> 1] & 0xFFFFu);
-                    v[i] = QDT == SQUAT_BF16 ? as_f32(raw << 16)
-                                             : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(raw)));
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) qlds[qrow * QLD + qch + i] = v[i];
-        }
+        for (int i = 0; i < 4; ++i) qlds[qp.row * QLD + qp.ch + i] = qp.value(i);
     }
     __syncthreads();
 

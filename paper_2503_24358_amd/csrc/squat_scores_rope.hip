@@ -113,12 +113,18 @@ __device__ __forceinline__ h2 rotate_pair(h2 x, h2 cs) {
 __device__ __forceinline__ int freq_slot(int f) { return ((f >> 3) & 3) * 16 + (f >> 5) * 8 + (f & 7); }
 
 // Fills the key-side table trig[l][slot(f)] = (cos, sin)(l * inv_freq[f]) and step64[f] = (cos, sin)(64 inv_freq[f]).
-// 256 threads; thread (f, quarter) covers l = 16 quarter .. + 15 by the addition theorems from an fp64-reduced start.
-__device__ __forceinline__ void fill_trig_tables(const float* inv_freq, uint32_t* trig, float* step64) {
+// 256 threads; thread (f, quarter), with fr = inv_freq[f], covers l = 16 quarter .. + 15 by the addition theorems from an fp64-reduced start.
+__device__ __forceinline__ void fill_trig_tables(const float fr, uint32_t* trig, float* step64) {
     const int f = threadIdx.x & 63, quarter = threadIdx.x >> 6;
-    const float fr = inv_freq[f];
     float c, s, c1, s1;
-    turn_sincos(static_cast<double>(16 * quarter), fr, c, s);
+    // (the first quarter starts at no angle: it takes the step's instead, so that no wavefront reduces a third one)
+    turn_sincos(static_cast<double>(quarter == 0 ? kEpochTokens : 16 * quarter), fr, c, s);
+    if (quarter == 0) {
+        step64[2 * f] = c;
+        step64[2 * f + 1] = s;
+        c = 1.0f;
+        s = 0.0f;
+    }
     turn_sincos(1.0, fr, c1, s1);
     const int slot = freq_slot(f);
 #pragma unroll 4
@@ -127,12 +133,6 @@ __device__ __forceinline__ void fill_trig_tables(const float* inv_freq, uint32_t
         const float c2 = fmaf(c, c1, -(s * s1));
         s = fmaf(s, c1, c * s1);
         c = c2;
-    }
-    if (quarter == 0) {
-        float ce, se;
-        turn_sincos(static_cast<double>(kEpochTokens), fr, ce, se);
-        step64[2 * f] = ce;
-        step64[2 * f + 1] = se;
     }
 }
 
@@ -151,15 +151,39 @@ struct QuerySide {
     const float* step;           // (cos, sin) of one epoch's rotation (64 positions) per frequency, LDS
     int f0;                      // first frequency of this lane
 
-    __device__ __forceinline__ void init(const float* qlds, int qld, const float* step64, const float* inv_freq,
+    __device__ __forceinline__ void init(const float* qlds, int qld, const float* step64, float freq,
                                          double position, int lane, int qpk, uint32_t* atile) {
         (void)qpk;
         const int h = WIDE ? lane >> 3 : lane >> 4;
         f0 = WIDE ? 8 * (lane & 7) : 4 * (lane & 15);
         qrow = qlds + h * qld;
         step = step64;
+        // A frequency a lane, handed round through the exchange tile (several lanes hold each: 4 and 8 angles a lane were reduced
+        // before).  With the tables' third angle gone and the queries asked for in front of the keys, per-token store, 2 bits, 4 | 8 query
+        // heads, us: 1 x 8 x 32768 tokens 11.2 -> 10.8 | 12.8 -> 11.9, x 4096 6.75 -> 6.4, 64 x 8 x 2080 31.4 -> 30.5; per-channel store, 1 x 8 x
+        // 32768 11.6 -> 11.2 | 13.2 -> 12.2.
+        {
+            float c, s;
+            turn_sincos(position, freq, c, s);
+            float* ex = reinterpret_cast<float*>(atile);
+            ex[lane] = c;
+            ex[kWave + lane] = s;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int i = 0; i < NF; ++i) turn_sincos(position, inv_freq[f0 + i], ce[i], se[i]);
+            for (int i = 0; i < NF; i += 4) {
+                const f32x4 cv = *reinterpret_cast<const f32x4*>(ex + f0 + i), sv = *reinterpret_cast<const f32x4*>(ex + kWave + f0 + i);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    ce[i + k] = cv[k];
+                    se[i + k] = sv[k];
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
         // rows that `build` never writes (query heads past 4 in the narrow form) must read as zero
         for (int idx = lane; idx < 16 * kATileLd; idx += kWave) atile[idx] = 0u;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -212,29 +236,11 @@ struct QuerySide {
     }
 };
 
-// Loads the KV head's queries into LDS as fp32 (rows past q_per_kv zero).  256 threads, 8 x 128 values.
+// The KV head's queries to LDS as fp32 (rows past q_per_kv zero).
 template <int QDT>
-__device__ __forceinline__ void stage_queries(const RopeParams& p, int64_t b, int kvh, float* qlds, int qld) {
-    const int e0 = 4 * static_cast<int>(threadIdx.x);
-    const int qrow = e0 / kD, qch = e0 % kD;
-    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (qrow < p.qpk) {
-        const int64_t qoff = b * p.qsb + (static_cast<int64_t>(kvh) * p.qpk + qrow) * p.qsh + qch;
-        if constexpr (QDT == SQUAT_F32) {
-            const f32x4 t = *reinterpret_cast<const f32x4*>(p.q + qoff * 4);
-            v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
-        } else {
-            const u32x2 t = *reinterpret_cast<const u32x2*>(p.q + qoff * 2);
+__device__ __forceinline__ void stage_queries(const QueryPiece<QDT>& qp, float* qlds, int qld) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t raw = (i & 1) ? (t[i >> 1] >> 16) : (t[i >> 1] & 0xFFFFu);
-                v[i] = QDT == SQUAT_BF16 ? as_f32(raw << 16)
-                                         : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(raw)));
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qlds[qrow * qld + qch + i] = v[i];
+    for (int i = 0; i < 4; ++i) qlds[qp.row * qld + qp.ch + i] = qp.live ? qp.value(i) : 0.0f;
 }
 
 // Per-token store.  Lane (kb = lane >> 4, col = lane & 15): token col of the unit, rotary pairs
@@ -298,6 +304,8 @@ key_scores_rope_kernel(const RopeParams p) {
         u32x4 c;
         u32x4 m;
     };
+    const QueryPiece<QDT> qp(p, b, kvh);
+    const float freq = p.inv_freq[lane];
     Raw ring[kEpochUnits];
     typedef typename StorePiece<NG>::type piece;
     auto fetch = [&](Raw& r) {
@@ -320,14 +328,14 @@ key_scores_rope_kernel(const RopeParams p) {
     __shared__ float step64[2 * 64];
     __shared__ __attribute__((aligned(16))) uint32_t trig[kEpochTokens * kTrigLd];
     __shared__ __attribute__((aligned(16))) uint32_t atiles[kRopeWaves * 16 * kATileLd];
-    stage_queries<QDT>(p, b, kvh, qlds, QLD);
-    fill_trig_tables(p.inv_freq, trig, step64);
+    stage_queries<QDT>(qp, qlds, QLD);
+    fill_trig_tables(freq, trig, step64);
     __syncthreads();
     if (u0 >= u1) return;                                 // after the last workgroup barrier
 
     uint32_t* atile = atiles + wave * 16 * kATileLd;
     QuerySide<WIDE> qs;
-    qs.init(qlds, QLD, step64, p.inv_freq, static_cast<double>(p.pos0 + static_cast<int64_t>(u0) * kRopeUnit), lane,
+    qs.init(qlds, QLD, step64, freq, static_cast<double>(p.pos0 + static_cast<int64_t>(u0) * kRopeUnit), lane,
             p.qpk, atile);
 
     // result rows 4 kb + {0, 1}: high and low part of query head kb; rows + {2, 3}: query head kb + 4
@@ -582,20 +590,22 @@ __global__ void __launch_bounds__(kRopeWaves* kWave) key_scores_pc_rope_kernel(c
         for (int i = 0; i < NCL; ++i) r.c[i] = RP_LOAD(reinterpret_cast<const u32x4*>(cw + (i * 64 + lane) * 4));
         r.m = RP_LOAD(reinterpret_cast<const u32x4*>(((lane & 16) ? p.zero : p.scale) + tile * kD + 8 * (lane & 15)));
     };
+    const QueryPiece<QDT> qp(p, b, kvh);
+    const float freq = p.inv_freq[lane];
 
     constexpr int QLD = kD + 1;
     __shared__ float qlds[8 * QLD];
     __shared__ float step64[2 * 64];
     __shared__ __attribute__((aligned(16))) uint32_t trig[kEpochTokens * kTrigLd];
     __shared__ __attribute__((aligned(16))) uint32_t atiles[kRopeWaves * 16 * kATileLd];
-    stage_queries<QDT>(p, b, kvh, qlds, QLD);
-    fill_trig_tables(p.inv_freq, trig, step64);
+    stage_queries<QDT>(qp, qlds, QLD);
+    fill_trig_tables(freq, trig, step64);
     __syncthreads();
     if (t0 >= t1) return;                                 // after the last workgroup barrier
 
     uint32_t* atile = atiles + wave * 16 * kATileLd;
     QuerySide<WIDE> qs;
-    qs.init(qlds, QLD, step64, p.inv_freq, static_cast<double>(p.pos0 + static_cast<int64_t>(t0) * 32), lane, p.qpk, atile);
+    qs.init(qlds, QLD, step64, freq, static_cast<double>(p.pos0 + static_cast<int64_t>(t0) * 32), lane, p.qpk, atile);
 
     // result rows 4 kb + {0, 1}: high and low part of query head kb; rows + {2, 3}: query head kb + 4
     constexpr bool two = WIDE;
