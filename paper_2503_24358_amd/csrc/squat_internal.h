@@ -237,12 +237,38 @@ int plan_quantize(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t n_toke
 int plan_quantize_pc(squat_dtype k_dt, int64_t n_batch, int n_heads, int64_t n_tokens, bool has_update,
                      int64_t update_stride_batch, int g, QuantPlan& out);
 
-// Units (of 16 tokens, or token groups) per wavefront that a logits launch aims at.  `most` amortises a wavefront's
+// Units of 16 tokens per wavefront that a per-token logits launch aims at.  `most` amortises a wavefront's
 // set-up and is taken while `sequences` of `units` units fill the chip with it; a launch with less work (few sequences)
 // spreads it over about `workgroups` workgroups instead, down to `least` units a wavefront.
 inline int64_t units_per_wave(int64_t units, int64_t sequences, int waves, int64_t workgroups, int64_t least, int64_t most) {
     const int64_t spread = (units * sequences + waves * workgroups - 1) / (waves * workgroups);
     return spread > most ? most : (spread < least ? least : spread);
+}
+
+// How the other logits launches deal out a sequence: its steps (epochs, pairs of token groups) go to `waves` x gx wavefronts, the i-th
+// of which takes the steps from deal.start(i) to deal.start(i + 1), the same number within one; the larger number ends with the
+// last wavefront (whose last step may be a part of one) or, `late` being false, the smaller.  With a multiple of a step
+// for every wavefront, rounded up, 8 sequences of 32800 tokens ran half as long again as of 32768.  us, so | dealt out (2 bits, 4 query
+// heads; rotary per channel, rotary, per channel): 8 x 32800 13.8 | 11.5, 12.7 | 10.9, 8.8 | 8.4; 8 x 4128 8.2 | 6.3, 8.0 | 6.3, 5.6 | 4.8; 58 x
+// 17472 39 | 33.5, 33 | 28.4, 20.4 | 20.1; 8 x 32768 and 90 x 4992 the same.  (The per-token kernel gains nothing and loses up to 6 % by more,
+// shorter workgroups: 256 x 1056 6.9 | 7.4.)
+struct Deal {
+    uint64_t mul;            // steps per wavefront, times 2^32, rounded up (late) or down
+    uint32_t add;            // 0, or 2^32 - 1
+#if defined(__HIPCC__)
+    __device__ __forceinline__ int start(uint32_t wavefront) const { return static_cast<int>((wavefront * mul + add) >> 32); }
+#endif
+};
+// `wanted` workgroups per sequence, but at least `least` steps a wavefront, and where there is more work than `most` steps a wavefront, which
+// amortise its set-up, as many as that makes.
+inline Deal deal_steps(int64_t steps, int64_t wanted, int waves, int64_t least, int64_t most, bool late, int64_t& gx) {
+    gx = wanted;
+    const int64_t full = (2 * steps + waves * most) / (2 * waves * most), room = (steps + waves * least - 1) / (waves * least);
+    gx = gx < full ? full : gx;
+    gx = gx > room ? room : gx;
+    gx = gx < 1 ? 1 : gx;
+    const uint64_t all = static_cast<uint64_t>(waves * gx);
+    return Deal{((static_cast<uint64_t>(steps) << 32) + (late ? all - 1 : 0)) / all, late ? 0u : 0xFFFFFFFFu};
 }
 
 // Number of compute units of the current device (256 if the query fails); a device is asked once per process.

@@ -34,7 +34,7 @@ namespace {
 constexpr int kPcDepth = 2;            // token groups whose loads are in flight per wavefront
 constexpr int kPcWaves = 4;
 constexpr int kPcTilesPerWave = 16;    // token groups a wavefront aims at (amortises its set-up) ...
-constexpr int kPcMinTilesPerWave = 2;  // ... unless that leaves the chip idle: then the launch is spread over
+// ... unless that leaves the chip idle: then the launch is spread over
 constexpr int kPcWorkgroups = 512;     // about this many workgroups (two per CU), down to one step a wavefront
 // Measured (2-bit, 8 KV heads x 4 query heads; us with 16 groups a wavefront | 256 workgroups | 512 | 1024 | 2048): 1
 // sequence of 1024 tokens 6.3 | 3.8 | 3.8 | 3.8 | 3.8; 1 of 4096 10.0 | 4.2 | 4.2 | 4.2 | 4.2; 1 of 32768 10.8 | 7.4 |
@@ -57,7 +57,7 @@ struct ScorePcParams {
     int n_kv_heads;
     int qpk;
     float out_scale;
-    int tiles_per_wave;
+    Deal deal;                       // steps of NT token groups
     ResidualKeys res;                // (RES kernels) logits of these keys by further workgroups
     int lines;                       // whole lines, or non-temporal stores pay all the same (host side)
 };
@@ -74,7 +74,7 @@ __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
     return v > o ? v : o;
 }
 
-// grid: x over slabs of kPcWaves * tiles_per_wave token groups, y / z over (batch, KV head); RES: and rows along y for the
+// grid: x over the wavefronts of a sequence (kPcWaves each), y / z over (batch, KV head); RES: and rows along y for the
 // full-precision keys (residual_rows), z = 0
 // NT = token groups per step.  With at most four query heads per KV head only 8 of the 16 operand rows
 // are in use, so NT = 2 gives rows 0..7 to one token group and rows 8..15 to the next one (same queries,
@@ -107,10 +107,11 @@ __global__ void __launch_bounds__(kPcWaves* kWave) key_scores_pc_kernel(const Sc
     const int64_t b = bh / p.n_kv_heads;
     const int kvh = static_cast<int>(bh - b * p.n_kv_heads);
 
-    // ---- this wavefront's token groups (tiles_per_wave is a multiple of NT); the loads of its first steps are
+    // ---- this wavefront's token groups (whole steps); the loads of its first steps are
     // issued before anything else, so that their latency overlaps the set-up of the query-side registers
-    const int t0 = (static_cast<int>(blockIdx.x) * kPcWaves + wave) * p.tiles_per_wave;
-    const int t1 = min(t0 + p.tiles_per_wave, p.n_tiles);
+    const uint32_t me = blockIdx.x * kPcWaves + wave;
+    const int t0 = NT * p.deal.start(me);
+    const int t1 = min(NT * p.deal.start(me + 1), p.n_tiles);
     const int64_t tile0 = bh * p.store_tiles;
     // loads per token group: lane L fetches the words of channels 2 L and 2 L + 1 (16 or 32 contiguous
     // bytes); metadata per step: 2 NT arrays of 128 halves (scales of group 0 (, 1), zero-points of group
@@ -504,18 +505,10 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     p.out_scale = out_scale;
     p.res = ResidualKeys{};
 
-    // workgroups along the sequence: about kPcWaves * aim token groups each, spread evenly
-    const int64_t n_tiles = p.n_tiles;
-    const int64_t aim = units_per_wave(n_tiles, n_batch * n_kv_heads, kPcWaves, kPcWorkgroups, kPcMinTilesPerWave, kPcTilesPerWave);
-    const int64_t slab = kPcWaves * aim;
-    int64_t gx = (n_tiles + slab / 2) / slab;
-    if (gx < 1) gx = 1;
-    int64_t tpw = (n_tiles + kPcWaves * gx - 1) / (kPcWaves * gx);
-    if (tpw < kPcMinTilesPerWave) tpw = kPcMinTilesPerWave;
     const bool two = q_per_kv <= 4;                       // two token groups per step (see the kernel)
-    if (two) tpw += tpw & 1;
-    p.tiles_per_wave = static_cast<int>(tpw);
-    gx = (n_tiles + kPcWaves * tpw - 1) / (kPcWaves * tpw);
+    const int nt = two ? 2 : 1;
+    int64_t gx;
+    p.deal = deal_steps((int64_t(p.n_tiles) + nt - 1) / nt, kPcWorkgroups / (n_batch * n_kv_heads), kPcWaves, 2 / nt, kPcTilesPerWave / nt, true, gx);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {

@@ -43,9 +43,15 @@ constexpr int kRopeUnit = 16;          // tokens per matrix product (MFMA N)
 // store 37.1 us with 64 workgroups of 64 units, 13.1 us with 256, 10.7 with 512, 12.5 with 1024; per-token store
 // 32.1 us, 12.0, 10.2, 12.4; with 4096 tokens 36.2 -> 6.0 and 30.8 -> 6.0 us; 512 sequences of 4096: no difference.
 constexpr int kRopeMaxUnitsPerWave = 64;
-constexpr int kRopeMinUnitsPerWave = 4;
 constexpr int kRopeWorkgroups = 512;
 constexpr int kRopeWaves = 4;
+// Workgroups of a sequence: as many as make no more than that.  Of more sequences than CUs, a sequence as two halves where the CUs with
+// most of them then have half a sequence less to do.
+inline int64_t rope_workgroups(int64_t sequences) {
+    constexpr int64_t cus = kRopeWorkgroups / 2;
+    if (sequences <= cus) return kRopeWorkgroups / sequences;
+    return sequences < 4 * cus && (2 * sequences + cus - 1) / cus < 2 * ((sequences + cus - 1) / cus) ? 2 : 1;
+}
 
 struct RopeParams {
     const uint32_t* codes;
@@ -63,7 +69,7 @@ struct RopeParams {
     int n_kv_heads;
     int qpk;
     float out_scale;
-    int units_per_wave;
+    Deal deal;                       // epochs
     bool lines;                      // per-token store: logits by non-temporal stores
 };
 
@@ -267,8 +273,9 @@ key_scores_rope_kernel(const RopeParams p) {
     // first units are issued before anything else: their latency overlaps the set-up of queries and tables.
     const int n_tok = static_cast<int>(p.n_tokens);
     const int n_units = (n_tok + kRopeUnit - 1) / kRopeUnit;
-    const int u0 = (static_cast<int>(blockIdx.x) * kRopeWaves + wave) * p.units_per_wave;
-    const int u1 = min(u0 + p.units_per_wave, n_units);
+    const uint32_t me = blockIdx.x * kRopeWaves + wave;
+    const int u0 = kEpochUnits * p.deal.start(me);
+    const int u1 = min(kEpochUnits * p.deal.start(me + 1), n_units);
     const int64_t row0 = bh * p.store_stride;
     // A unit's packed words (contiguous in memory) and its scales and zero-points (two contiguous runs of 32 NG
     // bytes) pass through a small per-wavefront LDS tile, as in the unrotated kernel: whole units with one 16-byte
@@ -556,7 +563,7 @@ key_scores_rope_kernel(const RopeParams p) {
 // units of 16 tokens (lane = token of the unit x K block, as above).  A rotary pair's two codes come from two
 // channels' words: one v_perm picks the byte that holds the lane's token from both, one v_and leaves the two codes
 // as fp16 subnormals at a lane-constant bit, one packed multiply by a lane-constant power of two normalises them.
-// p.n_tokens and p.store_stride are multiples of 32; p.units_per_wave counts TILES here (a multiple of 2).
+// p.n_tokens and p.store_stride are multiples of 32.
 template <int BITS, int QDT, bool WIDE>
 __global__ void __launch_bounds__(kRopeWaves* kWave) key_scores_pc_rope_kernel(const RopeParams p) {
     constexpr int TW = kD * BITS;                         // packed words per tile
@@ -574,8 +581,9 @@ __global__ void __launch_bounds__(kRopeWaves* kWave) key_scores_pc_rope_kernel(c
 
     // ---- this wavefront's tiles (whole epochs of two)
     const int n_tiles = static_cast<int>(p.n_tokens / 32);
-    const int t0 = (static_cast<int>(blockIdx.x) * kRopeWaves + wave) * p.units_per_wave;
-    const int t1 = min(t0 + p.units_per_wave, n_tiles);
+    const uint32_t me = blockIdx.x * kRopeWaves + wave;
+    const int t0 = 2 * p.deal.start(me);
+    const int t1 = min(2 * p.deal.start(me + 1), n_tiles);
     const int64_t tile0 = bh * (p.store_stride / 32);
     struct Raw {
         u32x4 c[NCL];
@@ -851,18 +859,11 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
     const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
     p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) || (out_bytes > (int64_t(5) << 20) && out_bytes < (int64_t(18) << 20));
 
-    // workgroups along the sequence: about kRopeWaves * aim units each, spread evenly
+    // whole epochs: a range starts where the query-side operand changes (units that are no pair are slow: not behind the larger number)
     const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit;
-    const int64_t aim = units_per_wave(n_units, n_batch * n_kv_heads, kRopeWaves, kRopeWorkgroups, kRopeMinUnitsPerWave,
-                                       kRopeMaxUnitsPerWave);
-    const int64_t slab = kRopeWaves * aim;
-    int64_t gx = (n_units + slab / 2) / slab;
-    if (gx < 1) gx = 1;
-    int64_t upw = (n_units + kRopeWaves * gx - 1) / (kRopeWaves * gx);
-    if (upw < kRopeMinUnitsPerWave) upw = kRopeMinUnitsPerWave;
-    upw = (upw + kEpochUnits - 1) / kEpochUnits * kEpochUnits;       // whole epochs: a range starts where the query-side operand changes
-    p.units_per_wave = static_cast<int>(upw);
-    gx = (n_units + kRopeWaves * upw - 1) / (kRopeWaves * upw);
+    int64_t gx;
+    p.deal = deal_steps((n_units + kEpochUnits - 1) / kEpochUnits, rope_workgroups(n_batch * n_kv_heads), kRopeWaves, 1,
+                        kRopeMaxUnitsPerWave / kEpochUnits, n_tokens % (2 * kRopeUnit) == 0, gx);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {
@@ -931,18 +932,10 @@ int squat::key_scores_pc_rope_from(const uint32_t* codes, const uint16_t* scale,
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
 
-    // workgroups along the sequence: about kRopeWaves * aim tiles (of two units) each, spread evenly
-    const int64_t n_tiles = n_tokens / group;
-    const int64_t aim = units_per_wave(n_tiles, n_batch * n_kv_heads, kRopeWaves, kRopeWorkgroups, kRopeMinUnitsPerWave / 2,
-                                       kRopeMaxUnitsPerWave / 2);
-    const int64_t slab = kRopeWaves * aim;
-    int64_t gx = (n_tiles + slab / 2) / slab;
-    if (gx < 1) gx = 1;
-    int64_t tpw = (n_tiles + kRopeWaves * gx - 1) / (kRopeWaves * gx);
-    if (tpw < kRopeMinUnitsPerWave / 2) tpw = kRopeMinUnitsPerWave / 2;
-    tpw += tpw & 1;                                       // whole epochs of two tiles
-    p.units_per_wave = static_cast<int>(tpw);
-    gx = (n_tiles + kRopeWaves * tpw - 1) / (kRopeWaves * tpw);
+    // whole epochs of two token groups
+    int64_t gx;
+    p.deal = deal_steps((n_tokens / group + 1) / 2, rope_workgroups(n_batch * n_kv_heads), kRopeWaves, 1,
+                        kRopeMaxUnitsPerWave / kEpochUnits, true, gx);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {
