@@ -17,11 +17,12 @@
 //   eig_tridiag_kernel  r <= 64: Householder tridiagonalisation, Sturm-count search
 //                 for the r largest eigenvalues, twisted factorisations (inverse iteration
 //                 for close eigenvalues), back-transformation with block reflectors
-//                 (squat_tridiag.h), one workgroup per KV head; flags a head whose result
-//                 fails its own residual checks.
+//                 (squat_tridiag.h), one workgroup per KV head; a head whose result
+//                 fails its own residual checks is redone by the Jacobi routine (r <= 32) or
+//                 flagged.
 //   eig_kernel    cyclic one-sided Jacobi in fp64 on the 128 x 128 Gram matrix in
 //                 LDS, one workgroup per KV head, then picks the r largest: r > 64, and
-//                 the heads the kernel above flagged.
+//                 the heads the kernel above or the block iteration flagged.
 #include "squat_internal.h"
 #include "squat_jacobi.h"
 #include "squat_tridiag.h"
@@ -541,13 +542,92 @@ constexpr int kEigTeam = 16;                    // lanes per row pair
 constexpr int kEigThreads = 64 * kEigTeam;
 constexpr int kEigLd = kD;       // rows are read with unit stride by consecutive lanes
 
+// The r largest eigenpairs of g by cyclic Jacobi, one workgroup of THREADS = 64 TEAM.
+template <int THREADS, int TEAM>
+__device__ __forceinline__ void jacobi_top_eigs(const double* g, int r, float* qhat, float* eig, int* sweeps_out, unsigned char* smem) {
+    double* A = reinterpret_cast<double*>(smem);                 // 128 x 128
+    double* nrm = A + kD * kEigLd;                               // 128
+    int* rank = reinterpret_cast<int*>(nrm + kD);                // 128
+    int* flag = rank + kD;
+    for (int i = threadIdx.x; i < kD * kD; i += THREADS) A[i] = g[i];
+    __syncthreads();
+    const int sweeps = jacobi_rows_resident<THREADS, TEAM, kD / TEAM>(A, kEigLd, nrm, flag, 60, 1e-13);
+    __syncthreads();
+    if (sweeps_out && threadIdx.x == 0) *sweeps_out = sweeps;
+
+    // eigenvalue of row i = its norm
+    for (int row = threadIdx.x >> 3; row < kD; row += THREADS / 8) {     // 8 lanes per row
+        const int tl = threadIdx.x & 7;
+        double s = 0.0;
+        for (int c = tl; c < kD; c += 8) s += A[row * kEigLd + c] * A[row * kEigLd + c];
+        s = team_sum<8>(s);
+        if (tl == 0) nrm[row] = sqrt(s);
+    }
+    __syncthreads();
+    if (threadIdx.x < kD) {
+        const int i = threadIdx.x;
+        const double ni = nrm[i];
+        int rk = 0;
+        for (int j = 0; j < kD; ++j) {
+            const double nj = nrm[j];
+            rk += (nj > ni) || (nj == ni && j < i);
+        }
+        rank[i] = rk;
+    }
+    __syncthreads();
+    // row i with rank < r  ->  qhat[rank] = row / sqrt(norm), sign: largest |component| positive
+    for (int row = threadIdx.x >> 3; row < kD; row += THREADS / 8) {
+        const int tl = threadIdx.x & 7;
+        const int rk = rank[row];
+        if (rk < r) {
+            double best = -1.0, bestv = 0.0;
+            int besti = kD;
+            for (int c = tl; c < kD; c += 8) {
+                const double v = A[row * kEigLd + c];
+                if (fabs(v) > best) { best = fabs(v); bestv = v; besti = c; }
+            }
+#pragma unroll
+            for (int off = 4; off > 0; off >>= 1) {
+                const double ob = __shfl_xor(best, off, 8);
+                const double ov = __shfl_xor(bestv, off, 8);
+                const int oi = __shfl_xor(besti, off, 8);
+                if (ob > best || (ob == best && oi < besti)) { best = ob; bestv = ov; besti = oi; }
+            }
+            const double lam = nrm[row];
+            const double sc = lam > 0.0 ? (bestv < 0.0 ? -1.0 : 1.0) / sqrt(lam) : 0.0;
+            float* dst = qhat + static_cast<int64_t>(rk) * kD;
+            for (int c = tl; c < kD; c += 8) dst[c] = static_cast<float>(A[row * kEigLd + c] * sc);
+            if (eig && tl == 0) eig[rk] = static_cast<float>(lam);
+        }
+    }
+}
+
+// need: NULL = every head; else only the heads with need[head] != 0
+__global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* g64, int r, float* qhat, float* eig,
+                                                          int* sweeps_out, const int* need) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if (need && need[blockIdx.x] == 0) return;
+    const int64_t kvh = blockIdx.x;
+    jacobi_top_eigs<kEigThreads, kEigTeam>(g64 + kvh * kD * kD, r, qhat + kvh * r * kD, eig ? eig + kvh * r : nullptr,
+                                           sweeps_out ? sweeps_out + kvh : nullptr, smem);
+}
+
+// A head that fails its checks is marked in need, and up to 32 directions redone by the Jacobi routine at once: a launch of its own for such
+// heads cost 1.0 to 1.5 us where there were none (one head 133.3 -> 131.7 us for the whole path, 8 x 4 heads of 8192 tokens 129.3 ->
+// 128.2).  More directions, which fail where the 33rd eigenvalue is not clear of the 32nd, keep that launch: its 1024 threads take 2.5 ms
+// to the 3.4 of these 256.
 __global__ void __launch_bounds__(kTriThreads) eig_tridiag_kernel(const double* g64, double* vws, int r, float* qhat,
                                                                   float* eig, int* need) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int64_t kvh = blockIdx.x;
-    const bool ok = tridiag_top_eigs(g64 + kvh * kD * kD, vws + kvh * kTriWsDoubles, r, qhat + kvh * r * kD,
-                                     eig ? eig + kvh * r : nullptr, reinterpret_cast<double*>(smem));
+    const double* g = g64 + kvh * kD * kD;
+    qhat += kvh * r * kD;
+    if (eig) eig += kvh * r;
+    const bool ok = tridiag_top_eigs(g, vws + kvh * kTriWsDoubles, r, qhat, eig, reinterpret_cast<double*>(smem));
     if (threadIdx.x == 0) need[kvh] = ok ? 0 : 1;
+    if (ok || r > kTriMaxR) return;                       // uniform
+    __syncthreads();
+    jacobi_top_eigs<kTriThreads, kTriThreads / 64>(g, r, qhat, eig, nullptr, smem);
 }
 
 // Block power iteration + Rayleigh-Ritz (squat_subiter.h), one workgroup per KV head; need[head] = 1 asks the
@@ -571,70 +651,6 @@ __global__ void __launch_bounds__(256) fill_float(float* p, int n, float v) {
     if (i < n) p[i] = v;
 }
 
-// need: NULL = every head; else only the heads with need[head] != 0
-__global__ void __launch_bounds__(kEigThreads) eig_kernel(const double* g64, int r, float* qhat, float* eig,
-                                                          int* sweeps_out, const int* need) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (need && need[blockIdx.x] == 0) return;
-    double* A = reinterpret_cast<double*>(smem);                 // 128 x 128
-    double* nrm = A + kD * kEigLd;                               // 128
-    int* rank = reinterpret_cast<int*>(nrm + kD);                // 128
-    int* flag = rank + kD;
-    const int kvh = blockIdx.x;
-    const double* g = g64 + static_cast<int64_t>(kvh) * kD * kD;
-    for (int i = threadIdx.x; i < kD * kD; i += kEigThreads) A[i] = g[i];
-    __syncthreads();
-    const int sweeps = jacobi_rows_resident<kEigThreads, kEigTeam, kD / kEigTeam>(A, kEigLd, nrm, flag, 60, 1e-13);
-    __syncthreads();
-    if (sweeps_out && threadIdx.x == 0) sweeps_out[kvh] = sweeps;
-
-    // eigenvalue of row i = its norm
-    for (int row = threadIdx.x >> 3; row < kD; row += kEigThreads / 8) {     // 8 lanes per row
-        const int tl = threadIdx.x & 7;
-        double s = 0.0;
-        for (int c = tl; c < kD; c += 8) s += A[row * kEigLd + c] * A[row * kEigLd + c];
-        s = team_sum<8>(s);
-        if (tl == 0) nrm[row] = sqrt(s);
-    }
-    __syncthreads();
-    if (threadIdx.x < kD) {
-        const int i = threadIdx.x;
-        const double ni = nrm[i];
-        int rk = 0;
-        for (int j = 0; j < kD; ++j) {
-            const double nj = nrm[j];
-            rk += (nj > ni) || (nj == ni && j < i);
-        }
-        rank[i] = rk;
-    }
-    __syncthreads();
-    // row i with rank < r  ->  qhat[rank] = row / sqrt(norm), sign: largest |component| positive
-    for (int row = threadIdx.x >> 3; row < kD; row += kEigThreads / 8) {
-        const int tl = threadIdx.x & 7;
-        const int rk = rank[row];
-        if (rk < r) {
-            double best = -1.0, bestv = 0.0;
-            int besti = kD;
-            for (int c = tl; c < kD; c += 8) {
-                const double v = A[row * kEigLd + c];
-                if (fabs(v) > best) { best = fabs(v); bestv = v; besti = c; }
-            }
-#pragma unroll
-            for (int off = 4; off > 0; off >>= 1) {
-                const double ob = __shfl_xor(best, off, 8);
-                const double ov = __shfl_xor(bestv, off, 8);
-                const int oi = __shfl_xor(besti, off, 8);
-                if (ob > best || (ob == best && oi < besti)) { best = ob; bestv = ov; besti = oi; }
-            }
-            const double lam = nrm[row];
-            const double sc = lam > 0.0 ? (bestv < 0.0 ? -1.0 : 1.0) / sqrt(lam) : 0.0;
-            float* dst = qhat + (static_cast<int64_t>(kvh) * r + rk) * kD;
-            for (int c = tl; c < kD; c += 8) dst[c] = static_cast<float>(A[row * kEigLd + c] * sc);
-            if (eig && tl == 0) eig[static_cast<int64_t>(kvh) * r + rk] = static_cast<float>(lam);
-        }
-    }
-}
-
 struct SubspacePlan {
     int wgs_per_head;
     size_t off_partial, off_g64, off_v, off_need, total;
@@ -653,7 +669,7 @@ SubspacePlan plan(int64_t n_tokens, int n_kv_heads, int q_per_kv, int cus) {
     pl.off_g64 = (partial + 255) & ~size_t(255);
     const size_t mat = static_cast<size_t>(n_kv_heads) * kD * kD * sizeof(double);
     pl.off_v = pl.off_g64 + mat;                               // Householder reflectors of every head, as matrix operands
-    pl.off_need = pl.off_v + static_cast<size_t>(n_kv_heads) * kTriWsDoubles * sizeof(double);   // per head: 1 = the Jacobi kernel must redo it
+    pl.off_need = pl.off_v + static_cast<size_t>(n_kv_heads) * kTriWsDoubles * sizeof(double);   // per head: 1 = redone by the Jacobi routine
     pl.total = pl.off_need + ((static_cast<size_t>(n_kv_heads) * sizeof(int) + 255) & ~size_t(255));
     return pl;
 }
@@ -671,6 +687,7 @@ extern "C" size_t squat_build_subspace_workspace(int64_t n_tokens, int n_kv_head
 namespace {
 
 constexpr size_t kEigLdsBytes = kD * kEigLd * sizeof(double) + kD * sizeof(double) + kD * sizeof(int) + 16;
+static_assert(kEigLdsBytes <= kTriLdsBytes, "the Jacobi routine works in the tridiagonal kernel's LDS");
 constexpr size_t kGramLdsBytes = 2 * kPartialFloats * sizeof(float);      // 80 KB
 constexpr size_t kGramLdsMost = kGramWaves * kPartialFloats * sizeof(float);   // 160 KB: a wavefront's sums each
 
@@ -788,15 +805,14 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
 // for larger r and for the heads that route flags.
 int run_exact_solver(const double* g64, int n_kv_heads, int r, float* qhat, float* eig, const SubspacePlan& pl, void* ws,
                      hipStream_t s) {
-    int rc = SQUAT_OK;
     int* need = nullptr;
     if (r <= 2 * kTriMaxR) {
         need = reinterpret_cast<int*>(static_cast<unsigned char*>(ws) + pl.off_need);
         double* vws = reinterpret_cast<double*>(static_cast<unsigned char*>(ws) + pl.off_v);
         hipLaunchKernelGGL(eig_tridiag_kernel, dim3(n_kv_heads), dim3(kTriThreads), kTriLdsBytes, s, g64, vws, r, qhat,
                            eig, need);
-        rc = check_launch();
-        if (rc) return rc;
+        const int rc = check_launch();
+        if (rc || r <= kTriMaxR) return rc;
     }
     hipLaunchKernelGGL(eig_kernel, dim3(n_kv_heads), dim3(kEigThreads), kEigLdsBytes, s, g64, r, qhat, eig,
                        static_cast<int*>(nullptr), static_cast<const int*>(need));

@@ -30,7 +30,7 @@
 //      in global memory while steps 2-4 use that LDS block).
 //
 // A matrix whose result fails the checks of step 4 (never seen with fp64, kept as
-// a safety net) is flagged and handed to the Jacobi kernel.  About 40 times fewer
+// a safety net) is handed to the Jacobi routine of squat_jacobi.h.  About 40 times fewer
 // floating-point operations than cyclic Jacobi on the full matrix.
 #pragma once
 
