@@ -272,14 +272,14 @@ int squat_quantize_keys(const void* k, squat_dtype k_dt, int64_t n_batch, int n_
  * tiles of 32 consecutive tokens of one (batch entry, head).  The tiles that
  * share an update matrix (a head's, over the whole batch, or one batch
  * entry's when update_stride_batch != 0) form a "problem"; each problem gets
- * W persistent workgroups whose wavefronts take tiles
- *     w, w + S, w + 2 S, ...     (w = wavefront_in_workgroup * W +
- *     workgroup_in_problem,  S = W * wavefronts_per_workgroup)
- * until tiles_per_problem is reached.  workgroups_per_problem is the number
- * that fills the device once (rounded up, at most one per tile); W is that
- * number where the workgroups of all problems fit the device at once, else
- * compute units / problems, rounded down (at least one).  A wavefront therefore
- * runs floor(tiles_per_problem / S) or one more tile, and a problem with fewer
+ * workgroups_per_problem persistent workgroups (compute units / problems,
+ * rounded down so that all of them fit the device at once, at least one and at
+ * most one per tile) whose wavefronts take tiles
+ *     w, w + S, w + 2 S, ...     (w = wavefront_in_workgroup *
+ *     workgroups_per_problem + workgroup_in_problem,
+ *     S = workgroups_per_problem * wavefronts_per_workgroup)
+ * until tiles_per_problem is reached.  A wavefront therefore runs
+ * floor(tiles_per_problem / S) or one more tile, and a problem with fewer
  * tiles than S leaves the higher-numbered wavefronts of every workgroup idle
  * rather than whole workgroups.
  *

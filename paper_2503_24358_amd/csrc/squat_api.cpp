@@ -32,7 +32,7 @@ extern "C" int squat_quantize_keys_plan(squat_dtype k_dt, int64_t n_batch, int n
     }
     if (rc) return rc;
     out->problems = plan.n_prob;
-    out->workgroups_per_problem = plan.wgs_to_fill;
+    out->workgroups_per_problem = plan.wgs_per_prob;
     out->wavefronts_per_workgroup = plan.waves;
     out->tiles_per_problem = plan.units_per_prob;
     return SQUAT_OK;

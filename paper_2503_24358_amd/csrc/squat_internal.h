@@ -210,7 +210,6 @@ struct QuantPlan {
     int64_t tiles_per_seq;
     int64_t units_per_prob;
     int wgs_per_prob;
-    int wgs_to_fill;         // the same without the bound by what the device holds at once
     int waves;
 };
 // Logits: result rows that begin on 64-byte lines are written by non-temporal stores (whole lines leave the chip once; 64 x 256 x 2080
@@ -294,11 +293,10 @@ inline int device_cu_count() {
 // the compute units stay idle so, 98 heads x 2; the launch is bound by the memory, which the others keep busy.)
 inline int spread_problems(QuantPlan& plan) {
     const int64_t cus = device_cu_count(), tiles = plan.units_per_prob;
-    const auto within = [tiles](int64_t wgs) { return wgs > tiles ? tiles : (wgs < 1 ? 1 : wgs); };
-    const int64_t fill = within((cus + plan.n_prob - 1) / plan.n_prob), held = within(cus / plan.n_prob);
-    if (plan.n_prob * fill > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
+    int64_t held = cus / plan.n_prob;
+    held = held > tiles ? tiles : (held < 1 ? 1 : held);
+    if (plan.n_prob * held > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
     plan.wgs_per_prob = static_cast<int>(held);
-    plan.wgs_to_fill = static_cast<int>(fill);
     return SQUAT_OK;
 }
 
