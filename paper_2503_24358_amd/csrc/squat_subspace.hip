@@ -42,11 +42,10 @@ struct GramParams {
     int64_t n_tokens;
     int q_per_kv;
     int wgs_per_head;
-    unsigned idle;               // FEWER: workgroups at the front of the grid that have no share
     int64_t chunks_per_qhead;    // ceil(n_tokens / 16)
     int64_t units_per_head;      // q_per_kv * chunks_per_qhead
     int64_t step_qh, step_c;     // from a wavefront's unit to its next one: query heads, chunks
-    int64_t pause;               // FEWER, > 0: the sums over the units before this one are put aside (all of LDS), see run_gram
+    int64_t pause;               // HALVES: the sums over the units before this one are put aside (all of LDS), see run_gram
     float* partial;              // [n_kv_heads][wgs_per_head][10][1024]
 };
 
@@ -152,19 +151,14 @@ __device__ __forceinline__ void reduce_and_store(f32x16 (&acc)[kTiles], unsigned
 }
 
 // Accumulate one workgroup's share of Q^T Q.  16-bit element types.
-template <int DT, bool FEWER>
+template <int DT, bool HALVES>
 __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const GramParams p) {
     typedef typename GramOps<DT>::op_t op_t;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, m = lane & 31;
-    unsigned block = blockIdx.x;
-    if constexpr (FEWER) {
-        if (block < p.idle) return;
-        block -= p.idle;
-    }
-    const int kvh = block / p.wgs_per_head;
-    const int wg = block % p.wgs_per_head;
+    const int kvh = blockIdx.x / p.wgs_per_head;
+    const int wg = blockIdx.x % p.wgs_per_head;
 
     f32x16 acc[kTiles];
 #pragma unroll
@@ -261,7 +255,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
             issue(ci, raw[i]);
             advance(ci);
         }
-        int64_t end = FEWER && p.pause > 0 ? p.pause : last_unit + 1;
+        int64_t end = HALVES ? p.pause : last_unit + 1;
         for (;;) {
             while (cc.u < end) {
 #pragma unroll
@@ -272,7 +266,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
                     advance(ci);
                 }
             }
-            if (!FEWER || end > last_unit) break;
+            if (!HALVES || end > last_unit) break;
             end = last_unit + 1;
             put_tiles<0, kTiles>(acc, aside, lane);
 #pragma unroll
@@ -280,11 +274,9 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
         }
-        if constexpr (FEWER)
-            if (p.pause > 0) add_tiles<0, kTiles>(acc, aside, lane);
+        if constexpr (HALVES) add_tiles<0, kTiles>(acc, aside, lane);
     }
-    if constexpr (FEWER)
-        if (p.pause > 0) __syncthreads();                // the places below are others' as well
+    if constexpr (HALVES) __syncthreads();               // the places below are others' as well
 
     reduce_and_store(acc, smem, wave, lane, p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats);
 }
@@ -292,18 +284,13 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_16(const G
 // fp32 inputs: products on the fp32 matrix cores (32x32x2), two tokens per step.
 // Bound by the matrix cores: 80 products of 64 cycles a chunk.  Positions kept as above, loads without conditions and two chunks
 // in flight (a division and a test per load, one chunk, before): 32 x 4 heads of 8192 tokens 202 -> 165 us (137 at 2.4 GHz).
-template <bool FEWER>
+template <bool HALVES>
 __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const GramParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, m = lane & 31;
-    unsigned block = blockIdx.x;
-    if constexpr (FEWER) {
-        if (block < p.idle) return;
-        block -= p.idle;
-    }
-    const int kvh = block / p.wgs_per_head;
-    const int wg = block % p.wgs_per_head;
+    const int kvh = blockIdx.x / p.wgs_per_head;
+    const int wg = blockIdx.x % p.wgs_per_head;
 
     f32x16 acc[kTiles];
 #pragma unroll
@@ -381,7 +368,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
             issue(ci, raw[i]);
             advance(ci);
         }
-        int64_t end = FEWER && p.pause > 0 ? p.pause : last_unit + 1;
+        int64_t end = HALVES ? p.pause : last_unit + 1;
         for (;;) {
             while (cc.u < end) {
 #pragma unroll
@@ -392,7 +379,7 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
                     advance(ci);
                 }
             }
-            if (!FEWER || end > last_unit) break;
+            if (!HALVES || end > last_unit) break;
             end = last_unit + 1;
             put_tiles<0, kTiles>(acc, aside, lane);
 #pragma unroll
@@ -400,11 +387,9 @@ __global__ void __launch_bounds__(kGramWaves * kWave, 1) gram_partial_f32(const 
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
         }
-        if constexpr (FEWER)
-            if (p.pause > 0) add_tiles<0, kTiles>(acc, aside, lane);
+        if constexpr (HALVES) add_tiles<0, kTiles>(acc, aside, lane);
     }
-    if constexpr (FEWER)
-        if (p.pause > 0) __syncthreads();                // the places below are others' as well
+    if constexpr (HALVES) __syncthreads();               // the places below are others' as well
 
     reduce_and_store(acc, smem, wave, lane, p.partial + (static_cast<int64_t>(kvh) * p.wgs_per_head + wg) * kPartialFloats);
 }
@@ -696,8 +681,8 @@ struct GramKernels {
     void (*f16)(GramParams);
     void (*f32)(GramParams);
 };
-GramKernels gram_kernels(bool fewer) {
-    return fewer ? GramKernels{gram_partial_16<SQUAT_BF16, true>, gram_partial_16<SQUAT_F16, true>, gram_partial_f32<true>}
+GramKernels gram_kernels(bool halves) {
+    return halves ? GramKernels{gram_partial_16<SQUAT_BF16, true>, gram_partial_16<SQUAT_F16, true>, gram_partial_f32<true>}
                  : GramKernels{gram_partial_16<SQUAT_BF16, false>, gram_partial_16<SQUAT_F16, false>, gram_partial_f32<false>};
 }
 
@@ -765,12 +750,12 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     } else if (n_kv_heads * wide <= 16) {
         wgs = narrow < room ? narrow : room;
     }
-    // Up to 128 heads: where that makes a few workgroups more than compute units, a head keeps as many as all hold at once, and the
-    // rest of the grid, at its front, leaves at once; in a second round those few would read their share alone.  Build of the
+    // Up to 128 heads: where that makes a few workgroups more than compute units, a head gets as many as all hold at once; in a
+    // second round those few would read their share alone.  Build of the
     // subspace, us, two rounds | one, 2^20 queries: bf16, 7 heads 187 | 160, 48 193 | 170; fp32, 7 heads 469 | 280, 48 442 | 299.  (More heads
     // than 128 would come down to one workgroup each: 130 bf16 199 | 197, 200 194 | 183, fp32 367 | 339, with longer sums.)
-    p.wgs_per_head = static_cast<int>(wgs > per_cu && per_cu > 1 ? per_cu : wgs);
-    p.idle = static_cast<unsigned>(n_kv_heads) * static_cast<unsigned>(wgs - p.wgs_per_head);
+    const bool fewer = wgs > per_cu && per_cu > 1;
+    p.wgs_per_head = static_cast<int>(fewer ? per_cu : wgs);
     p.chunks_per_qhead = (n_tokens + 15) / 16;
     p.units_per_head = p.chunks_per_qhead * q_per_kv;
     p.step_qh = static_cast<int64_t>(p.wgs_per_head) * kGramWaves / p.chunks_per_qhead;
@@ -778,21 +763,21 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     // The fewer workgroups' sums are longer, by up to a half; each is then made of two (workgroups of a head, 2-norm of the error of Qhat,
     // before | fewer | of two sums: 48 heads x 4 of 2000 tokens, r = 16, bf16 3.4e-8 | 3.6e-8 | 3.1e-8, fp32 5.7e-8 | 6.6e-8 | 4.3e-8; 100 x 4,
     // bf16 4.7e-8 | 6.3e-8 | 4.3e-8).
-    const bool halves = p.idle > 0 && p.wgs_per_head < 16;
+    const bool halves = fewer && p.wgs_per_head < 16;
     p.pause = halves ? p.units_per_head / 2 : 0;
     const size_t lds = halves ? kGramLdsMost : kGramLdsBytes;
     p.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + pl.off_partial);
-    const dim3 grid(static_cast<unsigned>(n_kv_heads) * p.wgs_per_head + p.idle);
-    const GramKernels k = gram_kernels(p.idle > 0);
+    const dim3 grid(static_cast<unsigned>(n_kv_heads) * p.wgs_per_head);
+    const GramKernels k = gram_kernels(halves);
     hipLaunchKernelGGL(q_dt == SQUAT_BF16 ? k.bf16 : q_dt == SQUAT_F16 ? k.f16 : k.f32, grid, dim3(kGramWaves * kWave), lds, s, p);
     int rc = check_launch();
     if (rc) return rc;
     // A workgroup per 256 entries where a head has several partials or there are few heads, else a workgroup per head, which has its
     // row of results to itself (the others write 8 bytes here and there).  Gram and reduction, us per head | spread (graphs of such
     // calls): bf16, 1 partial a head, 16 heads of 200 tokens 15.8 | 12.3, 24 14.1 | 13.0, 32 14.2 | 14.1, 40 14.5 | 15.3, 64 15.3 |
-    // 19.4, 256 of 512 21.3 | 37.4; 2 partials, 32 of 1024 18.2 | 16.4, 40 18.8 | 17.7, 48 19.5 | 19.3, 64 20.2 | 21.8.  (The lines are a
-    // little low: 32 and 48 would do.)
-    if (wgs >= 4 || n_kv_heads <= (wgs == 1 ? 24 : 32))
+    // 19.4, 256 of 512 21.3 | 37.4; 2 partials, 32 of 1024 18.2 | 16.4, 40 18.8 | 17.7, 48 19.5 | 19.3, 64 20.2 | 21.8; 3 partials, 65 x 4 of
+    // 2000 37.5 | 38.3, 85 of 4096 31.4 | 33.5.  (The lines are a little low: 32 and 48 would do.)
+    if (p.wgs_per_head >= 4 || n_kv_heads <= (p.wgs_per_head == 1 ? 24 : 32))
         hipLaunchKernelGGL(gram_reduce_tiles, dim3(kRedTileBlocks, static_cast<unsigned>(n_kv_heads)), dim3(kRedTileThreads), 0, s, p.partial,
                            p.wgs_per_head, g64, gram_out, accumulate);
     else

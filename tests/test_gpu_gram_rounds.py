@@ -1,5 +1,5 @@
-"""Gram matrices of head counts that do not divide the compute units: the launch's first workgroups have no share, and where the
-others' sums become much longer each is made of two (48 and 100 heads; not 7).  Against float64.
+"""Gram matrices of head counts that do not divide the compute units: a head gets as many workgroups as all hold at once, and where
+their sums become much longer than those of the rounded-up number each is made of two (48 and 100 heads; not 7).  Against float64.
 
 A wavefront adds at most 8 products (of 2 tokens; 16-bit: one of 16) per chunk of 16 tokens to a sum, each addition off by at most
 2^-23 of it (the 16-bit matrix cores truncate), and the sums of a diagonal entry only grow: the bound, which holds for the
