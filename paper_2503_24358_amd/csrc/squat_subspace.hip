@@ -761,14 +761,15 @@ int run_gram(const void* q, squat_dtype q_dt, int64_t n_tokens, int n_kv_heads, 
     p.step_qh = static_cast<int64_t>(p.wgs_per_head) * kGramWaves / p.chunks_per_qhead;
     p.step_c = static_cast<int64_t>(p.wgs_per_head) * kGramWaves % p.chunks_per_qhead;
     // The fewer workgroups' sums are longer, by up to a half; each is then made of two (workgroups of a head, 2-norm of the error of Qhat,
-    // before | fewer | of two sums: 48 heads x 4 of 2000 tokens, r = 16, bf16 3.4e-8 | 3.6e-8 | 3.1e-8, fp32 5.7e-8 | 6.6e-8 | 4.3e-8; 100 x 4,
-    // bf16 4.7e-8 | 6.3e-8 | 4.3e-8).
-    const bool halves = fewer && p.wgs_per_head < 16;
-    p.pause = halves ? p.units_per_head / 2 : 0;
-    const size_t lds = halves ? kGramLdsMost : kGramLdsBytes;
+    // rounded up | fewer | of two sums: 48 heads x 4 of 2000 tokens, r = 16, bf16 3.4e-8 | 3.6e-8 | 3.1e-8, fp32 5.7e-8 | 6.6e-8 | 4.3e-8; 100 x 4,
+    // bf16 4.7e-8 | 6.3e-8 | 4.3e-8; of Qhat'Qhat, x 4 of 8192 tokens, 13 heads, bf16 6.5e-8 | 6.6e-8 | 5.7e-8, 15, fp32 6.9e-8 | 7.0e-8 |
+    // 5.8e-8).  The second sum costs 0.8 to 2.5 us (Gram and reduction, us, rounded up | fewer | of two sums: 5 heads x 4 of 8192, bf16 29.3 |
+    // 20.0 | 21.6, fp32 66.5 | 41.3 | 43.9; 15, bf16 46.2 | 32.2 | 33.0, fp32 169 | 92.4 | 92.9).
+    p.pause = fewer ? p.units_per_head / 2 : 0;
+    const size_t lds = fewer ? kGramLdsMost : kGramLdsBytes;
     p.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + pl.off_partial);
     const dim3 grid(static_cast<unsigned>(n_kv_heads) * p.wgs_per_head);
-    const GramKernels k = gram_kernels(halves);
+    const GramKernels k = gram_kernels(fewer);
     hipLaunchKernelGGL(q_dt == SQUAT_BF16 ? k.bf16 : q_dt == SQUAT_F16 ? k.f16 : k.f32, grid, dim3(kGramWaves * kWave), lds, s, p);
     int rc = check_launch();
     if (rc) return rc;

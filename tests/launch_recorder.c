@@ -1,11 +1,11 @@
 /* A stand-in for the launch calls of the HIP runtime, for tests of the library's host side on machines without a GPU: it
- * records every kernel launch (its function, grid and the first bytes of its first argument) and fails the launches it is
+ * records every kernel launch (its function, grid, dynamic LDS and the first bytes of its first argument) and fails the launches it is
  * told to.  Loaded (RTLD_GLOBAL) before the library, so that these definitions come first. */
 #include <stdint.h>
 #include <string.h>
 
 typedef struct { uint32_t x, y, z; } dim3_t;
-typedef struct { uint64_t func; uint32_t grid[3], block[3]; uint64_t head[2]; int failed; } launch_t;
+typedef struct { uint64_t func; uint32_t grid[3], block[3]; uint64_t head[2]; int failed; uint64_t shared; } launch_t;
 
 enum { kMost = 4096, kOk = 0, kLaunchFailure = 719 };
 static launch_t launches[kMost];
@@ -28,8 +28,8 @@ int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* shared, void*
     return kOk;
 }
 int hipLaunchKernel(const void* func, dim3_t grid, dim3_t block, void** args, size_t shared, void* stream) {
-    (void)shared; (void)stream;
-    launch_t l = {(uint64_t)(uintptr_t)func, {grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, {0, 0}, n_launches == fail_at};
+    (void)stream;
+    launch_t l = {(uint64_t)(uintptr_t)func, {grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, {0, 0}, n_launches == fail_at, shared};
     memcpy(l.head, args[0], sizeof l.head);
     if (n_launches < kMost) launches[n_launches] = l;
     ++n_launches;

@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 
 class Launch(ctypes.Structure):
     _fields_ = [("func", ctypes.c_uint64), ("grid", ctypes.c_uint32 * 3), ("block", ctypes.c_uint32 * 3),
-                ("head", ctypes.c_uint64 * 2), ("failed", ctypes.c_int)]
+                ("head", ctypes.c_uint64 * 2), ("failed", ctypes.c_int), ("shared", ctypes.c_uint64)]
 
 
 class CacheConfig(ctypes.Structure):

@@ -15,7 +15,7 @@ for dt, n, heads, qpk in %r:
     n0 = rec.recorded()
     assert lib.squat_build_subspace(0x10000, dt, n, heads, qpk, 128, n * 128, 128, 0, None, None, None, 0x100000, ws, None) == 0
     assert rec.recorded() == n0 + 2
-    out.append([list(rec.launch_at(n0 + i).contents.grid) for i in range(2)])
+    out.append([list(rec.launch_at(n0 + i).contents.grid) + [rec.launch_at(n0 + i).contents.shared] for i in range(2)])
 print(json.dumps(out))
 """
 
@@ -49,4 +49,12 @@ def test_kernel_of_the_reduction(grids):
     for (dt, n, heads, qpk), (gram, reduce) in grids.items():
         wgs = gram[0] // heads
         spread = wgs >= 4 or heads <= (24 if wgs == 1 else 32)
-        assert reduce == ([40, heads, 1] if spread else [heads, 1, 1])
+        assert reduce[:3] == ([40, heads, 1] if spread else [heads, 1, 1])
+
+
+def test_longer_sums_are_made_of_two(grids):
+    """A head with fewer workgroups than the number rounded up has longer sums than that number's: each wavefront then puts its first
+    half's aside, all of a compute unit's 160 KB of LDS for four of them."""
+    for (dt, n, heads, qpk), (gram, _) in grids.items():
+        rounded_up = min(-(-qpk * -(-n // 16) // (8 * WAVES)), -(-CUS // heads))
+        assert gram[3] == (160 if gram[0] // heads < rounded_up else 80) * 1024
