@@ -199,18 +199,24 @@ int launch_pc(squat_dtype dt, const DeqParams& p, int64_t tiles, dim3 grid, hipS
 // Non-temporal stores for outputs of 4 MB and more.  The last of them is on its way to memory when the kernel ends, which a short
 // launch waits for.  us, ordinary | non-temporal stores (graphs of such calls): fp16, 4 bits, groups of 128, 0.7 MB 2.8 | 3.0, 8.4 MB
 // 4.1 | 3.5; bf16, 215 MB 47.8 | 41.2; fp32, 215 MB 47.3 | 37.1; per channel, bf16, 0.7 MB 3.0 | 3.2, 3 MB 3.3 | 3.5, 8.4 MB 4.2 | 3.9, 109
-// MB 29.6 | 25.9, 537 MB 125 | 121, fp32, 217 MB 50.1 | 48.3 (1 GB 231 | 244).
+// MB 29.6 | 25.9, fp32, 217 MB 50.1 | 48.3.
 //
 // Only where the rows are whole lines, or begin on half lines with room between them: of a line that two rows share a non-temporal
 // store sends each part, which the L2 puts together for ordinary ones.  2 bits, bf16, rows of 272 bytes, 25 MB 7.6 | 10.8, 272 MB 112 | 154; of
 // 256 bytes 16 bytes off a line, 24 MB 7.5 | 9.7, 256 MB 70 | 120, 64 bytes off, 24 MB 6.8 | 7.5, 512 MB 154 | 175; of 320 bytes, 30 MB
 // 6.8 | 6.2, 320 MB 89 | 63; per channel, rows of 272 bytes, 272 MB 117 | 136, 256 bytes 16 off, 256 MB 67 | 95, 320 bytes, 320 MB 91 | 64.
-bool streamed(const DeqParams& p, int64_t n_batch, int es) {
+//
+// Per channel, whole lines: up to 512 MB, fp32 256 MB (us, ordinary | non-temporal, dense rows, 2 bits: bf16, 256 MB 59.0 | 57.5, 384 MB 86.8 | 87.2, 512 MB
+// 115 | 117, 768 MB 170 | 178, 2 GB 465 | 479; fp32, 192 MB 42.5 | 41.3, 256 MB 55.9 | 55.5, 384 MB 81.9 | 84.9, 1 GB 217 | 226; 4 bits: bf16, 512 MB
+// 124 | 122, 768 MB 186 | 189, 1 GB 249 | 254; fp32, 256 MB 59.3 | 59.0, 384 MB 86.7 | 89.3, 1 GB 226 | 240).  Half lines (rows of 320 bytes)
+// 1280 MB 351 | 261.
+bool streamed(const DeqParams& p, int64_t n_batch, int es, bool per_channel) {
     const int64_t row = kD * es, oh = p.n_heads > 1 ? p.oh : p.ot, ob = n_batch > 1 ? p.ob : p.ot;
     const uint64_t starts = reinterpret_cast<uintptr_t>(p.out) | static_cast<uint64_t>(p.ot | oh | ob);
     const bool apart = p.ot > row && oh > row && ob > row;
     if (starts % (apart ? 64 : 128)) return false;
-    return static_cast<double>(n_batch) * p.n_heads * p.n_tokens * row >= 4 << 20;
+    const double megabytes = static_cast<double>(n_batch) * p.n_heads * p.n_tokens * row / (1 << 20);
+    return megabytes >= 4 && !(per_channel && starts % 128 == 0 && megabytes > (es == 4 ? 256 : 512));
 }
 
 // (batch, head) pairs over grid y / z: an exact factorisation so that every (y, z) is a real pair.
@@ -290,7 +296,7 @@ extern "C" int squat_dequantize_keys(const uint32_t* codes, const uint16_t* scal
     if (!split_bh(n_batch * n_heads, gy, gz) || gx > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (streamed(p, n_batch, es))
+    if (streamed(p, n_batch, es, false))
         return bits == 2 ? launch_group<2, true>(group, out_dt, p, grid, s) : launch_group<4, true>(group, out_dt, p, grid, s);
     return bits == 2 ? launch_group<2, false>(group, out_dt, p, grid, s) : launch_group<4, false>(group, out_dt, p, grid, s);
 }
@@ -339,7 +345,7 @@ extern "C" int squat_dequantize_keys_per_channel(const uint32_t* codes, const ui
     if (!split_bh(n_batch * n_heads, gy, gz) || gx > 0x7FFFFFFF) return SQUAT_E_BADSHAPE;
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (streamed(p, n_batch, es))
+    if (streamed(p, n_batch, es, true))
         return bits == 2 ? launch_pc<2, true>(out_dt, p, tiles, grid, s) : launch_pc<4, true>(out_dt, p, tiles, grid, s);
     return bits == 2 ? launch_pc<2, false>(out_dt, p, tiles, grid, s) : launch_pc<4, false>(out_dt, p, tiles, grid, s);
 }

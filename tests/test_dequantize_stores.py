@@ -51,3 +51,17 @@ def test_rows_that_share_lines_are_written_by_ordinary_stores(recorder, name, bi
     rows = (4 << 20) // (128 * es) // 2                                  # of each of two batch entries
     sizes = [(1, rows, 0, (rows * 128, 8, 128)), (1, rows - 32, 0, (rows * 128, 8, 128)), (rows // 32, 32, 0, _heads_first(rows // 32, 32, 128))]
     assert recorded.run(recorder, CODE % (name, bits, dtype, sizes)) == [True, False, True]
+
+
+@pytest.mark.parametrize("dtype", [0, 1, 2])
+@pytest.mark.parametrize("per_channel", [False, True])
+def test_large_outputs(recorder, per_channel, dtype):
+    """Per channel whole lines are streamed up to 512 MB (fp32 256 MB), per token and half lines whatever the size."""
+    name = "lib.squat_dequantize_keys" + ("_per_channel" if per_channel else "")
+    n, pad = 1 << 17, 32 if dtype else 16
+    sizes = [(8, n, 0, _heads_first(8, n, 128)), (8, n + 32, 0, _heads_first(8, n + 32, 128)), (8, n + 32, 0, _heads_first(8, n + 32, 128 + pad))]
+    assert dtype == 0 or 2 * 8 * n * 256 == 512 << 20
+    if dtype == 0:
+        sizes = [(8, n // 4, 0, _heads_first(8, n // 4, 128)), (8, n // 4 + 32, 0, _heads_first(8, n // 4 + 32, 128)), sizes[2]]
+        assert 2 * 8 * (n // 4) * 512 == 256 << 20
+    assert recorded.run(recorder, CODE % (name, 2, dtype, sizes)) == [True, not per_channel, True]
