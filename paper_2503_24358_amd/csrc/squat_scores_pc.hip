@@ -44,10 +44,14 @@ constexpr int kPcWorkgroups = 512;     // about this many workgroups (two per CU
 // Workgroups of a sequence: as many as make no more than that, and two of up to half as many sequences again as there are CUs, where the
 // CUs with most of them then have a sequence and a half to read and not two.  us, one workgroup | two, 2 bits, 4 query heads: 257 x
 // 2560 tokens 16.3 | 13.8, 300 x 1024 9.4 | 8.9, 384 x 512 7.2 | 6.9, x 2560 18.2 | 15.8; 8 query heads, 257 x 2560 20.1 | 15.8, 384 x 2560
-// 22.6 | 18.8.  (Two of 513 to 640 and 769 to 896 sequences: 640 x 1024, 4 query heads 12.6 | 13.6, x 2560 24.9 | 23.9.)
-inline int64_t pc_workgroups(int64_t sequences) {
+// 22.6 | 18.8.  (Two of 513 to 640 and 769 to 896 sequences: 640 x 1024, 4 query heads 12.6 | 13.6, x 2560 24.9 | 23.9.)  Three of 171 to 204
+// with more than 4 query heads and 48 token groups or more (us, two | three, 8 query heads, 180 x 1024 7.6 | 8.0, x 2560 12.8 | 12.5, x 4992 22.0 |
+// 20.3; 4 query heads, x 2560 11.1 | 11.9).
+inline int64_t pc_workgroups(int64_t sequences, int n_tiles, bool wide) {
     constexpr int64_t cus = kPcWorkgroups / 2;
-    return sequences <= cus ? kPcWorkgroups / sequences : (2 * sequences <= 3 * cus ? 2 : 1);
+    if (sequences > cus) return 2 * sequences <= 3 * cus ? 2 : 1;
+    const int64_t within = kPcWorkgroups / sequences;
+    return within == 2 && wide && n_tiles >= 48 && 5 * sequences <= 2 * kPcWorkgroups ? 3 : within;
 }
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
@@ -518,7 +522,7 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     const bool two = q_per_kv <= 4;                       // two token groups per step (see the kernel)
     const int nt = two ? 2 : 1;
     int64_t gx;
-    p.deal = deal_steps((int64_t(p.n_tiles) + nt - 1) / nt, pc_workgroups(n_batch * n_kv_heads), kPcWaves, 2 / nt, kPcTilesPerWave / nt, true, gx);
+    p.deal = deal_steps((int64_t(p.n_tiles) + nt - 1) / nt, pc_workgroups(n_batch * n_kv_heads, p.n_tiles, !two), kPcWaves, 2 / nt, kPcTilesPerWave / nt, true, gx);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
     if (gy > 65535) {

@@ -45,11 +45,18 @@ constexpr int kRopeUnit = 16;          // tokens per matrix product (MFMA N)
 constexpr int kRopeMaxUnitsPerWave = 64;
 constexpr int kRopeWorkgroups = 512;
 constexpr int kRopeWaves = 4;
-// Workgroups of a sequence: as many as make no more than that.  Of more sequences than CUs, a sequence as two halves where the CUs with
-// most of them then have half a sequence less to do.
-inline int64_t rope_workgroups(int64_t sequences) {
+// Workgroups of a sequence: as many as make no more than that; three of 171 to 204 sequences of 48 epochs and more (us, two | three, 2 bits, 4 query
+// heads, per token, per channel: 180 x 2560 tokens 17.0 | 17.8, 18.9 | 20.1, x 4992 28.8 | 27.0, 33.4 | 31.5, x 8192 43.1 | 40.1, 50.9 | 47.9; not
+// with 8 query heads per channel, x 8192 56.6 | 61.5).  Of more sequences than CUs, a sequence as two halves where the CUs with most of
+// them then have half a sequence less to do; beyond half as many again only of more than 12 epochs (640 x 512 tokens, per token, one
+// workgroup | two, 12.7 | 13.5, x 1024 19.1 | 18.5, per channel, 8 query heads, 769 x 512 20.6 | 21.6, 640 x 960 26.2 | 24.9).
+inline int64_t rope_workgroups(int64_t sequences, int64_t epochs, bool third) {
     constexpr int64_t cus = kRopeWorkgroups / 2;
-    if (sequences <= cus) return kRopeWorkgroups / sequences;
+    if (sequences <= cus) {
+        const int64_t within = kRopeWorkgroups / sequences;
+        return within == 2 && third && epochs >= 48 && 5 * sequences <= 2 * kRopeWorkgroups ? 3 : within;
+    }
+    if (2 * sequences > 3 * cus && epochs <= 3 * kRopeWaves) return 1;
     return sequences < 4 * cus && (2 * sequences + cus - 1) / cus < 2 * ((sequences + cus - 1) / cus) ? 2 : 1;
 }
 
@@ -862,9 +869,9 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
               (out_bytes > (int64_t(5) << 20) && out_bytes < (int64_t(18) << 20));
 
     // whole epochs: a range starts where the query-side operand changes (units that are no pair are slow: not behind the larger number)
-    const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit;
+    const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit, epochs = (n_units + kEpochUnits - 1) / kEpochUnits;
     int64_t gx;
-    p.deal = deal_steps((n_units + kEpochUnits - 1) / kEpochUnits, rope_workgroups(n_batch * n_kv_heads), kRopeWaves, 1,
+    p.deal = deal_steps(epochs, rope_workgroups(n_batch * n_kv_heads, epochs, true), kRopeWaves, 1,
                         kRopeMaxUnitsPerWave / kEpochUnits, n_tokens % (2 * kRopeUnit) == 0, gx);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;
@@ -935,8 +942,9 @@ int squat::key_scores_pc_rope_from(const uint32_t* codes, const uint16_t* scale,
     p.out_scale = out_scale;
 
     // whole epochs of two token groups
+    const int64_t epochs = (n_tokens / group + 1) / 2;
     int64_t gx;
-    p.deal = deal_steps((n_tokens / group + 1) / 2, rope_workgroups(n_batch * n_kv_heads), kRopeWaves, 1,
+    p.deal = deal_steps(epochs, rope_workgroups(n_batch * n_kv_heads, epochs, q_per_kv <= 4), kRopeWaves, 1,
                         kRopeMaxUnitsPerWave / kEpochUnits, true, gx);
     const int64_t bh = n_batch * n_kv_heads;
     int64_t gy = bh, gz = 1;

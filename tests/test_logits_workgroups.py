@@ -37,3 +37,22 @@ def _workgroups(recorder, name, qpk, cases):
 def test_per_channel_sequences_in_halves(recorder, qpk):
     cases = [(h, n) for h in (257, 300, 341, 342, 384, 385, 512, 513, 600, 1100) for n in (512, 1024, 2560)]
     assert _workgroups(recorder, PC, qpk, cases) == [2 if h <= 384 else 1 for h, _ in cases]
+
+
+@pytest.mark.parametrize("name,qpk,line", [(ROPE, 1, 3072), (ROPE, 4, 3072), (ROPE, 8, 3072), (PC_ROPE, 1, 3072), (PC_ROPE, 4, 3072), (PC_ROPE, 8, None),
+                                           (PC, 1, None), (PC, 4, None), (PC, 8, 1536)])
+def test_third_workgroup_of_long_sequences(recorder, name, qpk, line):
+    """512 divided by 171 to 204 sequences is nearer to three than to two."""
+    lengths = (512, 1024, 1536 - 64, 1536, 3072 - 64, 3072, 4096)
+    cases = [(h, n) for h in (170, 171, 190, 204, 205, 256) for n in lengths]
+    want = [3 if h <= 170 or (h <= 204 and line and n >= line) else 2 for h, n in cases]
+    want = [min(w, -(-n // 256)) for w, (_, n) in zip(want, cases)]          # 64 tokens a wavefront at least
+    assert _workgroups(recorder, name, qpk, cases) == want
+
+
+@pytest.mark.parametrize("name", [ROPE, PC_ROPE])
+def test_rotary_sequences_in_halves(recorder, name):
+    """Of more than 384 sequences only those of more than 12 epochs of 64 tokens."""
+    cases = [(h, n) for h in (257, 384, 385, 512, 513, 640, 641, 769, 896, 897, 1100) for n in (512, 768, 800, 2560)]
+    want = [2 if h <= 384 or (n > 768 and (513 <= h <= 640 or 769 <= h <= 896)) else 1 for h, n in cases]
+    assert _workgroups(recorder, name, 4, cases) == want
