@@ -217,8 +217,7 @@ struct QuantPlan {
 // where non-temporal stores send each part (per-channel store, 4 query heads per KV head, 8 MB of logits: 1.24 times the write
 // requests, 47 MB 1.21; 8 query heads, 17 MB 1.47, 94 MB 1.31).  An ordinary store's line waits in the L2 until the kernel
 // ends, which costs the kernels that leave the memory time to spare more than the requests do: the per-channel and the rotary
-// kernel have a range of sizes of their own beside this rule, and small outputs take ordinary stores also where the rows are whole lines
-// (each entry has its line and figures).  Per-token store, rows off the lines, us with non-temporal | ordinary stores, 2 bits, heads of about 2050 tokens (medians of 15 graphs of 20 calls on
+// kernel have a range of sizes of their own beside this rule.  Per-token store, rows off the lines, us with non-temporal | ordinary stores, 2 bits, heads of about 2050 tokens (medians of 15 graphs of 20 calls on
 // four sets of buffers in turn; their spread is 1 %): 1 query head, 1 MB 6.6 | 6.4, 2 MB 9.4 | 9.5, 4 MB 14.3 | 13.9, 8 MB 26.3 | 25.0, 30
 // MB 90 | 89; 4, 1 MB 4.6 | 4.2, 2.8 MB 6.6 | 6.7, 4 MB 7.0 | 7.0, 8 MB 11.0 | 10.7, 16 MB 20.9 | 18.8, 45 MB 59 | 45; 8, 1 MB 4.3 | 3.9, 4
 // MB 6.3 | 6.1, 5.6 MB 7.3 | 7.6, 8 MB 8.0 | 8.3, 11 MB 11.8 | 10.5, 45 MB 50 | 32.

@@ -65,7 +65,6 @@ struct ScoreParams {
     int qpk;
     float out_scale;
     int units_per_wave;
-    bool lines;                      // logits by non-temporal stores (host side)
     ResidualKeys res;                // (RES kernels) logits of these keys by further workgroups
 };
 
@@ -431,7 +430,7 @@ __global__ void __launch_bounds__(kScoreWaves* kWave) key_scores_kernel(const Sc
 template <int BITS, int NG, int QDT, bool RES>
 void launch_lines(const ScoreParams& p, dim3 grid, hipStream_t s) {
     const dim3 block(kScoreWaves * kWave);
-    if (p.lines)
+    if (rows_on_lines(p.scores, p.ssb, p.ssh))
         hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, RES, true>), grid, block, 0, s, p);
     else
         hipLaunchKernelGGL((key_scores_kernel<BITS, NG, QDT, RES, false>), grid, block, 0, s, p);
@@ -507,10 +506,6 @@ int squat::key_scores_from(const uint32_t* codes, const uint16_t* scale, const u
     p.n_kv_heads = n_kv_heads;
     p.qpk = q_per_kv;
     p.out_scale = out_scale;
-    // Below 2 MB of logits ordinary stores, whole lines or not: the kernel ends before the L2 has anything to write back.  us with
-    // non-temporal | ordinary stores, 8 heads x 4 queries: 2048 tokens 3.98 | 3.65, 6144 4.40 | 4.05, 8192 4.53 | 4.15, 12288 5.00 | 4.68;
-    // 16384 (2 MB) 5.46 | 5.37, 4 MB the same, 8 MB and more longer.
-    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) && n_batch * n_kv_heads * q_per_kv * n_tokens * 4 >= (int64_t(2) << 20);
     p.res = ResidualKeys{};
 
     const int64_t n_units = (n_tokens + kUnitTokens - 1) / kUnitTokens;

@@ -507,10 +507,9 @@ int squat::key_scores_pc_from(const uint32_t* codes, const uint16_t* scale, cons
     // 27.5, 18 MB 53.2 | 55.3, 30 MB 86.6 | 86.4; 4 query heads, 1 MB 4.4 | 4.0, 2 MB 5.6 | 5.2, 2.8 MB 6.9 | 7.1, 4 MB 7.1 | 7.6, 8 MB
     // 10.3 | 11.3, 11 MB 14.5 | 16.1, 16 MB 18.2 | 18.4 (rows of 11904 tokens: 22.2 | 21.2), 18 MB 22.6 | 22.0, 30 MB 32.7 | 29.0, 45 MB
     // 48.0 | 41.8; 8 query heads, ordinary stores 0.90 to 0.94 as long up to 2.8 MB, 0.98 at 4 to 6 MB, 1.01 at 8, 0.57 at 45.  With 4 bits
-    // 0.95 to 1.03 as long from 2 to 22 MB, 1 to 4 query heads.  Rows on the lines: ordinary stores below 1 MB, 8 heads x 4 queries:
-    // 2048 tokens 4.66 | 4.31, 6144 4.81 | 4.43; 8192 (1 MB) 4.88 | 4.46, 2 MB the same.
+    // 0.95 to 1.03 as long from 2 to 22 MB, 1 to 4 query heads.
     const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
-    p.lines = (rows_on_lines(scores, s_stride_batch, s_stride_head) && out_bytes >= (int64_t(1) << 20)) ||
+    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) ||
               (q_per_kv <= 4 && out_bytes > (int64_t(bits == 2 ? 5 : 8) << 19) && out_bytes < (int64_t(18) << 20));
     p.n_tiles = static_cast<int>(n_tokens / 32);
     p.store_tiles = store_tokens / 32;

@@ -862,11 +862,9 @@ int squat::key_scores_rope_from(const uint32_t* codes, const uint16_t* scale, co
     // 8 query heads per KV head, 2 MB 9.0 | 8.6, 4 MB 11.5 | 11.3, 5.6 MB 11.6 | 11.8, 8 MB 14.4 | 15.1, 11 MB 17.7 | 18.9, 16 MB 20.6 |
     // 21.8, 18 MB 26.3 | 27.5 (rows of 12289 tokens: 22.2 | 22.0), 22 MB 31.0 | 31.7 (of 11265: 26.3 | 25.2), 30 MB 35.6 | 33.0, 45 MB
     // 54.8 | 43.0; 4 query heads, 2 MB 10.0 | 9.7, 4 MB 12.6 | 12.7, 5.6 MB 15.8 | 16.3, 8 MB 17.9 | 18.5, 16 MB 28.1 | 28.9, 22 MB 36.9 |
-    // 37.9 (4 bits: 0.93 as long), 30 MB 51.1 | 49.0; 1 query head, 0.99 to 1.025 throughout.  Rows on the lines: ordinary stores below
-    // 1 MB, 8 heads x 4 queries: 2048 tokens 6.20 | 5.80, 6144 6.40 | 6.00; 8192 (1 MB) 6.52 | 6.06, 4 MB the same.
+    // 37.9 (4 bits: 0.93 as long), 30 MB 51.1 | 49.0; 1 query head, 0.99 to 1.025 throughout.
     const int64_t out_bytes = n_batch * n_kv_heads * q_per_kv * n_tokens * 4;
-    p.lines = (rows_on_lines(scores, s_stride_batch, s_stride_head) && out_bytes >= (int64_t(1) << 20)) ||
-              (out_bytes > (int64_t(5) << 20) && out_bytes < (int64_t(18) << 20));
+    p.lines = rows_on_lines(scores, s_stride_batch, s_stride_head) || (out_bytes > (int64_t(5) << 20) && out_bytes < (int64_t(18) << 20));
 
     // whole epochs: a range starts where the query-side operand changes (units that are no pair are slow: not behind the larger number)
     const int64_t n_units = (n_tokens + kRopeUnit - 1) / kRopeUnit, epochs = (n_units + kEpochUnits - 1) / kEpochUnits;
