@@ -14,6 +14,10 @@ OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libsquat.so")
 EXT = os.path.join(PKG, "_squat_torch.so")         # the hot calls of the Python binding
 
+# For tests: the subspace calls alone, whose eigen-solver refuses heads (odd exponents) that it would accept, so that they take its fallback.
+REFUSING_LIB = os.path.join(ROOT, "tests", "libsquat_refusing.so")
+REFUSING = ("squat_subspace.hip", "_refusing", ("-DSQUAT_TRI_REFUSED(exponent)=(((exponent) & 1) != 0)",))
+
 SOURCES = ["squat_api.cpp", "squat_quantize.hip", "squat_quantize_pc.hip", "squat_dequantize.hip",
            "squat_subspace.hip", "squat_prepare.hip", "squat_scores.hip", "squat_scores_pc.hip", "squat_scores_rope.hip",
            "squat_cache.hip"]
@@ -41,23 +45,34 @@ EXTRA = {"squat_prepare.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "squat_scores_rope.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *FLAGS, *EXTRA.get(src, []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(src: str, suffix: str = "", extra=()) -> str:
+    obj = os.path.join(OBJ, os.path.splitext(src)[0] + suffix + ".o")
+    cmd = [_hipcc(), *FLAGS, *EXTRA.get(src, []), *extra, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s" % (src, res.stderr[-4000:]))
     return obj
 
 
+def _link(lib: str, objs) -> None:
+    res = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("link failed:\n" + res.stderr[-4000:])
+
+
+def build_refusing() -> str:
+    os.makedirs(OBJ, exist_ok=True)
+    _link(REFUSING_LIB, [_compile(*REFUSING)])
+    return REFUSING_LIB
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        refusing = ex.submit(_compile, *REFUSING)
         objs = list(ex.map(_compile, SOURCES))
-    cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("link failed:\n" + res.stderr[-4000:])
+    _link(LIB, objs)
+    _link(REFUSING_LIB, [refusing.result()])
     _build_binding()
     if verbose:
         print("built", LIB, "and", EXT)

@@ -49,6 +49,9 @@ constexpr double kTriBound = 3.0001;     // > the largest eigenvalue of a tridia
 constexpr double kTriPart = 2.0 * kTriBound / 257.0;
 constexpr double kTriWidth = 4.5e-16;   // width of an eigenvalue's bracket (one unit in the last place of numbers from 2 to 4)
 constexpr double kTriAccept = 1e-9;     // ||T x - lambda x|| / ||T|| and |x_i . x_j| allowed before the fallback
+#ifndef SQUAT_TRI_REFUSED               // matrices refused all the same, by the exponent of their largest entry: a build for tests has some
+#define SQUAT_TRI_REFUSED(exponent) false
+#endif
 
 // LDS plan, in doubles
 constexpr int kTriSs = 0;               // [2][4][64] in the reduction: the wavefronts' parts of x'A x (lanes 16 .. 31)
@@ -1233,7 +1236,7 @@ __device__ __forceinline__ bool tridiag_top_eigs(const double* g, double* vws, i
             for (int q = 0; q < 8; ++q) res += P[512 + 32 * q + j];
             const double w = j < rb ? sqrt(res) : 0.0;
             // every wavefront sees all 32 vectors
-            if (__ballot(!(w <= kTriAccept)) != 0ull) ok = false;
+            if (__ballot(!(w <= kTriAccept)) != 0ull || SQUAT_TRI_REFUSED(aexp)) ok = false;
         }
         if (!ok) return false;                                // uniform: every thread saw the same flags
 
