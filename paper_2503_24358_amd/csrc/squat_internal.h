@@ -285,11 +285,12 @@ inline int device_cu_count() {
 }
 
 // Workgroups per problem of a quantize launch: as many as the device holds at once (a workgroup's LDS fills a compute unit), at
-// least one and at most one per tile.  Rounded down: where rounding up makes a launch of 257 to 300 workgroups, the few beyond 256
+// least one and at most one per tile.  Rounded down: where rounding up makes a launch of 257 to 381 workgroups, those beyond 256
 // start when the others have ended and read their share alone.  Up | down, us, 2 bits, bf16, groups of 32, 16384 tiles in all: 3 heads
 // 59.8 | 42.7, 7 58.7 | 42.1, 40 57.3 | 41.8, 56 59.0 | 44.9, 98 54.3 | 44.2, 200 48.5 | 46.8; 4096 tiles: 7 heads 22.0 | 14.5,
-// 40 22.8 | 14.9, 130 22.5 | 17.8; 16 tiles a head, 24 heads 9.6 | 6.1, 56 11.4 | 7.1; per channel, 4 bits, g = 64, 40 heads 56.8 | 42.9; fp32, 7 heads 45.2 | 31.9.  (Up to a quarter of
-// the compute units stay idle so, 98 heads x 2; the launch is bound by the memory, which the others keep busy.)
+// 40 22.8 | 14.9, 130 22.5 | 17.8; 16 tiles a head, 24 heads 9.6 | 6.1, 56 11.4 | 7.1; per channel, 4 bits, g = 64, 40 heads 56.8 | 42.9; fp32, 7 heads 45.2 | 31.9.  Up to half of
+// the compute units stay idle so, and a launch's few more rounds still cost more than they give: 129 heads x 1, 128 tiles each 57.8 | 50.6, 16 15.5 | 11.5,
+// fp32, 48 40.2 | 33.8; 86 x 2, 128 41.1 | 30.0; 170 x 1, 128 66.5 | 52.0.
 inline int spread_problems(QuantPlan& plan) {
     const int64_t cus = device_cu_count(), tiles = plan.units_per_prob;
     int64_t held = cus / plan.n_prob;

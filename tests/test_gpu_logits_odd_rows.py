@@ -1,5 +1,5 @@
 """Per-token stores whose rows (scales of one head) start at a multiple of 4 bytes only, or of 2: whole units of 16 tokens are
-fetched with 16-byte loads in the first case and word by word in the second.  Bounds as derived in test_gpu_scores.py
+fetched with 16-byte loads in both cases.  Bounds as derived in test_gpu_scores.py
 (4e-5 of sum_c |q_c| (step code_c + |zero|), the two parts that are summed apart) and, for the rotary form without a
 turn (inv_freq = 0), 2e-3 of the same sum (four roundings to fp16)."""
 import pytest
